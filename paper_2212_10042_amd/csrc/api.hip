@@ -181,7 +181,7 @@ int run_sim(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bo
     } else {
         CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * P.d * sizeof(unsigned long long), st));
         Timed tm(keys ? "binom2_calib" : "binom2", st);
-        CSE_LAUNCH(cse::launch_binom2(P, seed, P.d_Rw, P.d_Tw, (uint4 *)keys, st));
+        CSE_LAUNCH(cse::launch_binom2(P, seed, P.d_Rw, P.d_Tw, (uint2 *)keys, st));
     }
     return CSE_OK;
 }
@@ -209,13 +209,18 @@ int run_sim_h4(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st,
     return CSE_OK;
 }
 
+// Calibration workspace: its documented size (the static workspace's limit), and the bytes used
+// (the 2-arm threshold groups' counts, at most the 16 bytes per simulation and batch stated).
 size_t key_bytes(const cse::Platten &P) {
     const size_t esz = (P.design.kind == CSE_BINOM2_Z) ? cse::REC2_BYTES : 4;
     return (size_t)P.n_keys * esz;
 }
+size_t key_bytes_used(const cse::Platten &P) {
+    return P.design.kind == CSE_BINOM2_Z ? (size_t)P.b2_recs * sizeof(uint2) : key_bytes(P);
+}
 
 int ensure_keys(cse::Platten &P) {
-    const size_t need = key_bytes(P);
+    const size_t need = key_bytes_used(P);
     if (P.d_keys && P.keys_bytes >= need) return CSE_OK;
     if (P.d_keys) {
         (void)hipFree(P.d_keys);

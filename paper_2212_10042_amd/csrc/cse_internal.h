@@ -30,13 +30,29 @@ struct Blk2 {
     int32_t tile[B2U * B2V];   // tile id of slot (u, v) = u * B2V + v, or -1
     int32_t n_sims;            // simulations of every tile of this block
     int32_t pad;
-    int64_t key_base;          // calibration records: simulation k of this block has its record
-                               // (Rec2) at key_base + k (k < n_sims rounded up to 64)
+    int64_t rec0, rec1;        // calibration counts: simulation k's arm-0 counts at the block's 8
+                               // thresholds are the bytes of entry rec0 + k, its arm-1 counts those
+                               // of rec1 + k (Grp2's rec of its two threshold groups)
 };
-// Calibration record of one simulation of a 2-arm block: the success counts at the block's
-// thresholds, y0[u] in byte u of (w0, w1) and y1[v] in byte v of (w2, w3).  Every tile's outcome
-// y0[u] (n+1) + y1[v] follows from it, so 16 bytes serve the block's 64 tiles.
-constexpr int REC2_BYTES = 16;
+// Threshold group of a 2-arm platten: 8 neighbouring distinct thresholds of one arm, counted once
+// per simulation for every block that has them (one row or column of the 8 x 8 grid of blocks of
+// one simulation count).
+//  * unit: first 128-byte unit of the group in the count table.  A granule (16 simulations) takes
+//    one unit for arm 1, the counts y1 + 128 as bytes, threshold-major ([8][16]), and two units for
+//    arm 0, the counts y0 and then the design's cut points c(y0) (64, no rejection, past n_sims).
+//  * rec: first entry (8 bytes: one simulation's counts at the 8 thresholds) in the calibration
+//    workspace, simulations padded to whole chunks of 64.
+struct Grp2 {
+    uint32_t T[B2U];
+    int32_t arm;
+    int32_t n_sims;
+    int64_t unit;
+    int64_t rec;
+};
+constexpr int GRAN2 = 16;              // simulations per granule of the count table
+constexpr int UNIT2 = B2U * GRAN2;     // bytes per unit
+constexpr int64_t B2_TABLE_MAX = (int64_t)64 << 20;   // count-table bytes (more: simulation windows)
+constexpr int REC2_BYTES = 16;   // calibration workspace bound: bytes per (simulation, batch)
 
 // z-test: 64 tiles share each simulation's normal draw.
 constexpr int B1T = 64;
@@ -91,16 +107,18 @@ constexpr int H4_PCAP = 1024;
 constexpr int H4_MAXS = 1024;   // item ranges per group at most (the selection's region table)
 constexpr int H4_BROWS = 128;   // key rows per wave whose counters live in LDS (the rest: global atomics)
 
-// Workgroup item of the 2-arm kernel: its 16 waves simulate [k_begin, k_end) for the batches of a
-// 4 x 4 square of the threshold grid (equal N): blk[4 r + c] is the batch of row group r (8 arm-0
-// thresholds) and column group c (8 arm-1 thresholds) of the square (-1: none), so the square's
-// 32 + 32 distinct thresholds serve 1,024 tiles.
-constexpr int SQ2 = 4;                   // square side (batches)
-constexpr int SQ2W = SQ2 * SQ2;          // waves per workgroup
+// Workgroup item of the 2-arm kernel: wave w takes the 8 thresholds of row group rg[w] (-1: none)
+// against the up to 64 thresholds of the column groups cg[0..7] (ascending; the first ncg are
+// valid) over the granules [g_begin, g_end); blk[w][c] is the batch of (rg[w], cg[c]), or -1.
+constexpr int SQ2R = 4, SQ2C = 8;
 struct SquareItem {
-    int32_t blk[SQ2W];
-    uint32_t k_begin;
-    uint32_t k_end;
+    int32_t rg[SQ2R];
+    int32_t cg[SQ2C];
+    int32_t blk[SQ2R][SQ2C];
+    int32_t ncg;
+    uint32_t g_begin;
+    uint32_t g_end;
+    int32_t pad;
 };
 
 // Per-node constants of the hierarchical posterior (90 nodes equally spaced in log s2 on
@@ -176,6 +194,12 @@ struct Platten {
     int64_t n_items = 0;
     GroupItem *d_gitems = nullptr;       // 4-arm designs
     SquareItem *d_sqitems = nullptr;     // 2-arm design
+    Grp2 *d_grp2 = nullptr;              // 2-arm design: threshold groups
+    int32_t n_grp2 = 0;
+    int64_t b2_units = 0;                // count table: 128-byte units
+    int64_t b2_recs = 0;                 // calibration workspace: 8-byte entries
+    uint4 *d_b2tab = nullptr;            // count table (one window of b2_win granules)
+    int64_t b2_win = 0;                  // granules of a window (a multiple of 4)
     int64_t n_gitems = 0;
     // 4-arm calibration with bracketed keys (CSE_HIER4): pilot items over the first H4_PILOT
     // simulations; per tile the bracket (lo, hi), the keys below lo, the candidates kept per region
@@ -215,6 +239,7 @@ struct Platten {
     int64_t tune_waves = 16384, tune_wgs = 16384;
     std::vector<int64_t> blk_sims;       // simulations of each block
     std::vector<int64_t> blk_row, blk_col;   // 2-arm: each block's row / column group of 8 thresholds
+    std::vector<int32_t> blk_rg, blk_cg;     // 2-arm: their indices in d_grp2
     std::vector<int64_t> p23_item_off;   // [n_tiles + 1] first queue item of each tile
     int64_t h4_outcomes = 0;
     double table_ms = 0.0;               // time to build the design table at platten creation

@@ -64,6 +64,16 @@ constexpr int B2_NOUT = B2_N1 * B2_N1;     // 1,296 outcomes
 constexpr int B2_HB = 4096;                // LDS histogram bins of one batch (16 KB)
 
 __device__ __forceinline__ uint32_t rec_byte(uint32_t w, int b) { return (w >> (8 * b)) & 0xFFu; }
+// simulation j's record of a block: arm-0 counts in (x, y), arm-1 counts in (z, w)
+struct Recs2 {
+    const uint2 *__restrict__ a, *__restrict__ b;
+    __device__ __forceinline__ Recs2(const uint2 *__restrict__ recs, const Blk2 *__restrict__ B)
+        : a(recs + B->rec0), b(recs + B->rec1) {}
+    __device__ __forceinline__ uint4 operator[](int j) const {
+        const uint2 p = a[j], q = b[j];
+        return make_uint4(p.x, p.y, q.x, q.y);
+    }
+};
 __device__ __forceinline__ uint32_t rec_outcome(const uint4 r, int s) {
     const int u = s >> 3, v = s & 7;
     const uint32_t y0 = rec_byte(u < 4 ? r.x : r.y, u & 3);
@@ -166,7 +176,7 @@ __global__ __launch_bounds__(WAVE) void k_b2_bracket(const Blk2 *__restrict__ bl
 // lane = tile: position lookup and histogram add without divergence.
 constexpr int B2_ROUND = 4;
 __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_b2_select(
-    const Blk2 *__restrict__ blocks, const uint4 *__restrict__ recs, const int32_t *__restrict__ kk,
+    const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs, const int32_t *__restrict__ kk,
     const int2 *__restrict__ br, const uint4 *__restrict__ cut, const int32_t *__restrict__ S_pos,
     const int32_t *__restrict__ S_order, const int32_t *__restrict__ S_group, const double *__restrict__ S_tbl,
     double *__restrict__ lam, int32_t *__restrict__ rej_at, uint32_t *__restrict__ fb) {
@@ -223,7 +233,7 @@ __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         }
     }
     __syncthreads();
-    const uint4 *__restrict__ rb = recs + B->key_base;
+    const Recs2 rb(recs, B);
     const int nch = (N + WAVE - 1) / WAVE;
     uint32_t acc[B2U][2];   // per row and half: packed byte counts of simulations below the bracket
 #pragma unroll
@@ -352,7 +362,8 @@ __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 
 // Exact selection from the full histogram of a tile's 1,296 outcomes, for the tiles listed in fb;
 // a fixed grid of workgroups takes the listed tiles in turn.
-__global__ __launch_bounds__(SEL_WG) void k_b2_full(const uint4 *__restrict__ recs, const int64_t *__restrict__ key_off,
+__global__ __launch_bounds__(SEL_WG) void k_b2_full(const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs,
+                                                    const int64_t *__restrict__ key_off,
                                                     const int64_t *__restrict__ key_slot,
                                                     const int32_t *__restrict__ N, const int32_t *__restrict__ kk,
                                                     const double *__restrict__ S_tbl,
@@ -368,7 +379,7 @@ __global__ __launch_bounds__(SEL_WG) void k_b2_full(const uint4 *__restrict__ re
         const int32_t t = (int32_t)fb[1 + li];
         const int32_t n = N[t], k = kk[t];
         const int s = (int)key_slot[t];
-        const uint4 *__restrict__ rb = recs + key_off[t];
+        const Recs2 rb(recs, blocks + key_off[t]);   // the tile's block
         for (int j = tid; j < B2_NOUT; j += SEL_WG) hist[j] = 0u;
         __syncthreads();
         constexpr int LPT = 4;   // records in flight per thread
@@ -1066,7 +1077,7 @@ __device__ __forceinline__ void tbb_take(uint32_t j, uint64_t m, uint32_t *buf, 
 }
 
 template <int MODE>
-__device__ __forceinline__ void tbb_sweep(const uint4 *__restrict__ rb, int N, const uint4 (*ct)[B2_N1],
+__device__ __forceinline__ void tbb_sweep(const Recs2 &rb, int N, const uint4 (*ct)[B2_N1],
                                           TbbList &L, uint32_t *buf, uint32_t *fill, const uint32_t *pre,
                                           const uint32_t *off, const uint32_t *cnt, int lvl, uint32_t key0,
                                           uint32_t key1) {
@@ -1157,7 +1168,7 @@ __device__ __forceinline__ void tbb_select(const uint32_t *v, uint32_t n, uint32
     lt = below;
 }
 
-__global__ __launch_bounds__(TBB_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_b2_tiebreak(const Blk2 *__restrict__ blocks, const uint4 *__restrict__ recs,
+__global__ __launch_bounds__(TBB_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_b2_tiebreak(const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs,
                                                         const int32_t *__restrict__ kk, const uint4 *__restrict__ cut,
                                                         uint32_t key0, uint32_t key1, int32_t *__restrict__ rej_at,
                                                         uint32_t *__restrict__ c_out) {
@@ -1194,7 +1205,7 @@ __global__ __launch_bounds__(TBB_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) 
         fill[lane] = 0u;
     }
     __syncthreads();
-    const uint4 *__restrict__ rb = recs + B->key_base;
+    const Recs2 rb(recs, B);
     // c of slot s: the need-th smallest of the n uniforms at buf[o..o+n) (wave-wide), written out
     auto finish_rank = [&](int s, uint32_t o, uint32_t n) {
         const int32_t t = B->tile[s];
@@ -1443,11 +1454,11 @@ hipError_t launch_select(const Platten &P, const void *keys, const int32_t *k, d
                            (const float *)keys, P.d_key_off, P.d_key_stride, P.d_N, k, lam, rej_at);
     else {   // the 2-arm bracket (launch_b2_bracket) must have run after k was computed
         const Blk2 *blk = (const Blk2 *)P.d_blocks;
-        hipLaunchKernelGGL(k_b2_select, dim3((uint32_t)P.n_blocks), dim3(SEL_WG), 0, st, blk, (const uint4 *)keys, k,
+        hipLaunchKernelGGL(k_b2_select, dim3((uint32_t)P.n_blocks), dim3(SEL_WG), 0, st, blk, (const uint2 *)keys, k,
                            P.d_b2br, P.d_b2cut, P.d_S_pos, P.d_S_order, P.d_S_group, P.d_S_tbl, lam, rej_at,
                            P.d_b2fb);
         const uint32_t grid = (uint32_t)std::min<int64_t>(P.n_tiles, 1024);
-        hipLaunchKernelGGL(k_b2_full, dim3(grid), dim3(SEL_WG), 0, st, (const uint4 *)keys, P.d_key_off,
+        hipLaunchKernelGGL(k_b2_full, dim3(grid), dim3(SEL_WG), 0, st, blk, (const uint2 *)keys, P.d_key_off,
                            P.d_key_stride, P.d_N, k, P.d_S_tbl, P.d_S_order, P.d_S_group, P.d_b2fb, lam, rej_at);
     }
     return hipGetLastError();
@@ -1490,7 +1501,7 @@ hipError_t launch_tiebreak(const Platten &P, uint64_t seed, const int32_t *k, co
             hipLaunchKernelGGL(k_b2_tiecut, dim3((uint32_t)P.n_blocks), dim3(WAVE), 0, st, blk2, k, lam, P.d_S_tbl,
                                P.d_S_order, P.d_gstart, P.d_gcut, P.n_groups, P.d_b2cut, c_tile);
             hipLaunchKernelGGL(k_b2_tiebreak, dim3((uint32_t)P.n_blocks), dim3(TBB_WG), 0, st, blk2,
-                               (const uint4 *)P.d_keys, k, P.d_b2cut, k0, k1, rej_at, c_tile);
+                               (const uint2 *)P.d_keys, k, P.d_b2cut, k0, k1, rej_at, c_tile);
         }
     } else if (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) {   // 64-key chunks at 256-byte offsets
         hipLaunchKernelGGL(k_tiebreak<TB_F32V4>, grid, blk, 0, st, P.d_keys, P.d_key_off, P.d_key_stride, P.d_N, k,

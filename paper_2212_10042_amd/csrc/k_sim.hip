@@ -1,12 +1,12 @@
-// k_sim.hip -- fused Monte Carlo kernels for gfx950.
+// k_sim.hip -- Monte Carlo kernels of the z-test and the 2-arm design for gfx950.
 //
-// One wave owns one tile batch for a range of simulations.  Per simulation (one per lane)
-// the Philox words are generated in registers, turned into draws, shared by every tile
-// of the batch (common random numbers, Section 7.3), and reduced into per-tile rejection
-// counts R and score sums (sufficient statistic over rejections, Example 1).  In
-// calibration mode the 2-arm kernel also stores, per (simulation, batch), the 16 success
-// counts from which every tile's outcome follows (one 16-byte record for 64 tiles), and the
-// z-test each (simulation, tile)'s statistic S in float32.  Nothing else reaches memory.
+// A simulation's random words do not depend on the tile (common random numbers, Section 7.3), so
+// what depends on the words alone is formed once and shared by every tile: the z-test's normal
+// draw, and the 2-arm design's success counts at each distinct threshold.  The per-tile work is
+// the decision and its sums: rejection counts R and score sums (sufficient statistic over
+// rejections, Example 1).
+#include <algorithm>
+
 #include "cse_internal.h"
 #include "kernels.h"
 #include "philox.hpp"
@@ -22,212 +22,151 @@ __device__ __forceinline__ void wave_sync() {
 
 // ------------------------------------------------------------------------------------
 // 2-arm binomial, n = 35 per arm, pooled z.  Words 0..34 are arm 0, 35..69 arm 1
-// (18 Philox blocks).  Each wave's batch is an 8 x 8 product of thresholds: the success
-// counts y0[u], y1[v] at 16 thresholds give the outcomes of all 64 tiles.  The 16 waves of a
-// workgroup run the 16 batches of a 4 x 4 square of the threshold grid over the same
-// simulations (wave 4 r + c: row group r, column group c): the Philox blocks of two chunks at a
-// time (36) are generated once into LDS (two or three per wave), and the square's eight sets
-// of 8 thresholds (four arm-0 row groups, four arm-1 column groups) are each counted once per
-// simulation, by a pair of waves over the two halves of the arm's 35 words; the partial counts
-// (8 bytes per simulation, a byte per threshold) go through LDS, and a batch adds the two
-// halves of its row set and of its column set (bytes stay below 36: no carries).  Rejection at
-// the design's cut is y1 >= c(y0) (z is increasing in y1 for fixed y0; checked on the host).
+// (18 Philox blocks).  Two kernels:
 //
-// In calibration mode each lane also writes its simulation's record (Rec2: y0[0..7], y1[0..7] as
-// bytes, 16 bytes; a wave stores 1 KB contiguous per chunk).
+// k_b2_count: the success counts of every simulation at every threshold group (8 neighbouring
+// distinct thresholds of one arm), once for the whole platten: 16,384 simulations at 2 x 1,024
+// thresholds are 1.2e9 word comparisons, where counting per rectangle of tiles repeats them for
+// every rectangle (1024 x 1024 boxes: 32-fold).  A workgroup takes one chunk of 64 simulations
+// (one per lane): its words go to LDS once, then each wave counts threshold groups and writes them
+// to the count table (Grp2: bytes, 16 simulations of a threshold contiguous) and, for a
+// calibration, to the workspace the selection reads (8 bytes per simulation and group).
 //
-// Per-lane accumulators are packed per tile: bits 0-5 rejections, 6-17 sum of y0 over
-// rejections, 18-29 sum of y1 over rejections; exact for up to 63 simulations per lane
-// between flushes (63 * 35 < 4096).  A flush transposes the 64 x 64 (lane, tile) matrix through
-// LDS in two halves of 32 tiles, lanes l and l + 32 each summing half of tile l's column into
-// 32-bit totals (joined by one shuffle at the end); the final totals are added to global
-// memory with integer atomics (order-independent, hence deterministic).  The word buffer and
-// the transpose buffers share 130 KB of LDS (workgroup barriers separate their uses): one
-// workgroup of 16 waves per CU, four waves per SIMD.
+// k_b2_tiles: per (simulation, tile) the decision y1 >= c(y0) and its sums, four simulations per
+// instruction.  A wave takes 8 arm-0 thresholds (wave-uniform, so their counts and cut points are
+// scalar loads) against 64 arm-1 thresholds, one per lane, so a lane's 8 tiles keep their sums in
+// registers and nothing crosses lanes.  With y1 + 128 and c in the bytes of two words, bit 7 of
+// each byte of their difference is the decision (y1 + 128 - c lies in [64, 163]: no borrow);
+// masked to those bits it is the weight (128 or 0) of three accumulations: a bit count for R and
+// two 4-byte dot products for the sums of y0 and y1: 5 instructions per 4 simulations and tile.
+// Bound by VALU issue (89% of its peak).  1024 x 1024 boxes x 16,384 simulations: counts 0.08 ms
+// and sums 0.61 ms, where one kernel counting per 4 x 4 batches and deciding one simulation at a
+// time took 5.06 ms and wrote 4.3 GB of records that the selection read back; 256 x 256 lower
+// triangle x 8,192: 0.168 -> 0.017 + 0.041 ms.
 // ------------------------------------------------------------------------------------
-constexpr int WG2 = SQ2W * WAVE;   // 1024 threads
-template <bool KEYS>
-__global__ __launch_bounds__(WG2) void k_binom2(const Blk2 *__restrict__ blocks,
-                                                const SquareItem *__restrict__ items,
-                                                int64_t n_items, uint32_t key0, uint32_t key1,
-                                                const int32_t *__restrict__ cut_tbl,
-                                                uint32_t *__restrict__ R,
-                                                unsigned long long *__restrict__ sumT,
-                                                uint4 *__restrict__ recs) {
-    constexpr int NT = B2U * B2V;
-    constexpr int NW = 2 * NP35;
-    constexpr int NB = (NW + 3) / 4;
-    constexpr int NWAVES = SQ2W;
-    constexpr int HALF = NT / 2;   // slots per flush half
-    constexpr int JH = (NP35 + 1) / 2;   // words of the first counting half (18; the second 17)
-    // flush transposes (per wave HALF x (64 + 1) words, padded against bank conflicts); between
-    // flushes the same memory holds the chunk's Philox words
-    // Two chunks per barrier phase: their 36 Philox blocks spread over the 16 waves (at most three
-    // per wave, against two of one chunk's 18 on waves 0 and 1 while the other 14 wait), and half
-    // the barriers.
-    constexpr int CPB = 2;
-    __shared__ uint32_t lds[NWAVES][HALF][WAVE + 1];
-    __shared__ int32_t s_cut[64];
-    __shared__ uint2 cnt[CPB][NWAVES][WAVE];   // per chunk, counting wave and lane: its 8 partial counts as bytes
-    uint32_t(*words)[WAVE] = reinterpret_cast<uint32_t(*)[WAVE]>(&lds[0][0][0]);   // [CPB][4*NB][64]
-    static_assert(CPB * 4 * NB * WAVE <= NWAVES * HALF * (WAVE + 1), "word buffer must fit");
-    static_assert(CPB * NB <= 3 * NWAVES, "at most three Philox blocks per wave");
-
+template <bool RECS>
+__global__ __launch_bounds__(WG) void k_b2_count(const Grp2 *__restrict__ grp, int32_t n_grp, uint32_t win_b,
+                                                 uint32_t win_e, uint32_t key0, uint32_t key1,
+                                                 const int32_t *__restrict__ cut_tbl, uint2 *__restrict__ tab,
+                                                 uint2 *__restrict__ recs) {
+    constexpr int NB = (2 * NP35 + 3) / 4;
+    constexpr int NWV = WG / WAVE;
+    __shared__ uint32_t words[4 * NB][WAVE];
+    __shared__ uint8_t s_cut[WAVE];
+    __shared__ uint2 tr[NWV][WAVE];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x < 64) s_cut[threadIdx.x] = threadIdx.x <= NP35 ? cut_tbl[threadIdx.x] : 64;
-    const int64_t it = blockIdx.x;
-    if (it >= n_items) return;   // uniform over the workgroup
-    const SquareItem *__restrict__ G = items + it;
-    const int32_t blk = G->blk[wv];   // read in place: a register copy indexed by wv would go to scratch
-    const bool live = blk >= 0;       // this wave's batch (row group wv >> 2, column group wv & 3)
-    const Blk2 *__restrict__ B = blocks + (live ? blk : 0);   // dereferenced only when live
-    const uint32_t kb = G->k_begin, ke = G->k_end;
-    // counting set of this wave: set cs = wv >> 1 (0..3: arm 0, row group cs; 4..7: arm 1, column
-    // group cs - 4) over word half wv & 1; thresholds from a block of the square that has them
-    const int cs = wv >> 1, carm = cs >> 2, cgrp = cs & 3, chalf = wv & 1;
-    int32_t csrc = -1;
-    for (int i = 0; i < SQ2; ++i) {   // uniform
-        const int32_t b = carm == 0 ? G->blk[cgrp * SQ2 + i] : G->blk[i * SQ2 + cgrp];
-        if (csrc < 0 && b >= 0) csrc = b;
+    const uint32_t k0 = win_b * GRAN2 + blockIdx.x * WAVE;
+    const uint32_t k = k0 + (uint32_t)lane;
+    if (threadIdx.x < WAVE) s_cut[threadIdx.x] = threadIdx.x <= NP35 ? (uint8_t)cut_tbl[threadIdx.x] : (uint8_t)64;
+    for (int b = wv; b < NB; b += NWV) {
+        const u32x4 w = philox_block((uint32_t)b, k, key0, key1);
+        words[4 * b + 0][lane] = w.x;
+        words[4 * b + 1][lane] = w.y;
+        words[4 * b + 2][lane] = w.z;
+        words[4 * b + 3][lane] = w.w;
     }
-    const bool counting = csrc >= 0;   // false: no batch of the square uses this set
-    uint32_t Tc[B2U];
+    __syncthreads();
+    for (int g = (int)blockIdx.y * NWV + wv; g < n_grp; g += (int)gridDim.y * NWV) {   // uniform over the wave
+        const Grp2 *__restrict__ G = grp + g;
+        const uint32_t n = (uint32_t)G->n_sims;
+        if (k0 >= n) continue;
+        const int arm = G->arm;
+        uint32_t T[B2U], y[B2U];
 #pragma unroll
-    for (int u = 0; u < B2U; ++u) Tc[u] = counting ? (carm == 0 ? blocks[csrc].T0[u] : blocks[csrc].T1[u]) : 0u;
-    const int jw0 = carm * NP35 + (chalf ? JH : 0);   // first word of this wave's half
-    const int jn = chalf ? NP35 - JH : JH;            // its word count
-    uint4 *__restrict__ rbase = recs + ((KEYS && live) ? B->key_base : 0);
-    const int rsrc = (wv >> 2) * 2, csrc2 = 2 * (SQ2 + (wv & 3));   // counting waves of this batch's sets
-
-    uint32_t acc[NT];
-#pragma unroll
-    for (int s = 0; s < NT; ++s) acc[s] = 0u;
-    // lane l: partial totals (over the lanes of half l >> 5) of slots l & 31 ([0]) and 32 + (l & 31) ([1])
-    uint32_t totR[2] = {0u, 0u}, tot0[2] = {0u, 0u}, tot1[2] = {0u, 0u};
-
-    auto flush = [&]() {
-        __syncthreads();   // every wave is done with the word buffer
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int s = 0; s < HALF; ++s) lds[wv][s][lane] = acc[h * HALF + s];
-            wave_sync();
-            const int sl = lane & (HALF - 1), j0 = (lane >> 5) * HALF;
-            for (int l = j0; l < j0 + HALF; ++l) {
-                const uint32_t x = lds[wv][sl][l];
-                totR[h] += x & 63u;
-                tot0[h] += (x >> 6) & 4095u;
-                tot1[h] += (x >> 18) & 4095u;
-            }
-            wave_sync();
+        for (int u = 0; u < B2U; ++u) {
+            T[u] = G->T[u];
+            y[u] = 0u;
         }
+        const uint32_t(*w)[WAVE] = words + arm * NP35;
+#pragma unroll 7
+        for (int j = 0; j < NP35; ++j) {
+            const uint32_t x = w[j][lane];
 #pragma unroll
-        for (int s = 0; s < NT; ++s) acc[s] = 0u;
-        __syncthreads();   // transposes read before the next chunk's words land
-    };
+            for (int u = 0; u < B2U; ++u) y[u] += (x < T[u]) ? 1u : 0u;
+        }
+        const uint2 c8 = make_uint2(y[0] | (y[1] << 8) | (y[2] << 16) | (y[3] << 24),
+                                    y[4] | (y[5] << 8) | (y[6] << 16) | (y[7] << 24));
+        if (RECS) recs[G->rec + k] = c8;   // chunks are padded: past n_sims too
+        // (simulation, threshold) bytes -> threshold-major granules: lane = granule q of the chunk,
+        // threshold t, half h of its 16 simulations
+        tr[wv][lane] = c8;
+        wave_sync();
+        const int q = lane >> 4, t = (lane >> 1) & 7, h = lane & 1;
+        const uint8_t *src = reinterpret_cast<const uint8_t *>(&tr[wv][16 * q + 8 * h]) + t;
+        uint32_t b[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = src[8 * i];
+        wave_sync();
+        const uint32_t kq = k0 + (uint32_t)(16 * q);   // the granule's first simulation
+        if (kq >= n) continue;
+        const int64_t gi = (int64_t)(kq / GRAN2 - win_b);
+        uint2 *__restrict__ dst = tab + (G->unit + gi * (arm ? 1 : 2)) * (UNIT2 / 8) + 2 * t + h;
+        const uint2 v = make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24),
+                                   b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
+        if (arm) {
+            dst[0] = make_uint2(v.x | 0x80808080u, v.y | 0x80808080u);
+        } else {
+            dst[0] = v;
+            uint32_t c[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                c[i] = kq + (uint32_t)(8 * h + i) < n ? (uint32_t)s_cut[b[i]] : 64u;
+            dst[UNIT2 / 8] = make_uint2(c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24),
+                                        c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24));
+        }
+    }
+}
 
-    int since = 0;
-    for (uint32_t k00 = kb; k00 < ke; k00 += CPB * WAVE) {
-        // this wave's Philox blocks of the phase's chunks, (chunk, block) pairs numbered 0..35: wv and
-        // wv + 16, and 32 + wv / 2 for waves 1, 3, 5 and 7, which count the shorter (17-word) halves
-        // (words of a chunk past the item's end are generated and never used)
-        static_assert(CPB * NB == 2 * NWAVES + 4, "two blocks per wave and four more");
-        const int nbb = (wv & 1) && wv < 8 ? 3 : 2;
-        for (int i = 0; i < nbb; ++i) {
-            const int bb = i < 2 ? wv + i * NWAVES : 2 * NWAVES + (wv >> 1);
-            const int c = bb / NB, b = bb - c * NB;
-            const u32x4 w = philox_block((uint32_t)b, k00 + (uint32_t)(c * WAVE + lane), key0, key1);
-            uint32_t(*wc)[WAVE] = words + c * 4 * NB;
-            wc[4 * b + 0][lane] = w.x;
-            wc[4 * b + 1][lane] = w.y;
-            wc[4 * b + 2][lane] = w.z;
-            wc[4 * b + 3][lane] = w.w;
+__global__ __launch_bounds__(WG) void k_b2_tiles(const Blk2 *__restrict__ blocks, const SquareItem *__restrict__ items,
+                                                 const Grp2 *__restrict__ grp, const uint4 *__restrict__ tab,
+                                                 uint32_t win_b, uint32_t win_e, uint32_t *__restrict__ R,
+                                                 unsigned long long *__restrict__ sumT) {
+    static_assert(SQ2R == WG / WAVE && SQ2C * B2V == WAVE, "one wave per row group, one lane per arm-1 threshold");
+    constexpr uint32_t H = 0x80808080u;
+    constexpr int U4 = UNIT2 / 16;   // uint4 per unit
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const SquareItem *__restrict__ I = items + blockIdx.x;
+    const int32_t rg = I->rg[wv];
+    const uint32_t gb = max(I->g_begin, win_b), ge = min(I->g_end, win_e);
+    if (rg < 0 || gb >= ge) return;
+    const int32_t blk = I->blk[wv][lane >> 3];
+    const uint4 *__restrict__ pa = tab + (grp[rg].unit + 2 * (int64_t)(gb - win_b)) * U4;
+    const uint4 *__restrict__ pb = tab + (grp[I->cg[lane >> 3]].unit + (int64_t)(gb - win_b)) * U4 + (lane & 7);
+    uint32_t aR[B2U], a0[B2U], a1[B2U];
+#pragma unroll
+    for (int u = 0; u < B2U; ++u) aR[u] = a0[u] = a1[u] = 0u;
+    for (uint32_t g = gb; g < ge; ++g, pa += 2 * U4, pb += U4) {
+        const uint4 y1 = *pb;
+        uint4 y0[B2U], c0[B2U];
+#pragma unroll
+        for (int u = 0; u < B2U; ++u) {
+            y0[u] = pa[u];
+            c0[u] = pa[U4 + u];
         }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < CPB; ++c) {
-            uint32_t yc[B2U];
-#pragma unroll
-            for (int u = 0; u < B2U; ++u) yc[u] = 0u;
-            if (counting) {
-                uint32_t(*wc)[WAVE] = words + c * 4 * NB;
-#pragma unroll 6
-                for (int j = 0; j < jn; ++j) {
-                    const uint32_t x = wc[jw0 + j][lane];
-#pragma unroll
-                    for (int u = 0; u < B2U; ++u) yc[u] += (x < Tc[u]) ? 1u : 0u;
-                }
-            }
-            cnt[c][wv][lane] = make_uint2(yc[0] | (yc[1] << 8) | (yc[2] << 16) | (yc[3] << 24),
-                                          yc[4] | (yc[5] << 8) | (yc[6] << 16) | (yc[7] << 24));
-        }
-        __syncthreads();   // words consumed, counts shared: the next phase (or a flush) may overwrite the words
-#pragma unroll
-        for (int c = 0; c < CPB; ++c) {
-        const uint32_t k0 = k00 + (uint32_t)(c * WAVE);
-        if (!live || k0 >= ke) break;   // uniform: the item's range ends in the phase's first chunk
-        const uint32_t k = k0 + (uint32_t)lane;
-        const bool act = k < ke;
-        {
-            // the batch's row set (arm-0 counts) and column set (arm-1 counts), each the byte-wise
-            // sum of its two halves
-            const uint2 ra = cnt[c][rsrc][lane], rb = cnt[c][rsrc + 1][lane];
-            const uint2 ca = cnt[c][csrc2][lane], cb = cnt[c][csrc2 + 1][lane];
-            const uint2 rc = make_uint2(ra.x + rb.x, ra.y + rb.y);
-            const uint2 cc = make_uint2(ca.x + cb.x, ca.y + cb.y);
-            int y0[B2U], y1[B2V];
-#pragma unroll
-            for (int u = 0; u < B2U; ++u) y0[u] = (int)(((u < 4 ? rc.x : rc.y) >> (8 * (u & 3))) & 0xFFu);
-#pragma unroll
-            for (int v = 0; v < B2V; ++v) y1[v] = (int)(((v < 4 ? cc.x : cc.y) >> (8 * (v & 3))) & 0xFFu);
-            if (KEYS) {
-                // the block's records are padded to whole chunks: lanes past N store too (the
-                // selection reads records k < N only)
-                rbase[k] = make_uint4(rc.x, rc.y, cc.x, cc.y);
-            }
-            // reject indicator r = [y1 >= c(y0)] = med3(y1 - c + 1, 0, 1), added as r * packed
-            // (24-bit multiply-add; no compare masks, so nothing is held in scalar registers)
-            int cm[B2U];
-            uint32_t P0[B2U], P1[B2V];
+        auto quad = [&](uint32_t v, auto part) {
 #pragma unroll
             for (int u = 0; u < B2U; ++u) {
-                cm[u] = (act ? s_cut[y0[u]] : 64) - 1;
-                P0[u] = 1u | ((uint32_t)y0[u] << 6);
+                const uint32_t m = (v - part(c0[u])) & H;
+                aR[u] += (uint32_t)__popc(m);
+                a0[u] = __builtin_amdgcn_udot4(m, part(y0[u]), a0[u], false);
+                a1[u] = __builtin_amdgcn_udot4(m, v, a1[u], false);
             }
-#pragma unroll
-            for (int v = 0; v < B2V; ++v) P1[v] = (uint32_t)y1[v] << 18;
-#pragma unroll
-            for (int u = 0; u < B2U; ++u)
-#pragma unroll
-                for (int v = 0; v < B2V; ++v) {
-                    const uint32_t r = (uint32_t)min(max(y1[v] - cm[u], 0), 1);
-                    acc[u * B2V + v] += __umul24(r, P0[u] + P1[v]);
-                }
-        }
-        }
-        since += CPB;
-        if (since > 63 - CPB) {   // at most 63 simulations per lane between flushes
-            flush();
-            since = 0;
-        }
+        };
+        quad(y1.x, [](const uint4 &q) { return q.x; });
+        quad(y1.y, [](const uint4 &q) { return q.y; });
+        quad(y1.z, [](const uint4 &q) { return q.z; });
+        quad(y1.w, [](const uint4 &q) { return q.w; });
     }
-    flush();
-    if (!live) return;
+    if (blk < 0) return;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {   // combine the two lane halves of each slot
-        totR[h] += __shfl_xor(totR[h], HALF);
-        tot0[h] += __shfl_xor(tot0[h], HALF);
-        tot1[h] += __shfl_xor(tot1[h], HALF);
-    }
-    if (lane >= HALF) return;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int32_t tile = B->tile[h * HALF + lane];
-        if (tile >= 0) {
-            atomicAdd(&R[tile], totR[h]);
-            atomicAdd(&sumT[2 * (int64_t)tile], (unsigned long long)tot0[h]);
-            atomicAdd(&sumT[2 * (int64_t)tile + 1], (unsigned long long)tot1[h]);
+    for (int u = 0; u < B2U; ++u) {
+        const int32_t t = blocks[blk].tile[u * B2V + (lane & 7)];
+        if (t >= 0 && aR[u]) {
+            atomicAdd(&R[t], aR[u]);
+            atomicAdd(&sumT[2 * (int64_t)t], (unsigned long long)(a0[u] >> 7));
+            atomicAdd(&sumT[2 * (int64_t)t + 1], (unsigned long long)((a1[u] >> 7) - 128u * aR[u]));
         }
     }
 }
@@ -376,18 +315,25 @@ __global__ __launch_bounds__(WG) void k_ztest1_plain(float theta, float cut, uin
 
 // ------------------------------------------------------------------------------ launchers
 hipError_t launch_binom2(const Platten &P, uint64_t seed, uint32_t *R, unsigned long long *sumT,
-                         uint4 *keys, hipStream_t st) {
-    const int64_t grid = P.n_gitems;
-    if (grid <= 0) return hipSuccess;
+                         uint2 *recs, hipStream_t st) {
+    if (P.n_gitems <= 0) return hipSuccess;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-    if (keys)
-        hipLaunchKernelGGL(k_binom2<true>, dim3((uint32_t)grid), dim3(WG2), 0, st,
-                           (const Blk2 *)P.d_blocks, P.d_sqitems, P.n_gitems, k0, k1, P.d_cut_tbl, R,
-                           sumT, keys);
-    else
-        hipLaunchKernelGGL(k_binom2<false>, dim3((uint32_t)grid), dim3(WG2), 0, st,
-                           (const Blk2 *)P.d_blocks, P.d_sqitems, P.n_gitems, k0, k1, P.d_cut_tbl, R,
-                           sumT, keys);
+    const uint32_t total = (uint32_t)((P.max_N + GRAN2 - 1) / GRAN2);
+    for (uint32_t wb = 0; wb < total; wb += (uint32_t)P.b2_win) {
+        const uint32_t we = std::min<uint32_t>(total, wb + (uint32_t)P.b2_win);
+        // counting: enough workgroups to fill the chip, each chunk's words drawn once per workgroup
+        const uint32_t chunks = (we - wb + 3) / 4;
+        const uint32_t per = (uint32_t)((P.n_grp2 + WG / WAVE - 1) / (WG / WAVE));
+        const uint32_t split = std::min<uint32_t>(per, std::max<uint32_t>(1u, 4096u / chunks));
+        if (recs)
+            hipLaunchKernelGGL(k_b2_count<true>, dim3(chunks, split), dim3(WG), 0, st, P.d_grp2, P.n_grp2, wb, we, k0,
+                               k1, P.d_cut_tbl, (uint2 *)P.d_b2tab, recs);
+        else
+            hipLaunchKernelGGL(k_b2_count<false>, dim3(chunks, split), dim3(WG), 0, st, P.d_grp2, P.n_grp2, wb, we, k0,
+                               k1, P.d_cut_tbl, (uint2 *)P.d_b2tab, recs);
+        hipLaunchKernelGGL(k_b2_tiles, dim3((uint32_t)P.n_gitems), dim3(WG), 0, st, (const Blk2 *)P.d_blocks,
+                           P.d_sqitems, P.d_grp2, P.d_b2tab, wb, we, R, sumT);
+    }
     return hipGetLastError();
 }
 

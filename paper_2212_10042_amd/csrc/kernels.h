@@ -4,8 +4,10 @@
 
 namespace cse {
 
+// counts of every threshold group into the count table (and, when recs is not NULL, the calibration
+// workspace), then the per-tile sums
 hipError_t launch_binom2(const Platten &P, uint64_t seed, uint32_t *R, unsigned long long *sumT,
-                         uint4 *recs, hipStream_t st);
+                         uint2 *recs, hipStream_t st);
 hipError_t launch_ztest1(const Platten &P, uint64_t seed, uint32_t *R, unsigned long long *sumZfx,
                          float *keys, hipStream_t st);
 hipError_t launch_plain_tile(const Platten &P, uint64_t seed, int64_t t, uint32_t T0, uint32_t T1,

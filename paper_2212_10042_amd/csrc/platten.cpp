@@ -735,10 +735,11 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
                 Blk2 nb{};
                 for (int j = 0; j < B2U * B2V; ++j) nb.tile[j] = -1;
                 int64_t b0 = (c0 / B2U) * B2U, b1 = (c1 / B2V) * B2V;
+                // past the last distinct value: repeat it (no tile there; the thresholds stay ascending)
                 for (int u = 0; u < B2U; ++u)
-                    nb.T0[u] = (b0 + u < (int64_t)u0.size()) ? bern_threshold(u0[b0 + u]) : 0u;
+                    nb.T0[u] = bern_threshold(u0[std::min<size_t>(b0 + u, u0.size() - 1)]);
                 for (int v = 0; v < B2V; ++v)
-                    nb.T1[v] = (b1 + v < (int64_t)u1.size()) ? bern_threshold(u1[b1 + v]) : 0u;
+                    nb.T1[v] = bern_threshold(u1[std::min<size_t>(b1 + v, u1.size() - 1)]);
                 nb.n_sims = P->tile_N[t];
                 vec.push_back(nb);
                 B = &vec.back();
@@ -753,17 +754,62 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
                 P->blk_col.push_back(std::get<2>(kv.first));
             }
         P->n_blocks = (int64_t)blks.size();
-        for (auto &B : blks) {
+        // threshold groups: one per (simulation count, row) and (simulation count, column) of blocks
+        std::vector<Grp2> grps;
+        {
+            std::map<std::pair<int32_t, int64_t>, int32_t> rows, cols;
+            for (size_t b = 0; b < blks.size(); ++b)
+                for (int arm = 0; arm < 2; ++arm) {
+                    auto &m = arm ? cols : rows;
+                    const int64_t at = arm ? P->blk_col[b] : P->blk_row[b];
+                    auto ins = m.emplace(std::make_pair(blks[b].n_sims, at), (int32_t)grps.size());
+                    if (ins.second) {
+                        Grp2 g{};
+                        memcpy(g.T, arm ? blks[b].T1 : blks[b].T0, sizeof g.T);
+                        g.arm = arm;
+                        g.n_sims = blks[b].n_sims;
+                        grps.push_back(g);
+                    }
+                    (arm ? P->blk_cg : P->blk_rg).push_back(ins.first->second);
+                }
+        }
+        // count table: all simulations of every group at once where that fits B2_TABLE_MAX, else
+        // equal windows of simulations (at least one chunk of 64)
+        auto granules = [](const Grp2 &g) { return ((int64_t)g.n_sims + GRAN2 - 1) / GRAN2; };
+        auto units = [&](int64_t win) {
+            int64_t n = 0;
+            for (auto &g : grps) n += std::min(win, granules(g)) * (g.arm ? 1 : 2);
+            return n;
+        };
+        P->b2_win = (((int64_t)P->max_N + GRAN2 - 1) / GRAN2 + 3) / 4 * 4;
+        while (P->b2_win > 4 && units(P->b2_win) * UNIT2 > B2_TABLE_MAX) P->b2_win = (P->b2_win / 2 + 3) / 4 * 4;
+        P->b2_units = units(P->b2_win);
+        {
+            int64_t u = 0, r = 0;
+            for (auto &g : grps) {
+                g.unit = u;
+                g.rec = r;
+                u += std::min(P->b2_win, granules(g)) * (g.arm ? 1 : 2);
+                r += ((int64_t)g.n_sims + 63) / 64 * 64;
+            }
+            P->b2_recs = r;
+        }
+        P->n_grp2 = (int32_t)grps.size();
+        for (size_t b = 0; b < blks.size(); ++b) {
+            Blk2 &B = blks[b];
             blk_sims.push_back(B.n_sims);
-            // one 16-byte record per simulation of the block (chunks of 64, the last one padded)
-            B.key_base = P->n_keys;
+            B.rec0 = grps[P->blk_rg[b]].rec;
+            B.rec1 = grps[P->blk_cg[b]].rec;
             for (int j = 0; j < B2U * B2V; ++j)
                 if (B.tile[j] >= 0) {
-                    key_off[B.tile[j]] = B.key_base;   // the block's first record
+                    key_off[B.tile[j]] = (int64_t)b;   // the tile's block
                     key_stride[B.tile[j]] = j;         // the tile's slot u * 8 + v
                 }
+            // key slots: 16 bytes per (simulation, block); the groups' entries (8 bytes per
+            // simulation and group, at most two groups per block) never take more
             P->n_keys += ((int64_t)B.n_sims + 63) / 64 * 64;
         }
+        stage.add(&P->d_grp2, grps.data(), grps.size());
         stage.add((Blk2 **)&P->d_blocks, blks.data(), blks.size());
 
         // design tables of the pooled z test
@@ -891,6 +937,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
     CSE_HIP_TRY(hipMalloc((void **)&P->d_lamg, sizeof(double)));
     CSE_HIP_TRY(hipMalloc((void **)&P->d_minpart, 2 * MIN_PARTS * sizeof(double)));
     if (kind == CSE_BINOM2_Z) {
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2tab, (size_t)P->b2_units * UNIT2));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2cut, (size_t)P->n_blocks * B2U * (NP35 + 1) * sizeof(uint4)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2br, nt * sizeof(int2)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2fb, (nt + 1) * sizeof(uint32_t)));
@@ -958,19 +1005,19 @@ int h4_regions(Platten *P) {
 }
 
 int plan_group_items(Platten *P, int64_t target_wgs) {
-    std::vector<std::vector<int64_t>> groups;   // up to 4 (16 for the 2-arm design) blocks each (-1: none)
+    std::vector<std::vector<int64_t>> groups;   // up to 4 (32 for the 2-arm design) blocks each (-1: none)
     const bool sq2 = P->design.kind == CSE_BINOM2_Z;
     if (sq2) {
-        // 4 x 4 squares of blocks of equal N: block (row r, column c) goes to position
-        // 4 (r & 3) + (c & 3) of square (r >> 2, c >> 2); a second block with the same
-        // coordinates (two tiles at one grid point) opens another square
+        // rectangles of 4 row groups x 8 column groups of blocks of equal N: block (row r, column
+        // c) goes to position 8 (r & 3) + (c & 7) of rectangle (r >> 2, c >> 3); a second block
+        // with the same coordinates (two tiles at one grid point) opens another rectangle
         std::map<std::tuple<int64_t, int64_t, int64_t, int64_t>, std::vector<int64_t>> sq;
         for (int64_t b = 0; b < P->n_blocks; ++b) {
             const int64_t r = P->blk_row[b], c = P->blk_col[b];
-            const int pos = (int)(((r & (SQ2 - 1)) * SQ2) | (c & (SQ2 - 1)));
+            const int pos = (int)((r % SQ2R) * SQ2C + c % SQ2C);
             for (int64_t dup = 0;; ++dup) {
-                auto &g = sq[std::make_tuple(P->blk_sims[b], r / SQ2, c / SQ2, dup)];
-                if (g.empty()) g.assign(SQ2W, -1);
+                auto &g = sq[std::make_tuple(P->blk_sims[b], r / SQ2R, c / SQ2C, dup)];
+                if (g.empty()) g.assign(SQ2R * SQ2C, -1);
                 if (g[pos] < 0) {
                     g[pos] = b;
                     break;
@@ -991,6 +1038,9 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
     // at least 4 chunks of 64 simulations per item: an item's fixed work (thresholds, the final
     // transposes and atomics) then stays small beside its simulations
     constexpr int64_t MIN_ITEM_CHUNKS = 4;
+    // 2-arm items: the kernel's 32-bit sums hold 2^32 / (128 * 163) simulations; below two granules
+    // an item's fixed work (the atomics) is most of it
+    constexpr int64_t B2_ITEM_MAX = 8192, B2_ITEM_MIN = 2;
     std::vector<GroupItem> gi, gpil;
     std::vector<SquareItem> si;
     int64_t gs = 0;
@@ -1000,9 +1050,40 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
         for (int64_t b : g)
             if (b >= 0 && first < 0) first = b;
         const int64_t N = P->blk_sims[first];
+        if (sq2) {
+            // granules per item: at most B2_ITEM_MAX (the kernel's 32-bit sums)
+            const int64_t ng16 = (N + GRAN2 - 1) / GRAN2;
+            const int64_t per = std::min<int64_t>(B2_ITEM_MAX, std::max<int64_t>(B2_ITEM_MIN, (ng16 + slices - 1) / slices));
+            SquareItem it{};
+            for (int c = 0; c < SQ2C; ++c) {   // the columns that hold a block, packed to the front
+                int32_t cg = -1;
+                for (int r = 0; r < SQ2R; ++r)
+                    if (g[r * SQ2C + c] >= 0) cg = P->blk_cg[g[r * SQ2C + c]];
+                if (cg < 0) continue;
+                it.cg[it.ncg] = cg;
+                for (int r = 0; r < SQ2R; ++r) it.blk[r][it.ncg] = (int32_t)g[r * SQ2C + c];
+                ++it.ncg;
+            }
+            for (int c = it.ncg; c < SQ2C; ++c) {   // the rest: the last one's counts, no block
+                it.cg[c] = it.cg[it.ncg - 1];
+                for (int r = 0; r < SQ2R; ++r) it.blk[r][c] = -1;
+            }
+            for (int r = 0; r < SQ2R; ++r) {
+                it.rg[r] = -1;
+                for (int c = 0; c < it.ncg; ++c)
+                    if (it.blk[r][c] >= 0) it.rg[r] = P->blk_rg[it.blk[r][c]];
+            }
+            for (int64_t k0 = 0; k0 < ng16; k0 += per) {
+                it.g_begin = (uint32_t)k0;
+                it.g_end = (uint32_t)std::min<int64_t>(ng16, k0 + per);
+                gs += std::min<int64_t>(N, it.g_end * (int64_t)GRAN2) - (int64_t)it.g_begin * GRAN2;
+                si.push_back(it);
+            }
+            continue;
+        }
         const int64_t chunks = (N + WAVE - 1) / WAVE;
         const int64_t per = std::max<int64_t>(MIN_ITEM_CHUNKS, (chunks + slices - 1) / slices) * WAVE;
-        if (!sq2) {
+        {
             // bracketed keys: the pilot's ranges, and room for twice the candidates an item range
             // expects (the bracket holds at most SEL_FILL_H4 of H4_SELCAND keys of the tile on
             // average) plus 32
@@ -1026,13 +1107,7 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
         for (int64_t k0 = 0; k0 < N; k0 += per) {
             const uint32_t kb = (uint32_t)k0, ke = (uint32_t)std::min<int64_t>(N, k0 + per);
             gs += (int64_t)(ke - kb);
-            if (sq2) {
-                SquareItem it{};
-                for (int w = 0; w < SQ2W; ++w) it.blk[w] = w < (int)g.size() ? (int32_t)g[w] : -1;
-                it.k_begin = kb;
-                it.k_end = ke;
-                si.push_back(it);
-            } else {
+            {
                 GroupItem it{};
                 for (int w = 0; w < 4; ++w) it.blk[w] = w < (int)g.size() ? (int32_t)g[w] : -1;
                 it.k_begin = kb;
@@ -1104,7 +1179,7 @@ void free_platten(Platten *P) {
                     P->d_cls_off, P->d_cp_base, P->d_cp_mark, P->d_cp_tbl,  P->d_radii,
                     P->d_is_box, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
                     P->d_queue,  P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
-                    P->d_h4mask, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
+                    P->d_h4mask, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
                     P->d_gitems_pilot, P->d_h4brk, P->d_h4below, P->d_h4cnt, P->d_h4cand, P->d_h4fb};
     auto in_arena = [&](void *q) {
         for (auto &a : P->arenas)
