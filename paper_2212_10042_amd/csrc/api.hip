@@ -179,7 +179,7 @@ int run_sim(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bo
         Timed tm(keys ? "phase23_calib" : "phase23", st);
         CSE_LAUNCH(cse::launch_phase23(P, seed, P.d_Rw, P.d_Tw, (float *)keys, st));
     } else {
-        CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * P.d * sizeof(unsigned long long), st));
+        CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * sizeof(unsigned long long), st));   // packed pairs
         Timed tm(keys ? "binom2_calib" : "binom2", st);
         CSE_LAUNCH(cse::launch_binom2(P, seed, P.d_Rw, P.d_Tw, (uint2 *)keys, st));
     }

@@ -51,7 +51,7 @@ struct Grp2 {
 };
 constexpr int GRAN2 = 16;              // simulations per granule of the count table
 constexpr int UNIT2 = B2U * GRAN2;     // bytes per unit
-constexpr int64_t B2_TABLE_MAX = (int64_t)64 << 20;   // count-table bytes (more: simulation windows)
+constexpr int64_t B2_TABLE_MAX = (int64_t)128 << 20;   // count-table bytes (more: simulation windows)
 constexpr int REC2_BYTES = 16;   // calibration workspace bound: bytes per (simulation, batch)
 
 // z-test: 64 tiles share each simulation's normal draw.

@@ -1387,7 +1387,7 @@ __global__ __launch_bounds__(1024) void k_min_part(const double *__restrict__ v,
 
 // Score-function gradient (sum over rejections of T(x) - R grad A(theta)) / N, float64;
 // also the float64 score sums and int32 counts for the caller's buffers.
-__global__ void k_finish(int fam, int n, int d, int score_n, int64_t n_tiles, const double *__restrict__ theta,
+__global__ void k_finish(int fam, int n, int d, int score_n, int packed, int64_t n_tiles, const double *__restrict__ theta,
                          const int32_t *__restrict__ N, const uint32_t *__restrict__ R,
                          const unsigned long long *__restrict__ sumT,
                          const unsigned long long *__restrict__ sumZfx, int32_t *__restrict__ R_out,
@@ -1419,8 +1419,9 @@ __global__ void k_finish(int fam, int n, int d, int score_n, int64_t n_tiles, co
         }
         return;
     }
+    const unsigned long long pair = packed ? sumT[t] : 0ull;   // 2-arm sums: y0 in the low word, y1 in the high one
     for (int a = 0; a < d; ++a) {
-        const unsigned long long s = sumT[t * d + a];
+        const unsigned long long s = packed ? (a ? pair >> 32 : pair & 0xFFFFFFFFull) : sumT[t * d + a];
         if (T_out) T_out[t * d + a] = (int64_t)s;
         if (grad) {
             const double th = theta[t * d + a];
@@ -1547,7 +1548,8 @@ hipError_t launch_finish(const Platten &P, const uint32_t *R, const unsigned lon
                          double *Z_out, double *grad, hipStream_t st) {
     const int64_t grid = (P.n_tiles + 255) / 256;
     hipLaunchKernelGGL(k_finish, dim3((uint32_t)grid), dim3(256), 0, st, P.family, P.n_per_arm, P.d,
-                       P.design.kind == CSE_PHASE23 ? 1 : 0, P.n_tiles, P.d_theta, P.d_N, R, sumT, sumZfx, R_out, T_out, Z_out, grad);
+                       P.design.kind == CSE_PHASE23 ? 1 : 0,
+                       P.design.kind == CSE_BINOM2_Z ? 1 : 0, P.n_tiles, P.d_theta, P.d_N, R, sumT, sumZfx, R_out, T_out, Z_out, grad);
     return hipGetLastError();
 }
 

@@ -39,10 +39,16 @@ __device__ __forceinline__ void wave_sync() {
 // each byte of their difference is the decision (y1 + 128 - c lies in [64, 163]: no borrow);
 // masked to those bits it is the weight (128 or 0) of three accumulations: a bit count for R and
 // two 4-byte dot products for the sums of y0 and y1: 5 instructions per 4 simulations and tile.
-// Bound by VALU issue (89% of its peak).  1024 x 1024 boxes x 16,384 simulations: counts 0.08 ms
-// and sums 0.61 ms, where one kernel counting per 4 x 4 batches and deciding one simulation at a
-// time took 5.06 ms and wrote 4.3 GB of records that the selection read back; 256 x 256 lower
-// triangle x 8,192: 0.168 -> 0.017 + 0.041 ms.
+// A quad (4 simulations) that none of the wave's 512 tiles rejects, or that all of them reject, is
+// recognised by its extremes and takes none or 9 instructions instead of 40: far from the power
+// curve's slope that is nearly every quad.  The sums of y0 and y1 (at most 35 * 2^24 each) go to
+// memory as the halves of one 64-bit atomic.
+//
+// Bound by VALU issue on large grids, by the atomics and load latency on small ones.  1024 x 1024
+// boxes x 16,384 simulations: counts 0.08 ms and sums 0.33 ms (0.61 with the 5 instructions for
+// every quad: 89% of the VALU issue peak), where one kernel that counted per square of batches and
+// decided one simulation at a time took 5.06 ms and wrote 4.3 GB of records for the selection to
+// read back; 256 x 256 lower triangle x 8,192: 0.168 -> 0.017 + 0.018 ms.
 // ------------------------------------------------------------------------------------
 template <bool RECS>
 __global__ __launch_bounds__(WG) void k_b2_count(const Grp2 *__restrict__ grp, int32_t n_grp, uint32_t win_b,
@@ -137,6 +143,12 @@ __global__ __launch_bounds__(WG) void k_b2_tiles(const Blk2 *__restrict__ blocks
     uint32_t aR[B2U], a0[B2U], a1[B2U];
 #pragma unroll
     for (int u = 0; u < B2U; ++u) aR[u] = a0[u] = a1[u] = 0u;
+    // simulations of the quads that every tile rejects, and their sums
+    uint32_t all = 0u, a1all = 0u, a0all[B2U];
+#pragma unroll
+    for (int u = 0; u < B2U; ++u) a0all[u] = 0u;
+    uint32_t h = H;
+    asm("" : "+v"(h));   // the weight in a vector register, beside a scalar operand
     for (uint32_t g = gb; g < ge; ++g, pa += 2 * U4, pb += U4) {
         const uint4 y1 = *pb;
         uint4 y0[B2U], c0[B2U];
@@ -145,13 +157,30 @@ __global__ __launch_bounds__(WG) void k_b2_tiles(const Blk2 *__restrict__ blocks
             y0[u] = pa[u];
             c0[u] = pa[U4 + u];
         }
-        auto quad = [&](uint32_t v, auto part) {
+        // the granule's scalar loads issued together, ahead of the branches (not one by one inside)
 #pragma unroll
-            for (int u = 0; u < B2U; ++u) {
-                const uint32_t m = (v - part(c0[u])) & H;
-                aR[u] += (uint32_t)__popc(m);
-                a0[u] = __builtin_amdgcn_udot4(m, part(y0[u]), a0[u], false);
-                a1[u] = __builtin_amdgcn_udot4(m, v, a1[u], false);
+        for (int u = 0; u < B2U; ++u)
+            asm volatile("" ::"s"(y0[u].x), "s"(y0[u].y), "s"(y0[u].z), "s"(y0[u].w), "s"(c0[u].x), "s"(c0[u].y),
+                         "s"(c0[u].z), "s"(c0[u].w));
+        auto quad = [&](uint32_t v, auto part) {
+            // counts and cut points ascend with the threshold: lane 63 has the largest y1, row 0 the
+            // smallest c, and the other way round
+            const uint32_t hi = (__builtin_amdgcn_readlane(v, WAVE - 1) - part(c0[0])) & H;
+            const uint32_t lo = (__builtin_amdgcn_readlane(v, 0) - part(c0[B2U - 1])) & H;
+            if (hi != 0u && lo != H) {
+#pragma unroll
+                for (int u = 0; u < B2U; ++u) {
+                    const uint32_t m = (v - part(c0[u])) & H;
+                    aR[u] += (uint32_t)__popc(m);
+                    a0[u] = __builtin_amdgcn_udot4(m, part(y0[u]), a0[u], false);
+                    a1[u] = __builtin_amdgcn_udot4(m, v, a1[u], false);
+                }
+            }
+            if (lo == H) {
+                all += 4u;
+                a1all = __builtin_amdgcn_udot4(v, H, a1all, false);
+#pragma unroll
+                for (int u = 0; u < B2U; ++u) a0all[u] = __builtin_amdgcn_udot4(h, part(y0[u]), a0all[u], false);
             }
         };
         quad(y1.x, [](const uint4 &q) { return q.x; });
@@ -163,10 +192,11 @@ __global__ __launch_bounds__(WG) void k_b2_tiles(const Blk2 *__restrict__ blocks
 #pragma unroll
     for (int u = 0; u < B2U; ++u) {
         const int32_t t = blocks[blk].tile[u * B2V + (lane & 7)];
-        if (t >= 0 && aR[u]) {
-            atomicAdd(&R[t], aR[u]);
-            atomicAdd(&sumT[2 * (int64_t)t], (unsigned long long)(a0[u] >> 7));
-            atomicAdd(&sumT[2 * (int64_t)t + 1], (unsigned long long)((a1[u] >> 7) - 128u * aR[u]));
+        const uint32_t r = aR[u] + all;
+        if (t >= 0 && r) {
+            atomicAdd(&R[t], r);
+            const uint32_t s0 = (a0[u] + a0all[u]) >> 7, s1 = ((a1[u] + a1all) >> 7) - 128u * r;
+            atomicAdd(&sumT[t], (unsigned long long)s0 | ((unsigned long long)s1 << 32));
         }
     }
 }

@@ -886,9 +886,8 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
     for (int64_t b = 0; b < P->n_blocks; ++b) P->block_sims += blk_sims[b];
     if (P->n_blocks > 0)
         if (int e = plan_work_items(P, P->tune_waves)) return e;
-    // default workgroup counts (measured against cse_autotune): the 2-arm kernel's workgroups
-    // hold 16 waves, the 4-arm kernels' 4
-    if (kind == CSE_BINOM2_Z) P->tune_wgs = 2048;
+    // default workgroup counts, measured (the 2-arm design's: plan_group_items, from its rectangles)
+    if (kind == CSE_BINOM2_Z) P->tune_wgs = 0;
     if (kind == CSE_BINOM2_Z || kind == CSE_HIER4 || kind == CSE_BASKET4)
         if (int e = plan_group_items(P, P->tune_wgs)) return e;
 
@@ -1033,6 +1032,21 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
         }
     }
     const int64_t ng = (int64_t)groups.size();
+    if (sq2 && target_wgs == 0) {
+        // 64 granules (1,024 simulations) per item: shorter items spend their time in the final
+        // atomics, longer ones leave the chip waiting for the rectangles where most quads need the
+        // full step; at least 1,024 workgroups while there are granules for them.  1024 x 1024 boxes
+        // x 16,384 with 2,048 / 4,096 / 8,192 / 16,384 workgroups: 430 / 362 / 333 / 351 us; 256 x 256
+        // triangle x 8,192 with 512 / 1,024 / 2,048: 20.8 / 18.4 / 22.2 us
+        int64_t work = 0;
+        for (auto &g : groups)
+            for (int64_t b : g)
+                if (b >= 0) {
+                    work += (P->blk_sims[b] + GRAN2 - 1) / GRAN2;
+                    break;
+                }
+        target_wgs = std::min<int64_t>(8192, std::max<int64_t>(1024, work / 64));
+    }
     int64_t slices = std::max<int64_t>(1, (target_wgs + ng - 1) / ng);
     if (P->design.kind == CSE_HIER4) slices = std::min<int64_t>(slices, H4_MAXS);
     // at least 4 chunks of 64 simulations per item: an item's fixed work (thresholds, the final

@@ -51,8 +51,8 @@ def test_group_edges_order_and_duplicates(shape):
 
 
 def test_simulation_windows():
-    # five simulation counts of 600,000 each have their own threshold groups: 72 MB of counts at
+    # five simulation counts of 1,150,000 each have their own threshold groups: 138 MB of counts at
     # once, so the table takes the simulations in windows
     th = np.array([[-1.0, -1.1], [-1.5, -1.0], [0.2, 0.4], [-2.0, -1.2], [-0.7, -0.7]])
-    sims = np.array([600_000, 600_001, 600_015, 600_016, 600_063], np.int32)
+    sims = np.array([1_150_000, 1_150_001, 1_150_015, 1_150_016, 1_150_063], np.int32)
     _compare(th, np.full(th.shape, 0.01), sims, 11, calibrate=False)
