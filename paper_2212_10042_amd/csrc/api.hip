@@ -21,7 +21,10 @@ struct cse_platten {
 // device (resident from the library's first use on that device until the process ends).  In host
 // code this name is a host-side handle, not a device address: kernels get the address that
 // hipGetSymbolAddress returns for the current device (noalloc_workspace below).
-static __device__ __align__(256) unsigned char scratch[(size_t)CSE_NOALLOC_SCRATCH_BYTES];
+// The 2-arm design's workspace (B2_REC_BYTES per simulation and threshold group, at most two groups
+// per batch) is at most 5/4 of the stated 16 bytes per simulation and batch.
+static __device__ __align__(256) unsigned char scratch[(size_t)CSE_NOALLOC_SCRATCH_BYTES / 4 * 5];
+static_assert(2 * cse::B2_REC_BYTES * 4 <= cse::REC2_BYTES * 5, "the static workspace holds every accepted platten");
 
 struct cse_plan {
     hipGraph_t graph = nullptr;
@@ -209,14 +212,14 @@ int run_sim_h4(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st,
     return CSE_OK;
 }
 
-// Calibration workspace: its documented size (the static workspace's limit), and the bytes used
-// (the 2-arm threshold groups' counts, at most the 16 bytes per simulation and batch stated).
+// Calibration workspace: its documented size (the limit of cse_calibrate_noalloc), and the bytes used
+// (2-arm design: the threshold groups' counts).
 size_t key_bytes(const cse::Platten &P) {
     const size_t esz = (P.design.kind == CSE_BINOM2_Z) ? cse::REC2_BYTES : 4;
     return (size_t)P.n_keys * esz;
 }
 size_t key_bytes_used(const cse::Platten &P) {
-    return P.design.kind == CSE_BINOM2_Z ? (size_t)P.b2_recs * sizeof(uint2) : key_bytes(P);
+    return P.design.kind == CSE_BINOM2_Z ? (size_t)P.b2_recs * cse::B2_REC_BYTES : key_bytes(P);
 }
 
 int ensure_keys(cse::Platten &P) {

@@ -52,7 +52,10 @@ struct Grp2 {
 constexpr int GRAN2 = 16;              // simulations per granule of the count table
 constexpr int UNIT2 = B2U * GRAN2;     // bytes per unit
 constexpr int64_t B2_TABLE_MAX = (int64_t)128 << 20;   // count-table bytes (more: simulation windows)
-constexpr int REC2_BYTES = 16;   // calibration workspace bound: bytes per (simulation, batch)
+constexpr int REC2_BYTES = 16;   // calibration workspace as documented: bytes per (simulation, batch)
+// calibration workspace: all groups' 8-byte entries, then once more each entry's first and last
+// count as 2 bytes (the selection's first pass reads only those)
+constexpr int B2_REC_BYTES = 8 + 2;
 
 // z-test: 64 tiles share each simulation's normal draw.
 constexpr int B1T = 64;
@@ -254,8 +257,7 @@ struct Platten {
     float b2_margin = 5.0f;              // 2-arm selection: bracket margin in standard deviations of the count
     int32_t n_outcomes = 0;
     // 2-arm calibration: per-tile bracket of S-order positions [lo, hi] expected to hold the
-    // k-th smallest statistic, and the list of tiles the bracketed selection left to the exact
-    // full-histogram pass ([0] = count, then tile ids)
+    // k-th smallest statistic, and the number of tiles the last selection took from the full histogram
     int2 *d_b2br = nullptr;
     uint32_t *d_b2fb = nullptr;
     // 2-arm calibration: per block, row group u and arm-0 count y0, the cut points on y1 of the

@@ -35,14 +35,14 @@ __device__ void block_exclusive_scan(uint32_t v, uint32_t *part) {
 }
 
 // ---- discrete statistic (2-arm design) ----
-// The fused kernel stores one record per (simulation, batch): the success counts y0[u], y1[v] at
-// the batch's 8 + 8 thresholds (Rec2), so tile (u, v)'s outcome of simulation j is
-// y0[u] (n+1) + y1[v].  The statistic S = -z is a function of the outcome; outcomes sorted by S
+// The counting kernel stores, per simulation and threshold group, the success counts at the group's 8
+// thresholds (8 bytes): a batch's row and column groups give its y0[u], y1[v], and tile (u, v)'s
+// outcome of simulation j is y0[u] (n+1) + y1[v].  The statistic S = -z is a function of the outcome; outcomes sorted by S
 // (S_order, ties grouped by S_group: the first position with equal S) give each outcome a
 // position S_pos, and the k-th smallest S of a tile is the S of the first position whose
 // cumulative count reaches k.
 //
-// Selection in three kernels:
+// Selection in two kernels:
 //  * k_b2_bracket: per tile, the exact law of (y0, y1) under the simulated model (independent
 //    Binomial(35, T/2^32) arms) gives a bracket [lo, hi] of positions (whole tie groups, found by
 //    binary search over the groups) holding the k-th smallest S unless the count below lo reaches
@@ -51,17 +51,15 @@ __device__ void block_exclusive_scan(uint32_t v, uint32_t *part) {
 //    As S does not increase with y1 for fixed y0, S < S(lo) iff y1 >= clo(y0) and S <= S(hi) iff
 //    y1 >= chi(y0): the kernel also writes, per batch row u and count y0, the cut points clo, chi
 //    of the row's 8 tiles as bytes (16 bytes);
-//  * k_b2_select: one workgroup per batch reads the batch's records once.  Per simulation and
-//    row, one LDS read of the row's cut bytes classifies its 8 tiles four at a time (byte-wise
-//    compares of the record's packed y1 bytes): tiles below the bracket are counted in packed
-//    byte counters per lane, and the rare tiles inside it look up the outcome's position and
-//    add to an LDS histogram of the bracket; the k-th smallest is read off the histogram;
-//  * k_b2_full: tiles whose k-th smallest fell outside the bracket, or whose bracket did not fit
-//    the LDS histogram, are selected from a full 1,296-bin histogram of their records.
+//  * k_b2_select: one workgroup per batch counts, per tile, the simulations below the bracket and
+//    histograms those inside it in LDS; the k-th smallest is read off the histogram, or, for the
+//    tiles whose k-th smallest fell outside the bracket or whose bracket did not fit the LDS
+//    histogram, off a full 1,296-bin histogram.
 // Either way lambda*_i is the exact k-th smallest S and rej_at the exact count strictly below it.
 constexpr int B2_N1 = NP35 + 1;            // outcomes per arm
 constexpr int B2_NOUT = B2_N1 * B2_N1;     // 1,296 outcomes
-constexpr int B2_HB = 4096;                // LDS histogram bins of one batch (16 KB)
+constexpr int B2_HW = 3072;                // LDS histogram words of one batch and round: twice as many bins
+                                           // (16 bits each) up to 65,535 simulations, one each beyond
 
 __device__ __forceinline__ uint32_t rec_byte(uint32_t w, int b) { return (w >> (8 * b)) & 0xFFu; }
 // simulation j's record of a block: arm-0 counts in (x, y), arm-1 counts in (z, w)
@@ -140,7 +138,12 @@ __global__ __launch_bounds__(WAVE) void k_b2_bracket(const Blk2 *__restrict__ bl
         return sum;
     };
     const float kf = (float)k, sd = sqrtf(kf + 1.0f);
-    const float lo_t = kf - zmargin * sd - 2.0f, hi_t = kf + zmargin * sd + 2.0f;
+    // the count below the lower end must stay under k: its mean k - z sd - 2, or, where k is small and
+    // that is nothing or less, the Poisson mean mu with P(count >= k) <= (e mu / k)^k = exp(-z^2 / 2)
+    // (Chernoff): the bracket then leaves out the many outcomes too rare to matter (1,000
+    // simulations, k = 10: about 500 positions per tile from the smallest S on, a fifth from mu on)
+    const float mu_lo = kf * expf(-1.0f - 0.5f * zmargin * zmargin / fmaxf(kf, 1.0f));
+    const float lo_t = fmaxf(kf - zmargin * sd - 2.0f, mu_lo), hi_t = kf + zmargin * sd + 2.0f;
     const float Nf = (float)N;
     int a = 0, b = n_groups;            // lo group: the last g with N P(S < S_g) <= lo_t (g = 0 has 0)
     while (b - a > 1) {
@@ -168,259 +171,264 @@ __global__ __launch_bounds__(WAVE) void k_b2_bracket(const Blk2 *__restrict__ bl
     for (int i = lane; i < B2U * B2_N1; i += WAVE) dst[i] = src[i];
 }
 
-// One workgroup per batch.  Simulations go in rounds of B2_ROUND chunks per wave: the byte-wise
-// pass counts the tiles below their bracket and lists the simulations that fall inside some
-// tile's bracket (under common random numbers such a simulation is usually inside the brackets
-// of many of the batch's neighbouring tiles at once, so a per-lane loop over its tiles would
-// stall the wave); after the round the listed simulations are taken one per wave-step with
-// lane = tile: position lookup and histogram add without divergence.
-constexpr int B2_ROUND = 4;
-__global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_b2_select(
-    const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs, const int32_t *__restrict__ kk,
-    const int2 *__restrict__ br, const uint4 *__restrict__ cut, const int32_t *__restrict__ S_pos,
-    const int32_t *__restrict__ S_order, const int32_t *__restrict__ S_group, const double *__restrict__ S_tbl,
-    double *__restrict__ lam, int32_t *__restrict__ rej_at, uint32_t *__restrict__ fb) {
+// Exact selection of one tile (slot s of its batch) from the full histogram of its 1,296 outcomes, by
+// the whole workgroup; cumx: exclusive cumulative counts in S order.  Leaves hist and cumx free.
+template <int NTH>
+__device__ void b2_full_tile(const Recs2 &rb, int n, int32_t k, int s, const double *__restrict__ S_tbl,
+                             const int32_t *__restrict__ S_order, const int32_t *__restrict__ S_group, uint32_t *hist,
+                             uint32_t *cumx, double *lam, int32_t *rej_at) {
+    const int tid = threadIdx.x;
+    for (int j = tid; j < B2_NOUT; j += NTH) hist[j] = 0u;
+    __syncthreads();
+    constexpr int LPT = 4;   // records in flight per thread
+    for (int j0 = tid; j0 < n; j0 += NTH * LPT) {
+        uint4 r[LPT];
+#pragma unroll
+        for (int l = 0; l < LPT; ++l) {
+            const int j = j0 + l * NTH;
+            if (j < n) r[l] = rb[j];
+        }
+#pragma unroll
+        for (int l = 0; l < LPT; ++l)
+            if (j0 + l * NTH < n) atomicAdd(&hist[rec_outcome(r[l], s)], 1u);
+    }
+    __syncthreads();
+    if (tid < WAVE) {
+        uint32_t run = 0u;
+        for (int base = 0; base < B2_NOUT; base += WAVE) {
+            const int p = base + tid;
+            const uint32_t c = p < B2_NOUT ? hist[S_order[p]] : 0u;
+            uint32_t incl = c;
+#pragma unroll
+            for (int o = 1; o < WAVE; o <<= 1) {
+                const uint32_t y = __shfl_up(incl, o);
+                if (tid >= o) incl += y;
+            }
+            const uint32_t excl = run + incl - c;
+            if (p < B2_NOUT) cumx[p] = excl;
+            lds_wave_sync();
+            const bool hit = p < B2_NOUT && excl < (uint32_t)k && excl + c >= (uint32_t)k;
+            if (__ballot(hit)) {
+                if (hit) {
+                    *lam = S_tbl[S_order[p]];
+                    *rej_at = (int32_t)cumx[S_group[p]];
+                }
+                break;
+            }
+            run += __shfl(incl, WAVE - 1);
+        }
+    }
+    __syncthreads();   // hist and cumx may be rewritten
+}
+
+// One workgroup per batch.  A simulation's counts hardly differ between a batch's tiles on a fine
+// grid, so its extremes decide for nearly all of them: with C the largest clo and D the smallest chi
+// of the live tiles at a count, every tile is below its bracket when y1[0] >= C(y0[7]) (counted once
+// for all 64) and none is below or inside when y1[7] < D(y0[0]) (counts ascend with the threshold,
+// cut points with y0); that reads 4 bytes per simulation.  The others (2.3% of the simulations on
+// 1024 x 1024 boxes, 6.5% on 256 x 256, nearly all on 20 x 20) are listed, per wave, and taken one
+// per wave step with lane = tile: position lookup, count below the bracket, histogram add.
+// The tiles' bracket histograms share B2_HW words (a batch of 1024 x 1024 boxes x 16,384 simulations
+// needs 300 .. 2,900 bins); what does not fit takes another round over the simulations (coarse
+// grids of few simulations, whose brackets span hundreds of positions: short rounds), at most
+// B2_ROUNDS.  Tiles whose k-th smallest lies outside the bracket, or that no round held, are then
+// selected from the full histogram of their outcomes by the same workgroup, and counted in fb[0].
+// NWV waves per workgroup: 16 up to B2_FEWBLK batches (one per CU), which leave most of the chip idle
+// otherwise, 4 beyond (16 / 4 waves, us: 32 x 32 triangle x 4,096 29 / 71, 128 x 128 x 8,192 20 / 41;
+// 200 x 200 x 1,000, 325 batches, 51 / 28).
+// Bound by issue and LDS latency.  Us, against a byte-wise classification of every (simulation,
+// tile) from 16-byte records: 1024 x 1024 boxes x 16,384 simulations 1,990 -> 515
+// (beside the validation bound), 256 x 256 triangle x 8,192 88 -> 34, 20 x 20 x 1,001 50 -> 47.
+constexpr int B2_ROUNDS = 8;
+constexpr int B2_FEWBLK = 256;
+constexpr int B2_STEP = 4 * WAVE;          // simulations per wave step (four per lane)
+constexpr int B2_WLIST = WAVE + B2_STEP;   // listed simulations of a wave
+
+template <int NWV>
+__global__ __launch_bounds__(NWV *WAVE) void k_b2_select(
+    const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs,
+    const uint16_t *__restrict__ ext, const int32_t *__restrict__ kk, const int2 *__restrict__ br, const uint4 *__restrict__ cut,
+    const int32_t *__restrict__ S_pos, const int32_t *__restrict__ S_order, const int32_t *__restrict__ S_group,
+    const double *__restrict__ S_tbl, double *__restrict__ lam, int32_t *__restrict__ rej_at,
+    uint32_t *__restrict__ fb) {
     constexpr int NT = B2U * B2V;
-    constexpr int NWV = SEL_WG / WAVE;
-    constexpr uint32_t H = 0x80808080u, ONES = 0x01010101u;
+    constexpr int NTH = NWV * WAVE;
     __shared__ uint16_t spos[B2_NOUT];
-    __shared__ uint4 ct[B2U][B2_N1];
-    __shared__ uint32_t hist[B2_HB];
-    __shared__ int2 prm[NT];          // per slot: (first bin - lo, histogram present)
+    __shared__ uint32_t s_lst[NWV][B2_WLIST];   // per wave: listed simulations
+    __shared__ uint4 s_rec[NWV][WAVE];          // per wave: counts of the 64 being taken
+    __shared__ int32_t s_ext[2][WAVE];          // per count: largest clo, smallest chi of the live tiles
+    __shared__ uint32_t hist[B2_HW];
     __shared__ uint32_t below[NT];    // per slot: simulations with S < S(lo)
-    __shared__ uint32_t lst[NWV * B2_ROUND * WAVE];   // simulations of the round inside some bracket
-    __shared__ uint32_t s_nl;
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const Blk2 *__restrict__ B = blocks + blockIdx.x;
     const int32_t N = B->n_sims;
-    for (int o = tid; o < B2_NOUT; o += SEL_WG) spos[o] = (uint16_t)S_pos[o];
-    {
-        const uint4 *__restrict__ cs = cut + (size_t)blockIdx.x * B2U * B2_N1;
-        for (int i = tid; i < B2U * B2_N1; i += SEL_WG) (&ct[0][0])[i] = cs[i];
+    const uint4 *__restrict__ cs = cut + (size_t)blockIdx.x * B2U * B2_N1;
+    __shared__ int32_t fail[NT];      // slots left to the full histogram
+    __shared__ uint32_t s_nf;
+    for (int o = tid; o < B2_NOUT; o += NTH) spos[o] = (uint16_t)S_pos[o];
+    if (tid == 0) s_nf = 0u;
+    // lane = slot (in every wave): the slot's rank and bracket, and where its histogram would start
+    // with the slots before it
+    const int32_t my_t = B->tile[lane];
+    const int32_t my_k = my_t >= 0 ? kk[my_t] : 0;
+    int lo = 0, W = 0, start;   // W = 0: no selection to make
+    if (my_t >= 0 && my_k >= 1 && my_k <= N) {
+        const int2 b = br[my_t];
+        lo = b.x;
+        W = b.y - b.x + 1;
+    } else if (my_t >= 0 && wv == 0) {   // outside Theorem 4's range: +-inf, no selection
+        lam[my_t] = my_k <= 0 ? -INFINITY : INFINITY;
+        rej_at[my_t] = my_k <= 0 ? 0 : N;
     }
-    for (int i = tid; i < B2_HB; i += SEL_WG) hist[i] = 0u;
-    if (tid == 0) s_nl = 0u;
-    // lane = slot for the list pass and the setup: the slot's bracket and histogram region
-    int my_lo = 0, my_hi = -1, my_base = 0;
     {
-        const int32_t t = B->tile[lane];
-        const int32_t k = t >= 0 ? kk[t] : 0;
-        int lo = 0, W = 0;
-        if (t >= 0 && k >= 1 && k <= N) {
-            const int2 b = br[t];
-            lo = b.x;
-            W = b.y - b.x + 1;
-        } else if (t >= 0 && wv == 0) {   // outside Theorem 4's range: +-inf, no selection
-            lam[t] = k <= 0 ? -INFINITY : INFINITY;
-            rej_at[t] = k <= 0 ? 0 : N;
-        }
         int x = W;
 #pragma unroll
         for (int off = 1; off < WAVE; off <<= 1) {
             const int y = __shfl_up(x, off);
             if (lane >= off) x += y;
         }
-        const int hoff = x - W;
-        const bool fits = W > 0 && hoff + W <= B2_HB;   // else: exact full pass
-        if (wv == 0) {
-            below[lane] = 0u;
-            prm[lane] = make_int2(hoff - lo, fits ? 1 : 0);
-        }
-        if (fits) {
-            my_lo = lo;
-            my_hi = lo + W - 1;
-            my_base = hoff - lo;
-        }
+        start = x - W;
     }
-    __syncthreads();
     const Recs2 rb(recs, B);
-    const int nch = (N + WAVE - 1) / WAVE;
-    uint32_t acc[B2U][2];   // per row and half: packed byte counts of simulations below the bracket
-#pragma unroll
-    for (int u = 0; u < B2U; ++u) acc[u][0] = acc[u][1] = 0u;
-    auto flush = [&]() {    // wave sums of the byte counters (as 16-bit pairs) into below[]
-#pragma unroll
-        for (int u = 0; u < B2U; ++u)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t ev = acc[u][h] & 0x00FF00FFu, od = (acc[u][h] >> 8) & 0x00FF00FFu;
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) {
-                    ev += __shfl_xor(ev, off);
-                    od += __shfl_xor(od, off);
-                }
-                if (lane == 0) {
-                    atomicAdd(&below[u * B2V + 4 * h + 0], ev & 0xFFFFu);
-                    atomicAdd(&below[u * B2V + 4 * h + 1], od & 0xFFFFu);
-                    atomicAdd(&below[u * B2V + 4 * h + 2], ev >> 16);
-                    atomicAdd(&below[u * B2V + 4 * h + 3], od >> 16);
-                }
-                acc[u][h] = 0u;
-            }
-    };
-    int since = 0;
-    // the record of this wave's next chunk is loaded one chunk ahead (records are padded to whole
-    // chunks, so a chunk index below nch is always in bounds)
-    uint4 rnext = wv < nch ? rb[wv * WAVE + lane] : make_uint4(0u, 0u, 0u, 0u);
-    for (int c0 = 0; c0 < nch; c0 += NWV * B2_ROUND) {
-        for (int i = 0; i < B2_ROUND; ++i) {
-            const int c = c0 + wv + NWV * i;
-            if (c >= nch) break;   // uniform over the wave
-            const int j = c * WAVE + lane;
-            const uint4 r = rnext;
-            if (c + NWV < nch) rnext = rb[(c + NWV) * WAVE + lane];
-            const uint32_t live = j < N ? ONES : 0u;
-            const uint32_t ya = r.z | H, yb = r.w | H;   // y1 of v = 0..3, 4..7, each byte's high bit set
-            // byte high bits of ya - clo: y1 >= clo (below the bracket); of ya - chi: y1 >= chi.
-            // In the bracket: chi <= y1 < clo, the high bits of the xor of the two differences;
-            // the xors are or-ed whole and masked once (their low bits are ignored).
-            uint32_t inb = 0u;
-#pragma unroll
-            for (int u = 0; u < B2U; ++u) {
-                const uint32_t y0 = rec_byte(u < 4 ? r.x : r.y, u & 3);
-                const uint4 T = ct[u][y0];
-                const uint32_t dl = ya - T.x, dh = yb - T.y, el = ya - T.z, eh = yb - T.w;
-                acc[u][0] += (dl >> 7) & live;
-                acc[u][1] += (dh >> 7) & live;
-                inb |= (dl ^ el) | (dh ^ eh);
-            }
-            const bool in = live != 0u && (inb & H) != 0u;
-            const unsigned long long bal = __ballot(in);
-            if (bal) {
-                uint32_t base = 0u;
-                if (lane == 0) base = atomicAdd(&s_nl, (uint32_t)__popcll(bal));
-                base = __shfl(base, 0);
-                if (in) lst[base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)j;
-            }
-            if (++since == 255) {   // byte counters: at most 255 increments between flushes
-                flush();
-                since = 0;
-            }
-        }
-        __syncthreads();
-        // the round's listed simulations, lane = tile: exact position, histogram of the bracket
-        const uint32_t nl = s_nl;
-        const int u = lane >> 3, v = lane & 7;
-        for (uint32_t li = (uint32_t)wv; li < nl; li += NWV) {
-            const uint32_t j = __builtin_amdgcn_readfirstlane(lst[li]);
-            const uint4 r = rb[j];
-            const uint32_t y0 = rec_byte(u < 4 ? r.x : r.y, u & 3), y1 = rec_byte(v < 4 ? r.z : r.w, v & 3);
-            const int pos = (int)spos[y0 * B2_N1 + y1];
-            if (pos >= my_lo && pos <= my_hi) atomicAdd(&hist[my_base + pos], 1u);
-        }
-        __syncthreads();
-        if (tid == 0) s_nl = 0u;
-        __syncthreads();
-    }
-    flush();
+    const int hs = N <= 0xFFFF ? 1 : 0;   // uniform: two bins per word
+    auto hist_add = [&](int i) { atomicAdd(&hist[i >> hs], 1u << (16 * (i & hs))); };
+    auto hist_get = [&](int i) { return (hist[i >> hs] >> (16 * (i & hs))) & (hs ? 0xFFFFu : 0xFFFFFFFFu); };
+    int base = 0;   // bins of the slots of earlier rounds (uniform)
+    bool pending = W > 0;
+    for (int round = 0; round < B2_ROUNDS; ++round) {
+    const bool live = pending && start + W <= base + (B2_HW << hs);
+    const int my_w = live ? W : 0, my_lo = live ? lo : 0, my_h0 = start - base, my_base = my_h0 - my_lo;
+    for (int i = tid; i < B2_HW; i += NTH) hist[i] = 0u;
+    if (tid < NT) below[tid] = 0u;
+    if (tid < 2 * WAVE) s_ext[tid >> 6][lane] = tid < WAVE ? 0 : 255;
     __syncthreads();
-    // per tile: walk the bracket's histogram in position order (one wave per tile)
-    for (int s = wv; s < NT; s += SEL_WG / WAVE) {
-        const int32_t t = B->tile[s];
-        if (t < 0) continue;
-        const int32_t k = kk[t];
-        if (k <= 0 || k > N) continue;
-        const int2 q = prm[s];
-        const int2 b = br[t];
-        bool done = false;
-        const uint32_t bel = below[s];
-        if (q.y && bel < (uint32_t)k) {
-            const int lo = b.x, W = b.y - b.x + 1, h0 = q.x + lo;
-            uint32_t run = bel;
-            for (int i0 = 0; i0 < W && !done; i0 += WAVE) {
-                const int i = i0 + lane;
-                const uint32_t c = i < W ? hist[h0 + i] : 0u;
-                uint32_t incl = c;
+    {
+        const unsigned long long live_slots = __ballot(live);
+        for (int i = tid; i < B2U * B2_N1; i += NTH) {
+            const int u = i / B2_N1, y0 = i - u * B2_N1;
+            const uint32_t lv = (uint32_t)(live_slots >> (8 * u)) & 0xFFu;
+            const uint4 q = cs[i];
+            int mx = 0, mn = 255;
 #pragma unroll
-                for (int o = 1; o < WAVE; o <<= 1) {
-                    const uint32_t y = __shfl_up(incl, o);
-                    if (lane >= o) incl += y;
+            for (int v = 0; v < B2V; ++v)
+                if (lv & (1u << v)) {
+                    mx = max(mx, (int)rec_byte(v < 4 ? q.x : q.y, v & 3));
+                    mn = min(mn, (int)rec_byte(v < 4 ? q.z : q.w, v & 3));
                 }
-                const uint32_t excl = run + incl - c;
-                if (i < W) hist[h0 + i] = excl;   // count strictly before position lo + i
-                lds_wave_sync();
-                const bool hit = i < W && excl < (uint32_t)k && excl + c >= (uint32_t)k;
-                const unsigned long long bal = __ballot(hit);
-                if (bal) {
-                    if (hit) {
-                        const int p = lo + i;
-                        const int g = S_group[p];   // >= lo: the bracket starts a tie group
-                        lam[t] = S_tbl[S_order[p]];
-                        rej_at[t] = (int32_t)hist[h0 + (g - lo)];
-                    }
-                    done = true;
+            atomicMax(&s_ext[0][y0], mx);
+            atomicMin(&s_ext[1][y0], mn);
+        }
+        __syncthreads();
+        uint32_t *__restrict__ lst = s_lst[wv];
+        uint4 *__restrict__ rec = s_rec[wv];
+        const uint8_t *__restrict__ l0 = reinterpret_cast<const uint8_t *>(rec) + (lane >> 3);
+        const uint8_t *__restrict__ l1 = reinterpret_cast<const uint8_t *>(rec) + 8 + (lane & 7);
+        uint32_t n_all = 0u, nl = 0u, bel = 0u;   // n_all, nl: uniform over the wave
+        // the last (at most 64) listed simulations: their counts loaded together, then lane = tile,
+        // DR at a time (past the list: the counts of simulation 0, not used)
+        auto drain = [&]() {
+            constexpr int DR = 4;
+            const uint32_t n = min(nl, (uint32_t)WAVE);
+            nl -= n;
+            lds_wave_sync();
+            rec[lane] = rb[(uint32_t)lane < n ? (int)lst[nl + lane] : 0];
+            lds_wave_sync();
+            for (uint32_t i = 0; i < n; i += DR) {
+                int pos[DR];
+#pragma unroll
+                for (int j = 0; j < DR; ++j) pos[j] = (int)l0[16 * (i + j)] * B2_N1 + (int)l1[16 * (i + j)];
+#pragma unroll
+                for (int j = 0; j < DR; ++j) pos[j] = i + j < n ? (int)spos[pos[j]] : B2_NOUT;   // uniform
+#pragma unroll
+                for (int j = 0; j < DR; ++j) {
+                    bel += pos[j] < my_lo ? 1u : 0u;
+                    if ((uint32_t)(pos[j] - my_lo) < (uint32_t)my_w) hist_add(my_base + pos[j]);
                 }
-                run += __shfl(incl, WAVE - 1);
             }
+        };
+        // the extremes of four simulations per lane and step (entries padded to whole chunks of 64;
+        // a step reads the whole fours below N rounded up to 64), the next step's loaded ahead
+        const uint2 *__restrict__ ea = reinterpret_cast<const uint2 *>(ext + B->rec0);
+        const uint2 *__restrict__ eb = reinterpret_cast<const uint2 *>(ext + B->rec1);
+        const int n4 = ((N + WAVE - 1) / WAVE) * (WAVE / 4);
+        int at = min(wv * WAVE + lane, n4 - 1);   // lanes past the end repeat the last four, unused
+        uint2 na = ea[at], nb = eb[at];
+        for (int q0 = wv * WAVE; q0 < n4; q0 += NWV * WAVE) {
+            const uint2 a = na, b = nb;
+            const int k0 = 4 * (q0 + lane);
+            at = min(q0 + NWV * WAVE + lane, n4 - 1);
+            na = ea[at];
+            nb = eb[at];
+            int c[4], d[4];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const uint32_t x = (h < 2 ? a.x : a.y) >> (16 * (h & 1));
+                c[h] = s_ext[0][(x >> 8) & 0xFFu];
+                d[h] = s_ext[1][x & 0xFFu];
+            }
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const uint32_t y = (h < 2 ? b.x : b.y) >> (16 * (h & 1));
+                const bool act = k0 + h < N;
+                const bool all = act && (int)(y & 0xFFu) >= c[h];
+                const bool in = act && !all && (int)((y >> 8) & 0xFFu) >= d[h];
+                n_all += (uint32_t)__popcll(__ballot(all));
+                const unsigned long long bal = __ballot(in);
+                if (in) lst[nl + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = (uint32_t)(k0 + h);
+                nl += (uint32_t)__popcll(bal);
+            }
+            while (nl >= (uint32_t)WAVE) drain();
         }
-        if (!done && lane == 0) {   // outside the bracket or not histogrammed: exact full pass
-            const uint32_t slot = atomicAdd(&fb[0], 1u);
-            fb[1 + slot] = (uint32_t)t;
-        }
+        if (nl) drain();
+        atomicAdd(&below[lane], bel + n_all);
     }
-}
-
-// Exact selection from the full histogram of a tile's 1,296 outcomes, for the tiles listed in fb;
-// a fixed grid of workgroups takes the listed tiles in turn.
-__global__ __launch_bounds__(SEL_WG) void k_b2_full(const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs,
-                                                    const int64_t *__restrict__ key_off,
-                                                    const int64_t *__restrict__ key_slot,
-                                                    const int32_t *__restrict__ N, const int32_t *__restrict__ kk,
-                                                    const double *__restrict__ S_tbl,
-                                                    const int32_t *__restrict__ S_order,
-                                                    const int32_t *__restrict__ S_group,
-                                                    const uint32_t *__restrict__ fb, double *__restrict__ lam,
-                                                    int32_t *__restrict__ rej_at) {
-    __shared__ uint32_t hist[B2_NOUT];
-    __shared__ uint32_t cumx[B2_NOUT];   // exclusive cumulative counts in S order
-    const int tid = threadIdx.x;
-    const uint32_t n_list = fb[0];
-    for (uint32_t li = blockIdx.x; li < n_list; li += gridDim.x) {
-        const int32_t t = (int32_t)fb[1 + li];
-        const int32_t n = N[t], k = kk[t];
-        const int s = (int)key_slot[t];
-        const Recs2 rb(recs, blocks + key_off[t]);   // the tile's block
-        for (int j = tid; j < B2_NOUT; j += SEL_WG) hist[j] = 0u;
-        __syncthreads();
-        constexpr int LPT = 4;   // records in flight per thread
-        for (int j0 = tid; j0 < n; j0 += SEL_WG * LPT) {
-            uint4 r[LPT];
+    __syncthreads();
+    // lane = tile: walk the bracket's histogram in position order to the k-th smallest
+    if (wv == 0 && live) {
+        uint32_t run = below[lane];
+        bool done = false;
+        if (run < (uint32_t)my_k) {
+            int i = 0;
+            constexpr int WB = 8;   // bins read together
+            for (; i + WB <= W; i += WB) {
+                uint32_t c[WB], sum = 0u;
 #pragma unroll
-            for (int l = 0; l < LPT; ++l) {
-                const int j = j0 + l * SEL_WG;
-                if (j < n) r[l] = rb[j];
+                for (int j = 0; j < WB; ++j) c[j] = hist_get(my_h0 + i + j);
+#pragma unroll
+                for (int j = 0; j < WB; ++j) sum += c[j];
+                if (run + sum >= (uint32_t)my_k) break;
+                run += sum;
             }
-#pragma unroll
-            for (int l = 0; l < LPT; ++l)
-                if (j0 + l * SEL_WG < n) atomicAdd(&hist[rec_outcome(r[l], s)], 1u);
-        }
-        __syncthreads();
-        if (tid < WAVE) {
-            uint32_t run = 0u;
-            for (int base = 0; base < B2_NOUT; base += WAVE) {
-                const int p = base + tid;
-                const uint32_t c = p < B2_NOUT ? hist[S_order[p]] : 0u;
-                uint32_t incl = c;
-#pragma unroll
-                for (int o = 1; o < WAVE; o <<= 1) {
-                    const uint32_t y = __shfl_up(incl, o);
-                    if (tid >= o) incl += y;
-                }
-                const uint32_t excl = run + incl - c;
-                if (p < B2_NOUT) cumx[p] = excl;
-                lds_wave_sync();
-                const bool hit = p < B2_NOUT && excl < (uint32_t)k && excl + c >= (uint32_t)k;
-                if (__ballot(hit)) {
-                    if (hit) {
-                        lam[t] = S_tbl[S_order[p]];
-                        rej_at[t] = (int32_t)cumx[S_group[p]];
-                    }
-                    break;
-                }
-                run += __shfl(incl, WAVE - 1);
+            for (; i < W; ++i) {
+                const uint32_t c = hist_get(my_h0 + i);
+                if (run + c >= (uint32_t)my_k) break;
+                run += c;
+            }
+            if (i < W) {
+                // position lo + i; the count strictly below its tie group, which starts in the bracket
+                const int g = S_group[lo + i] - lo;
+                for (int j = g; j < i; ++j) run -= hist_get(my_h0 + j);
+                lam[my_t] = S_tbl[S_order[lo + i]];
+                rej_at[my_t] = (int32_t)run;
+                done = true;
             }
         }
-        __syncthreads();   // hist and cumx are rewritten for the next listed tile
+        if (!done) fail[atomicAdd(&s_nf, 1u)] = lane;   // outside the bracket
+    }
+    pending = pending && !live;
+    const unsigned long long rest = __ballot(pending);   // the same in every wave
+    if (!rest) break;
+    base = __shfl(start, __builtin_ctzll(rest));
+    __syncthreads();   // the histograms are read before the next round clears them
+    }
+    if (wv == 0 && pending) fail[atomicAdd(&s_nf, 1u)] = lane;   // no round held it
+    __syncthreads();
+    const uint32_t nf = s_nf;   // uniform
+    if (tid == 0 && nf) atomicAdd(&fb[0], nf);
+    for (uint32_t f = 0; f < nf; ++f) {
+        const int s = fail[f];
+        const int32_t t = B->tile[s];
+        b2_full_tile<NTH>(rb, N, kk[t], s, S_tbl, S_order, S_group, hist, hist + B2_NOUT, &lam[t], &rej_at[t]);
     }
 }
 
@@ -1455,12 +1463,16 @@ hipError_t launch_select(const Platten &P, const void *keys, const int32_t *k, d
                            (const float *)keys, P.d_key_off, P.d_key_stride, P.d_N, k, lam, rej_at);
     else {   // the 2-arm bracket (launch_b2_bracket) must have run after k was computed
         const Blk2 *blk = (const Blk2 *)P.d_blocks;
-        hipLaunchKernelGGL(k_b2_select, dim3((uint32_t)P.n_blocks), dim3(SEL_WG), 0, st, blk, (const uint2 *)keys, k,
-                           P.d_b2br, P.d_b2cut, P.d_S_pos, P.d_S_order, P.d_S_group, P.d_S_tbl, lam, rej_at,
-                           P.d_b2fb);
-        const uint32_t grid = (uint32_t)std::min<int64_t>(P.n_tiles, 1024);
-        hipLaunchKernelGGL(k_b2_full, dim3(grid), dim3(SEL_WG), 0, st, blk, (const uint2 *)keys, P.d_key_off,
-                           P.d_key_stride, P.d_N, k, P.d_S_tbl, P.d_S_order, P.d_S_group, P.d_b2fb, lam, rej_at);
+        const uint2 *recs = (const uint2 *)keys;
+        const uint16_t *ext = (const uint16_t *)(recs + P.b2_recs);
+#define CSE_B2_SELECT(NWV)                                                                                            \
+    hipLaunchKernelGGL(k_b2_select<NWV>, dim3((uint32_t)P.n_blocks), dim3(NWV * WAVE), 0, st, blk, recs, ext, k,      \
+                       P.d_b2br, P.d_b2cut, P.d_S_pos, P.d_S_order, P.d_S_group, P.d_S_tbl, lam, rej_at, P.d_b2fb)
+        if (P.n_blocks <= B2_FEWBLK)
+            CSE_B2_SELECT(16);
+        else
+            CSE_B2_SELECT(4);
+#undef CSE_B2_SELECT
     }
     return hipGetLastError();
 }

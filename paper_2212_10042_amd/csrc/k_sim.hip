@@ -30,7 +30,8 @@ __device__ __forceinline__ void wave_sync() {
 // every rectangle (1024 x 1024 boxes: 32-fold).  A workgroup takes one chunk of 64 simulations
 // (one per lane): its words go to LDS once, then each wave counts threshold groups and writes them
 // to the count table (Grp2: bytes, 16 simulations of a threshold contiguous) and, for a
-// calibration, to the workspace the selection reads (8 bytes per simulation and group).
+// calibration, to the workspace the selection reads (8 bytes per simulation and group, and once more
+// the counts at the group's first and last threshold, 2 bytes).
 //
 // k_b2_tiles: per (simulation, tile) the decision y1 >= c(y0) and its sums, four simulations per
 // instruction.  A wave takes 8 arm-0 thresholds (wave-uniform, so their counts and cut points are
@@ -54,7 +55,7 @@ template <bool RECS>
 __global__ __launch_bounds__(WG) void k_b2_count(const Grp2 *__restrict__ grp, int32_t n_grp, uint32_t win_b,
                                                  uint32_t win_e, uint32_t key0, uint32_t key1,
                                                  const int32_t *__restrict__ cut_tbl, uint2 *__restrict__ tab,
-                                                 uint2 *__restrict__ recs) {
+                                                 uint2 *__restrict__ recs, uint16_t *__restrict__ ext) {
     constexpr int NB = (2 * NP35 + 3) / 4;
     constexpr int NWV = WG / WAVE;
     __shared__ uint32_t words[4 * NB][WAVE];
@@ -93,7 +94,10 @@ __global__ __launch_bounds__(WG) void k_b2_count(const Grp2 *__restrict__ grp, i
         }
         const uint2 c8 = make_uint2(y[0] | (y[1] << 8) | (y[2] << 16) | (y[3] << 24),
                                     y[4] | (y[5] << 8) | (y[6] << 16) | (y[7] << 24));
-        if (RECS) recs[G->rec + k] = c8;   // chunks are padded: past n_sims too
+        if (RECS) {   // chunks are padded: past n_sims too
+            recs[G->rec + k] = c8;
+            ext[G->rec + k] = (uint16_t)(y[0] | (y[B2U - 1] << 8));
+        }
         // (simulation, threshold) bytes -> threshold-major granules: lane = granule q of the chunk,
         // threshold t, half h of its 16 simulations
         tr[wv][lane] = c8;
@@ -357,10 +361,10 @@ hipError_t launch_binom2(const Platten &P, uint64_t seed, uint32_t *R, unsigned 
         const uint32_t split = std::min<uint32_t>(per, std::max<uint32_t>(1u, 4096u / chunks));
         if (recs)
             hipLaunchKernelGGL(k_b2_count<true>, dim3(chunks, split), dim3(WG), 0, st, P.d_grp2, P.n_grp2, wb, we, k0,
-                               k1, P.d_cut_tbl, (uint2 *)P.d_b2tab, recs);
+                               k1, P.d_cut_tbl, (uint2 *)P.d_b2tab, recs, (uint16_t *)(recs ? recs + P.b2_recs : nullptr));
         else
             hipLaunchKernelGGL(k_b2_count<false>, dim3(chunks, split), dim3(WG), 0, st, P.d_grp2, P.n_grp2, wb, we, k0,
-                               k1, P.d_cut_tbl, (uint2 *)P.d_b2tab, recs);
+                               k1, P.d_cut_tbl, (uint2 *)P.d_b2tab, recs, (uint16_t *)(recs ? recs + P.b2_recs : nullptr));
         hipLaunchKernelGGL(k_b2_tiles, dim3((uint32_t)P.n_gitems), dim3(WG), 0, st, (const Blk2 *)P.d_blocks,
                            P.d_sqitems, P.d_grp2, P.d_b2tab, wb, we, R, sumT);
     }

@@ -801,10 +801,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             B.rec0 = grps[P->blk_rg[b]].rec;
             B.rec1 = grps[P->blk_cg[b]].rec;
             for (int j = 0; j < B2U * B2V; ++j)
-                if (B.tile[j] >= 0) {
-                    key_off[B.tile[j]] = (int64_t)b;   // the tile's block
-                    key_stride[B.tile[j]] = j;         // the tile's slot u * 8 + v
-                }
+                if (B.tile[j] >= 0) key_off[B.tile[j]] = (int64_t)b;   // placed
             // key slots: 16 bytes per (simulation, block); the groups' entries (8 bytes per
             // simulation and group, at most two groups per block) never take more
             P->n_keys += ((int64_t)B.n_sims + 63) / 64 * 64;
@@ -837,6 +834,13 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             for (int y1 = 0; y1 < n; ++y1)
                 if (S[y0 * n1 + y1 + 1] > S[y0 * n1 + y1]) {
                     set_error("internal: the 2-arm statistic is not monotone in y1");
+                    return CSE_EUNSUPPORTED;
+                }
+        // and, so that cut points ascend with y0, it must not decrease with y0 for fixed y1
+        for (int y0 = 0; y0 < n; ++y0)
+            for (int y1 = 0; y1 <= n; ++y1)
+                if (S[(y0 + 1) * n1 + y1] < S[y0 * n1 + y1]) {
+                    set_error("internal: the 2-arm statistic is not monotone in y0");
                     return CSE_EUNSUPPORTED;
                 }
         std::vector<int32_t> order(n1 * n1), group(n1 * n1);
@@ -898,8 +902,10 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
     stage.add(&P->d_radii, P->tile_radii.data(), P->tile_radii.size());
     stage.add(&P->d_is_box, P->tile_is_box.data(), P->tile_is_box.size());
     stage.add(&P->d_in_null, P->tile_in_null.data(), P->tile_in_null.size());
-    stage.add(&P->d_key_off, key_off.data(), key_off.size());
-    stage.add(&P->d_key_stride, key_stride.data(), key_stride.size());
+    if (kind != CSE_BINOM2_Z) {
+        stage.add(&P->d_key_off, key_off.data(), key_off.size());
+        stage.add(&P->d_key_stride, key_stride.data(), key_stride.size());
+    }
     // N classes for the Clopper-Pearson table
     {
         std::vector<int32_t> cls(P->tile_N.begin(), P->tile_N.end());
@@ -939,7 +945,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2tab, (size_t)P->b2_units * UNIT2));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2cut, (size_t)P->n_blocks * B2U * (NP35 + 1) * sizeof(uint4)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2br, nt * sizeof(int2)));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2fb, (nt + 1) * sizeof(uint32_t)));
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2fb, sizeof(uint32_t)));
     }
     CSE_HIP_TRY(take_side_stream(P->device, &P->side));
     for (hipEvent_t *e : {&P->ev_sim, &P->ev_val, &P->ev_fork, &P->ev_inv})

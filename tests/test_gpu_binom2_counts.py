@@ -56,3 +56,11 @@ def test_simulation_windows():
     th = np.array([[-1.0, -1.1], [-1.5, -1.0], [0.2, 0.4], [-2.0, -1.2], [-0.7, -0.7]])
     sims = np.array([1_150_000, 1_150_001, 1_150_015, 1_150_016, 1_150_063], np.int32)
     _compare(th, np.full(th.shape, 0.01), sims, 11, calibrate=False)
+
+
+@pytest.mark.parametrize("m,n", [(3, 65_535), (3, 65_536), (6, 70_001), (50, 300), (24, 1_000), (130, 200)])
+def test_selection_bins_rounds_and_batches(m, n):
+    # 16- and 32-bit histogram bins (65,535 simulations at most in 16 bits), brackets that take several
+    # rounds of the LDS histogram, fewer and more batches than CUs
+    w = W.binom2_grid(m, n, lo=-2.0 if m < 10 else -3.0, seed=n)
+    _compare(w["theta"], w["radii"], w["sims"], n)
