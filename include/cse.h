@@ -439,7 +439,7 @@ int cse_simulate_per_tile(const cse_platten *p, uint64_t seed, int64_t tile_begi
  * On a CSE_BINOM2_Z platten: out[0] = tiles that the last calibration's bracketed selection
  * left to the exact full-histogram pass (k-th statistic outside the bracket, or the batch's
  * brackets too wide for the histogram), out[1..3] = 0.  On a CSE_HIER4 platten: out[0] = tiles
- * whose k-th key the last bracketed calibration did not hold among its candidates (selected
+ * whose k-th key the last calibration from candidates did not hold among them (selected
  * exactly from keys regenerated by the counter-based generator), out[1..3] = 0.
  * Synchronises `stream`.  Used to state the kernel's arithmetic per launch.
  * Errors: CSE_EINVAL (NULL out), CSE_EUNSUPPORTED (other designs), CSE_EHIP.
@@ -450,26 +450,22 @@ int cse_work_counters(const cse_platten *p, int64_t out[4], void *stream);
  * cse_platten_set_option -- tuning options of a platten (host call, no kernel launch).
  *   CSE_OPT_B2_MARGIN (CSE_BINOM2_Z calibration): the selection's bracket around each tile's
  *        k-th statistic, in standard deviations of the count (default 5).  Results do not
- *        depend on it: tiles whose k-th statistic falls outside the bracket take an exact
- *        full-histogram pass (cse_work_counters counts them); a smaller margin lists fewer
- *        simulations in the bracketed pass but sends more tiles to the exact one.  A plan
+ *        depend on it: tiles whose k-th statistic falls outside the bracket are selected from the
+ *        full histogram of their outcomes (cse_work_counters counts them); a smaller margin lists
+ *        fewer simulations in the bracketed pass but leaves more tiles to that.  A plan
  *        captured earlier keeps the margin it was captured with.
- *   CSE_OPT_H4_BRACKET (CSE_HIER4 calibration): 1 selects from bracketed keys: a pilot pass keeps
- *        the float32 keys of the first 2,048 simulations, whose order statistics around rank
- *        (k/N) 2048 bracket each tile's k-th key; the fused pass over the other simulations
- *        counts the keys below the bracket and keeps only those inside it (about a tenth of the
- *        HBM traffic of storing every key).  0 (default) stores every float32 key and selects
- *        from them, as cse_calibrate_tiebreak always does.  Same results either way.  Turning
- *        it on allocates the candidate regions (device memory; about 20 KB per tile at 32,768
- *        simulations per tile with the default launch shape), turning it off frees them; the
- *        plattens whose batches hold more than 128 key rows keep the every-key path.
- *   CSE_OPT_H4_MARGIN (CSE_HIER4 bracketed calibration): the bracket's margin in standard
- *        deviations of the pilot rank (default 6, lowered towards 3 where the bracket would
- *        hold too many keys).  Results do not depend on it: a tile whose k-th key is not among
- *        the kept ones is selected from its keys regenerated one by one from the counter-based
- *        generator (slow; cse_work_counters counts them).
+ *   CSE_OPT_H4_BRACKET (CSE_HIER4 and CSE_BASKET4 calibration): 0 or 1, accepted and without effect:
+ *        the calibration keeps only candidate keys whenever (max N + 1) alpha <= 832 and alpha <=
+ *        0.05 (a pilot over the first simulations, a sixteenth of them, 256 to 2,048, bounds each
+ *        tile's k-th key from above; the pass over all simulations keeps the keys below the bound),
+ *        and every float32 key otherwise, as cse_calibrate_tiebreak always does.  Same results
+ *        either way.
+ *   CSE_OPT_H4_MARGIN (the calibration from candidates): the bound's margin in standard
+ *        deviations of the pilot rank (default 6).  Results do not depend on it: a tile whose k-th
+ *        key is not among the candidates is selected from its keys regenerated one by one from the
+ *        counter-based generator (slow; cse_work_counters counts them).
  * Errors: CSE_EINVAL (bad handle, unknown option, value outside [0, 100]; 0 or 1 for
- * CSE_OPT_H4_BRACKET), CSE_ENOMEM (the candidate regions could not be allocated).
+ * CSE_OPT_H4_BRACKET).
  */
 #define CSE_OPT_B2_MARGIN 1
 #define CSE_OPT_H4_MARGIN 2

@@ -165,8 +165,10 @@ void prof_collect() {
 // Simulation with the design's fixed rule into the workspaces (R, score sums) and, when `keys` is not
 // NULL, the calibration keys into `keys` (n_keys entries laid out as the platten's key offsets say).
 // The 4-arm designs form score sums only when `scores` is set (they cost that kernel extra work);
-// the others always do.
-int run_sim(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bool scores = false) {
+// the others always do.  cand_k: with keys, 4-arm designs: store the candidates of each tile's
+// cand_k-th smallest key instead of every key.
+int run_sim(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bool scores = false,
+            const int32_t *cand_k = nullptr) {
     CSE_LAUNCH(cse::launch_zero(P.d_Rw, P.n_tiles * sizeof(uint32_t), st));
     if (P.family == cse::FAM_NORMAL) {
         CSE_LAUNCH(cse::launch_zero(P.d_Zw, P.n_tiles * sizeof(unsigned long long), st));
@@ -174,9 +176,9 @@ int run_sim(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bo
         CSE_LAUNCH(cse::launch_ztest1(P, seed, P.d_Rw, P.d_Zw, (float *)keys, st));
     } else if (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) {
         const bool bk = P.design.kind == CSE_BASKET4;
-        if (scores) CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * P.d * sizeof(unsigned long long), st));
+        if (scores) CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * 2 * sizeof(unsigned long long), st));   // packed pairs
         Timed tm(keys ? (bk ? "basket4_calib" : "hier4_calib") : (bk ? "basket4" : "hier4"), st);
-        CSE_LAUNCH(cse::launch_hier4(P, seed, P.d_Rw, scores ? P.d_Tw : nullptr, (float *)keys, st));
+        CSE_LAUNCH(cse::launch_hier4(P, seed, P.d_Rw, scores ? P.d_Tw : nullptr, (float *)keys, cand_k, st));
     } else if (P.design.kind == CSE_PHASE23) {
         CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * 2 * P.d * sizeof(unsigned long long), st));
         Timed tm(keys ? "phase23_calib" : "phase23", st);
@@ -186,29 +188,6 @@ int run_sim(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bo
         Timed tm(keys ? "binom2_calib" : "binom2", st);
         CSE_LAUNCH(cse::launch_binom2(P, seed, P.d_Rw, P.d_Tw, (uint2 *)keys, st));
     }
-    return CSE_OK;
-}
-
-// The 4-arm calibration with bracketed keys: pilot pass (float32 keys of the first H4_PILOT
-// simulations), brackets once k is known (k_ready: the event after which it is, or null when
-// it already is on st), then the pass over the other simulations (bracketed keys).  R and the
-// score sums cover every simulation, as run_sim's.
-int run_sim_h4(const cse::Platten &P, uint64_t seed, void *keys, hipStream_t st, bool scores, hipEvent_t k_ready,
-               const int32_t *kk, double *lam, int32_t *rej_at) {
-    CSE_LAUNCH(cse::launch_zero(P.d_Rw, P.n_tiles * sizeof(uint32_t), st));
-    if (scores) CSE_LAUNCH(cse::launch_zero(P.d_Tw, P.n_tiles * P.d * sizeof(unsigned long long), st));
-    unsigned long long *sT = scores ? P.d_Tw : nullptr;
-    {
-        Timed tm("hier4_pilot", st);
-        CSE_LAUNCH(cse::launch_hier4(P, seed, P.d_Rw, sT, (float *)keys, st, cse::H4_PASS_PILOT));
-    }
-    if (k_ready) CSE_HIP_TRY(hipStreamWaitEvent(st, k_ready, 0));
-    {
-        Timed tm("h4_bracket", st);
-        CSE_LAUNCH(cse::launch_h4_bracket(P, (const float *)keys, kk, lam, rej_at, st));
-    }
-    Timed tm("hier4_calib", st);
-    CSE_LAUNCH(cse::launch_hier4(P, seed, P.d_Rw, sT, nullptr, st, cse::H4_PASS_MAIN));
     return CSE_OK;
 }
 
@@ -284,9 +263,11 @@ int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alph
                    int32_t *reject, int64_t *score_T, double *score_Z, double *grad, double *cp_upper,
                    double *tile_bound, hipStream_t st, bool full_keys = false) {
     double *ap = alpha_prime ? alpha_prime : P.d_apw;
-    // 4-arm design: bracketed keys when the platten asks for them (CSE_OPT_H4_BRACKET) and every key
-    // need not reach HBM (the randomised tie-break reads them)
-    const bool h4b = P.design.kind == CSE_HIER4 && !full_keys && P.h4_bracket && P.d_h4cand;
+    // 4-arm designs: candidate keys where a tile's candidates stay few (alpha' <= alpha, so k is at most
+    // (N + 1) alpha), unless every key is asked for (the randomised tie-break reads them); beyond,
+    // every key and the two-sided bracket of the f32 selection
+    const bool h4c = (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys &&
+                     alpha <= cse::H4_CAND_ALPHA && alpha * ((double)P.max_N + 1.0) <= cse::H4_CAND_K;
     int32_t *kk = k ? k : P.d_kw;
     double *lam = lambda_tile ? lambda_tile : P.d_lamw;
     // The step's dependencies: alpha' -> k -> selection; simulation -> selection, finish and
@@ -314,13 +295,8 @@ int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alph
         }
         if (branch_invert) CSE_HIP_TRY(hipEventRecord(P.ev_inv, is));
     }
-    if (h4b) {
-        if (int e = run_sim_h4(P, seed, keys, st, score_T || grad, branch_invert ? P.ev_inv : nullptr, kk, lam,
-                               reject_at_lambda))
-            return e;
-    } else if (int e = run_sim(P, seed, keys, st, score_T || grad)) {
-        return e;
-    }
+    if (h4c && branch_invert) CSE_HIP_TRY(hipStreamWaitEvent(st, P.ev_inv, 0));   // the pilot's bounds need k
+    if (int e = run_sim(P, seed, keys, st, score_T || grad, h4c ? kk : nullptr)) return e;
     const bool want_bound = cp_upper || tile_bound;
     if (want_bound) {
         hipStream_t side = P.side;
@@ -338,8 +314,8 @@ int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alph
     if (branch_invert) CSE_HIP_TRY(hipStreamWaitEvent(st, P.ev_inv, 0));   // k before the selection
     {
         Timed tm("select", st);
-        if (h4b)
-            CSE_LAUNCH(cse::launch_h4_select(P, seed, kk, lam, reject_at_lambda, st));
+        if (h4c)
+            CSE_LAUNCH(cse::launch_h4_select(P, seed, (const float *)keys, kk, lam, reject_at_lambda, st));
         else
             CSE_LAUNCH(cse::launch_select(P, keys, kk, lam, reject_at_lambda, st));
     }
@@ -671,13 +647,17 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
     // one-wave-per-block (z-test) or group kernels (2-arm, 4-arm): time the calibration launch
     if (int e = ensure_keys(P)) return e;
     const bool group = P.design.kind == CSE_BINOM2_Z || P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4;
+    auto replan = [&](int64_t v) {
+        return !group ? cse::plan_work_items(&P, v)
+                      : (P.design.kind == CSE_BINOM2_Z ? cse::plan_group_items(&P, v) : cse::plan_h4_items(&P, v));
+    };
     const int64_t cands[7] = {1024, 2048, 4096, 8192, 16384, 32768, 65536};
     const int64_t wave_cands[7] = {4096, 8192, 16384, 32768, 65536, 131072, 262144};
     float best = 3.4e38f;
     int64_t bv = group ? P.tune_wgs : P.tune_waves;
     for (int i = 0; i < 7; ++i) {
         const int64_t v = group ? cands[i] : wave_cands[i];
-        if (int e = group ? cse::plan_group_items(&P, v) : cse::plan_work_items(&P, v)) return e;
+        if (int e = replan(v)) return e;
         // the calibration launch (keys) and the validation launch (no keys) together: the
         // best shape of one need not be the best of the other
         float ms = 0.0f, ms_val = 0.0f;
@@ -689,7 +669,7 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
             bv = v;
         }
     }
-    if (int e = group ? cse::plan_group_items(&P, bv) : cse::plan_work_items(&P, bv)) return e;
+    if (int e = replan(bv)) return e;
     out[0] = bv;
     return CSE_OK;
 }
@@ -874,11 +854,6 @@ int cse_platten_set_option(cse_platten *p, int32_t option, double value) {
         if (value != 0.0 && value != 1.0) {
             set_error("cse_platten_set_option: CSE_OPT_H4_BRACKET takes 0 or 1");
             return CSE_EINVAL;
-        }
-        p->P.h4_bracket = value == 1.0;
-        if (int e = cse::h4_regions(&p->P)) {   // the candidate regions live while the option is on
-            p->P.h4_bracket = false;
-            return e;
         }
         return CSE_OK;
     }

@@ -67,21 +67,70 @@ struct Blk1 {
     int64_t key_base;          // keys of slot s live at key_base + s * n_sims + k
 };
 
-// 4-arm designs: a 4 x 4 x 2 x 2 product of distinct thresholds (arms 0..3) = 64 box slots;
-// slot (u0,u1,u2,u3) = ((u0 * 4 + u1) * 2 + u2) * 2 + u3.  A box's tiles (one per null
-// configuration b present, b ascending) are consecutive key rows starting at row0[slot] and
-// consecutive tile ids starting at tile0[slot]; bmask bit b marks configuration b.
-constexpr int B4N0 = 4, B4N1 = 4, B4N2 = 2, B4N3 = 2;
-constexpr int B4S = B4N0 * B4N1 * B4N2 * B4N3;
-struct Blk4 {
-    uint32_t T0[B4N0], T1[B4N1], T2[B4N2], T3[B4N3];
-    int32_t row0[B4S];         // first key row of the slot's tiles, -1 when the slot has no box
-    int32_t tile0[B4S];        // first tile id of the slot's box
-    uint32_t bmask[B4S];       // configurations present (bit b, b = 1..7)
-    int32_t n_rows;            // key rows (tiles) of this block
+// 4-arm designs.  Threshold group: up to 8 neighbouring distinct thresholds of one arm among the tiles
+// of one simulation count, counted once per simulation for all of them.  Threshold t has a row of
+// the count table, one 16-byte unit per granule (16 simulations, one byte each), at row + t *
+// stride; arms 2 and 3 have a second row, 8 * stride further on, with the counts' codes for the
+// statistic's table (h4_code2, h4_code3).
+struct Grp4 {
+    uint32_t T[8];
+    int32_t arm;
     int32_t n_sims;
-    int64_t key_base;          // key of row r, simulation k at key_base + ((k/64) * n_rows + r) * 64 + k%64
+    int32_t n_thr;
+    int32_t pad;
+    int64_t row;      // units
+    int64_t stride;   // units: granules of a window
 };
+// A wave's 64 tiles, one per lane (lanes past n_lanes repeat lane 0's rows and have no tile).  The
+// distinct count-table rows of the set are listed from row_at on; a lane's four count rows and two
+// code rows (arms 2 and 3) are places in that list.
+constexpr int H4_ROWS = 6;
+struct H4Set {
+    int32_t tile[64];
+    uint16_t row[H4_ROWS][64];
+    uint32_t cfg[64];       // null configuration b
+    int32_t n_sims;
+    int32_t n_lanes;
+    int32_t slice;          // granules per item
+    int32_t n_slices;
+    int32_t n_rows;
+    int32_t pad;
+    int64_t row_at;
+    int64_t key_base;       // key of lane l, simulation k at key_base + (k / 64) * 64 n_lanes + 64 l + k % 64
+    int64_t cnt_base;       // candidates kept by lane l in slice s: entry cnt_base + 64 s + l
+};
+constexpr int H4_ROW_LDS = 5;   // 16-byte units of a staged row: a chunk's four and one of padding (no bank conflicts)
+// Wave item: the granules [g_begin, g_end) of a set (its slice `slice`).
+struct H4Item {
+    int32_t set;
+    int32_t slice;
+    uint32_t g_begin;
+    uint32_t g_end;
+};
+// Table of the statistic S_b of each configuration b, one plane per b: outcome (y0, y1, y2, y3) at
+// ((36 y0 + y1) * H4_SLAB + 8 code2(y2) + code3(y3)), so that 4 x 8 neighbouring (y2, y3) share a
+// 128-byte line.
+constexpr int H4_SLAB = 9 * 5 * 32;
+constexpr int64_t H4_PLANE = (int64_t)(NP35 + 1) * (NP35 + 1) * H4_SLAB;   // floats
+__host__ __device__ inline uint32_t h4_code2(uint32_t y) { return 20u * (y >> 2) + (y & 3u); }
+__host__ __device__ inline uint32_t h4_code3(uint32_t y) { return ((y >> 3) << 5) + (y & 7u); }
+// Calibration of the 4-arm designs from candidate keys: a pilot over the first h4_pilot(N)
+// simulations of a set gives each tile an upper bound of its k-th smallest key; the pass over all
+// simulations keeps only the keys below it.
+constexpr int64_t H4_SLICE_MAX = 256;    // granules per item at most (4,096 simulations)
+constexpr int64_t H4_WGS = 2048;         // workgroups of four waves, default
+constexpr int H4_PILOT_MIN_N = 1024;     // fewer simulations: every key is kept
+constexpr int H4_PILOT_MAX = 2048;
+constexpr int H4_CAND_MAX = 3072;        // candidates selected from LDS (more: exact path)
+constexpr double H4_CAND_K = 832.0;      // largest (max N + 1) * alpha that takes candidates
+constexpr double H4_CAND_ALPHA = 0.05;   // and largest alpha
+// candidate slots of a tile per slice of `slice` granules (a pilot leaves an eighth of the keys at most;
+// a set's slots fit its keys' place in the workspace)
+__host__ __device__ inline int h4_cap(int n, int slice) { return n < H4_PILOT_MIN_N ? slice * GRAN2 : slice * GRAN2 / 2; }
+__host__ __device__ inline int h4_pilot(int n) {   // a multiple of 64
+    const int m = n / 16 / 64 * 64;
+    return m < 256 ? 256 : (m > H4_PILOT_MAX ? H4_PILOT_MAX : m);
+}
 
 // Work item: one wave simulates sims [k_begin, k_end) of block blk.
 struct WorkItem {
@@ -90,25 +139,6 @@ struct WorkItem {
     uint32_t k_end;
     int32_t pad;
 };
-
-// Workgroup item of the 4-arm kernels: its 4 waves simulate the same sims [k_begin, k_end) for up
-// to 4 blocks of equal N (blk = -1: no block), sharing each simulation's Philox words.
-struct GroupItem {
-    int32_t blk[4];
-    uint32_t k_begin;
-    uint32_t k_end;
-    int32_t slice;   // index of the item's simulation range among its group's ranges
-    int32_t pad;
-};
-
-// 4-arm calibration with bracketed keys: a pilot pass stores the keys of the first H4_PILOT
-// simulations; per tile they give a bracket [lo, hi] around the k-th smallest key; the fused pass
-// over the remaining simulations counts the keys below lo and keeps those in [lo, hi] in the
-// tile's candidate regions (H4_PCAP slots for the pilot's, then h4_caps per item range).
-constexpr int H4_PILOT = 2048;
-constexpr int H4_PCAP = 1024;
-constexpr int H4_MAXS = 1024;   // item ranges per group at most (the selection's region table)
-constexpr int H4_BROWS = 128;   // key rows per wave whose counters live in LDS (the rest: global atomics)
 
 // Workgroup item of the 2-arm kernel: wave w takes the 8 thresholds of row group rg[w] (-1: none)
 // against the up to 64 thresholds of the column groups cg[0..7] (ascending; the first ncg are
@@ -195,7 +225,6 @@ struct Platten {
     int64_t n_blocks = 0;
     WorkItem *d_items = nullptr;
     int64_t n_items = 0;
-    GroupItem *d_gitems = nullptr;       // 4-arm designs
     SquareItem *d_sqitems = nullptr;     // 2-arm design
     Grp2 *d_grp2 = nullptr;              // 2-arm design: threshold groups
     int32_t n_grp2 = 0;
@@ -204,27 +233,31 @@ struct Platten {
     uint4 *d_b2tab = nullptr;            // count table (one window of b2_win granules)
     int64_t b2_win = 0;                  // granules of a window (a multiple of 4)
     int64_t n_gitems = 0;
-    // 4-arm calibration with bracketed keys (CSE_HIER4): pilot items over the first H4_PILOT
-    // simulations; per tile the bracket (lo, hi), the keys below lo, the candidates kept per region
-    // ([0] the pilot's, [1 + s] item range s) and the candidate regions themselves; the tiles the
-    // last selection regenerated ([0] = count)
-    GroupItem *d_gitems_pilot = nullptr;
-    int64_t n_gitems_pilot = 0;
-    int32_t h4_maxs = 0, h4_caps = 0;    // item ranges per group (at most), candidate slots per range
-    int32_t h4_max_rows = 0;             // most key rows of a block
-    int64_t h4_tot = 0;                  // candidate slots per tile: H4_PCAP + h4_maxs * h4_caps
-    size_t h4_cnt_alloc = 0, h4_cand_alloc = 0;   // entries of d_h4cnt / d_h4cand now allocated
-    float2 *d_h4brk = nullptr;
-    uint32_t *d_h4below = nullptr;
+    // 4-arm designs: threshold groups, tile sets, wave items, count table (one window of b4_win
+    // granules); calibration from candidates: per tile the upper bound of the k-th key and the
+    // keys equal to it, the candidates kept per slice, the tile's place (set * 64 + lane) and the number of tiles the
+    // last selection regenerated
+    Grp4 *d_grp4 = nullptr;
+    int32_t n_grp4 = 0;
+    H4Set *d_h4set = nullptr;
+    H4Item *d_h4item = nullptr;
+    int64_t n_h4set = 0, n_h4item = 0;
+    std::vector<H4Set> h4set;            // host copy (launch shapes)
+    int64_t b4_units = 0, b4_win = 0;
+    uint32_t *d_h4rows = nullptr;        // the sets' row lists
+    int32_t h4_max_rows = 0;             // longest of them
+    uint4 *d_b4tab = nullptr;
+    float *d_h4u = nullptr;
+    uint32_t *d_h4eq = nullptr;
     uint32_t *d_h4cnt = nullptr;
-    float *d_h4cand = nullptr;
+    int32_t *d_h4at = nullptr;
     uint32_t *d_h4fb = nullptr;
-    float h4_margin = 6.0f;              // bracket margin in standard deviations of the pilot rank
-    bool h4_bracket = false;             // calibrate with bracketed keys (else every key in HBM, the f32 selection)
+    float h4_margin = 6.0f;              // pilot margin in standard deviations of the rank
 
     // design tables (device)
     float4 *d_h4tbl = nullptr;           // 4-arm: (1 - P_1, 1 - P_2, 1 - P_3, 0) per outcome
     uint8_t *d_h4mask = nullptr;         // 4-arm designs: rejection mask at the cut per outcome
+    float *d_h4plane = nullptr;          // 4-arm designs: S_b per outcome, one plane per configuration
     HierNode *d_hnodes = nullptr;        // per-node constants of the hierarchical posterior
     // Phase II/III design: per-tile thresholds / configurations, the work queue
     uint32_t *d_tileT = nullptr;
@@ -318,7 +351,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
 void free_platten(Platten *P);
 int plan_work_items(Platten *P, int64_t target_waves);
 int plan_group_items(Platten *P, int64_t target_wgs);
-int h4_regions(Platten *P);
+int plan_h4_items(Platten *P, int64_t target_wgs);
 int plan_queue_items(Platten *P, int32_t chunk, int64_t grid);
 
 }  // namespace cse

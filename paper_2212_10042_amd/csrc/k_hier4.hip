@@ -7,6 +7,8 @@
 // The table holds float32 (1 - P_1, 1 - P_2, 1 - P_3, 0) per outcome, index ((y0 m + y1) m + y2) m + y3.
 #include <math.h>
 
+#include <algorithm>
+
 #include "cse_internal.h"
 #include "fp64_math.hpp"
 #include "hier_post.hpp"
@@ -96,546 +98,476 @@ hipError_t launch_hier4_table(int n, float4 *tbl, const HierNode *nodes, hipStre
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------------------
-// Fused simulation, 4 arms x 35 patients (words a*35 .. a*35+34 for arm a: 35 Philox blocks).
-// The four waves of a workgroup run four box batches over the same simulations and share each
-// chunk's 140 words through LDS.  Per (simulation, box slot): one 16-byte gather of
-// (1 - P_1, 1 - P_2, 1 - P_3) at the outcome y; the design rejects treatment arm i when
-// 1 - P_i < cut, giving a 3-bit mask m; configuration b's FWER event is m & b != 0.  Per box the
-// lanes count each mask value (7 packed 2-bit counters per slot, two slots per word, exact for
-// 3 simulations per lane between flushes, which transpose the counters through the word
-// buffer), so R_b = sum_{m & b != 0} count[m] for every b of the box.  LDS is the 35 KB word
-// buffer and the score rows, so four workgroups fit on a CU.
-// Calibration keys: S_b = min_{i in b} (1 - P_i) per (simulation, tile), float32.
-// ------------------------------------------------------------------------------------------
 __device__ __forceinline__ void wave_sync4() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// BASKET: the basket design (four hypotheses, arm a <-> bit a, q.w used): every slot holds one
-// piece with a single configuration b, so each lane counts that configuration's events in one
-// 16-bit field per slot (two slots per word, flushed every 4,096 chunks).
-// SCORE: also the score sums of every tile, sum over its rejecting simulations of the arm counts
-// y_a (the sufficient statistic, Example 1), as packed pairs (y0 | y1 << 16, y2 | y3 << 16),
-// added to the tile's row in LDS with LDS atomics.  4-arm lanes add their own pairs (rejections
-// are rare at that design's cut).  Basket slots, where most simulations of a piece may reject, do
-// so only when a few lanes reject; otherwise the pairs are first summed over each 16-lane row by
-// DPP shifts and the four row totals are added (atomics of many lanes to one LDS word
-// serialise).  At most 64 * 35 per row and
-// chunk, so the 16-bit fields hold 15 chunks; the rows are added to the 64-bit tile sums in global
-// memory at every flush.  Rows past H4_SROWS (rare batches with many cut boxes) add to global
-// memory directly.
-constexpr int H4_SROWS = 128;
-constexpr int H4_FEW = 4;   // at most this many rejecting lanes: atomics straight from the lanes
-
-// Inclusive scan over the 16 lanes of each DPP row by row shifts of 1, 2, 4, 8 (shifted-in lanes
-// read 0): lane 15 of each row ends with the row's total.  Call with every lane active.
-__device__ __forceinline__ uint32_t row16_sum(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    return v;
+// Statistic planes: S_b = min_{a in b} of the outcome's row, for every configuration b = 1..nb, at the
+// outcome's tiled place (H4_SLAB).
+__global__ void k_h4_planes(const float4 *__restrict__ tbl, int64_t n, int nb, float *__restrict__ planes) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    constexpr int M1 = NP35 + 1;
+    const float4 q = tbl[i];
+    const uint32_t y3 = (uint32_t)(i % M1), y2 = (uint32_t)(i / M1 % M1);
+    const int64_t at = i / (M1 * M1) * H4_SLAB + 8 * h4_code2(y2) + h4_code3(y3);
+    for (int b = 1; b <= nb; ++b) {
+        float sb = INFINITY;
+        if (b & 1) sb = fminf(sb, q.x);
+        if (b & 2) sb = fminf(sb, q.y);
+        if (b & 4) sb = fminf(sb, q.z);
+        if (b & 8) sb = fminf(sb, q.w);
+        planes[(b - 1) * H4_PLANE + at] = sb;
+    }
 }
-constexpr uint64_t H4_REJ = 0xFEFCFAF0EECCAA00ull;   // byte m: configurations b (bits 1..7) with m & b != 0
 
-// Bracketed keys (KEYS = 2; blocks of at most H4_BROWS key rows): per tile the bracket (lo, hi)
-// from the pilot; the pass counts the keys below lo (per wave and key row in LDS, added to the
-// tile at the end of the item) and keeps
-// those in [lo, hi] in the tile's region of the item's range (caps slots; the count goes on past
-// caps, which sends the tile to the exact path).
-struct H4Brk {
-    const float2 *brk;
-    uint32_t *below;
-    uint32_t *cnt;     // per tile [1 + maxs]: [0] the pilot's candidates, [1 + s] item range s
-    float *cand;       // per tile [tot]: H4_PCAP pilot slots, then caps per item range
-    int64_t tot;
-    int32_t maxs, caps;
-    uint32_t k_lo;     // first simulation of the pass (the pilot holds the ones before)
-};
-template <int KEYS, bool BASKET, bool SCORE>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_hier4(const Blk4 *__restrict__ blocks,
-                                              const GroupItem *__restrict__ items, int64_t n_items,
-                                              uint32_t key0, uint32_t key1,
-                                              const float4 *__restrict__ tbl, const uint8_t *__restrict__ mtbl,
-                                              float cut, uint32_t *__restrict__ R,
-                                              unsigned long long *__restrict__ sumT, float *__restrict__ keys,
-                                              H4Brk hb) {
-    static_assert(KEYS != 2 || !BASKET, "bracketed keys serve the 4-arm design");
-    constexpr int NP = NP35;
-    constexpr int NW = 4 * NP;
-    constexpr int NB = NW / 4;   // 35 Philox blocks
-    constexpr int NBH = (NB + 1) / 2;   // blocks of the first half (18: words 0..71), then 17 (words 72..139)
-    constexpr int NWH = 4 * NBH;        // words held at once
-    constexpr int NWAVES = WG / WAVE;
-    constexpr int M1 = NP + 1;
-    constexpr int FLUSH_EVERY = 15;        // score rows: 16-bit fields hold 15 chunks
-    // Half of the chunk's Philox words at a time; between chunks the same memory holds the
-    // counter transposes (per wave 16 x (64 + 1) words, padded against bank conflicts).
-    __shared__ uint32_t words[NWH][WAVE];
-    __shared__ uint2 ysum[SCORE ? NWAVES : 1][SCORE ? H4_SROWS : 1];   // per wave and key row: packed y sums
-    // bracketed keys: per wave and key row, the tile's bracket (lo, hi as float bits), the keys
-    // below it and the candidates kept in this item; and the row's tile
-    __shared__ uint4 rcnt[KEYS == 2 ? NWAVES : 1][KEYS == 2 ? H4_BROWS : 1];
-    __shared__ int32_t rtile[KEYS == 2 ? NWAVES : 1][KEYS == 2 ? H4_BROWS : 1];
+hipError_t launch_h4_planes(const float4 *tbl, int nb, float *planes, hipStream_t st) {
+    const int64_t n = (int64_t)(NP35 + 1) * (NP35 + 1) * (NP35 + 1) * (NP35 + 1);
+    hipLaunchKernelGGL(k_h4_planes, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, tbl, n, nb, planes);
+    return hipGetLastError();
+}
 
+// ------------------------------------------------------------------------------------------
+// Simulation, 4 arms x 35 patients (words a*35 .. a*35+34 for arm a: 35 Philox blocks).
+//
+// k_h4_count counts every simulation's successes at every distinct threshold of each arm once for the
+// whole platten (16^4 boxes: 64 thresholds, where counting per batch of 64 boxes repeated them
+// 340-fold) into the count table.
+//
+// k_h4_tiles takes 64 tiles per wave, one per lane, and one simulation at a time for all of them:
+// the tile's sums and candidate list are its lane's own, nothing crosses lanes.  Tiles are ordered
+// so that a wave mostly holds one pair of thresholds of arms 0 and 1 and 8 x 8 neighbouring ones of
+// arms 2 and 3: their outcomes lie in a few lines of the table (tiled for that, H4_SLAB), where one
+// lane per simulation touched one line per lane.  Four simulations share the arithmetic on packed
+// counts; per simulation the table offset is one packed 16-bit dot product.  A calibration stores
+// only candidate keys (k_h4_pilot).
+// Bound by the gathers' addresses (about 16 cycles per instruction and CU).  16^4 boxes x 32,768
+// simulations, 4-arm calibration: counts 0.012, pilot 0.18, tiles 2.13 ms (4.40 with Philox words
+// and counts per batch of 64 boxes, lane = simulation, and 7.9 GB of keys stored) and the selection
+// 1.52 -> 0.77 ms; basket validation: 0.015 + 1.37 ms (6.50).
+// ------------------------------------------------------------------------------------------
+constexpr int H4C_NB = NP35;   // Philox blocks of a simulation
+__global__ __launch_bounds__(WG) void k_h4_count(const Grp4 *__restrict__ grp, int32_t n_grp, uint32_t win_b,
+                                                 uint32_t key0, uint32_t key1, uint2 *__restrict__ tab) {
+    constexpr int NWV = WG / WAVE;
+    __shared__ uint32_t words[4 * H4C_NB][WAVE];
+    __shared__ uint2 tr[NWV][WAVE];
     const int lane = threadIdx.x & (WAVE - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t it = blockIdx.x;
+    const uint32_t k0 = win_b * GRAN2 + blockIdx.x * WAVE;
+    for (int b = wv; b < H4C_NB; b += NWV) {
+        const u32x4 w = philox_block((uint32_t)b, k0 + (uint32_t)lane, key0, key1);
+        words[4 * b + 0][lane] = w.x;
+        words[4 * b + 1][lane] = w.y;
+        words[4 * b + 2][lane] = w.z;
+        words[4 * b + 3][lane] = w.w;
+    }
+    __syncthreads();
+    for (int g = (int)blockIdx.y * NWV + wv; g < n_grp; g += (int)gridDim.y * NWV) {   // uniform over the wave
+        const Grp4 *__restrict__ G = grp + g;
+        const uint32_t n = (uint32_t)G->n_sims;
+        if (k0 >= n) continue;
+        const int arm = G->arm;
+        uint32_t T[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            T[u] = G->T[u];
+            y[u] = 0u;
+        }
+        const uint32_t(*w)[WAVE] = words + arm * NP35;
+#pragma unroll 7
+        for (int j = 0; j < NP35; ++j) {
+            const uint32_t x = w[j][lane];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) y[u] += (x < T[u]) ? 1u : 0u;
+        }
+        // (simulation, threshold) bytes -> threshold-major granules: lane = granule q of the chunk,
+        // threshold t, half h of its 16 simulations
+        tr[wv][lane] = make_uint2(y[0] | (y[1] << 8) | (y[2] << 16) | (y[3] << 24),
+                                  y[4] | (y[5] << 8) | (y[6] << 16) | (y[7] << 24));
+        wave_sync4();
+        const int q = lane >> 4, t = (lane >> 1) & 7, h = lane & 1;
+        const uint8_t *src = reinterpret_cast<const uint8_t *>(&tr[wv][16 * q + 8 * h]) + t;
+        uint32_t b[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = src[8 * i];
+        wave_sync4();
+        const uint32_t kq = k0 + (uint32_t)(16 * q);   // the granule's first simulation
+        if (kq >= n || t >= G->n_thr) continue;
+        const int64_t stride = G->stride;
+        uint2 *__restrict__ dst = tab + (G->row + t * stride + (int64_t)(kq / GRAN2 - win_b)) * 2 + h;
+        dst[0] = make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24), b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
+        if (arm >= 2) {   // the code rows
+#pragma unroll
+            for (int i = 0; i < 8; ++i) b[i] = arm == 2 ? h4_code2(b[i]) : h4_code3(b[i]);
+            dst[16 * stride] =
+                make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24), b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
+        }
+    }
+}
+
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ us2 as_us2(uint32_t v) { return __builtin_bit_cast(us2, v); }
+__device__ __forceinline__ uint32_t as_u32(us2 v) { return __builtin_bit_cast(uint32_t, v); }
+// Table offsets of four simulations, whose counts (or codes) are the bytes of y0, y1, y2 and y3:
+// w01 (36 y0 + y1) + w23 (m2 y2 + y3) + base.
+__device__ __forceinline__ void h4_offsets(uint32_t y0, uint32_t y1, uint32_t y2, uint32_t y3, uint16_t m2, uint32_t w,
+                                           uint32_t base, uint32_t off[4]) {
+    auto ev = [](uint32_t v) { return as_us2(v & 0x00FF00FFu); };                               // simulations 0, 2
+    auto od = [](uint32_t v) { return as_us2(__builtin_amdgcn_perm(0u, v, 0x0C030C01u)); };     // simulations 1, 3
+    const us2 c36 = {(unsigned short)(NP35 + 1), (unsigned short)(NP35 + 1)}, cm = {m2, m2};
+    const uint32_t ae = as_u32(ev(y0) * c36 + ev(y1)), ao = as_u32(od(y0) * c36 + od(y1));
+    const uint32_t be = as_u32(ev(y2) * cm + ev(y3)), bo = as_u32(od(y2) * cm + od(y3));
+    // (low or high halves of a and b side by side) . (w01, w23)
+    off[0] = __builtin_amdgcn_udot2(as_us2(__builtin_amdgcn_perm(be, ae, 0x05040100u)), as_us2(w), base, false);
+    off[1] = __builtin_amdgcn_udot2(as_us2(__builtin_amdgcn_perm(bo, ao, 0x05040100u)), as_us2(w), base, false);
+    off[2] = __builtin_amdgcn_udot2(as_us2(__builtin_amdgcn_perm(be, ae, 0x07060302u)), as_us2(w), base, false);
+    off[3] = __builtin_amdgcn_udot2(as_us2(__builtin_amdgcn_perm(bo, ao, 0x07060302u)), as_us2(w), base, false);
+}
+__device__ __forceinline__ uint32_t u4_get(const uint4 &v, int i) {
+    return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w));
+}
+constexpr uint32_t H4_W_PLANE = (uint32_t)(4 * H4_SLAB) | (4u << 16);            // byte offsets into a plane (codes, m2 = 8)
+constexpr uint32_t H4_W_MASK = (uint32_t)((NP35 + 1) * (NP35 + 1)) | (1u << 16);   // into the mask table (counts, m2 = 36)
+static_assert(4 * H4_SLAB < 65536 && 15 * 4 * H4_PLANE < (1ll << 32), "16-bit weights, 32-bit offsets");
+
+// A set's count rows in LDS, a chunk (64 simulations) at a time: the distinct rows are loaded once for
+// the wave, 16 rows per instruction, and each lane reads its own from LDS (a global 16-byte load per
+// lane and arm took 63 cycles whether the lanes' addresses agreed or not, and 960 of 1,640 us on the
+// basket's 16^4 boxes).  The next chunk's first H4_AHEAD * 16 rows are loaded ahead.
+constexpr int H4_AHEAD = 3;
+struct H4Rows {
+    const uint4 *__restrict__ tab;
+    const uint32_t *__restrict__ rows;
+    uint4 *__restrict__ lds;
+    int32_t n;
+    const uint4 *src[H4_AHEAD];   // this lane's piece of chunk 0 of the rows loaded ahead (past the list: its last row)
+    uint4 nx[H4_AHEAD];
+    __device__ __forceinline__ H4Rows(const uint4 *__restrict__ tab_, const uint32_t *__restrict__ rows_, int32_t n_,
+                                      uint4 *lds_)
+        : tab(tab_), rows(rows_), lds(lds_), n(n_) {
+        const int lane = threadIdx.x & (WAVE - 1);
+#pragma unroll
+        for (int i = 0; i < H4_AHEAD; ++i) src[i] = tab + rows[min(16 * i + (lane >> 2), n - 1)] + (lane & 3);
+    }
+    __device__ __forceinline__ void load(uint32_t chunk) {
+#pragma unroll
+        for (int i = 0; i < H4_AHEAD; ++i) nx[i] = src[i][4 * chunk];
+    }
+    __device__ __forceinline__ void store(uint32_t chunk) {   // the loaded chunk and its further rows into LDS
+        const int lane = threadIdx.x & (WAVE - 1);
+        wave_sync4();
+#pragma unroll
+        for (int i = 0; i < H4_AHEAD; ++i) {
+            const int r = 16 * i + (lane >> 2);
+            if (r < n) lds[r * H4_ROW_LDS + (lane & 3)] = nx[i];
+        }
+        for (int r = 16 * H4_AHEAD + (lane >> 2); r < n; r += 16)
+            lds[r * H4_ROW_LDS + (lane & 3)] = tab[rows[r] + 4 * chunk + (lane & 3)];
+        wave_sync4();
+    }
+};
+
+// Upper bound of each tile's k-th smallest key from the first h4_pilot(N) simulations: about the order
+// statistic of rank r = mu + z sd + z^2 / 6 + 1, mu = m k / N (z = 6 by default; the z^2 / 6 is the
+// skewness of a Poisson count: without it and at z = 5 one seed in three left some of the 60,112
+// tiles of 16^4 boxes short).  A histogram finds the bin of that order statistic, 8 bins per octave
+// from 2^-20 to 1/4, then 256 per unit up to 1 (keys of tiles deep in the null crowd towards 1); the
+// bound is its upper edge, unless that admits too many pilot keys: then the bin is divided
+// again, down to a single value where the statistic has an atom there (few distinct outcomes), and
+// the tile's keys equal to the bound are counted, not kept.  One workgroup per set, lane = tile, its
+// four waves share the pilot's simulations.
+constexpr int H4P_LOG = 18 * 8, H4P_BINS = H4P_LOG + 192 + 1;
+constexpr uint32_t H4P_BIN0 = (127u - 20u) << 3;
+__device__ __forceinline__ int h4p_bin(float v) {   // v in [0, 1]
+    const int lo = max((int)(__float_as_uint(v) >> 20) - (int)H4P_BIN0, 0);
+    const int hi = H4P_LOG - 64 + (int)(v * 256.0f);
+    return v < 0.25f ? lo : min(hi, H4P_BINS - 1);
+}
+__device__ __forceinline__ float h4p_edge(int b) {   // upper edge: every key of the bin lies below it
+    return b < H4P_LOG ? __uint_as_float(((uint32_t)b + 1u + H4P_BIN0) << 20) : 0.25f + (float)(b + 1 - H4P_LOG) * (1.0f / 256.0f);
+}
+__global__ __launch_bounds__(WG) void k_h4_pilot(const H4Set *__restrict__ sets, const uint32_t *__restrict__ rows,
+                                                 int32_t max_rows, const uint4 *__restrict__ tab,
+                                                 const float *__restrict__ planes, const int32_t *__restrict__ kk,
+                                                 float margin, float *__restrict__ U, uint32_t *__restrict__ eq,
+                                                 uint32_t *__restrict__ fb) {
+    constexpr int NWV = WG / WAVE;
+    __shared__ uint32_t hist[H4P_BINS * WAVE / 2];   // 16-bit counts, two lanes per word
+    __shared__ uint2 range[WAVE];                    // per tile: the keys' bits [x, y) being divided
+    __shared__ uint32_t more;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const H4Set *__restrict__ S = sets + blockIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) fb[0] = 0u;
+    const int32_t N = S->n_sims;
+    const int32_t t = S->tile[lane];
+    const int32_t k = t >= 0 ? kk[t] : 0;
+    if (wv == 0 && t >= 0) eq[t] = 0u;
+    if (N < H4_PILOT_MIN_N) {   // uniform: every key is a candidate
+        if (wv == 0 && t >= 0) U[t] = INFINITY;
+        return;
+    }
+    const bool sel = k >= 1 && k <= N;
+    const int m = h4_pilot(N), nch = m / WAVE;
+    const uint32_t base = (S->cfg[lane] - 1u) * (uint32_t)(4 * H4_PLANE);
+    extern __shared__ uint4 h4_lds[];
+    H4Rows rr(tab, rows + S->row_at, S->n_rows, h4_lds + (size_t)wv * max_rows * H4_ROW_LDS);
+    const uint4 *__restrict__ l0 = rr.lds + S->row[0][lane] * H4_ROW_LDS, *__restrict__ l1 = rr.lds + S->row[1][lane] * H4_ROW_LDS,
+                *__restrict__ l2 = rr.lds + S->row[4][lane] * H4_ROW_LDS, *__restrict__ l3 = rr.lds + S->row[5][lane] * H4_ROW_LDS;
+    const float pr = (float)k / (float)N, mean = pr * (float)m;
+    const float rank = mean + margin * sqrtf(mean * (1.0f - pr)) + margin * margin * (1.0f / 6.0f) + 1.0f;
+    // pilot keys the bound may admit before its bin is divided: those of 1,800 candidates, or a quarter
+    // over rank
+    const float most = fmaxf(1.25f * rank + 8.0f, 1800.0f * (float)m / (float)N);
+    uint2 r = make_uint2(0u, 0xFFFFFFFFu);    // first pass: the fixed bins
+    float below = 0.0f;                       // pilot keys below the range (wave 0)
+    bool open = sel && wv == 0;               // wave 0: the tile's bound is not final
+    for (int pass = 0;; ++pass) {
+        for (int i = threadIdx.x; i < H4P_BINS * WAVE / 2; i += WG) hist[i] = 0u;
+        if (threadIdx.x == 0) more = 0u;
+        if (pass > 0) r = range[lane];
+        // later passes: bins of 2^sh consecutive floats, at most 256
+        const uint32_t width = r.y - r.x, sh = width > 256u ? 24u - (uint32_t)__builtin_clz(width - 1u) : 0u;
+        __syncthreads();
+        if (wv < nch) rr.load(wv);
+        for (int c = wv; c < nch; c += NWV) {
+            rr.store(c);
+            if (c + NWV < nch) rr.load(c + NWV);
+            for (int g = 0; g < 4; ++g) {
+                const uint4 y0 = l0[g], y1 = l1[g], y2 = l2[g], y3 = l3[g];
+                float v[GRAN2];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint32_t off[4];
+                    h4_offsets(u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q), 8, H4_W_PLANE, base, off);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        v[4 * q + j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(planes) + off[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < GRAN2; ++j) {
+                    const uint32_t bits = __float_as_uint(v[j]);
+                    if (pass == 0 || (bits >= r.x && bits < r.y)) {
+                        const int b = pass == 0 ? h4p_bin(v[j]) : (int)((bits - r.x) >> sh);
+                        atomicAdd(&hist[b * (WAVE / 2) + (lane >> 1)], 1u << (16 * (lane & 1)));
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (open) {
+            float run = below;
+            int b = 0;
+            const int nb = pass == 0 ? H4P_BINS : 256;
+            float c = 0.0f;
+            for (; b < nb; ++b) {
+                c = (float)((hist[b * (WAVE / 2) + (lane >> 1)] >> (16 * (lane & 1))) & 0xFFFFu);
+                if (run + c >= rank) break;
+                run += c;
+            }
+            float u = INFINITY;   // fewer than r pilot keys: every key is a candidate
+            open = false;
+            if (b < nb) {
+                if (pass == 0) {
+                    u = h4p_edge(b);
+                    r = make_uint2(b == 0 ? 0u : __float_as_uint(h4p_edge(b - 1)), __float_as_uint(u));
+                } else {
+                    r.x += (uint32_t)b << sh;
+                    r.y = min(r.y, r.x + (1u << sh));
+                    u = __uint_as_float(r.y);
+                }
+                if (run + c > most) {
+                    if (r.y - r.x <= 1u) u = __uint_as_float(r.x);   // one value: its keys are counted
+                    else open = true;
+                }
+                below = run;
+            }
+            if (open) atomicAdd(&more, 1u);
+            else U[t] = u;
+        }
+        if (wv == 0) range[lane] = open ? r : make_uint2(0u, 0u);
+        __syncthreads();
+        if (more == 0u) break;   // uniform
+        __syncthreads();         // `more` is read before the next pass clears it
+    }
+    if (wv == 0 && t >= 0 && !sel) U[t] = -INFINITY;   // no selection
+}
+
+// MODE 0: rejection counts and score sums from the one-byte mask table; 1: from the statistic planes,
+// every key stored; 2: from the planes, the keys below the tile's bound U stored as candidates, those
+// equal to it counted.
+template <int MODE, bool SCORE>
+__global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets, const H4Item *__restrict__ items,
+                                                 int64_t n_items, const uint32_t *__restrict__ rows, int32_t max_rows,
+                                                 const uint4 *__restrict__ tab, uint32_t win_b,
+                                                 uint32_t win_e, const uint8_t *__restrict__ mtbl,
+                                                 const float *__restrict__ planes, float cut,
+                                                 uint32_t *__restrict__ R, unsigned long long *__restrict__ sumT,
+                                                 float *__restrict__ keys, const float *__restrict__ U,
+                                                 uint32_t *__restrict__ eq, uint32_t *__restrict__ cnt) {
+    constexpr uint32_t H = 0x80808080u;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t it = (int64_t)blockIdx.x * (WG / WAVE) + wv;
     if (it >= n_items) return;
-    const GroupItem *__restrict__ G = items + it;
-    const int32_t blk = G->blk[wv];   // read in place: a register copy indexed by wv would go to scratch
-    const bool live = blk >= 0;
-    const Blk4 *__restrict__ B = blocks + (live ? blk : G->blk[0]);
-    const uint32_t kb = KEYS == 2 ? max(G->k_begin, hb.k_lo) : G->k_begin, ke = G->k_end;
-    uint32_t T0[B4N0], T1[B4N1], T2[B4N2], T3[B4N3];
-#pragma unroll
-    for (int u = 0; u < B4N0; ++u) T0[u] = B->T0[u];
-#pragma unroll
-    for (int u = 0; u < B4N1; ++u) T1[u] = B->T1[u];
-#pragma unroll
-    for (int u = 0; u < B4N2; ++u) T2[u] = B->T2[u];
-#pragma unroll
-    for (int u = 0; u < B4N3; ++u) T3[u] = B->T3[u];
-    const int32_t n_rows = B->n_rows;
-    float *__restrict__ kbase = keys + (KEYS == 1 ? B->key_base : 0);
-    const int32_t slice = G->slice;
-    if (KEYS == 2 && live) {
-        static_assert(B4S == WAVE, "one lane per slot");
-        const int32_t r0 = B->row0[lane];
-        if (r0 >= 0) {
-            const int nq = __popc(B->bmask[lane]);
-            for (int q = 0; q < nq && r0 + q < H4_BROWS; ++q) {
-                const int32_t t = B->tile0[lane] + q;
-                const float2 br = hb.brk[t];
-                rtile[wv][r0 + q] = t;
-                rcnt[wv][r0 + q] = make_uint4(__float_as_uint(br.x), __float_as_uint(br.y), 0u, 0u);
-            }
-        }
-        wave_sync4();
+    const H4Item *__restrict__ I = items + it;
+    const uint32_t gb = max(I->g_begin, win_b), ge = min(I->g_end, win_e);
+    if (gb >= ge) return;
+    const H4Set *__restrict__ S = sets + I->set;
+    const int32_t N = S->n_sims, t = S->tile[lane];
+    const uint32_t cfg = S->cfg[lane];
+    extern __shared__ uint4 h4_lds[];
+    H4Rows rr(tab, rows + S->row_at, S->n_rows, h4_lds + (size_t)wv * max_rows * H4_ROW_LDS);
+    auto lrow = [&](int a) { return rr.lds + S->row[a][lane] * H4_ROW_LDS; };
+    const uint4 *__restrict__ l0 = lrow(0), *__restrict__ l1 = lrow(1), *__restrict__ l2 = lrow(2),
+                *__restrict__ l3 = lrow(3), *__restrict__ c2 = lrow(4), *__restrict__ c3 = lrow(5);
+    const uint32_t base = (cfg - 1u) * (uint32_t)(4 * H4_PLANE), cfg4 = cfg * 0x01010101u;
+    const float bound = MODE == 2 ? (t >= 0 ? U[t] : -INFINITY) : 0.0f;
+    // MODE 2: keys at or above it matter to nothing (the float after the bound: keys equal to it count)
+    const float look = fmaxf(cut, bound >= 0.0f && bound < INFINITY ? __uint_as_float(__float_as_uint(bound) + 1u) : bound);
+    uint32_t ncand = 0u, neq = 0u, cap = 0u;
+    float *__restrict__ kp = keys;
+    if (MODE == 1) kp = keys + S->key_base + (int64_t)lane * WAVE;
+    if (MODE == 2) {
+        cap = (uint32_t)h4_cap(N, S->slice);
+        kp = keys + S->key_base + ((int64_t)lane * S->n_slices + I->slice) * cap;
     }
-    // one key of a bracketed row (every lane of the wave calls): below the bracket it is counted,
-    // inside it kept at the next free slot of the tile's region for this item range
-    // (the plattens that take this pass have at most H4_BROWS key rows per block)
-    auto take_key = [&](bool act_key, int32_t row, int32_t tile, float sb) {
-        const uint4 v = rcnt[wv][row];   // bracket and counts (one LDS read, the same address in every lane)
-        const float lo = __uint_as_float(v.x), hi = __uint_as_float(v.y);
-        const bool bl = act_key && sb < lo;
-        const bool in = act_key && sb >= lo && sb <= hi;
-        const unsigned long long mb = __ballot(bl), mi = __ballot(in);
-        if (!(mb | mi)) return;   // uniform
-        if (lane == 0) {
-            rcnt[wv][row].z = v.z + (uint32_t)__popcll(mb);
-            rcnt[wv][row].w = v.w + (uint32_t)__popcll(mi);
-        }
-        if (in) {
-            const uint32_t pos = v.w + (uint32_t)__popcll(mi & ((1ull << lane) - 1ull));
-            if (pos < (uint32_t)hb.caps) hb.cand[(int64_t)tile * hb.tot + H4_PCAP + (int64_t)slice * hb.caps + pos] = sb;
+    const int64_t kstride = (int64_t)S->n_lanes * WAVE;
+    uint32_t aR = 0u, a0 = 0u, a1 = 0u, a2 = 0u, a3 = 0u;
+    auto add = [&](uint32_t f, uint32_t y0, uint32_t y1, uint32_t y2, uint32_t y3) {   // f: 128 per rejecting simulation
+        aR += (uint32_t)__popc(f);
+        if (SCORE) {
+            a0 = __builtin_amdgcn_udot4(f, y0, a0, false);
+            a1 = __builtin_amdgcn_udot4(f, y1, a1, false);
+            a2 = __builtin_amdgcn_udot4(f, y2, a2, false);
+            a3 = __builtin_amdgcn_udot4(f, y3, a3, false);
         }
     };
-
-    if (SCORE)
-        for (int r = lane; r < H4_SROWS; r += WAVE) ysum[wv][r] = make_uint2(0u, 0u);
-    // packed count pairs into a tile's row (LDS) or, past the LDS rows, its 64-bit sums
-    auto add_pairs = [&](int32_t row, int32_t tile, uint32_t lo, uint32_t hi) {
-        if (row < H4_SROWS) {
-            atomicAdd(&ysum[wv][row].x, lo);
-            atomicAdd(&ysum[wv][row].y, hi);
-        } else {
-            atomicAdd(&sumT[4 * (int64_t)tile + 0], (unsigned long long)(lo & 0xFFFFu));
-            atomicAdd(&sumT[4 * (int64_t)tile + 1], (unsigned long long)(lo >> 16));
-            atomicAdd(&sumT[4 * (int64_t)tile + 2], (unsigned long long)(hi & 0xFFFFu));
-            atomicAdd(&sumT[4 * (int64_t)tile + 3], (unsigned long long)(hi >> 16));
+    rr.load((gb - win_b) / 4);   // items and windows begin at chunks
+    for (uint32_t g0 = gb; g0 < ge; g0 += 4) {
+    rr.store((g0 - win_b) / 4);
+    if (g0 + 4 < ge) rr.load((g0 + 4 - win_b) / 4);
+    for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t g = g0 + i;
+        if (g >= ge) break;   // uniform
+        const uint4 y0 = l0[i], y1 = l1[i];
+        uint4 y2 = make_uint4(0u, 0u, 0u, 0u), y3 = y2, e2 = y2, e3 = y2;
+        if (MODE == 0 || SCORE) {
+            y2 = l2[i];
+            y3 = l3[i];
         }
-    };
-    // one lane's counts (y0, y1, y2, y3) into a tile's sums
-    auto add_counts = [&](int32_t row, int32_t tile, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-        if (row < H4_SROWS) {
-            atomicAdd(&ysum[wv][row].x, a | (b << 16));
-            atomicAdd(&ysum[wv][row].y, c | (d << 16));
-        } else {
-            atomicAdd(&sumT[4 * (int64_t)tile + 0], (unsigned long long)a);
-            atomicAdd(&sumT[4 * (int64_t)tile + 1], (unsigned long long)b);
-            atomicAdd(&sumT[4 * (int64_t)tile + 2], (unsigned long long)c);
-            atomicAdd(&sumT[4 * (int64_t)tile + 3], (unsigned long long)d);
+        if (MODE != 0) {
+            e2 = c2[i];
+            e3 = c3[i];
         }
-    };
-    // the counts of the lanes whose simulation rejects (ev) into the tile's sums; every lane calls
-    auto add_score = [&](bool ev, int32_t row, int32_t tile, uint32_t lo, uint32_t hi) {
-        const unsigned long long bal = __ballot(ev);
-        if (!bal) return;
-        if (__popcll(bal) <= H4_FEW) {
-            if (ev) add_pairs(row, tile, lo, hi);
-            return;
-        }
-        const uint32_t a = row16_sum(ev ? lo : 0u), b = row16_sum(ev ? hi : 0u);
-        if ((lane & 15) == 15 && (a | b)) add_pairs(row, tile, a, b);
-    };
-    // the LDS rows into the tiles' 64-bit sums (lanes take a slot's rows), then cleared
-    auto flush_scores = [&]() {
-        wave_sync4();
-        for (int s = 0; s < B4S; ++s) {
-            const int32_t r0 = B->row0[s];
-            if (r0 < 0) continue;   // uniform
-            const int nq = BASKET ? 1 : __popc(B->bmask[s]);
-            const int r = r0 + lane;
-            if (lane < nq && r < H4_SROWS) {
-                const uint2 v = ysum[wv][r];
-                if (v.x | v.y) {
-                    const int64_t t = (int64_t)B->tile0[s] + lane;
-                    atomicAdd(&sumT[4 * t + 0], (unsigned long long)(v.x & 0xFFFFu));
-                    atomicAdd(&sumT[4 * t + 1], (unsigned long long)(v.x >> 16));
-                    atomicAdd(&sumT[4 * t + 2], (unsigned long long)(v.y & 0xFFFFu));
-                    atomicAdd(&sumT[4 * t + 3], (unsigned long long)(v.y >> 16));
-                    ysum[wv][r] = make_uint2(0u, 0u);
-                }
+        const int nv = N - (int)(g * GRAN2);   // simulations from this granule on (uniform)
+        uint32_t m[GRAN2];
+        float v[GRAN2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t off[4];
+            if (MODE == 0) {
+                h4_offsets(u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q), NP35 + 1, H4_W_MASK, 0u, off);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) m[4 * q + j] = mtbl[off[j]];
+            } else {
+                h4_offsets(u4_get(y0, q), u4_get(y1, q), u4_get(e2, q), u4_get(e3, q), 8, H4_W_PLANE, base, off);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    v[4 * q + j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(planes) + off[j]);
             }
         }
-        wave_sync4();
-    };
-
-    // One word per pair of slots (2p, 2p + 1).  4-arm: seven 2-bit fields per slot, field m - 1 of
-    // slot 2p + h at bit 14 h + 2 (m - 1), counting the simulations with rejection mask m (at most
-    // ACC_EVERY = 3 per lane between flushes); basket: a 16-bit count per slot at bit 16 h.
-    // Half the registers of one word per slot, which leaves room for a whole group's table rows.
-    constexpr int NACC = B4S / 2;
-    constexpr int ACC_EVERY = BASKET ? 4096 : 3;
-    constexpr int TRW = NACC / 2;   // counter words per flush half
-    static_assert(NWAVES * TRW * (WAVE + 1) <= NWH * WAVE, "flush transposes must fit in the word buffer");
-    uint32_t(*tr)[TRW][WAVE + 1] = reinterpret_cast<uint32_t(*)[TRW][WAVE + 1]>(&words[0][0]);
-    uint32_t acc[NACC];
+        if (MODE == 1 && t >= 0) {
+            float *__restrict__ kc = kp + (int64_t)(g / 4) * kstride + (g % 4) * GRAN2;
 #pragma unroll
-    for (int p = 0; p < NACC; ++p) acc[p] = 0u;
-    // the counters of the chunks since the last flush into R: the wave transposes the words
-    // through the word buffer, lanes l and l + 32 sum word l over their halves of the simulations
-    // (byte-wise: four fields at a time, at most 3 x 64 per byte), and lane l adds the per-
-    // configuration totals of slots 2l and 2l + 1
-    auto flush = [&]() {
-        __syncthreads();   // the word buffer is free: every wave has finished counting
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {   // counter words 16 h .. 16 h + 15 (slots 32 h .. 32 h + 31)
-#pragma unroll
-            for (int p = 0; p < TRW; ++p) tr[wv][p][lane] = acc[h * TRW + p];
-            wave_sync4();
-            const int pw = lane & (TRW - 1), j0 = (lane / TRW) * (WAVE / 4);
-            uint32_t A[4] = {0u, 0u, 0u, 0u};
-            for (int j = j0; j < j0 + WAVE / 4; ++j) {
-                const uint32_t x = tr[wv][pw][j];
-                if (BASKET) {
-                    A[0] += x & 0xFFFFu;
-                    A[1] += x >> 16;
-                    continue;
-                }
-#pragma unroll
-                for (int c = 0; c < 4; ++c) A[c] += (x >> (2 * c)) & 0x03030303u;
-            }
-            wave_sync4();
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {   // the four lane groups' sums (at most 3 x 64 per byte)
-                A[c] += __shfl_xor(A[c], TRW);
-                A[c] += __shfl_xor(A[c], 2 * TRW);
-            }
-            if (live && lane < TRW) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                    const int s = 2 * (h * TRW + pw) + hh;
-                    const int32_t t0 = B->tile0[s];
-                    if (t0 < 0) continue;
-                    if (BASKET) {
-                        if (A[hh]) atomicAdd(&R[t0], A[hh]);
-                        continue;
-                    }
-                    uint32_t cnt[8];
-#pragma unroll
-                    for (int m = 1; m <= 7; ++m) {
-                        const int f = 7 * hh + m - 1;   // field f: byte f / 4 of class f % 4
-                        cnt[m] = (A[f % 4] >> (8 * (f / 4))) & 0xFFu;
-                    }
-                    const uint32_t bm = B->bmask[s];
-                    int q = 0;
-#pragma unroll
-                    for (int b = 1; b <= 7; ++b) {
-                        if (!(bm & (1u << b))) continue;
-                        uint32_t r = 0u;
-#pragma unroll
-                        for (int m = 1; m <= 7; ++m)
-                            if (m & b) r += cnt[m];
-                        if (r) atomicAdd(&R[t0 + q], r);
-                        ++q;
-                    }
-                }
-            }
-            wave_sync4();   // this half's transposes are read before the next half's are written
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4 *>(kc + 4 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
         }
 #pragma unroll
-        for (int p = 0; p < NACC; ++p) acc[p] = 0u;
-        __syncthreads();   // transposes read before the next chunk's words overwrite them
-    };
-
-    int since = 0, since_acc = 0;
-    for (uint32_t k0 = kb; k0 < ke; k0 += WAVE) {
-        const uint32_t k = k0 + (uint32_t)lane;
-        const bool act = k < ke;
-        // the words in two halves (LDS for half of them at a time): blocks 0..17 give arms 0
-        // and 1 and the first two words of arm 2, blocks 18..34 the rest of arm 2 and arm 3
-        int y0[B4N0], y1[B4N1], y2[B4N2], y3[B4N3];
+        for (int q = 0; q < 4; ++q) {
+            const int n4 = nv - 4 * q;   // uniform
+            const uint32_t valid = n4 >= 4 ? H : (n4 <= 0 ? 0u : H >> (8 * (4 - n4)));
+            uint32_t f = 0u;
+            if (MODE == 0) {
+                // bytes (mask & b) != 0: a sum with 0x7F sets bit 7 (masks are below 16)
+                const uint32_t x = (m[4 * q] | (m[4 * q + 1] << 8) | (m[4 * q + 2] << 16) | (m[4 * q + 3] << 24)) & cfg4;
+                f = (x + 0x7F7F7F7Fu) & valid;
+                add(f, u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q));
+            } else {
+                const float *vq = v + 4 * q;
+                const bool any = fminf(fminf(vq[0], vq[1]), fminf(vq[2], vq[3])) < (MODE == 2 ? look : cut);
+                if (__ballot(any) == 0ull) continue;   // rejections and candidates are a few per cent
 #pragma unroll
-        for (int u = 0; u < B4N0; ++u) y0[u] = 0;
+                for (int j = 0; j < 4; ++j) f |= vq[j] < cut ? 0x80u << (8 * j) : 0u;
+                f &= valid;
+                add(f, u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q));
+                if (MODE == 2) {
 #pragma unroll
-        for (int u = 0; u < B4N1; ++u) y1[u] = 0;
-#pragma unroll
-        for (int u = 0; u < B4N2; ++u) y2[u] = 0;
-#pragma unroll
-        for (int u = 0; u < B4N3; ++u) y3[u] = 0;
-        for (int b = wv; b < NBH; b += NWAVES) {
-            const u32x4 w = philox_block((uint32_t)b, k, key0, key1);
-            words[4 * b + 0][lane] = w.x;
-            words[4 * b + 1][lane] = w.y;
-            words[4 * b + 2][lane] = w.z;
-            words[4 * b + 3][lane] = w.w;
-        }
-        __syncthreads();
-        if (live) {
-#pragma unroll 7
-            for (int j = 0; j < NP; ++j) {
-                const uint32_t x = words[j][lane];
-#pragma unroll
-                for (int u = 0; u < B4N0; ++u) y0[u] += (x < T0[u]) ? 1 : 0;
-            }
-#pragma unroll 7
-            for (int j = NP; j < 2 * NP; ++j) {
-                const uint32_t x = words[j][lane];
-#pragma unroll
-                for (int u = 0; u < B4N1; ++u) y1[u] += (x < T1[u]) ? 1 : 0;
-            }
-#pragma unroll
-            for (int j = 2 * NP; j < NWH; ++j) {
-                const uint32_t x = words[j][lane];
-#pragma unroll
-                for (int u = 0; u < B4N2; ++u) y2[u] += (x < T2[u]) ? 1 : 0;
-            }
-        }
-        __syncthreads();   // the first half is counted: its memory takes the second
-        for (int b = NBH + wv; b < NB; b += NWAVES) {
-            const u32x4 w = philox_block((uint32_t)b, k, key0, key1);
-            words[4 * (b - NBH) + 0][lane] = w.x;
-            words[4 * (b - NBH) + 1][lane] = w.y;
-            words[4 * (b - NBH) + 2][lane] = w.z;
-            words[4 * (b - NBH) + 3][lane] = w.w;
-        }
-        __syncthreads();
-        if (live) {
-#pragma unroll 11
-            for (int j = NWH; j < 3 * NP; ++j) {
-                const uint32_t x = words[j - NWH][lane];
-#pragma unroll
-                for (int u = 0; u < B4N2; ++u) y2[u] += (x < T2[u]) ? 1 : 0;
-            }
-#pragma unroll 7
-            for (int j = 3 * NP; j < 4 * NP; ++j) {
-                const uint32_t x = words[j - NWH][lane];
-#pragma unroll
-                for (int u = 0; u < B4N3; ++u) y3[u] += (x < T3[u]) ? 1 : 0;
-            }
-        }
-        __syncthreads();
-        if (live) {
-            float *__restrict__ kc = kbase + (size_t)(k0 / WAVE) * n_rows * WAVE + lane;
-            // Neighbouring thresholds of an arm often give a simulation the same count, and then
-            // two slots share the outcome.  The slots of one u0 and GU1 consecutive u1 form a
-            // group (16 slots; 8 in the keyed variants, whose rows take three registers each and
-            // which run 5 waves per SIMD): its gathers are issued first, skipping a slot whose
-            // outcome equals that of the slot at the previous u1 (same group), u3 or u2 (fewer
-            // gathers are fewer L2 requests, the table being read at random rows), then one
-            // wait, then the slots are evaluated and their keys stored.  Vector memory counts
-            // loads and stores together, so a gather used right after the previous slot's key
-            // stores would also wait for those stores.
-            constexpr int S2 = B4N3, S1 = B4N2 * B4N3;
-            constexpr int GU1 = KEYS == 2 ? 1 : (KEYS ? 2 : B4N1);   // u1 values per group (keyed: fewer rows in registers)
-            constexpr int G = GU1 * S1;
-#pragma unroll
-            for (int ug = 0; ug < B4N0 * (B4N1 / GU1); ++ug) {
-                const int u0 = ug / (B4N1 / GU1), u1b = (ug % (B4N1 / GU1)) * GU1;
-                float4 qs[G];
-                uint32_t ms[G];
-                // whether slot i of the group repeats the outcome of the slot at u1 - 1 (same group),
-                // u3 - 1 or u2 - 1
-                auto repeats = [&](int i, bool &r1, bool &r3, bool &r2) {
-                    const int i1 = i / S1, u1 = u1b + i1, u2 = (i / S2) % B4N2, u3 = i % S2;
-                    const int s = (u0 * B4N1 + u1) * S1 + u2 * S2 + u3;
-                    r1 = i1 > 0 && B->row0[i1 > 0 ? s - S1 : s] >= 0 && y1[u1] == y1[u1 > 0 ? u1 - 1 : 0];
-                    r3 = u3 > 0 && B->row0[u3 > 0 ? s - 1 : s] >= 0 && y3[u3] == y3[u3 > 0 ? u3 - 1 : 0];
-                    r2 = u2 > 0 && B->row0[u2 > 0 ? s - S2 : s] >= 0 && y2[u2] == y2[u2 > 0 ? u2 - 1 : 0];
-                };
-#pragma unroll
-                for (int i = 0; i < G; ++i) {
-                    const int u1 = u1b + i / S1, u2 = (i / S2) % B4N2, u3 = i % S2;
-                    const int s = (u0 * B4N1 + u1) * S1 + u2 * S2 + u3;
-                    qs[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    ms[i] = 0u;
-                    if (B->row0[s] < 0) continue;   // uniform: the slot holds no box
-                    bool r1, r3, r2;
-                    repeats(i, r1, r3, r2);
-                    if (!(r1 || r2 || r3)) {
-                        const int idx = ((y0[u0] * M1 + y1[u1]) * M1 + y2[u2]) * M1 + y3[u3];
-                        if (KEYS) qs[i] = tbl[idx];
-                        else ms[i] = (uint32_t)mtbl[idx];
-                    }
-                }
-                // vmcnt 0, expcnt and lgkmcnt left alone: the group's rows are in registers
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-#pragma unroll
-                for (int i = 0; i < G; ++i) {
-                    const int u1 = u1b + i / S1, u2 = (i / S2) % B4N2, u3 = i % S2;
-                    const int s = (u0 * B4N1 + u1) * S1 + u2 * S2 + u3;
-                    const int32_t row0 = B->row0[s];
-                    if (row0 < 0) continue;   // uniform
-                    bool r1, r3, r2;
-                    repeats(i, r1, r3, r2);
-                    const int i1 = i >= S1 ? i - S1 : i, i3 = u3 > 0 ? i - 1 : i, i2 = u2 > 0 ? i - S2 : i;
-                    // a repeat takes its source's row (resolved earlier in the group); selects
-                    // between values, not between array elements (a select of addresses would keep
-                    // the arrays out of registers)
-                    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-                    uint32_t m;
-                    if (KEYS) {
-                        const float4 a1 = qs[i1], a3 = qs[i3], a2 = qs[i2], a0 = qs[i];
-                        q.x = r1 ? a1.x : (r3 ? a3.x : (r2 ? a2.x : a0.x));
-                        q.y = r1 ? a1.y : (r3 ? a3.y : (r2 ? a2.y : a0.y));
-                        q.z = r1 ? a1.z : (r3 ? a3.z : (r2 ? a2.z : a0.z));
-                        if (BASKET) q.w = r1 ? a1.w : (r3 ? a3.w : (r2 ? a2.w : a0.w));
-                        qs[i] = q;
-                        m = act ? ((q.x < cut ? 1u : 0u) | (q.y < cut ? 2u : 0u) | (q.z < cut ? 4u : 0u) |
-                                   (BASKET && q.w < cut ? 8u : 0u))
-                                : 0u;
-                    } else {
-                        const uint32_t mm = r1 ? ms[i1] : (r3 ? ms[i3] : (r2 ? ms[i2] : ms[i]));
-                        ms[i] = mm;
-                        m = act ? mm : 0u;
-                    }
-                            if (BASKET) {
-                                const uint32_t b = (uint32_t)__builtin_ctz(B->bmask[s]);   // the slot's one b
-                                acc[s >> 1] += (m & b) ? 1u << (16 * (s & 1)) : 0u;
-                                if (SCORE)
-                                    add_score((m & b) != 0u, row0, B->tile0[s], (uint32_t)(y0[u0] | (y1[u1] << 16)),
-                                              (uint32_t)(y2[u2] | (y3[u3] << 16)));
-                                if (KEYS) {
-                                    float sb = INFINITY;
-                                    if (b & 1u) sb = fminf(sb, q.x);
-                                    if (b & 2u) sb = fminf(sb, q.y);
-                                    if (b & 4u) sb = fminf(sb, q.z);
-                                    if (b & 8u) sb = fminf(sb, q.w);
-                                    kc[(size_t)row0 * WAVE] = sb;
-                                }
-                                continue;
+                    for (int j = 0; j < 4; ++j)
+                        if (vq[j] <= bound && j < n4) {
+                            if (vq[j] == bound) {
+                                ++neq;
+                            } else {
+                                if (ncand < cap) kp[ncand] = vq[j];
+                                ++ncand;
                             }
-                            acc[s >> 1] += m ? 1u << (14 * (s & 1) + 2 * (m - 1)) : 0u;
-                            if (SCORE) {
-                                // the box's configurations b whose event m & b != 0 happened: byte m of
-                                // H4_REJ has bit b set when m & b != 0.  Rejections are rare at the 4-arm
-                                // design's cut, so the lanes add their own counts.
-                                const uint32_t bm = B->bmask[s];
-                                uint32_t rej = (uint32_t)(H4_REJ >> (8u * m)) & bm;
-                                while (rej) {
-                                    const uint32_t b = (uint32_t)__builtin_ctz(rej);
-                                    rej &= rej - 1u;
-                                    const int q = __popc(bm & ((1u << b) - 1u));   // the tile's rank in the box
-                                    add_counts(row0 + q, B->tile0[s] + q, (uint32_t)y0[u0], (uint32_t)y1[u1],
-                                               (uint32_t)y2[u2], (uint32_t)y3[u3]);
-                                }
-                            }
-                            if constexpr (KEYS == 1) {
-                                const uint32_t bm = B->bmask[s];
-                                int row = row0;
-#pragma unroll
-                                for (int b = 1; b <= 7; ++b) {
-                                    if (!(bm & (1u << b))) continue;   // uniform
-                                    float sb = INFINITY;
-                                    if (b & 1) sb = fminf(sb, q.x);
-                                    if (b & 2) sb = fminf(sb, q.y);
-                                    if (b & 4) sb = fminf(sb, q.z);
-                                    kc[(size_t)row * WAVE] = sb;
-                                    ++row;
-                                }
-                            } else if constexpr (KEYS == 2) {
-                                // a loop, not unrolled: seven copies of the bracket step per slot would
-                                // keep the slot loop from unrolling (and its rows from registers)
-                                uint32_t bm = B->bmask[s];
-                                int row = row0;
-#pragma unroll 1
-                                while (bm) {   // uniform
-                                    const uint32_t b = (uint32_t)__builtin_ctz(bm);
-                                    bm &= bm - 1u;
-                                    float sb = INFINITY;
-                                    if (b & 1u) sb = fminf(sb, q.x);
-                                    if (b & 2u) sb = fminf(sb, q.y);
-                                    if (b & 4u) sb = fminf(sb, q.z);
-                                    take_key(act, row, B->tile0[s] + (row - row0), sb);
-                                    ++row;
-                                }
-                            }
+                        }
                 }
             }
-        }
-        if (++since_acc == ACC_EVERY) {
-            flush();
-            since_acc = 0;
-        }
-        if (SCORE && ++since == FLUSH_EVERY) {
-            if (live) flush_scores();
-            since = 0;
         }
     }
-    flush();
-    if (SCORE && live) flush_scores();
-    if (KEYS == 2 && live) {   // this item's counts of the LDS rows into their tiles
-        wave_sync4();
-        const int nr = min(B->n_rows, H4_BROWS);
-        for (int r = lane; r < nr; r += WAVE) {
-            const uint4 v = rcnt[wv][r];
-            const int32_t t = rtile[wv][r];
-            if (v.z) atomicAdd(&hb.below[t], v.z);
-            hb.cnt[(int64_t)t * (hb.maxs + 1) + 1 + slice] = v.w;
+    }
+    if (t < 0) return;
+    if (MODE == 2) {
+        cnt[S->cnt_base + (int64_t)I->slice * WAVE + lane] = ncand;
+        if (neq) atomicAdd(&eq[t], neq);
+    }
+    if (aR) {
+        atomicAdd(&R[t], aR);
+        if (SCORE) {   // the sums of two arms in the halves of one 64-bit word (at most 35 * 2^24 each)
+            atomicAdd(&sumT[2 * (int64_t)t], (unsigned long long)(a0 >> 7) | ((unsigned long long)(a1 >> 7) << 32));
+            atomicAdd(&sumT[2 * (int64_t)t + 1], (unsigned long long)(a2 >> 7) | ((unsigned long long)(a3 >> 7) << 32));
         }
     }
 }
 
 hipError_t launch_hier4(const Platten &P, uint64_t seed, uint32_t *R, unsigned long long *sumT, float *keys,
-                        hipStream_t st, int pass) {
+                        const int32_t *k, hipStream_t st) {
+    if (P.n_h4item == 0) return hipSuccess;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     const float cut = (float)P.design.cut;
-    const bool basket = P.design.kind == CSE_BASKET4;
-    H4Brk hb{P.d_h4brk, P.d_h4below, P.d_h4cnt, P.d_h4cand, P.h4_tot, P.h4_maxs, P.h4_caps, (uint32_t)H4_PILOT};
-    const GroupItem *items = P.d_gitems;
-    int64_t n_items = P.n_gitems;
-    if (pass == H4_PASS_PILOT) {
-        if (basket || !keys) return hipErrorInvalidValue;
-        items = P.d_gitems_pilot;
-        n_items = P.n_gitems_pilot;
-    } else if (pass == H4_PASS_MAIN && (basket || !P.d_h4cand)) {
-        return hipErrorInvalidValue;
-    }
-    if (n_items == 0) return hipSuccess;
-#define CSE_H4_LAUNCH(K, BK, SC)                                                                                  \
-    hipLaunchKernelGGL((k_hier4<K, BK, SC>), dim3((uint32_t)n_items), dim3(WG), 0, st, (const Blk4 *)P.d_blocks, \
-                       items, n_items, k0, k1, P.d_h4tbl, P.d_h4mask, cut, R, sumT, keys, hb)
-#define CSE_H4_SC(K, BK)            \
-    if (sumT)                       \
-        CSE_H4_LAUNCH(K, BK, true); \
-    else                            \
-        CSE_H4_LAUNCH(K, BK, false)
-    if (pass == H4_PASS_MAIN) {
-        CSE_H4_SC(2, false);
-    } else if (keys && basket) {
-        CSE_H4_SC(1, true);
-    } else if (keys) {
-        CSE_H4_SC(1, false);
-    } else if (basket) {
-        CSE_H4_SC(0, true);
-    } else {
-        CSE_H4_SC(0, false);
+    const uint32_t total = (uint32_t)((P.max_N + GRAN2 - 1) / GRAN2);
+    const dim3 grid((uint32_t)((P.n_h4item + WG / WAVE - 1) / (WG / WAVE)));
+    const size_t lds = (size_t)(WG / WAVE) * P.h4_max_rows * H4_ROW_LDS * sizeof(uint4);
+#define CSE_H4_LAUNCH(M, SC)                                                                                          \
+    hipLaunchKernelGGL((k_h4_tiles<M, SC>), grid, dim3(WG), lds, st, P.d_h4set, P.d_h4item, P.n_h4item, P.d_h4rows,     \
+                       P.h4_max_rows, P.d_b4tab, wb,                                                                  \
+                       we, P.d_h4mask, P.d_h4plane, cut, R, sumT, keys, P.d_h4u, P.d_h4eq, P.d_h4cnt)
+#define CSE_H4_SC(M)             \
+    if (sumT)                    \
+        CSE_H4_LAUNCH(M, true);  \
+    else                         \
+        CSE_H4_LAUNCH(M, false)
+    for (uint32_t wb = 0; wb < total; wb += (uint32_t)P.b4_win) {
+        const uint32_t we = std::min<uint32_t>(total, wb + (uint32_t)P.b4_win);
+        const uint32_t chunks = (we - wb + 3) / 4;
+        const uint32_t per = (uint32_t)((P.n_grp4 + WG / WAVE - 1) / (WG / WAVE));
+        const uint32_t split = std::min<uint32_t>(per, std::max<uint32_t>(1u, 2048u / chunks));
+        hipLaunchKernelGGL(k_h4_count, dim3(chunks, split), dim3(WG), 0, st, P.d_grp4, P.n_grp4, wb, k0, k1,
+                           (uint2 *)P.d_b4tab);
+        if (keys && k && wb == 0)
+            hipLaunchKernelGGL(k_h4_pilot, dim3((uint32_t)P.n_h4set), dim3(WG), lds, st, P.d_h4set, P.d_h4rows,
+                               P.h4_max_rows, P.d_b4tab, P.d_h4plane, k, P.h4_margin, P.d_h4u, P.d_h4eq, P.d_h4fb);
+        if (!keys) {
+            CSE_H4_SC(0);
+        } else if (!k) {
+            CSE_H4_SC(1);
+        } else {
+            CSE_H4_SC(2);
+        }
     }
 #undef CSE_H4_SC
 #undef CSE_H4_LAUNCH

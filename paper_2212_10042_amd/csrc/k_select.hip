@@ -668,107 +668,9 @@ __global__ __launch_bounds__(SEL_WG) void k_select_f32(const float *__restrict__
     }
 }
 
-// ---- 4-arm design, bracketed keys ----
-// The pilot pass stores the float32 keys of the first H4_PILOT simulations.  k_h4_bracket takes
-// them as the sample of k_select_f32 (order statistics of rank (k/N) m -+ z sd, widened to 22-bit
-// bins, z at most the margin and lowered towards 3 so that the bracket expects at most H4_FILL of
-// the H4_SELCAND candidate slots), counts the pilot keys below the bracket and keeps those in it;
-// tiles of at most H4_PILOT simulations are selected there and then.  The fused pass over the
-// other simulations adds its own counts and candidates (k_hier4, KEYS = 2).  k_h4_select then
-// finds the k-th smallest key among the candidates when it lies there (count below < k <= count
-// below + candidates, no region overflowed); otherwise it takes three radix passes over the tile's
-// keys regenerated one by one from the counter-based generator (the fused pass's arithmetic on
-// the tile's own thresholds), so the result is the exact k-th smallest key either way.
-constexpr int H4_SELCAND = 4096;
-constexpr double H4_FILL = 0.45;
-
-__global__ __launch_bounds__(SEL_WG) void k_h4_bracket(const float *__restrict__ keys,
-                                                       const int64_t *__restrict__ key_off,
-                                                       const int64_t *__restrict__ key_stride,
-                                                       const int32_t *__restrict__ N, const int32_t *__restrict__ kk,
-                                                       float margin, int32_t maxs, int64_t tot,
-                                                       float2 *__restrict__ brk, uint32_t *__restrict__ below,
-                                                       uint32_t *__restrict__ cnt, float *__restrict__ cand,
-                                                       double *__restrict__ lam, int32_t *__restrict__ rej_at) {
-    __shared__ uint32_t hist[2048];
-    __shared__ uint32_t part[SEL_WG];
-    __shared__ uint32_t samp[H4_PILOT];
-    __shared__ uint32_t s_bin, s_below, s_lt, s_in;
-    const int64_t t = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int32_t n = N[t];
-    const int32_t k = kk[t];
-    uint32_t *__restrict__ ct = cnt + t * (int64_t)(maxs + 1);
-    for (int i = tid; i <= maxs; i += SEL_WG) ct[i] = 0u;   // the pass's regions start empty
-    const float2 none = make_float2(-INFINITY, -INFINITY);    // no key below or inside
-    if (k <= 0 || k > n) {   // outside Theorem 4's range: -+inf, no selection
-        if (tid == 0) {
-            lam[t] = k <= 0 ? -INFINITY : INFINITY;
-            if (rej_at) rej_at[t] = k <= 0 ? 0 : n;
-            brk[t] = none;
-            below[t] = 0u;
-        }
-        return;
-    }
-    const float *__restrict__ kt = keys + key_off[t];
-    const int64_t stride = key_stride[t];
-    const int m = n < H4_PILOT ? n : H4_PILOT;
-    for (int j = tid; j < m; j += SEL_WG) samp[j] = f2ord(kt[(int64_t)(j >> 6) * stride + (j & 63)]);
-    __syncthreads();
-    auto from_samp = [&](int j) { return samp[j]; };
-    if (n <= H4_PILOT) {   // the pilot is the whole tile
-        uint32_t key = 0u, bel = 0u;
-        radix_kth(n, (uint32_t)k, from_samp, hist, part, &s_bin, &s_below, key, bel);
-        if (tid == 0) {
-            lam[t] = (double)ord2f(key);
-            if (rej_at) rej_at[t] = (int32_t)bel;
-            brk[t] = none;
-            below[t] = 0u;
-        }
-        return;
-    }
-    const double pr = (double)k / (double)n;
-    const double sd = sqrt((double)m * pr * (1.0 - pr));
-    const double z_fit = (H4_FILL * H4_SELCAND * m / (double)n - 2.0) / (2.0 * sd);
-    const double z = fmin((double)margin, fmax(3.0, z_fit));
-    const int lo_r = (int)floor(pr * m - z * sd) - 1;
-    const int hi_r = (int)ceil(pr * m + z * sd) + 1;
-    uint32_t lo = 0u, hi = 0xFFFFFFFFu, dummy = 0u;
-    if (lo_r >= 1) radix_kth<2>(m, (uint32_t)lo_r, from_samp, hist, part, &s_bin, &s_below, lo, dummy);
-    if (hi_r <= m) {
-        radix_kth<2>(m, (uint32_t)hi_r, from_samp, hist, part, &s_bin, &s_below, hi, dummy);
-        hi |= 0x3FFu;
-    }
-    // float bounds, compared as the fused pass compares them
-    const float lo_f = lo_r >= 1 ? ord2f(lo) : -INFINITY;
-    const float hi_f = hi_r <= m ? ord2f(hi) : INFINITY;
-    if (tid == 0) {
-        s_lt = 0u;
-        s_in = 0u;
-    }
-    __syncthreads();
-    uint32_t lt = 0u;
-    float *__restrict__ cp = cand + t * tot;   // the pilot's region
-    for (int j = tid; j < m; j += SEL_WG) {
-        const float v = ord2f(samp[j]);
-        if (v < lo_f) {
-            ++lt;
-        } else if (v <= hi_f) {
-            const uint32_t p = atomicAdd(&s_in, 1u);
-            if (p < (uint32_t)H4_PCAP) cp[p] = v;
-        }
-    }
-    if (lt) atomicAdd(&s_lt, lt);
-    __syncthreads();
-    if (tid == 0) {
-        below[t] = s_lt;
-        ct[0] = s_in;   // more than H4_PCAP: the tile takes the exact path
-        brk[t] = make_float2(lo_f, hi_f);
-    }
-}
-
-// The 4-arm statistic of simulation k at one tile (thresholds T of the four arms, configuration
-// b): the fused pass's arithmetic for that single (simulation, tile).
+// ---- 4-arm designs: selection from the candidate keys ----
+// The statistic of simulation k at one tile (thresholds T of the four arms, configuration b) from
+// the counter-based generator: the arithmetic of the counting kernel for that single simulation.
 __device__ __forceinline__ float h4_regen_key(uint32_t k, const uint32_t T[4], uint32_t b, uint32_t key0,
                                               uint32_t key1, const float4 *__restrict__ tbl) {
     constexpr int M1 = NP35 + 1;
@@ -787,77 +689,156 @@ __device__ __forceinline__ float h4_regen_key(uint32_t k, const uint32_t T[4], u
     if (b & 1u) sb = fminf(sb, q.x);
     if (b & 2u) sb = fminf(sb, q.y);
     if (b & 4u) sb = fminf(sb, q.z);
+    if (b & 8u) sb = fminf(sb, q.w);   // basket design only
     return sb;
 }
 
-__global__ __launch_bounds__(SEL_WG) void k_h4_select(const int32_t *__restrict__ N, const int32_t *__restrict__ kk,
-                                                      const uint32_t *__restrict__ below,
+// The nd-th smallest c of the n <= 64 K values v[0..n) (wave-wide, K values per lane in
+// registers), and the number lt of values below it: c is fixed bit by bit from the top, bit b
+// staying 0 when at least nd values lie at or below the prefix with bits b-1..0 set.  One compare
+// and one ballot per bit and register; the result is the same in every lane.
+template <int K>
+__device__ __forceinline__ void wave_kth(const uint32_t *v, uint32_t n, uint32_t nd, uint32_t &c, uint32_t &lt) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    uint32_t x[K];
+    bool ok[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        const uint32_t i = (uint32_t)(lane + q * WAVE);
+        ok[q] = i < n;
+        x[q] = ok[q] ? v[i] : 0u;
+    }
+    uint32_t p = 0u;
+    for (int b = 31; b >= 0; --b) {
+        const uint32_t thr = p | ((1u << b) - 1u);
+        uint32_t le = 0u;
+#pragma unroll
+        for (int q = 0; q < K; ++q) le += (uint32_t)__popcll(__ballot(ok[q] && x[q] <= thr));
+        if (le < nd) p |= 1u << b;
+    }
+    uint32_t below = 0u;
+#pragma unroll
+    for (int q = 0; q < K; ++q) below += (uint32_t)__popcll(__ballot(ok[q] && x[q] < p));
+    c = p;
+    lt = below;
+}
+// The same over non-negative float bit patterns below 0xFFFFFFFF, padded with 0xFFFFFFFF.
+template <int K>
+__device__ __forceinline__ void wave_kth_pad(const uint32_t *v, uint32_t n, uint32_t nd, uint32_t &c, uint32_t &lt) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    uint32_t x[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+        const uint32_t i = (uint32_t)(lane + q * WAVE);
+        x[q] = i < n ? v[i] : 0xFFFFFFFFu;
+    }
+    uint32_t p = 0u;
+    for (int b = 30; b >= 0; --b) {
+        const uint32_t thr = p | ((1u << b) - 1u);
+        uint32_t le = 0u;
+#pragma unroll
+        for (int q = 0; q < K; ++q) le += (uint32_t)__popcll(__ballot(x[q] <= thr));
+        if (le < nd) p |= 1u << b;
+    }
+    uint32_t below = 0u;
+#pragma unroll
+    for (int q = 0; q < K; ++q) below += (uint32_t)__popcll(__ballot(x[q] < p));
+    c = p;
+    lt = below;
+}
+
+// One wave per tile: the candidates (every key below the pilot's bound, in slice order) go to LDS
+// and the k-th smallest is found bit by bit in registers; when only the keys equal to the bound
+// reach rank k, it is the bound.  Candidates that do not hold the k-th
+// key, that a slice could not keep or that outnumber H4_CAND_MAX send the tile to the whole
+// workgroup, which takes three radix passes over the tile's keys regenerated one by one.
+__global__ __launch_bounds__(SEL_WG) void k_h4_select(const H4Set *__restrict__ sets, const int32_t *__restrict__ at,
+                                                      int64_t n_tiles, const int32_t *__restrict__ kk,
+                                                      const float *__restrict__ U, const uint32_t *__restrict__ eq,
                                                       const uint32_t *__restrict__ cnt, const float *__restrict__ cand,
-                                                      int32_t maxs, int32_t caps, int64_t tot,
                                                       const uint32_t *__restrict__ tileT,
-                                                      const int32_t *__restrict__ cfg,
                                                       const float4 *__restrict__ tbl, uint32_t key0, uint32_t key1,
                                                       uint32_t *__restrict__ fb, double *__restrict__ lam,
                                                       int32_t *__restrict__ rej_at) {
-    __shared__ uint32_t hist[2048];
+    constexpr int NWV = SEL_WG / WAVE;
+    __shared__ uint32_t buf[NWV][H4_CAND_MAX];
     __shared__ uint32_t part[SEL_WG];
-    __shared__ uint32_t cbuf[H4_SELCAND];
-    __shared__ uint32_t spre[H4_MAXS + 2];   // first candidate of each region in cbuf
-    __shared__ uint32_t s_bin, s_below, s_over;
-    const int64_t t = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int32_t n = N[t];
-    const int32_t k = kk[t];
-    if (k <= 0 || k > n || n <= H4_PILOT) return;   // selected by k_h4_bracket
-    const uint32_t *__restrict__ ct = cnt + t * (int64_t)(maxs + 1);
-    if (tid == 0) s_over = 0u;
-    __syncthreads();
-    uint32_t run = 0u;   // the same in every thread
-    for (int base = 0; base <= maxs; base += SEL_WG) {
-        const int r = base + tid;
-        const uint32_t c = r <= maxs ? ct[r] : 0u;
-        if (r <= maxs && c > (r == 0 ? (uint32_t)H4_PCAP : (uint32_t)caps)) s_over = 1u;   // some keys were not kept
-        block_exclusive_scan(c, part);
-        if (r <= maxs) spre[r] = run + part[tid];
-        if (tid == SEL_WG - 1) s_bin = part[tid] + c;
-        __syncthreads();
-        run += s_bin;
-        __syncthreads();
-    }
-    if (tid == 0) spre[maxs + 1] = run;
-    const uint32_t bl = below[t];
-    __syncthreads();
-    uint32_t key = 0u, bel = 0u;
-    if (!s_over && run <= (uint32_t)H4_SELCAND && bl < (uint32_t)k && (uint32_t)k <= bl + run) {
-        const float *__restrict__ cp = cand + t * tot;
-        for (uint32_t i = tid; i < run; i += SEL_WG) {
-            int a = 0, b = maxs + 1;   // region: spre[a] <= i < spre[a + 1]
-            while (b - a > 1) {
-                const int mid = (a + b) >> 1;
-                if (spre[mid] <= i)
-                    a = mid;
-                else
-                    b = mid;
+    __shared__ uint32_t s_bin, s_below;
+    __shared__ int32_t fail[NWV];
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t t = (int64_t)blockIdx.x * NWV + wv;
+    if (lane == 0) fail[wv] = -1;
+    if (t < n_tiles) {
+        const int32_t a = at[t];
+        const H4Set *__restrict__ S = sets + (a >> 6);
+        const int l = a & 63;
+        const int32_t n = S->n_sims, k = kk[t];
+        if (k <= 0 || k > n) {   // outside Theorem 4's range: -+inf, no selection
+            if (lane == 0) {
+                lam[t] = k <= 0 ? -INFINITY : INFINITY;
+                if (rej_at) rej_at[t] = k <= 0 ? 0 : n;
             }
-            const uint32_t j = i - spre[a];
-            const int64_t off = a == 0 ? (int64_t)j : (int64_t)H4_PCAP + (int64_t)(a - 1) * caps + j;
-            cbuf[i] = f2ord(cp[off]);
+        } else {
+            const int cap = h4_cap(n, S->slice);
+            const float *__restrict__ cp = cand + S->key_base + (int64_t)l * S->n_slices * cap;
+            uint32_t total = 0u;
+            bool over = false;
+            for (int s0 = 0; s0 < S->n_slices; s0 += WAVE) {   // 64 slices at a time
+                const int ns = min(WAVE, S->n_slices - s0);
+                const uint32_t c = lane < ns ? cnt[S->cnt_base + (int64_t)(s0 + lane) * WAVE + l] : 0u;
+                over = over || __ballot(c > (uint32_t)cap) != 0ull;
+                for (int s = 0; s < ns; ++s) {
+                    const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)c, s);
+                    if (!over && total + m <= (uint32_t)H4_CAND_MAX)
+                        for (uint32_t i = (uint32_t)lane; i < m; i += WAVE)
+                            buf[wv][total + i] = __float_as_uint(cp[(int64_t)(s0 + s) * cap + i]);
+                    total += m;
+                }
+            }
+            lds_wave_sync();
+            uint32_t key = 0u, below = 0u;
+            if (!over && total <= (uint32_t)H4_CAND_MAX && total >= (uint32_t)k) {
+                if (total <= 4u * WAVE) wave_kth_pad<4>(buf[wv], total, (uint32_t)k, key, below);
+                else if (total <= 8u * WAVE) wave_kth_pad<8>(buf[wv], total, (uint32_t)k, key, below);
+                else if (total <= 12u * WAVE) wave_kth_pad<12>(buf[wv], total, (uint32_t)k, key, below);
+                else if (total <= 16u * WAVE) wave_kth_pad<16>(buf[wv], total, (uint32_t)k, key, below);
+                else if (total <= 24u * WAVE) wave_kth_pad<24>(buf[wv], total, (uint32_t)k, key, below);
+                else wave_kth_pad<48>(buf[wv], total, (uint32_t)k, key, below);
+                if (lane == 0) {
+                    lam[t] = (double)__uint_as_float(key);
+                    if (rej_at) rej_at[t] = (int32_t)below;
+                }
+            } else if (!over && total < (uint32_t)k && (uint32_t)k <= total + eq[t]) {   // the bound itself
+                if (lane == 0) {
+                    lam[t] = (double)U[t];
+                    if (rej_at) rej_at[t] = (int32_t)total;
+                }
+            } else if (lane == 0) {
+                fail[wv] = (int32_t)t;
+            }
         }
-        __syncthreads();
-        radix_kth((int)run, (uint32_t)k - bl, [&](int j) { return cbuf[j]; }, hist, part, &s_bin, &s_below, key, bel);
-        bel += bl;
-    } else {
-        if (tid == 0) fb[1 + atomicAdd(&fb[0], 1u)] = (uint32_t)t;
+    }
+    __syncthreads();
+    for (int w = 0; w < NWV; ++w) {
+        const int32_t ft = fail[w];
+        if (ft < 0) continue;   // uniform
+        const int32_t a = at[ft];
+        const H4Set *__restrict__ S = sets + (a >> 6);
+        const uint32_t b = S->cfg[a & 63];
+        const int32_t n = S->n_sims, k = kk[ft];
         uint32_t T[4];
 #pragma unroll
-        for (int a = 0; a < 4; ++a) T[a] = tileT[4 * t + a];
-        const uint32_t b = (uint32_t)cfg[t];
+        for (int i = 0; i < 4; ++i) T[i] = tileT[4 * (int64_t)ft + i];
+        if (tid == 0) atomicAdd(&fb[0], 1u);
+        __syncthreads();
+        uint32_t key = 0u, below = 0u;
         radix_kth(n, (uint32_t)k, [&](int j) { return f2ord(h4_regen_key((uint32_t)j, T, b, key0, key1, tbl)); },
-                  hist, part, &s_bin, &s_below, key, bel);
-    }
-    if (tid == 0) {
-        lam[t] = (double)ord2f(key);
-        if (rej_at) rej_at[t] = (int32_t)bel;
+                  &buf[0][0], part, &s_bin, &s_below, key, below);
+        if (tid == 0) {
+            lam[ft] = (double)ord2f(key);
+            if (rej_at) rej_at[ft] = (int32_t)below;
+        }
+        __syncthreads();
     }
 }
 
@@ -1146,36 +1127,6 @@ __device__ __forceinline__ void tbb_sweep(const Recs2 &rb, int N, const uint4 (*
     if (lane < nl) tbb_take<MODE>(L.j[wv][lane], L.m[wv][lane], buf, fill, pre, off, cnt, lvl, key0, key1);
 }
 
-// The nd-th smallest c of the n <= 64 K values v[0..n) (wave-wide, K values per lane in
-// registers), and the number lt of values below it: c is fixed bit by bit from the top, bit b
-// staying 0 when at least nd values lie at or below the prefix with bits b-1..0 set.  One compare
-// and one ballot per bit and register; the result is the same in every lane.
-template <int K>
-__device__ __forceinline__ void tbb_select(const uint32_t *v, uint32_t n, uint32_t nd, uint32_t &c, uint32_t &lt) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    uint32_t x[K];
-    bool ok[K];
-#pragma unroll
-    for (int q = 0; q < K; ++q) {
-        const uint32_t i = (uint32_t)(lane + q * WAVE);
-        ok[q] = i < n;
-        x[q] = ok[q] ? v[i] : 0u;
-    }
-    uint32_t p = 0u;
-    for (int b = 31; b >= 0; --b) {
-        const uint32_t thr = p | ((1u << b) - 1u);
-        uint32_t le = 0u;
-#pragma unroll
-        for (int q = 0; q < K; ++q) le += (uint32_t)__popcll(__ballot(ok[q] && x[q] <= thr));
-        if (le < nd) p |= 1u << b;
-    }
-    uint32_t below = 0u;
-#pragma unroll
-    for (int q = 0; q < K; ++q) below += (uint32_t)__popcll(__ballot(ok[q] && x[q] < p));
-    c = p;
-    lt = below;
-}
-
 __global__ __launch_bounds__(TBB_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_b2_tiebreak(const Blk2 *__restrict__ blocks, const uint2 *__restrict__ recs,
                                                         const int32_t *__restrict__ kk, const uint4 *__restrict__ cut,
                                                         uint32_t key0, uint32_t key1, int32_t *__restrict__ rej_at,
@@ -1223,10 +1174,10 @@ __global__ __launch_bounds__(TBB_WG) __attribute__((amdgpu_waves_per_eu(4, 4))) 
             return;
         }
         uint32_t c, lt;
-        if (n <= (uint32_t)WAVE) tbb_select<1>(buf + o, n, nd, c, lt);
-        else if (n <= 2u * WAVE) tbb_select<2>(buf + o, n, nd, c, lt);
-        else if (n <= 4u * WAVE) tbb_select<4>(buf + o, n, nd, c, lt);
-        else tbb_select<8>(buf + o, n, nd, c, lt);
+        if (n <= (uint32_t)WAVE) wave_kth<1>(buf + o, n, nd, c, lt);
+        else if (n <= 2u * WAVE) wave_kth<2>(buf + o, n, nd, c, lt);
+        else if (n <= 4u * WAVE) wave_kth<4>(buf + o, n, nd, c, lt);
+        else wave_kth<8>(buf + o, n, nd, c, lt);
         if (lane == 0) {
             c_out[t] = c;
             rej_at[t] += (int32_t)(bel[s] + lt);
@@ -1395,7 +1346,7 @@ __global__ __launch_bounds__(1024) void k_min_part(const double *__restrict__ v,
 
 // Score-function gradient (sum over rejections of T(x) - R grad A(theta)) / N, float64;
 // also the float64 score sums and int32 counts for the caller's buffers.
-__global__ void k_finish(int fam, int n, int d, int score_n, int packed, int64_t n_tiles, const double *__restrict__ theta,
+__global__ void k_finish(int fam, int n, int d, int score_n, int64_t n_tiles, const double *__restrict__ theta,
                          const int32_t *__restrict__ N, const uint32_t *__restrict__ R,
                          const unsigned long long *__restrict__ sumT,
                          const unsigned long long *__restrict__ sumZfx, int32_t *__restrict__ R_out,
@@ -1427,9 +1378,9 @@ __global__ void k_finish(int fam, int n, int d, int score_n, int packed, int64_t
         }
         return;
     }
-    const unsigned long long pair = packed ? sumT[t] : 0ull;   // 2-arm sums: y0 in the low word, y1 in the high one
     for (int a = 0; a < d; ++a) {
-        const unsigned long long s = packed ? (a ? pair >> 32 : pair & 0xFFFFFFFFull) : sumT[t * d + a];
+        // the sums of arms 2 i and 2 i + 1 in the low and high half of word i
+        const unsigned long long s = (sumT[t * (d / 2) + a / 2] >> (32 * (a & 1))) & 0xFFFFFFFFull;
         if (T_out) T_out[t * d + a] = (int64_t)s;
         if (grad) {
             const double th = theta[t * d + a];
@@ -1477,21 +1428,11 @@ hipError_t launch_select(const Platten &P, const void *keys, const int32_t *k, d
     return hipGetLastError();
 }
 
-hipError_t launch_h4_bracket(const Platten &P, const float *keys, const int32_t *k, double *lam, int32_t *rej_at,
-                             hipStream_t st) {
-    if (P.n_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_h4_bracket, dim3((uint32_t)P.n_tiles), dim3(SEL_WG), 0, st, keys, P.d_key_off,
-                       P.d_key_stride, P.d_N, k, P.h4_margin, P.h4_maxs, P.h4_tot, P.d_h4brk, P.d_h4below,
-                       P.d_h4cnt, P.d_h4cand, lam, rej_at);
-    return hipGetLastError();
-}
-
-hipError_t launch_h4_select(const Platten &P, uint64_t seed, const int32_t *k, double *lam, int32_t *rej_at,
-                            hipStream_t st) {
-    hipError_t e = launch_zero(P.d_h4fb, sizeof(uint32_t), st);   // the regenerated tiles' list starts empty
-    if (e != hipSuccess || P.n_tiles == 0) return e;
-    hipLaunchKernelGGL(k_h4_select, dim3((uint32_t)P.n_tiles), dim3(SEL_WG), 0, st, P.d_N, k, P.d_h4below, P.d_h4cnt,
-                       P.d_h4cand, P.h4_maxs, P.h4_caps, P.h4_tot, P.d_tileT, P.d_cfg, P.d_h4tbl, (uint32_t)seed,
+hipError_t launch_h4_select(const Platten &P, uint64_t seed, const float *keys, const int32_t *k, double *lam,
+                            int32_t *rej_at, hipStream_t st) {
+    constexpr int NWV = SEL_WG / WAVE;
+    hipLaunchKernelGGL(k_h4_select, dim3((uint32_t)((P.n_tiles + NWV - 1) / NWV)), dim3(SEL_WG), 0, st, P.d_h4set,
+                       P.d_h4at, P.n_tiles, k, P.d_h4u, P.d_h4eq, P.d_h4cnt, keys, P.d_tileT, P.d_h4tbl, (uint32_t)seed,
                        (uint32_t)(seed >> 32), P.d_h4fb, lam, rej_at);
     return hipGetLastError();
 }
@@ -1560,8 +1501,7 @@ hipError_t launch_finish(const Platten &P, const uint32_t *R, const unsigned lon
                          double *Z_out, double *grad, hipStream_t st) {
     const int64_t grid = (P.n_tiles + 255) / 256;
     hipLaunchKernelGGL(k_finish, dim3((uint32_t)grid), dim3(256), 0, st, P.family, P.n_per_arm, P.d,
-                       P.design.kind == CSE_PHASE23 ? 1 : 0,
-                       P.design.kind == CSE_BINOM2_Z ? 1 : 0, P.n_tiles, P.d_theta, P.d_N, R, sumT, sumZfx, R_out, T_out, Z_out, grad);
+                       P.design.kind == CSE_PHASE23 ? 1 : 0, P.n_tiles, P.d_theta, P.d_N, R, sumT, sumZfx, R_out, T_out, Z_out, grad);
     return hipGetLastError();
 }
 

@@ -567,8 +567,8 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         }
         if (int e = upload((Blk1 **)&P->d_blocks, blks.data(), blks.size())) return e;
     } else if (kind == CSE_HIER4 || kind == CSE_BASKET4) {
-        // distinct values per arm -> coordinates; 4 x 4 x 2 x 2 coordinate blocks per N class
-        const int BD[4] = {B4N0, B4N1, B4N2, B4N3};
+        // distinct values per arm -> coordinates; tiles ordered by simulation count, thresholds of arms
+        // 0 and 1, 8 x 8 blocks of arms 2 and 3, 64 consecutive ones of a count to a set
         std::vector<double> uv[4];
         for (int64_t t = 0; t < P->n_tiles; ++t)
             for (int a = 0; a < 4; ++a) uv[a].push_back(P->tile_theta[t * 4 + a]);
@@ -576,76 +576,118 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             std::sort(uv[a].begin(), uv[a].end());
             uv[a].erase(std::unique(uv[a].begin(), uv[a].end()), uv[a].end());
         }
-        typedef std::tuple<int32_t, int64_t, int64_t, int64_t, int64_t> Key4;
-        std::map<Key4, std::vector<Blk4>> blkmap;
-        for (int64_t t = 0; t < P->n_tiles;) {
-            // the tiles of one simulation point are consecutive (a box's pieces, or one basket piece)
-            int64_t t1 = t;
-            uint32_t bm = 0;
-            while (t1 < P->n_tiles && P->tile_box[t1] == P->tile_box[t] &&
-                   (kind != CSE_BASKET4 || t1 == t))
-                bm |= 1u << P->tile_cfg[t1++];
-            int64_t c[4];
+        struct At {
+            int32_t n, c[4], tile;
+        };
+        std::vector<At> order(P->n_tiles);
+        for (int64_t t = 0; t < P->n_tiles; ++t) {
+            order[t].n = P->tile_N[t];
+            order[t].tile = (int32_t)t;
             for (int a = 0; a < 4; ++a)
-                c[a] = std::lower_bound(uv[a].begin(), uv[a].end(), P->tile_theta[t * 4 + a]) - uv[a].begin();
-            Key4 key = std::make_tuple(P->tile_N[t], c[0] / BD[0], c[1] / BD[1], c[2] / BD[2], c[3] / BD[3]);
-            const int slot = (int)((((c[0] % BD[0]) * BD[1] + c[1] % BD[1]) * BD[2] + c[2] % BD[2]) * BD[3] + c[3] % BD[3]);
-            auto &vec = blkmap[key];
-            Blk4 *B = nullptr;
-            for (auto &b : vec)
-                if (b.row0[slot] < 0) {
-                    B = &b;
-                    break;
+                order[t].c[a] = (int32_t)(std::lower_bound(uv[a].begin(), uv[a].end(), P->tile_theta[t * 4 + a]) - uv[a].begin());
+        }
+        std::sort(order.begin(), order.end(), [](const At &x, const At &y) {
+            return std::make_tuple(x.n, x.c[0], x.c[1], x.c[2] / 8, x.c[3] / 8, x.c[2], x.c[3], x.tile) <
+                   std::make_tuple(y.n, y.c[0], y.c[1], y.c[2] / 8, y.c[3] / 8, y.c[2], y.c[3], y.tile);
+        });
+        // threshold groups: per simulation count and arm, the coordinates present, 8 to a group
+        std::vector<Grp4> grps;
+        std::vector<std::pair<int32_t, int32_t>> at_arm[4];   // per tile in order and arm: (group, threshold)
+        for (int a = 0; a < 4; ++a) at_arm[a].resize(order.size());
+        for (size_t i = 0; i < order.size();) {
+            size_t j = i;
+            while (j < order.size() && order[j].n == order[i].n) ++j;
+            for (int a = 0; a < 4; ++a) {
+                std::vector<std::pair<int32_t, int32_t>> of(uv[a].size(), {-1, -1});
+                for (size_t q = i; q < j; ++q) of[order[q].c[a]].first = 0;   // present
+                int n = 0;
+                for (size_t c = 0; c < of.size(); ++c) {
+                    if (of[c].first < 0) continue;
+                    if (n++ % 8 == 0) {
+                        Grp4 g{};
+                        g.arm = a;
+                        g.n_sims = order[i].n;
+                        grps.push_back(g);
+                    }
+                    Grp4 &g = grps.back();
+                    of[c] = std::make_pair((int32_t)grps.size() - 1, g.n_thr);
+                    g.T[g.n_thr++] = bern_threshold(uv[a][c]);
                 }
-            if (!B) {
-                Blk4 nb{};
-                for (int j = 0; j < B4S; ++j) {
-                    nb.row0[j] = -1;
-                    nb.tile0[j] = -1;
-                    nb.bmask[j] = 0;
-                }
-                uint32_t *T[4] = {nb.T0, nb.T1, nb.T2, nb.T3};
+                for (size_t q = i; q < j; ++q) at_arm[a][q] = of[order[q].c[a]];
+            }
+            i = j;
+        }
+        // count table: all simulations at once where that fits B2_TABLE_MAX, else windows (at least the
+        // pilot's simulations, a multiple of every slice)
+        auto granules = [](int32_t n) { return ((int64_t)n + GRAN2 - 1) / GRAN2; };
+        auto units = [&](int64_t win) {
+            int64_t n = 0;
+            for (auto &g : grps) n += std::min(win, granules(g.n_sims)) * (g.arm < 2 ? g.n_thr : 8 + g.n_thr);
+            return n;
+        };
+        P->b4_win = H4_SLICE_MAX;
+        while (P->b4_win < granules(P->max_N)) P->b4_win *= 2;
+        while (P->b4_win > H4_SLICE_MAX && units(P->b4_win) * 16 > B2_TABLE_MAX) P->b4_win /= 2;
+        for (auto &g : grps) {
+            g.stride = std::min(P->b4_win, granules(g.n_sims));
+            g.row = P->b4_units;
+            P->b4_units += g.stride * (g.arm < 2 ? g.n_thr : 8 + g.n_thr);
+        }
+        if (P->b4_units >= ((int64_t)1 << 32)) {
+            set_error("cse_platten_create: too many distinct thresholds for the count table");
+            return CSE_ENOMEM;
+        }
+        P->n_grp4 = (int32_t)grps.size();
+        std::vector<int32_t> at(P->n_tiles);
+        std::vector<uint32_t> rows;
+        for (size_t i = 0; i < order.size();) {
+            H4Set S{};
+            S.row_at = (int64_t)rows.size();
+            auto row_of = [&](int64_t r) {   // place of the row in the set's list (the latest first: neighbours share)
+                for (int64_t q = (int64_t)rows.size() - 1; q >= S.row_at; --q)
+                    if (rows[q] == (uint32_t)r) return (uint16_t)(q - S.row_at);
+                rows.push_back((uint32_t)r);
+                return (uint16_t)(rows.size() - 1 - S.row_at);
+            };
+            S.n_sims = order[i].n;
+            S.key_base = P->n_keys;
+            while (S.n_lanes < WAVE && i < order.size() && order[i].n == S.n_sims) {
+                const At &o = order[i];
+                const int l = S.n_lanes++;
+                S.tile[l] = o.tile;
+                S.cfg[l] = (uint32_t)P->tile_cfg[o.tile];
                 for (int a = 0; a < 4; ++a) {
-                    const int64_t base = (c[a] / BD[a]) * BD[a];
-                    for (int u = 0; u < BD[a]; ++u)
-                        T[a][u] = (base + u < (int64_t)uv[a].size()) ? bern_threshold(uv[a][base + u]) : 0u;
+                    const auto pl = at_arm[a][i];
+                    const Grp4 &g = grps[pl.first];
+                    S.row[a][l] = row_of(g.row + pl.second * g.stride);
+                    if (a >= 2) S.row[a + 2][l] = row_of(g.row + (8 + pl.second) * g.stride);
                 }
-                nb.n_sims = P->tile_N[t];
-                vec.push_back(nb);
-                B = &vec.back();
+                at[o.tile] = (int32_t)(P->h4set.size() * WAVE) + l;
+                ++i;
             }
-            B->row0[slot] = 0;   // rows assigned below
-            B->tile0[slot] = (int32_t)t;
-            B->bmask[slot] = bm;
-            t = t1;
+            for (int l = S.n_lanes; l < WAVE; ++l) {
+                S.tile[l] = -1;
+                S.cfg[l] = S.cfg[0];
+                for (int a = 0; a < H4_ROWS; ++a) S.row[a][l] = S.row[a][0];
+            }
+            S.n_rows = (int32_t)((int64_t)rows.size() - S.row_at);
+            P->h4_max_rows = std::max(P->h4_max_rows, S.n_rows);
+            for (int l = 0; l < S.n_lanes; ++l) {
+                key_off[S.tile[l]] = S.key_base + (int64_t)l * WAVE;
+                key_stride[S.tile[l]] = (int64_t)S.n_lanes * WAVE;
+            }
+            P->n_keys += ((int64_t)S.n_sims + 63) / 64 * 64 * S.n_lanes;
+            blk_sims.push_back(S.n_sims);
+            P->h4set.push_back(S);
         }
-        std::vector<Blk4> blks;
-        for (auto &kv : blkmap)
-            for (auto &b : kv.second) blks.push_back(b);
-        P->n_blocks = (int64_t)blks.size();
-        for (auto &B : blks) {
-            blk_sims.push_back(B.n_sims);
-            int32_t rows = 0;
-            for (int j = 0; j < B4S; ++j) {
-                if (B.row0[j] < 0) continue;
-                B.row0[j] = rows;
-                rows += __builtin_popcount(B.bmask[j]);
-            }
-            B.n_rows = rows;
-            P->h4_max_rows = std::max(P->h4_max_rows, rows);
-            B.key_base = P->n_keys;
-            for (int j = 0; j < B4S; ++j) {
-                if (B.row0[j] < 0) continue;
-                const int nt = __builtin_popcount(B.bmask[j]);
-                for (int q = 0; q < nt; ++q) {
-                    const int64_t tile = B.tile0[j] + q;
-                    key_off[tile] = B.key_base + (int64_t)(B.row0[j] + q) * 64;
-                    key_stride[tile] = (int64_t)rows * 64;
-                }
-            }
-            P->n_keys += ((int64_t)B.n_sims + 63) / 64 * rows * 64;
-        }
-        if (int e = upload((Blk4 **)&P->d_blocks, blks.data(), blks.size())) return e;
+        P->n_blocks = P->n_h4set = (int64_t)P->h4set.size();
+        stage.add(&P->d_grp4, grps.data(), grps.size());
+        stage.add(&P->d_h4at, at.data(), at.size());
+        stage.add(&P->d_h4rows, rows.data(), rows.size());
+        // chunks of four granules are read whole: up to three units past a row's end
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_b4tab, (size_t)(P->b4_units + 4) * 16));
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4u, (size_t)P->n_tiles * sizeof(float)));
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4eq, (size_t)P->n_tiles * sizeof(uint32_t)));
 
         // posterior table of the design (once per platten)
         const std::vector<HierNode> nodes = hier_nodes();
@@ -661,17 +703,14 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         CSE_HIP_TRY(hipMalloc((void **)&P->d_h4mask, (size_t)P->h4_outcomes));
         CSE_HIP_TRY(launch_h4_mask(P->d_h4tbl, P->h4_outcomes, (float)design->cut, kind == CSE_BASKET4 ? 4 : 3,
                                    P->d_h4mask, nullptr));
+        const int n_cfg = kind == CSE_BASKET4 ? 15 : 7;
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4plane, (size_t)n_cfg * H4_PLANE * sizeof(float)));
+        CSE_HIP_TRY(launch_h4_planes(P->d_h4tbl, n_cfg, P->d_h4plane, nullptr));
         CSE_HIP_TRY(hipDeviceSynchronize());
         P->table_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-        if (kind == CSE_HIER4) {   // bracketed calibration keys: the exact path regenerates a tile's keys
-            if (int e = upload(&P->d_tileT, P->tile_T.data(), P->tile_T.size())) return e;
-            if (int e = upload(&P->d_cfg, P->tile_cfg.data(), P->tile_cfg.size())) return e;
-            const size_t nt = (size_t)std::max<int64_t>(P->n_tiles, 1);
-            CSE_HIP_TRY(hipMalloc((void **)&P->d_h4brk, nt * sizeof(float2)));
-            CSE_HIP_TRY(hipMalloc((void **)&P->d_h4below, nt * sizeof(uint32_t)));
-            CSE_HIP_TRY(hipMalloc((void **)&P->d_h4fb, (nt + 1) * sizeof(uint32_t)));
-            CSE_HIP_TRY(hipMemset(P->d_h4fb, 0, sizeof(uint32_t)));
-        }
+        if (int e = upload(&P->d_tileT, P->tile_T.data(), P->tile_T.size())) return e;   // regenerated keys
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4fb, sizeof(uint32_t)));
+        CSE_HIP_TRY(hipMemset(P->d_h4fb, 0, sizeof(uint32_t)));
     } else if (kind == CSE_PHASE23) {
         // one trial per lane: keys contiguous per tile, work items of p23_chunk simulations
         for (int64_t t = 0; t < P->n_tiles; ++t) {
@@ -888,12 +927,15 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
 
     // ---- work items (launch shapes; cse_autotune may rebuild them) ----
     for (int64_t b = 0; b < P->n_blocks; ++b) P->block_sims += blk_sims[b];
-    if (P->n_blocks > 0)
+    if (kind == CSE_ZTEST1)
         if (int e = plan_work_items(P, P->tune_waves)) return e;
     // default workgroup counts, measured (the 2-arm design's: plan_group_items, from its rectangles)
     if (kind == CSE_BINOM2_Z) P->tune_wgs = 0;
-    if (kind == CSE_BINOM2_Z || kind == CSE_HIER4 || kind == CSE_BASKET4)
+    if (kind == CSE_BINOM2_Z)
         if (int e = plan_group_items(P, P->tune_wgs)) return e;
+    if (kind == CSE_HIER4 || kind == CSE_BASKET4)
+        if (int e = plan_h4_items(P, 0)) return e;
+    if (kind != CSE_ZTEST1) P->n_items = P->n_gitems;
 
     stage.add(&P->d_theta, P->tile_theta.data(), P->tile_theta.size());
     stage.add(&P->d_N, P->tile_N.data(), P->tile_N.size());
@@ -978,41 +1020,59 @@ int plan_work_items(Platten *P, int64_t target_waves) {
     return upload(&P->d_items, items.data(), items.size());
 }
 
-// Workgroup items of the 2-arm and 4-arm kernels: groups of 4 consecutive blocks of equal N
-// (blocks are ordered by N) whose four waves share the Philox words of a simulation range;
-// ranges sliced so that the grid has about target_wgs workgroups.
-// The candidate regions of the bracketed 4-arm calibration, sized for the current item ranges:
-// allocated while the platten asks for that calibration (and its blocks' key rows fit the
-// fused pass's LDS counters), freed otherwise.
-int h4_regions(Platten *P) {
-    const bool want = P->design.kind == CSE_HIER4 && P->h4_bracket && P->h4_max_rows <= H4_BROWS;
-    const size_t nt = (size_t)std::max<int64_t>(P->n_tiles, 1);
-    const size_t n_cnt = want ? nt * (size_t)(P->h4_maxs + 1) : 0, n_cand = want ? nt * (size_t)P->h4_tot : 0;
-    if (n_cnt == P->h4_cnt_alloc && n_cand == P->h4_cand_alloc) return CSE_OK;
-    if (P->d_h4cnt) CSE_HIP_TRY(hipFree(P->d_h4cnt));
-    if (P->d_h4cand) CSE_HIP_TRY(hipFree(P->d_h4cand));
-    P->d_h4cnt = nullptr;
-    P->d_h4cand = nullptr;
-    P->h4_cnt_alloc = P->h4_cand_alloc = 0;
-    if (!want) return CSE_OK;
-    if (hipMalloc((void **)&P->d_h4cnt, n_cnt * sizeof(uint32_t)) != hipSuccess ||
-        hipMalloc((void **)&P->d_h4cand, n_cand * sizeof(float)) != hipSuccess) {
-        (void)hipGetLastError();
-        if (P->d_h4cnt) (void)hipFree(P->d_h4cnt);
-        P->d_h4cnt = nullptr;
-        P->d_h4cand = nullptr;
-        set_error("cannot allocate the bracketed calibration's candidate regions");
-        return CSE_ENOMEM;
+// Wave items of the 4-arm designs: each set's granules in slices of a power of two, so that the grid
+// has about target_wgs workgroups (0: the default) of four waves.
+int plan_h4_items(Platten *P, int64_t target_wgs) {
+    int64_t most = 4;
+    auto wgs = [&](int64_t slice) {
+        int64_t n = 0;
+        for (auto &S : P->h4set) n += (((int64_t)S.n_sims + GRAN2 - 1) / GRAN2 + slice - 1) / slice;
+        return (n + WG / WAVE - 1) / (WG / WAVE);
+    };
+    if (target_wgs <= 0) target_wgs = H4_WGS;
+    while (most < H4_SLICE_MAX && wgs(2 * most) >= target_wgs) most *= 2;
+    std::vector<H4Item> items;
+    int64_t cnt = 0, gs = 0;
+    for (size_t i = 0; i < P->h4set.size(); ++i) {
+        H4Set &S = P->h4set[i];
+        const int64_t ng = ((int64_t)S.n_sims + GRAN2 - 1) / GRAN2;
+        // a set's candidate slots (n_slices * h4_cap) must fit its keys' place in the workspace
+        int64_t slice = 4;
+        while (S.n_sims >= H4_PILOT_MIN_N && slice < most && 2 * slice <= ng) slice *= 2;
+        S.slice = (int32_t)slice;
+        S.n_slices = (int32_t)((ng + slice - 1) / slice);
+        S.cnt_base = cnt;
+        cnt += (int64_t)S.n_slices * WAVE;
+        gs += S.n_sims;
+        for (int64_t s = 0; s < S.n_slices; ++s) {
+            H4Item it{};
+            it.set = (int32_t)i;
+            it.slice = (int32_t)s;
+            it.g_begin = (uint32_t)(s * slice);
+            it.g_end = (uint32_t)std::min<int64_t>(ng, (s + 1) * slice);
+            items.push_back(it);
+        }
     }
-    P->h4_cnt_alloc = n_cnt;
-    P->h4_cand_alloc = n_cand;
-    return CSE_OK;
+    P->shape_gen->fetch_add(1);   // plans captured on the old arrays become stale
+    for (void *q : {(void *)P->d_h4item, (void *)P->d_h4set, (void *)P->d_h4cnt})
+        if (q) CSE_HIP_TRY(hipFree(q));
+    P->d_h4item = nullptr;
+    P->d_h4set = nullptr;
+    P->d_h4cnt = nullptr;
+    P->n_h4item = (int64_t)items.size();
+    P->n_gitems = (P->n_h4item + WG / WAVE - 1) / (WG / WAVE);
+    P->group_sims = gs;
+    P->tune_wgs = target_wgs;
+    CSE_HIP_TRY(hipMalloc((void **)&P->d_h4cnt, (size_t)cnt * sizeof(uint32_t)));
+    if (int e = upload(&P->d_h4set, P->h4set.data(), P->h4set.size())) return e;
+    return upload(&P->d_h4item, items.data(), items.size());
 }
 
+// Workgroup items of the 2-arm kernel: rectangles of 4 row groups x 8 column groups of blocks of equal
+// N over ranges of granules.
 int plan_group_items(Platten *P, int64_t target_wgs) {
-    std::vector<std::vector<int64_t>> groups;   // up to 4 (32 for the 2-arm design) blocks each (-1: none)
-    const bool sq2 = P->design.kind == CSE_BINOM2_Z;
-    if (sq2) {
+    std::vector<std::vector<int64_t>> groups;   // 32 blocks each (-1: none)
+    {
         // rectangles of 4 row groups x 8 column groups of blocks of equal N: block (row r, column
         // c) goes to position 8 (r & 3) + (c & 7) of rectangle (r >> 2, c >> 3); a second block
         // with the same coordinates (two tiles at one grid point) opens another rectangle
@@ -1030,15 +1090,9 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
             }
         }
         for (auto &kv : sq) groups.push_back(kv.second);
-    } else {
-        for (int64_t b = 0; b < P->n_blocks; ++b) {
-            if (groups.empty() || groups.back().size() == 4 || P->blk_sims[groups.back()[0]] != P->blk_sims[b])
-                groups.push_back({});
-            groups.back().push_back(b);
-        }
     }
     const int64_t ng = (int64_t)groups.size();
-    if (sq2 && target_wgs == 0) {
+    if (target_wgs == 0) {
         // 64 granules (1,024 simulations) per item: shorter items spend their time in the final
         // atomics, longer ones leave the chip waiting for the rectangles where most quads need the
         // full step; at least 1,024 workgroups while there are granules for them.  1024 x 1024 boxes
@@ -1054,23 +1108,17 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
         target_wgs = std::min<int64_t>(8192, std::max<int64_t>(1024, work / 64));
     }
     int64_t slices = std::max<int64_t>(1, (target_wgs + ng - 1) / ng);
-    if (P->design.kind == CSE_HIER4) slices = std::min<int64_t>(slices, H4_MAXS);
-    // at least 4 chunks of 64 simulations per item: an item's fixed work (thresholds, the final
-    // transposes and atomics) then stays small beside its simulations
-    constexpr int64_t MIN_ITEM_CHUNKS = 4;
     // 2-arm items: the kernel's 32-bit sums hold 2^32 / (128 * 163) simulations; below two granules
     // an item's fixed work (the atomics) is most of it
     constexpr int64_t B2_ITEM_MAX = 8192, B2_ITEM_MIN = 2;
-    std::vector<GroupItem> gi, gpil;
     std::vector<SquareItem> si;
     int64_t gs = 0;
-    int32_t maxs = 0, caps = 64;
     for (auto &g : groups) {
         int64_t first = -1;
         for (int64_t b : g)
             if (b >= 0 && first < 0) first = b;
         const int64_t N = P->blk_sims[first];
-        if (sq2) {
+        {
             // granules per item: at most B2_ITEM_MAX (the kernel's 32-bit sums)
             const int64_t ng16 = (N + GRAN2 - 1) / GRAN2;
             const int64_t per = std::min<int64_t>(B2_ITEM_MAX, std::max<int64_t>(B2_ITEM_MIN, (ng16 + slices - 1) / slices));
@@ -1099,65 +1147,15 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
                 gs += std::min<int64_t>(N, it.g_end * (int64_t)GRAN2) - (int64_t)it.g_begin * GRAN2;
                 si.push_back(it);
             }
-            continue;
         }
-        const int64_t chunks = (N + WAVE - 1) / WAVE;
-        const int64_t per = std::max<int64_t>(MIN_ITEM_CHUNKS, (chunks + slices - 1) / slices) * WAVE;
-        {
-            // bracketed keys: the pilot's ranges, and room for twice the candidates an item range
-            // expects (the bracket holds at most SEL_FILL_H4 of H4_SELCAND keys of the tile on
-            // average) plus 32
-            maxs = std::max<int32_t>(maxs, (int32_t)((N + per - 1) / per));
-            if (N > H4_PILOT) {
-                const double expect = 0.45 * 4096.0 * (double)std::min<int64_t>(per, N) / (double)N;
-                caps = std::max<int32_t>(caps, (int32_t)((2.0 * expect + 32.0 + 31.0) / 32.0) * 32);
-            }
-            const int64_t np = std::min<int64_t>(N, H4_PILOT);
-            const int64_t pper = std::max<int64_t>(MIN_ITEM_CHUNKS * WAVE, std::min<int64_t>(per, 4 * WAVE));
-            for (int64_t k0 = 0; k0 < np; k0 += pper) {
-                GroupItem it{};
-                for (int w = 0; w < 4; ++w) it.blk[w] = w < (int)g.size() ? (int32_t)g[w] : -1;
-                it.k_begin = (uint32_t)k0;
-                it.k_end = (uint32_t)std::min<int64_t>(np, k0 + pper);
-                it.slice = -1;
-                gpil.push_back(it);
-            }
-        }
-        int32_t slice = 0;
-        for (int64_t k0 = 0; k0 < N; k0 += per) {
-            const uint32_t kb = (uint32_t)k0, ke = (uint32_t)std::min<int64_t>(N, k0 + per);
-            gs += (int64_t)(ke - kb);
-            {
-                GroupItem it{};
-                for (int w = 0; w < 4; ++w) it.blk[w] = w < (int)g.size() ? (int32_t)g[w] : -1;
-                it.k_begin = kb;
-                it.k_end = ke;
-                it.slice = slice++;
-                gi.push_back(it);
-            }
-        }
-    }
-    if (P->design.kind == CSE_HIER4) {
-        if (P->d_gitems_pilot) CSE_HIP_TRY(hipFree(P->d_gitems_pilot));
-        P->d_gitems_pilot = nullptr;
-        P->n_gitems_pilot = (int64_t)gpil.size();
-        if (!gpil.empty())
-            if (int e = upload(&P->d_gitems_pilot, gpil.data(), gpil.size())) return e;
-        P->h4_maxs = maxs;
-        P->h4_caps = caps;
-        P->h4_tot = (int64_t)H4_PCAP + (int64_t)maxs * caps;
-        if (int e = h4_regions(P)) return e;
     }
     P->shape_gen->fetch_add(1);   // plans captured on the old arrays become stale
-    if (P->d_gitems) CSE_HIP_TRY(hipFree(P->d_gitems));
     if (P->d_sqitems) CSE_HIP_TRY(hipFree(P->d_sqitems));
-    P->d_gitems = nullptr;
     P->d_sqitems = nullptr;
-    P->n_gitems = (int64_t)(sq2 ? si.size() : gi.size());
+    P->n_gitems = (int64_t)si.size();
     P->group_sims = gs;
     P->tune_wgs = target_wgs;
-    if (sq2) return upload(&P->d_sqitems, si.data(), si.size());
-    return upload(&P->d_gitems, gi.data(), gi.size());
+    return upload(&P->d_sqitems, si.data(), si.size());
 }
 
 // Queue items of the Phase II/III kernel: (tile, `chunk` consecutive trials); the persistent
@@ -1193,14 +1191,14 @@ void free_platten(Platten *P) {
     if (P->shape_gen) P->shape_gen->store(PLATTEN_GONE);   // plans on this platten refuse to replay
     (void)hipDeviceSynchronize();
     void *ptrs[] = {P->d_theta, P->d_N,    P->d_vert_off, P->d_verts,   P->d_key_off,
-                    P->d_blocks, P->d_items, P->d_gitems, P->d_cut_tbl, P->d_S_tbl,  P->d_S_order,
+                    P->d_blocks, P->d_items, P->d_cut_tbl, P->d_S_tbl,  P->d_S_order,
                     P->d_S_group, P->d_keys, P->d_Rw,      P->d_Tw,     P->d_Zw,
                     P->d_apw,    P->d_kw,    P->d_lamw,    P->d_lamg,   P->d_cls_N,
                     P->d_cls_off, P->d_cp_base, P->d_cp_mark, P->d_cp_tbl,  P->d_radii,
                     P->d_is_box, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
                     P->d_queue,  P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
                     P->d_h4mask, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
-                    P->d_gitems_pilot, P->d_h4brk, P->d_h4below, P->d_h4cnt, P->d_h4cand, P->d_h4fb};
+                    P->d_grp4, P->d_h4rows, P->d_h4set, P->d_h4item, P->d_b4tab, P->d_h4u, P->d_h4eq, P->d_h4at, P->d_h4cnt, P->d_h4fb, P->d_h4plane};
     auto in_arena = [&](void *q) {
         for (auto &a : P->arenas)
             if ((unsigned char *)q >= (unsigned char *)a.first && (unsigned char *)q < (unsigned char *)a.first + a.second)
