@@ -410,9 +410,9 @@ int cse_plan_destroy(cse_plan *plan);
  *                          batches), from {1024 .. 65536} (powers of 2; at least 4
  *                          chunks of 64 simulations per item), timed on the calibration
  *                          launch plus the validation launch;
- *   CSE_PHASE23:           trials per queue item {64, 128, 256, 512} x persistent grid
- *                          {512, 1024, 2048} workgroups, timed on a strided sample of tiles
- *                          holding at most max_trials trials.
+ *   CSE_PHASE23:           trials per work item {64, 128, 256, 512} x grid of the posterior
+ *                          kernel {512, 1024, 2048} workgroups, timed on a strided sample of
+ *                          tiles holding at most max_trials trials.
  * The fastest is kept in the platten.  Results of every later call are unchanged (integer
  * reductions are order-independent and keys are laid out by tile, not by launch shape).
  * Plans captured on this platten before the call become stale (cse_plan_launch refuses them).
@@ -434,8 +434,9 @@ int cse_simulate_per_tile(const cse_platten *p, uint64_t seed, int64_t tile_begi
 /*
  * cse_work_counters -- work done by the last simulation launch on a CSE_PHASE23 platten
  * (cse_simulate / cse_validate / cse_calibrate): out (host int64 [4]) = trials simulated,
- * posterior evaluations at Phase II looks and at Phase III looks (the first look of every
- * trial is a table lookup and is not counted), Newton steps over all nodes of those looks.
+ * posterior evaluations at Phase II looks and at Phase III looks (one per distinct state of the
+ * call, however many trials reach it; the first look of every trial is a table lookup and is
+ * not counted), Newton steps over all nodes of those evaluations.
  * On a CSE_BINOM2_Z platten: out[0] = tiles that the last calibration's bracketed selection
  * left to the exact full-histogram pass (k-th statistic outside the bracket, or the batch's
  * brackets too wide for the histogram), out[1..3] = 0.  On a CSE_HIER4 platten: out[0] = tiles

@@ -334,8 +334,8 @@ def cse_platten_set_option(h, option, value):
 
 
 def cse_work_counters(h, stream=None) -> dict:
-    """Phase II/III design: trials, posterior looks (Phase II, Phase III) and Newton steps of
-    the last simulation launch.  2-arm design: `trials` holds the tiles the last calibration
+    """Phase II/III design: trials, posterior evaluations (Phase II, Phase III looks; one per
+    distinct state) and Newton steps of the last simulation launch.  2-arm design: `trials` holds the tiles the last calibration
     left to the exact full-histogram pass; 4-arm design: the tiles whose k-th key the last
     calibration from candidates selected from regenerated keys."""
     out = np.zeros(4, np.int64)

@@ -628,7 +628,8 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
                 const int64_t gg = std::min(g, full);
                 float ms = 0.0f;
                 if (int e = timeit([&]() -> int {
-                        CSE_LAUNCH(cse::launch_phase23_items(P, seed, d_it.p, (int64_t)items.size(), gg, P.d_Rw, st));
+                        CSE_LAUNCH(cse::launch_phase23_list(P, seed, d_it.p, items.data(), (int64_t)items.size(), gg, P.d_Rw, nullptr,
+                                                            nullptr, nullptr, st));
                         return CSE_OK;
                     }, 1, &ms))
                     return e;

@@ -182,7 +182,46 @@ struct P23Args {
     const double *gh;               // Gauss-Hermite rule (weight e^{-x^2}): nodes [16], weights [16]
     const HierNode *nodes;          // per-node constants of the hierarchical posterior [90]
     const uint8_t *look1;           // decision code of the first look per outcome, 51^4 entries
+    const uint16_t *counts;         // count table, or NULL: trials draw their own words
+    const uint2 *tile_row;          // [n_tiles][4] (at, stride) of the tile's four rows
     double sqrt_pi, z95;            // sqrt(pi), Phi^{-1}(0.95)
+};
+
+// Phase II/III design, count table: the successes among the first n words of an arm's stream, for
+// every distinct threshold of the arm and every sample size n a trial can reach (P23_SIZES: nine
+// sizes of Phase II, and those with 100 and 200 patients of Phase III added), u16, simulations
+// contiguous.  Row r starts at at * 64, size column c of simulation k at (at + c * stride) * 64 + k.
+constexpr int P23_NSIZE = 9, P23_SIZES = 3 * P23_NSIZE;
+constexpr int64_t P23_TABLE_MAX = (int64_t)1 << 30;   // bytes (more: every trial draws its own words)
+struct P23Row {
+    uint32_t T;
+    int32_t arm;
+    uint32_t at;       // units of 64 entries
+    uint32_t stride;   // chunks of 64 simulations of the row
+};
+
+// Phase II/III design, states already evaluated in the call and the open trials (k_p23_*): slots of
+// 64-bit states and their outcomes, the states without a place in the table, the new states of a
+// round by phase, the open trials' records (two uint4 each, rounds alternate; workgroup b's are
+// range[b].y from range[b].x on) and counters: per round {new Phase II states, new Phase III states,
+// states without a place}, then the trials.  Each counter has a cache line of its own.
+constexpr int64_t P23_GRID = 512;                     // workgroups of the posterior kernel: two waves per SIMD
+constexpr int P23_ROUNDS = 5;                          // looks after the first, and the end
+constexpr int64_t P23_BLOCKS = 8192;                  // workgroups of k_p23_open and k_p23_step, at most
+constexpr int P23_CTR = 32, P23_COUNTERS = 3 * P23_ROUNDS + 1;
+constexpr int64_t P23_CAP_MAX = (int64_t)32 << 20;     // trials of a chunk
+struct P23Memo {
+    unsigned long long *state;
+    uint32_t *value;
+    uint64_t *own;
+    uint32_t *list[2];
+    uint4 *trial[2];
+    uint2 *range;
+    uint32_t *ctr;
+    uint32_t mask;
+    uint32_t pad;
+    __host__ __device__ uint32_t *count(int round, int j) const { return ctr + (3 * round + j) * P23_CTR; }
+    __host__ __device__ uint32_t *trials() const { return ctr + 3 * P23_ROUNDS * P23_CTR; }
 };
 
 // Family of the data model for the bound (Example 1 / Section 4.2).
@@ -269,6 +308,15 @@ struct Platten {
     WorkItem *d_p23items = nullptr;
     P23Args p23{};
     int64_t p23_grid = 0;
+    P23Memo p23memo{};
+    int64_t p23_cap = 0;                 // trials the records hold
+    void *d_p23mem = nullptr;            // all of p23memo's memory
+    std::vector<WorkItem> p23_items;     // host copy of the items
+    P23Row *d_p23row = nullptr;          // count table: rows (by arm), their place per tile, the table
+    int32_t n_p23row = 0, p23_arm_row[5] = {0, 0, 0, 0, 0};
+    int64_t p23_chunks = 0;              // chunks of 64 simulations of the longest row
+    uint2 *d_p23tilerow = nullptr;
+    uint16_t *d_p23counts = nullptr;
     int32_t p23_chunk = 256;             // simulations per queue item
     // launch shapes (cse_autotune): waves of the one-wave-per-block kernels, workgroups of the
     // group kernels

@@ -48,8 +48,10 @@ hipError_t launch_h4_select(const Platten &P, uint64_t seed, const float *keys, 
 hipError_t launch_phase23(const Platten &P, uint64_t seed, uint32_t *R, unsigned long long *sumT, float *keys,
                           hipStream_t st);
 hipError_t launch_p23_look1(const Platten &P, hipStream_t st);
-hipError_t launch_phase23_items(const Platten &P, uint64_t seed, const WorkItem *items, int64_t n_items, int64_t grid,
-                                uint32_t *R, hipStream_t st);
+// the same over a caller-made item list (device and host copies), which fits the platten's chunks
+hipError_t launch_phase23_list(const Platten &P, uint64_t seed, const WorkItem *d_items, const WorkItem *h_items,
+                               int64_t n_items, int64_t grid, uint32_t *R, unsigned long long *sumT, float *keys,
+                               unsigned long long *stats, hipStream_t st);
 hipError_t launch_phase23_tile(const Platten &P, uint64_t seed, int64_t t, uint32_t *R_tile, hipStream_t st);
 hipError_t launch_hier4_plain(const Platten &P, uint64_t seed, int64_t t, uint32_t *R_tile, hipStream_t st);
 

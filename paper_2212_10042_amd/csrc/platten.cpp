@@ -719,11 +719,78 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             P->n_keys += P->tile_N[t];
         }
         if (int e = plan_queue_items(P, P->p23_chunk, -1)) return e;
+        {
+            // the records of a chunk's trials, and a table of twice as many slots as trials (2^27 at
+            // most), in one allocation
+            P->p23_cap = std::max<int64_t>(512, std::min<int64_t>(P->total_sims, P23_CAP_MAX));
+            uint64_t slots = 1u << 12;
+            while (slots < (1u << 27) && slots < (uint64_t)P->total_sims) slots *= 2;
+            P23Memo &M = P->p23memo;
+            M.mask = (uint32_t)(slots - 1);
+            const size_t cap = (size_t)P->p23_cap;
+            size_t off = 0;
+            auto take = [&](size_t bytes) {
+                const size_t at = off;
+                off += (bytes + 255) & ~(size_t)255;
+                return at;
+            };
+            const size_t o_state = take(slots * 8), o_value = take((slots + cap) * 4), o_own = take(cap * 8),
+                         o_l0 = take(cap * 4), o_l1 = take(cap * 4), o_t0 = take(cap * 32), o_t1 = take(cap * 32),
+                         o_range = take(P23_BLOCKS * sizeof(uint2)), o_ctr = take(P23_COUNTERS * P23_CTR * sizeof(uint32_t));
+            CSE_HIP_TRY(hipMalloc(&P->d_p23mem, off));
+            unsigned char *m = (unsigned char *)P->d_p23mem;
+            M.state = (unsigned long long *)(m + o_state);
+            M.value = (uint32_t *)(m + o_value);
+            M.own = (uint64_t *)(m + o_own);
+            M.list[0] = (uint32_t *)(m + o_l0);
+            M.list[1] = (uint32_t *)(m + o_l1);
+            M.trial[0] = (uint4 *)(m + o_t0);
+            M.trial[1] = (uint4 *)(m + o_t1);
+            M.range = (uint2 *)(m + o_range);
+            M.ctr = (uint32_t *)(m + o_ctr);
+        }
         if (int e = upload(&P->d_tileT, P->tile_T.data(), P->tile_T.size())) return e;
         if (int e = upload(&P->d_cfg, P->tile_cfg.data(), P->tile_cfg.size())) return e;
         CSE_HIP_TRY(hipMalloc((void **)&P->d_queue, sizeof(uint32_t)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_p23stats, 4 * sizeof(unsigned long long)));
+        // count table rows: each arm's distinct thresholds, for the simulations of its longest tile
+        {
+            std::vector<P23Row> rows;
+            std::vector<uint2> tile_row(4 * (size_t)P->n_tiles);
+            uint64_t at = 0;
+            for (int a = 0; a < 4; ++a) {
+                std::vector<std::pair<uint32_t, int32_t>> v(P->n_tiles);   // (threshold, simulations)
+                for (int64_t t = 0; t < P->n_tiles; ++t) v[t] = {P->tile_T[4 * t + a], P->tile_N[t]};
+                std::sort(v.begin(), v.end());
+                const size_t first = rows.size();
+                for (size_t i = 0; i < v.size(); ++i) {
+                    if (i + 1 < v.size() && v[i + 1].first == v[i].first) continue;   // the largest count is last
+                    P23Row r{};
+                    r.T = v[i].first;
+                    r.arm = a;
+                    r.at = (uint32_t)std::min<uint64_t>(at, 0xFFFFFFFFull);
+                    r.stride = (uint32_t)((v[i].second + 63) / 64);
+                    P->p23_chunks = std::max<int64_t>(P->p23_chunks, r.stride);
+                    at += (uint64_t)r.stride * P23_SIZES;
+                    rows.push_back(r);
+                }
+                P->p23_arm_row[a + 1] = (int32_t)rows.size();
+                for (int64_t t = 0; t < P->n_tiles; ++t) {
+                    const auto it = std::lower_bound(rows.begin() + first, rows.end(), P->tile_T[4 * t + a],
+                                                     [](const P23Row &r, uint32_t T) { return r.T < T; });
+                    tile_row[4 * t + a] = make_uint2(it->at, it->stride);
+                }
+            }
+            if (at * 64 * sizeof(uint16_t) <= (uint64_t)P23_TABLE_MAX) {
+                P->n_p23row = (int32_t)rows.size();
+                if (int e = upload(&P->d_p23row, rows.data(), rows.size())) return e;
+                if (int e = upload(&P->d_p23tilerow, tile_row.data(), tile_row.size())) return e;
+                CSE_HIP_TRY(hipMalloc((void **)&P->d_p23counts, at * 64 * sizeof(uint16_t)));
+            }
+        }
         P23Args &A = P->p23;
+        A.counts = P->d_p23counts;
+        A.tile_row = P->d_p23tilerow;
         A.counter = P->d_queue;
         A.tileT = P->d_tileT;
         A.cfg = P->d_cfg;
@@ -1158,8 +1225,8 @@ int plan_group_items(Platten *P, int64_t target_wgs) {
     return upload(&P->d_sqitems, si.data(), si.size());
 }
 
-// Queue items of the Phase II/III kernel: (tile, `chunk` consecutive trials); the persistent
-// grid has `grid` workgroups (-1: enough to fill the chip, at most one per 4 items).
+// Work items of the Phase II/III design: (tile, `chunk` consecutive trials); the posterior kernel's grid
+// has `grid` workgroups (-1: two waves on every SIMD).
 int plan_queue_items(Platten *P, int32_t chunk, int64_t grid) {
     std::vector<WorkItem> items;
     P->p23_item_off.clear();
@@ -1182,7 +1249,8 @@ int plan_queue_items(Platten *P, int32_t chunk, int64_t grid) {
     P->p23.items = P->d_p23items;
     P->p23.n_items = (int64_t)items.size();
     const int64_t full = std::max<int64_t>(1, (P->p23.n_items + 3) / 4);
-    P->p23_grid = grid > 0 ? std::min<int64_t>(grid, full) : std::min<int64_t>(full, 2048);
+    P->p23_grid = grid > 0 ? std::min<int64_t>(grid, full) : P23_GRID;
+    P->p23_items = std::move(items);
     return CSE_OK;
 }
 
@@ -1196,7 +1264,7 @@ void free_platten(Platten *P) {
                     P->d_apw,    P->d_kw,    P->d_lamw,    P->d_lamg,   P->d_cls_N,
                     P->d_cls_off, P->d_cp_base, P->d_cp_mark, P->d_cp_tbl,  P->d_radii,
                     P->d_is_box, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
-                    P->d_queue,  P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
+                    P->d_queue,  P->d_p23mem, P->d_p23row, P->d_p23tilerow, P->d_p23counts, P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
                     P->d_h4mask, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
                     P->d_grp4, P->d_h4rows, P->d_h4set, P->d_h4item, P->d_b4tab, P->d_h4u, P->d_h4eq, P->d_h4at, P->d_h4cnt, P->d_h4fb, P->d_h4plane};
     auto in_arena = [&](void *q) {
