@@ -205,7 +205,8 @@ struct P23Row {
 // round by phase, the open trials' records (two uint4 each, rounds alternate; workgroup b's are
 // range[b].y from range[b].x on) and counters: per round {new Phase II states, new Phase III states,
 // states without a place}, then the trials.  Each counter has a cache line of its own.
-constexpr int64_t P23_GRID = 512;                     // workgroups of the posterior kernel: two waves per SIMD
+constexpr int P23_WAVES = 2;                          // waves per SIMD of the posterior kernel
+constexpr int64_t P23_GRID = 256 * P23_WAVES;          // and its workgroups
 constexpr int P23_ROUNDS = 5;                          // looks after the first, and the end
 constexpr int64_t P23_BLOCKS = 8192;                  // workgroups of k_p23_open and k_p23_step, at most
 constexpr int P23_CTR = 32, P23_COUNTERS = 3 * P23_ROUNDS + 1;

@@ -31,12 +31,12 @@ __global__ __launch_bounds__(128) void k_hier4_table(int n, int64_t n_out, float
         }
     }
     const double nv[4] = {(double)n, (double)n, (double)n, (double)n};
-    HierSummary s;
-    hier_posterior<false, false>(y, nv, nodes, s);
+    double Sc[3];
+    hier_complements(y, nv, nodes, Sc);
     float4 o;
-    o.x = (float)s.Sc[0];
-    o.y = (float)s.Sc[1];
-    o.z = (float)s.Sc[2];
+    o.x = (float)Sc[0];
+    o.y = (float)Sc[1];
+    o.z = (float)Sc[2];
     o.w = 0.0f;
     tbl[idx] = o;
 }

@@ -91,33 +91,46 @@ __device__ __forceinline__ int p23_ties(int y1, int y2, int y3, int n1, int n2, 
 // rounding their computed p_best carries: `ties` bit 0 (arms 1, 2), bit 1 (1, 3), bit 2 (2, 3).
 __device__ __forceinline__ int p23_phase2(const HierSummary &s, int ties, int look, int active, const double *gh,
                                           double sqrt_pi, double z95) {
-    double pb[4] = {0.0, 0.0, 0.0, 0.0};
-    double isd[4];   // 1 / (sd * sqrt 2): Phi(z / sd) = erfc(-z isd) / 2
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) isd[kk] = rsq_nr(2.0 * s.var[kk]);
-#pragma unroll
-    for (int i = 1; i < 4; ++i) {
-        const double si = sqrt(2.0 * s.var[i]);
-        double acc = 0.0;
-        for (int g = 0; g < 16; ++g) {
-            const double t = s.mean[i] + si * gh[g];
-            double prod = 1.0;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                if (kk != i) prod *= 0.5 * erfc(-(t - s.mean[kk]) * isd[kk]);
-            acc += gh[16 + g] * prod;
-        }
-        pb[i] = acc / sqrt_pi;
-    }
     const double thr = (look < 2) ? 0.70 : 0.60;
+    int qual = 0;   // active arms with p_succ above the threshold
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+        if (((active >> (i - 1)) & 1) &&
+            p23_psucc(s.mean[i] - s.mean[0], s.dvar[i - 1], s.mean[0], s.mean[i], 200.0, z95) > thr)
+            qual |= 1 << (i - 1);
+    // p_best of the arms it is asked of: several that qualify, or those that may be dropped
+    const int want = qual ? ((qual & (qual - 1)) ? qual : 0) : (look == 2 ? 0 : active);
+    double pb[4] = {0.0, 0.0, 0.0, 0.0};
+    if (want) {
+        double isd[4];   // 1 / (sd * sqrt 2): Phi(z / sd) = erfc(-z isd) / 2
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) isd[kk] = rsq_nr(2.0 * s.var[kk]);
+#pragma unroll
+        for (int i = 1; i < 4; ++i) {
+            if (!((want >> (i - 1)) & 1)) continue;
+            const double si = sqrt(2.0 * s.var[i]);
+            double acc = 0.0;
+            for (int g = 0; g < 16; ++g) {
+                const double t = s.mean[i] + si * gh[g];
+                double prod = 1.0;
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    if (kk == i) continue;
+                    const double x = (t - s.mean[kk]) * isd[kk], v = 0.5 * erfc_pos(fabs(x), rcp_nr);
+                    prod *= x > 0.0 ? 1.0 - v : v;   // Phi(sqrt 2 x)
+                }
+                acc += gh[16 + g] * prod;
+            }
+            pb[i] = acc / sqrt_pi;
+        }
+    }
     int best = 0;
     double pb_best = 0.0;
 #pragma unroll
     for (int i = 1; i < 4; ++i) {
-        if (!((active >> (i - 1)) & 1)) continue;
-        const double ps = p23_psucc(s.mean[i] - s.mean[0], s.dvar[i - 1], s.mean[0], s.mean[i], 200.0, z95);
+        if (!((qual >> (i - 1)) & 1)) continue;
         const bool same = best != 0 && ((ties >> (best + i - 3)) & 1);   // best < i
-        if (ps > thr && (best == 0 || (pb[i] > pb_best && !same))) {
+        if (best == 0 || (pb[i] > pb_best && !same)) {
             best = i;
             pb_best = pb[i];
         }
@@ -147,7 +160,7 @@ __global__ __launch_bounds__(128) void k_p23_look1(int64_t n_out, uint8_t *__res
     }
     const double n[4] = {50.0, 50.0, 50.0, 50.0};
     HierSummary s;
-    hier_posterior<true, true>(y, n, nodes, s, nullptr, 0);
+    hier_posterior(y, n, nodes, s, nullptr, 0);
     tbl[idx] = (uint8_t)p23_phase2(s, p23_ties(y[1], y[2], y[3], 50, 50, 50), 0, 7, gh, sqrt_pi, z95);
 }
 
@@ -284,7 +297,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 int wneed = 0;
 #pragma unroll
                 for (int i = 0; i < 3; ++i) wneed |= __ballot((mine >> i) & 1) ? (1 << i) : 0;
-                hier_posterior<true, true>(y, nd, A.nodes, s, &c_newton, __builtin_amdgcn_readfirstlane(wneed));
+                hier_posterior(y, nd, A.nodes, s, &c_newton, __builtin_amdgcn_readfirstlane(wneed));
             }
             if (look < 3) c_look2 += 1; else c_look3 += 1;
             if (look < 3) {
@@ -352,8 +365,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // one addition per wave and list made them 9.4, 9.1, 3.9 and 0.6 ms on the benchmark sample (23.3
 // million trials), about 10 ns per addition to a line.  So a workgroup keeps its trials in a range of
 // its own from the first look on, collects new slots in LDS for P23_STEPS passes, and adds once: 0.75,
-// 0.8, 0.4 and 0.2 ms.  post (6.4, 8.3, 2.9 and 0.6 ms) is float64 arithmetic, 70% of the issue slots.
-// All together: 144.8 ms trial by trial, 23.8 ms so.
+// 0.8, 0.4 and 0.2 ms.  post (4.2, 5.2, 1.9 and 0.4 ms) is float64 arithmetic (hier_sums; 6.4, 8.3, 2.9
+// and 0.6 ms with Newton's method and the library's functions).  All together: 144.8 ms trial by trial,
+// 17 ms so.
 // ------------------------------------------------------------------------------------------
 namespace {
 
@@ -665,20 +679,76 @@ __global__ __launch_bounds__(WG) void k_p23_open(P23Args A, P23Memo M, int per) 
     if (threadIdx.x == 0) M.range[blockIdx.x] = make_uint2(begin, L.kept);
 }
 
-// Outcome of every new state of the round, one per lane: Phase II the decision code, Phase III interim
-// 0 (go on), 1 (success) or 2 (futility), final analysis the bits of the float32 statistic.
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_p23_post(P23Args A, P23Memo M, int round) {
+// A state's outcome and its Newton steps.  Functions of their own, not inlined: the constants of their
+// polynomials are then held in registers over a state's node loop only, not over all loops of the
+// kernel at once.
+// `split` neighbouring lanes share the state's nodes, each a range of them.
+#define P23_EVAL __device__ __attribute__((noinline))
+P23_EVAL uint2 p23_eval2(int4 y, int4 n, int look, int active, int split, const HierNode *nodes, const double *gh,
+                         double sqrt_pi, double z95) {
+    const int yy[4] = {y.x, y.y, y.z, y.w};
+    const double nd[4] = {(double)n.x, (double)n.y, (double)n.z, (double)n.w};
+    HierSums H;
+    HierSummary h;
+    int steps = 0;
+    const int part = (int)threadIdx.x & (split - 1);
+    hier_sums(yy, nd, nodes, HP_NODES * part / split, HP_NODES * (part + 1) / split, H, &steps, 0);
+    hier_join(H, split);
+    hier_summary(H, h);
+    const int code = p23_phase2(h, p23_ties(y.y, y.z, y.w, n.y, n.z, n.w), look, active, gh, sqrt_pi, z95);
+    return make_uint2((uint32_t)code, (uint32_t)steps);
+}
+P23_EVAL uint2 p23_eval3(int4 y, int4 n, int look, int split, const HierNode *nodes, double z95) {
+    const int yy[4] = {y.x, y.y, y.z, y.w};
+    const double nd[4] = {(double)n.x, (double)n.y, (double)n.z, (double)n.w};
+    HierSums H;
+    HierSummary h;
+    int steps = 0;
+    const int part = (int)threadIdx.x & (split - 1);
+    hier_sums(yy, nd, nodes, HP_NODES * part / split, HP_NODES * (part + 1) / split, H, &steps, 1);
+    hier_join(H, split);
+    hier_summary(H, h);
+    uint32_t out;
+    if (look == 3)
+        out = h.P[0] > 0.95 ? 1u
+                            : (p23_psucc(h.mean[1] - h.mean[0], h.dvar[0], h.mean[0], h.mean[1], 100.0, z95) < 0.20 ? 2u : 0u);
+    else
+        out = __float_as_uint((float)h.Sc[0]);
+    return make_uint2(out, (uint32_t)steps);
+}
+
+constexpr int P23_SPLIT = 8;
+
+// Outcome of every new state of the round, one per lane or, where they are few, per `split` lanes: Phase
+// II the decision code, Phase III interim 0 (go on), 1 (success) or 2 (futility), final analysis the bits
+// of the float32 statistic.  Bound by its vector instructions, 740 per node and wave of 64 states, which
+// take 93% of the cycles with two waves per SIMD (three measure the same).
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(P23_WAVES, P23_WAVES))) void k_p23_post(
+    P23Args A, P23Memo M, int round) {
     const int lane = threadIdx.x & (WAVE - 1);
     const uint32_t wave = blockIdx.x * (WG / WAVE) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t waves = gridDim.x * (WG / WAVE);
     const uint32_t n2 = *M.count(round, 0), n3 = *M.count(round, 1);
-    const uint32_t b2 = (n2 + WAVE - 1) / WAVE, b3 = (n3 + WAVE - 1) / WAVE;
+    // Lanes per state: the batches that a wave takes one after the other, times the time of a lane's nodes
+    // (a quarter more where lanes of a wave are at different nodes, since the wave iterates as long as its
+    // slowest lane) and of a start and an end, about five nodes.  Rounds of the 3^4 x 1,024 grid with one
+    // lane per state: 275, 280, 155 and 147 us; the last two, with 4 and 8 lanes, 67 and 32 us.
+    int split = 1;
+    uint32_t best = ~0u;
+    for (int q = 1; q <= P23_SPLIT; q *= 2) {
+        const uint32_t nb = (n2 * q + WAVE - 1) / WAVE + (n3 * q + WAVE - 1) / WAVE;
+        const uint32_t cost = ((nb + waves - 1) / waves) * (uint32_t)((q == 1 ? HP_NODES : HP_NODES * 5 / 4 / q) + 5);
+        if (cost < best) {
+            best = cost;
+            split = q;
+        }
+    }
+    const uint32_t b2 = (n2 * split + WAVE - 1) / WAVE, b3 = (n3 * split + WAVE - 1) / WAVE;
     int c_newton = 0;
     for (uint32_t b = wave; b < b2 + b3; b += waves) {   // uniform
         const bool p3 = b >= b2;
-        const uint32_t i = (p3 ? b - b2 : b) * WAVE + (uint32_t)lane;
-        if (i >= (p3 ? n3 : n2)) continue;
-        const uint32_t slot = M.list[p3 ? 1 : 0][i];
+        const uint32_t i = ((p3 ? b - b2 : b) * WAVE + (uint32_t)lane) >> __builtin_ctz(split), last = (p3 ? n3 : n2) - 1u;
+        const uint32_t slot = M.list[p3 ? 1 : 0][min(i, last)];
         const uint64_t s = slot <= M.mask ? M.state[slot] : M.own[slot - M.mask - 1u];
         const int look = (int)((s >> 52) & 7u), active = (int)((s >> 55) & 7u);
         const int extra = p3 ? 100 * (look - 2) : 0;
@@ -688,19 +758,15 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             y[a] = (int)((s >> (9 * a)) & 511u);
             n[a] = p23_ncode_size((int)((s >> (36 + 4 * a)) & 15u)) + (a < 2 ? extra : 0);
         }
-        const double nd[4] = {(double)n[0], (double)n[1], (double)n[2], (double)n[3]};
-        HierSummary h;
-        hier_posterior<true, true>(y, nd, A.nodes, h, &c_newton, p3 ? 1 : 0);
-        uint32_t out;
-        if (!p3) {
-            out = (uint32_t)p23_phase2(h, p23_ties(y[1], y[2], y[3], n[1], n[2], n[3]), look, active, A.gh, A.sqrt_pi, A.z95);
-        } else if (look == 3) {
-            out = h.P[0] > 0.95 ? 1u
-                                : (p23_psucc(h.mean[1] - h.mean[0], h.dvar[0], h.mean[0], h.mean[1], 100.0, A.z95) < 0.20 ? 2u : 0u);
-        } else {
-            out = __float_as_uint((float)h.Sc[0]);
+        // (uniform branch)
+        const uint2 o = p3 ? p23_eval3(make_int4(y[0], y[1], y[2], y[3]), make_int4(n[0], n[1], n[2], n[3]), look, split, A.nodes,
+                                       A.z95)
+                           : p23_eval2(make_int4(y[0], y[1], y[2], y[3]), make_int4(n[0], n[1], n[2], n[3]), look, active,
+                                       split, A.nodes, A.gh, A.sqrt_pi, A.z95);
+        if (i <= last) {
+            c_newton += (int)o.y;
+            if ((lane & (split - 1)) == 0) M.value[slot] = o.x;
         }
-        M.value[slot] = out;
     }
     if (A.stats) {
         unsigned long long c = (unsigned long long)c_newton;
