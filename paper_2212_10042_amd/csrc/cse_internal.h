@@ -107,6 +107,21 @@ struct H4Item {
     uint32_t g_begin;
     uint32_t g_end;
 };
+// Runs of tiles that differ only in arm 3's threshold (and are of one configuration): up to H4_RUN
+// tiles per lane, 64 runs to a set.  row: places of the count rows of arms 0, 1 and 2 and of each tile's
+// arm 3 in the set's list.
+constexpr int H4_RUN = 8;
+constexpr int64_t H4_BITS = (int64_t)(NP35 + 1) * (NP35 + 1) * (NP35 + 1);
+struct H4Run {
+    int32_t tile[H4_RUN][64];
+    uint16_t row[3 + H4_RUN][64];
+    uint32_t cfg[64];
+    int32_t n_sims;
+    int32_t n_run;          // tiles of the longest run
+    int32_t n_rows;
+    int32_t pad;
+    int64_t row_at;
+};
 // Table of the statistic S_b of each configuration b, one plane per b: outcome (y0, y1, y2, y3) at
 // ((36 y0 + y1) * H4_SLAB + 8 code2(y2) + code3(y3)), so that 4 x 8 neighbouring (y2, y3) share a
 // 128-byte line.
@@ -296,7 +311,12 @@ struct Platten {
 
     // design tables (device)
     float4 *d_h4tbl = nullptr;           // 4-arm: (1 - P_1, 1 - P_2, 1 - P_3, 0) per outcome
-    uint8_t *d_h4mask = nullptr;         // 4-arm designs: rejection mask at the cut per outcome
+    std::vector<H4Run> h4run;            // runs of tiles along arm 3
+    H4Run *d_h4run = nullptr;
+    H4Item *d_h4runitem = nullptr;
+    int64_t n_h4runitem = 0;
+    int32_t h4_run_rows = 0;             // rows of the longest list of a set of runs
+    uint64_t *d_h4bits = nullptr;        // rejecting y3 (bits) per (b, y0, y1, y2)
     float *d_h4plane = nullptr;          // 4-arm designs: S_b per outcome, one plane per configuration
     HierNode *d_hnodes = nullptr;        // per-node constants of the hierarchical posterior
     // Phase II/III design: per-tile thresholds / configurations, the work queue

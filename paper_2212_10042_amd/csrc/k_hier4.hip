@@ -73,20 +73,25 @@ hipError_t launch_basket_table(int n, const double *theta0, float4 *tbl, const H
     return hipGetLastError();
 }
 
-// Rejection mask of every outcome at the design's cut (bit a-1 for treatment arm a of the
-// 4-arm design, bit a for arm a of the basket design): the forward pass gathers this byte
-// instead of the float4 row; the comparison is the one the keyed pass makes.
-__global__ void k_h4_mask(const float4 *__restrict__ tbl, int64_t n, float cut, int nbits, uint8_t *__restrict__ mask) {
+// Rejecting outcomes of configuration b = 1..nb (a treatment arm of b with its statistic below the cut;
+// the comparison is the one the keyed pass makes): bit y3 of word (b - 1) H4_BITS + (36 y0 + y1) 36 + y2.
+__global__ void k_h4_bits(const float4 *__restrict__ tbl, float cut, int nb, uint64_t *__restrict__ bits) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float4 q = tbl[i];
-    uint32_t m = (q.x < cut ? 1u : 0u) | (q.y < cut ? 2u : 0u) | (q.z < cut ? 4u : 0u);
-    if (nbits == 4 && q.w < cut) m |= 8u;
-    mask[i] = (uint8_t)m;
+    if (i >= H4_BITS) return;
+    uint64_t w[4] = {0, 0, 0, 0};   // per arm of the row
+    for (int y3 = 0; y3 <= NP35; ++y3) {
+        const float4 q = tbl[i * (NP35 + 1) + y3];
+        w[0] |= (uint64_t)(q.x < cut) << y3;
+        w[1] |= (uint64_t)(q.y < cut) << y3;
+        w[2] |= (uint64_t)(q.z < cut) << y3;
+        w[3] |= (uint64_t)(q.w < cut) << y3;
+    }
+    for (int b = 1; b <= nb; ++b)
+        bits[(b - 1) * H4_BITS + i] = (b & 1 ? w[0] : 0) | (b & 2 ? w[1] : 0) | (b & 4 ? w[2] : 0) | (b & 8 ? w[3] : 0);
 }
 
-hipError_t launch_h4_mask(const float4 *tbl, int64_t n, float cut, int nbits, uint8_t *mask, hipStream_t st) {
-    hipLaunchKernelGGL(k_h4_mask, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, tbl, n, cut, nbits, mask);
+hipError_t launch_h4_bits(const float4 *tbl, float cut, int nb, uint64_t *bits, hipStream_t st) {
+    hipLaunchKernelGGL(k_h4_bits, dim3((uint32_t)((H4_BITS + 255) / 256)), dim3(256), 0, st, tbl, cut, nb, bits);
     return hipGetLastError();
 }
 
@@ -136,17 +141,19 @@ hipError_t launch_h4_planes(const float4 *tbl, int nb, float *planes, hipStream_
 // whole platten (16^4 boxes: 64 thresholds, where counting per batch of 64 boxes repeated them
 // 340-fold) into the count table.
 //
-// k_h4_tiles takes 64 tiles per wave, one per lane, and one simulation at a time for all of them:
-// the tile's sums and candidate list are its lane's own, nothing crosses lanes.  Tiles are ordered
+// k_h4_tiles (with keys) takes 64 tiles per wave, one per lane, and one simulation at a time for all of
+// them: the tile's sums and candidate list are its lane's own, nothing crosses lanes.  Tiles are ordered
 // so that a wave mostly holds one pair of thresholds of arms 0 and 1 and 8 x 8 neighbouring ones of
 // arms 2 and 3: their outcomes lie in a few lines of the table (tiled for that, H4_SLAB), where one
 // lane per simulation touched one line per lane.  Four simulations share the arithmetic on packed
 // counts; per simulation the table offset is one packed 16-bit dot product.  A calibration stores
 // only candidate keys (k_h4_pilot).
-// Bound by the gathers' addresses (about 16 cycles per instruction and CU).  16^4 boxes x 32,768
+// Bound by the gathers' addresses (40 cache lines looked up per instruction).  16^4 boxes x 32,768
 // simulations, 4-arm calibration: counts 0.012, pilot 0.18, tiles 2.13 ms (4.40 with Philox words
 // and counts per batch of 64 boxes, lane = simulation, and 7.9 GB of keys stored) and the selection
-// 1.52 -> 0.77 ms; basket validation: 0.015 + 1.37 ms (6.50).
+// 1.52 -> 0.77 ms.  Rows of 36 or 64 floats instead of 4 x 8 tiles: 2.33 and 2.22 ms.
+//
+// k_h4_runs (without keys) takes up to 8 tiles per lane that differ in arm 3's threshold alone.
 // ------------------------------------------------------------------------------------------
 constexpr int H4C_NB = NP35;   // Philox blocks of a simulation
 __global__ __launch_bounds__(WG) void k_h4_count(const Grp4 *__restrict__ grp, int32_t n_grp, uint32_t win_b,
@@ -230,13 +237,12 @@ __device__ __forceinline__ uint32_t u4_get(const uint4 &v, int i) {
     return i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w));
 }
 constexpr uint32_t H4_W_PLANE = (uint32_t)(4 * H4_SLAB) | (4u << 16);            // byte offsets into a plane (codes, m2 = 8)
-constexpr uint32_t H4_W_MASK = (uint32_t)((NP35 + 1) * (NP35 + 1)) | (1u << 16);   // into the mask table (counts, m2 = 36)
 static_assert(4 * H4_SLAB < 65536 && 15 * 4 * H4_PLANE < (1ll << 32), "16-bit weights, 32-bit offsets");
 
 // A set's count rows in LDS, a chunk (64 simulations) at a time: the distinct rows are loaded once for
 // the wave, 16 rows per instruction, and each lane reads its own from LDS (a global 16-byte load per
 // lane and arm took 63 cycles whether the lanes' addresses agreed or not, and 960 of 1,640 us on the
-// basket's 16^4 boxes).  The next chunk's first H4_AHEAD * 16 rows are loaded ahead.
+// basket's 16^4 boxes with one tile per lane).  The next chunk's first H4_AHEAD * 16 rows are loaded ahead.
 constexpr int H4_AHEAD = 3;
 struct H4Rows {
     const uint4 *__restrict__ tab;
@@ -396,14 +402,13 @@ __global__ __launch_bounds__(WG) void k_h4_pilot(const H4Set *__restrict__ sets,
     if (wv == 0 && t >= 0 && !sel) U[t] = -INFINITY;   // no selection
 }
 
-// MODE 0: rejection counts and score sums from the one-byte mask table; 1: from the statistic planes,
-// every key stored; 2: from the planes, the keys below the tile's bound U stored as candidates, those
-// equal to it counted.
-template <int MODE, bool SCORE>
+// Rejection counts and score sums with keys, from the statistic planes: every key stored, or (CAND) the
+// keys below the tile's bound U as candidates, those equal to it counted.
+template <bool CAND, bool SCORE>
 __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets, const H4Item *__restrict__ items,
                                                  int64_t n_items, const uint32_t *__restrict__ rows, int32_t max_rows,
                                                  const uint4 *__restrict__ tab, uint32_t win_b,
-                                                 uint32_t win_e, const uint8_t *__restrict__ mtbl,
+                                                 uint32_t win_e,
                                                  const float *__restrict__ planes, float cut,
                                                  uint32_t *__restrict__ R, unsigned long long *__restrict__ sumT,
                                                  float *__restrict__ keys, const float *__restrict__ U,
@@ -424,14 +429,14 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
     auto lrow = [&](int a) { return rr.lds + S->row[a][lane] * H4_ROW_LDS; };
     const uint4 *__restrict__ l0 = lrow(0), *__restrict__ l1 = lrow(1), *__restrict__ l2 = lrow(2),
                 *__restrict__ l3 = lrow(3), *__restrict__ c2 = lrow(4), *__restrict__ c3 = lrow(5);
-    const uint32_t base = (cfg - 1u) * (uint32_t)(4 * H4_PLANE), cfg4 = cfg * 0x01010101u;
-    const float bound = MODE == 2 ? (t >= 0 ? U[t] : -INFINITY) : 0.0f;
+    const uint32_t base = (cfg - 1u) * (uint32_t)(4 * H4_PLANE);
+    const float bound = CAND ? (t >= 0 ? U[t] : -INFINITY) : 0.0f;
     // MODE 2: keys at or above it matter to nothing (the float after the bound: keys equal to it count)
     const float look = fmaxf(cut, bound >= 0.0f && bound < INFINITY ? __uint_as_float(__float_as_uint(bound) + 1u) : bound);
     uint32_t ncand = 0u, neq = 0u, cap = 0u;
     float *__restrict__ kp = keys;
-    if (MODE == 1) kp = keys + S->key_base + (int64_t)lane * WAVE;
-    if (MODE == 2) {
+    if (!CAND) kp = keys + S->key_base + (int64_t)lane * WAVE;
+    if (CAND) {
         cap = (uint32_t)h4_cap(N, S->slice);
         kp = keys + S->key_base + ((int64_t)lane * S->n_slices + I->slice) * cap;
     }
@@ -455,32 +460,23 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
         if (g >= ge) break;   // uniform
         const uint4 y0 = l0[i], y1 = l1[i];
         uint4 y2 = make_uint4(0u, 0u, 0u, 0u), y3 = y2, e2 = y2, e3 = y2;
-        if (MODE == 0 || SCORE) {
+        if (SCORE) {
             y2 = l2[i];
             y3 = l3[i];
         }
-        if (MODE != 0) {
-            e2 = c2[i];
-            e3 = c3[i];
-        }
+        e2 = c2[i];
+        e3 = c3[i];
         const int nv = N - (int)(g * GRAN2);   // simulations from this granule on (uniform)
-        uint32_t m[GRAN2];
         float v[GRAN2];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             uint32_t off[4];
-            if (MODE == 0) {
-                h4_offsets(u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q), NP35 + 1, H4_W_MASK, 0u, off);
+            h4_offsets(u4_get(y0, q), u4_get(y1, q), u4_get(e2, q), u4_get(e3, q), 8, H4_W_PLANE, base, off);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) m[4 * q + j] = mtbl[off[j]];
-            } else {
-                h4_offsets(u4_get(y0, q), u4_get(y1, q), u4_get(e2, q), u4_get(e3, q), 8, H4_W_PLANE, base, off);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    v[4 * q + j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(planes) + off[j]);
-            }
+            for (int j = 0; j < 4; ++j)
+                v[4 * q + j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(planes) + off[j]);
         }
-        if (MODE == 1 && t >= 0) {
+        if (!CAND && t >= 0) {
             float *__restrict__ kc = kp + (int64_t)(g / 4) * kstride + (g % 4) * GRAN2;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -491,37 +487,30 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
             const int n4 = nv - 4 * q;   // uniform
             const uint32_t valid = n4 >= 4 ? H : (n4 <= 0 ? 0u : H >> (8 * (4 - n4)));
             uint32_t f = 0u;
-            if (MODE == 0) {
-                // bytes (mask & b) != 0: a sum with 0x7F sets bit 7 (masks are below 16)
-                const uint32_t x = (m[4 * q] | (m[4 * q + 1] << 8) | (m[4 * q + 2] << 16) | (m[4 * q + 3] << 24)) & cfg4;
-                f = (x + 0x7F7F7F7Fu) & valid;
-                add(f, u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q));
-            } else {
-                const float *vq = v + 4 * q;
-                const bool any = fminf(fminf(vq[0], vq[1]), fminf(vq[2], vq[3])) < (MODE == 2 ? look : cut);
-                if (__ballot(any) == 0ull) continue;   // rejections and candidates are a few per cent
+            const float *vq = v + 4 * q;
+            const bool any = fminf(fminf(vq[0], vq[1]), fminf(vq[2], vq[3])) < (CAND ? look : cut);
+            if (__ballot(any) == 0ull) continue;   // rejections and candidates are a few per cent
 #pragma unroll
-                for (int j = 0; j < 4; ++j) f |= vq[j] < cut ? 0x80u << (8 * j) : 0u;
-                f &= valid;
-                add(f, u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q));
-                if (MODE == 2) {
+            for (int j = 0; j < 4; ++j) f |= vq[j] < cut ? 0x80u << (8 * j) : 0u;
+            f &= valid;
+            add(f, u4_get(y0, q), u4_get(y1, q), u4_get(y2, q), u4_get(y3, q));
+            if (CAND) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (vq[j] <= bound && j < n4) {
-                            if (vq[j] == bound) {
-                                ++neq;
-                            } else {
-                                if (ncand < cap) kp[ncand] = vq[j];
-                                ++ncand;
-                            }
+                for (int j = 0; j < 4; ++j)
+                    if (vq[j] <= bound && j < n4) {
+                        if (vq[j] == bound) {
+                            ++neq;
+                        } else {
+                            if (ncand < cap) kp[ncand] = vq[j];
+                            ++ncand;
                         }
-                }
+                    }
             }
         }
     }
     }
     if (t < 0) return;
-    if (MODE == 2) {
+    if (CAND) {
         cnt[S->cnt_base + (int64_t)I->slice * WAVE + lane] = ncand;
         if (neq) atomicAdd(&eq[t], neq);
     }
@@ -530,6 +519,117 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
         if (SCORE) {   // the sums of two arms in the halves of one 64-bit word (at most 35 * 2^24 each)
             atomicAdd(&sumT[2 * (int64_t)t], (unsigned long long)(a0 >> 7) | ((unsigned long long)(a1 >> 7) << 32));
             atomicAdd(&sumT[2 * (int64_t)t + 1], (unsigned long long)(a2 >> 7) | ((unsigned long long)(a3 >> 7) << 32));
+        }
+    }
+}
+
+// Rejection counts and score sums of runs: a lane takes up to 8 tiles that differ in arm 3's threshold
+// alone, so one gather per simulation (the rejecting y3 of its y0, y1, y2 and configuration, as bits)
+// serves them all, and each tile tests its own y3 in registers.  The four waves of a workgroup take
+// chunks of 64 simulations in turn and add up in LDS.  Bound by vector instructions (four per tile and
+// simulation, 58% of the issue slots with three waves per SIMD; four waves spill).  Basket, 16^4 boxes
+// x 32,768 simulations: 1.37 ms with one byte gathered per tile and simulation, 0.42 ms so (0.58 without
+// pieces of one length together, 0.50 with a wave's sums added to memory by itself).  Runs of one tile
+// are still faster than lanes of one tile (0.21 and 0.35 ms at 1,899 tiles x 131,072 simulations): the
+// words of one pair of thresholds of arms 0 and 1 lie in a line or two.
+template <bool SCORE>
+__global__ __launch_bounds__(WG) void k_h4_runs(const H4Run *__restrict__ sets, const H4Item *__restrict__ items,
+                                                const uint32_t *__restrict__ rows, int32_t max_rows,
+                                                const uint4 *__restrict__ tab, uint32_t win_b, uint32_t win_e,
+                                                const uint64_t *__restrict__ bits, uint32_t *__restrict__ R,
+                                                unsigned long long *__restrict__ sumT) {
+    constexpr uint32_t ONE = 0x01010101u;
+    constexpr uint32_t W = (uint32_t)(8 * (NP35 + 1)) | (8u << 16);   // bytes per (36 y0 + y1) and per y2
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const H4Item *__restrict__ I = items + blockIdx.x;
+    const uint32_t gb = max(I->g_begin, win_b), ge = min(I->g_end, win_e);
+    if (gb >= ge) return;   // the whole workgroup
+    const H4Run *__restrict__ S = sets + I->set;
+    const int32_t N = S->n_sims, n_run = S->n_run;
+    extern __shared__ uint4 h4_lds[];
+    H4Rows rr(tab, rows + S->row_at, S->n_rows, h4_lds + (size_t)wv * max_rows * H4_ROW_LDS);
+    auto lrow = [&](int a) { return rr.lds + S->row[a][lane] * H4_ROW_LDS; };
+    const uint4 *__restrict__ l0 = lrow(0), *__restrict__ l1 = lrow(1), *__restrict__ l2 = lrow(2);
+    const uint4 *__restrict__ l3[H4_RUN];
+#pragma unroll
+    for (int r = 0; r < H4_RUN; ++r) l3[r] = lrow(3 + r);
+    const uint32_t base = (S->cfg[lane] - 1u) * (uint32_t)(8 * H4_BITS);
+    uint32_t aR[H4_RUN], a0[H4_RUN], a1[H4_RUN], a2[H4_RUN], a3[H4_RUN];
+#pragma unroll
+    for (int r = 0; r < H4_RUN; ++r) aR[r] = a0[r] = a1[r] = a2[r] = a3[r] = 0u;
+    const uint32_t gw = gb + 4u * (uint32_t)wv;   // items and windows begin at chunks; the waves take them in turn
+    if (gw < ge) rr.load((gw - win_b) / 4);
+    for (uint32_t g0 = gw; g0 < ge; g0 += WG / WAVE * 4) {
+        rr.store((g0 - win_b) / 4);
+        if (g0 + WG / WAVE * 4 < ge) rr.load((g0 + WG / WAVE * 4 - win_b) / 4);
+#pragma unroll 1
+        for (uint32_t i = 0; i < 4; ++i) {
+            const uint32_t g = g0 + i;
+            if (g >= ge) break;   // uniform
+            const uint4 y0 = l0[i], y1 = l1[i], y2 = l2[i];
+            uint64_t m[GRAN2];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                uint32_t off[4];
+                h4_offsets(u4_get(y0, q), u4_get(y1, q), 0u, u4_get(y2, q), 0, W, base, off);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    m[4 * q + j] = *reinterpret_cast<const uint64_t *>(reinterpret_cast<const char *>(bits) + off[j]);
+            }
+            const int nv = N - (int)(g * GRAN2);   // simulations from this granule on (uniform)
+#pragma unroll
+            for (int r = 0; r < H4_RUN; ++r) {
+                if (r >= n_run) break;   // uniform
+                const uint4 y3 = l3[r][i];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int n4 = nv - 4 * q;
+                    const uint32_t valid = n4 >= 4 ? ONE : (n4 <= 0 ? 0u : ONE >> (8 * (4 - n4)));
+                    const uint32_t w = u4_get(y3, q);
+                    // shifts by the byte in the low 6 bits: counts are at most 35
+                    const uint32_t x0 = (uint32_t)(m[4 * q] >> (w & 63u)), x1 = (uint32_t)(m[4 * q + 1] >> ((w >> 8) & 63u)),
+                                   x2 = (uint32_t)(m[4 * q + 2] >> ((w >> 16) & 63u)), x3 = (uint32_t)(m[4 * q + 3] >> (w >> 24));
+                    const uint32_t x01 = __builtin_amdgcn_perm(x1, x0, 0x0C0C0400u), x23 = __builtin_amdgcn_perm(x3, x2, 0x04000C0Cu);
+                    const uint32_t f = (x01 | x23) & valid;
+                    aR[r] += (uint32_t)__popc(f);
+                    if (SCORE) {
+                        a0[r] = __builtin_amdgcn_udot4(f, u4_get(y0, q), a0[r], false);
+                        a1[r] = __builtin_amdgcn_udot4(f, u4_get(y1, q), a1[r], false);
+                        a2[r] = __builtin_amdgcn_udot4(f, u4_get(y2, q), a2[r], false);
+                        a3[r] = __builtin_amdgcn_udot4(f, w, a3[r], false);
+                    }
+                }
+            }
+        }
+    }
+    // the waves' sums through LDS: one addition to memory per tile and workgroup
+    constexpr int V = SCORE ? 5 : 1;
+    uint32_t *__restrict__ red = reinterpret_cast<uint32_t *>(h4_lds);
+    __syncthreads();
+    for (int i = threadIdx.x; i < V * H4_RUN * WAVE; i += WG) red[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < H4_RUN; ++r) {
+        if (aR[r] == 0u) continue;
+        uint32_t *__restrict__ w = red + V * r * WAVE + lane;
+        atomicAdd(&w[0], aR[r]);
+        if (SCORE) {
+            atomicAdd(&w[WAVE], a0[r]);
+            atomicAdd(&w[2 * WAVE], a1[r]);
+            atomicAdd(&w[3 * WAVE], a2[r]);
+            atomicAdd(&w[4 * WAVE], a3[r]);
+        }
+    }
+    __syncthreads();
+    for (int r = wv; r < n_run; r += WG / WAVE) {
+        const uint32_t *__restrict__ w = red + V * r * WAVE + lane;
+        const int32_t t = S->tile[r][lane];
+        if (t < 0 || w[0] == 0u) continue;
+        atomicAdd(&R[t], w[0]);
+        if (SCORE) {   // the sums of two arms in the halves of one 64-bit word (at most 35 * 2^24 each)
+            atomicAdd(&sumT[2 * (int64_t)t], (unsigned long long)w[WAVE] | ((unsigned long long)w[2 * WAVE] << 32));
+            atomicAdd(&sumT[2 * (int64_t)t + 1], (unsigned long long)w[3 * WAVE] | ((unsigned long long)w[4 * WAVE] << 32));
         }
     }
 }
@@ -545,7 +645,7 @@ hipError_t launch_hier4(const Platten &P, uint64_t seed, uint32_t *R, unsigned l
 #define CSE_H4_LAUNCH(M, SC)                                                                                          \
     hipLaunchKernelGGL((k_h4_tiles<M, SC>), grid, dim3(WG), lds, st, P.d_h4set, P.d_h4item, P.n_h4item, P.d_h4rows,     \
                        P.h4_max_rows, P.d_b4tab, wb,                                                                  \
-                       we, P.d_h4mask, P.d_h4plane, cut, R, sumT, keys, P.d_h4u, P.d_h4eq, P.d_h4cnt)
+                       we, P.d_h4plane, cut, R, sumT, keys, P.d_h4u, P.d_h4eq, P.d_h4cnt)
 #define CSE_H4_SC(M)             \
     if (sumT)                    \
         CSE_H4_LAUNCH(M, true);  \
@@ -561,13 +661,23 @@ hipError_t launch_hier4(const Platten &P, uint64_t seed, uint32_t *R, unsigned l
         if (keys && k && wb == 0)
             hipLaunchKernelGGL(k_h4_pilot, dim3((uint32_t)P.n_h4set), dim3(WG), lds, st, P.d_h4set, P.d_h4rows,
                                P.h4_max_rows, P.d_b4tab, P.d_h4plane, k, P.h4_margin, P.d_h4u, P.d_h4eq, P.d_h4fb);
-        if (!keys) {
-            CSE_H4_SC(0);
-        } else if (!k) {
-            CSE_H4_SC(1);
-        } else {
-            CSE_H4_SC(2);
+        if (keys) {
+            if (k) {
+                CSE_H4_SC(true);
+            } else {
+                CSE_H4_SC(false);
+            }
+            continue;
         }
+        const dim3 rgrid((uint32_t)P.n_h4runitem);
+        const size_t rlds = std::max((size_t)(WG / WAVE) * P.h4_run_rows * H4_ROW_LDS * sizeof(uint4),
+                                     (size_t)5 * H4_RUN * WAVE * sizeof(uint32_t));
+        if (sumT)
+            hipLaunchKernelGGL(k_h4_runs<true>, rgrid, dim3(WG), rlds, st, P.d_h4run, P.d_h4runitem, P.d_h4rows,
+                               P.h4_run_rows, P.d_b4tab, wb, we, P.d_h4bits, R, sumT);
+        else
+            hipLaunchKernelGGL(k_h4_runs<false>, rgrid, dim3(WG), rlds, st, P.d_h4run, P.d_h4runitem, P.d_h4rows,
+                               P.h4_run_rows, P.d_b4tab, wb, we, P.d_h4bits, R, sumT);
     }
 #undef CSE_H4_SC
 #undef CSE_H4_LAUNCH

@@ -34,11 +34,11 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_taylor(const Platten &P, const double *f, const double *g, double *bound, int32_t *vertex,
                          double *point, hipStream_t st);
 hipError_t launch_hier4_table(int n, float4 *tbl, const HierNode *nodes, hipStream_t st);
-hipError_t launch_h4_mask(const float4 *tbl, int64_t n, float cut, int nbits, uint8_t *mask, hipStream_t st);
 hipError_t launch_basket_table(int n, const double *theta0, float4 *tbl, const HierNode *nodes, hipStream_t st);
 hipError_t launch_h4_planes(const float4 *tbl, int nb, float *planes, hipStream_t st);
 // counts of every threshold group, then the per-tile sums; keys: NULL, or every float32 key, or (k
 // given, after k is known on the stream) the candidate keys of the tiles' k-th smallest
+hipError_t launch_h4_bits(const float4 *tbl, float cut, int nb, uint64_t *bits, hipStream_t st);
 hipError_t launch_hier4(const Platten &P, uint64_t seed, uint32_t *R, unsigned long long *sumT, float *keys,
                         const int32_t *k, hipStream_t st);
 // lambda*_i and the count below it from the candidates (exact; a tile whose k-th key is not among

@@ -569,26 +569,52 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
     } else if (kind == CSE_HIER4 || kind == CSE_BASKET4) {
         // distinct values per arm -> coordinates; tiles ordered by simulation count, thresholds of arms
         // 0 and 1, 8 x 8 blocks of arms 2 and 3, 64 consecutive ones of a count to a set
-        std::vector<double> uv[4];
-        for (int64_t t = 0; t < P->n_tiles; ++t)
-            for (int a = 0; a < 4; ++a) uv[a].push_back(P->tile_theta[t * 4 + a]);
-        for (int a = 0; a < 4; ++a) {
-            std::sort(uv[a].begin(), uv[a].end());
-            uv[a].erase(std::unique(uv[a].begin(), uv[a].end()), uv[a].end());
-        }
         struct At {
-            int32_t n, c[4], tile;
+            int32_t n, c[4], tile, cfg, at;
         };
         std::vector<At> order(P->n_tiles);
         for (int64_t t = 0; t < P->n_tiles; ++t) {
             order[t].n = P->tile_N[t];
             order[t].tile = (int32_t)t;
-            for (int a = 0; a < 4; ++a)
-                order[t].c[a] = (int32_t)(std::lower_bound(uv[a].begin(), uv[a].end(), P->tile_theta[t * 4 + a]) - uv[a].begin());
+            order[t].cfg = P->tile_cfg[t];
+        }
+        std::vector<double> uv[4];   // distinct values, ascending; found in an open-addressed table first
+        {
+            size_t slots = 64;
+            while (slots < 2 * (size_t)P->n_tiles) slots *= 2;
+            std::vector<int32_t> slot(slots), rank, by;
+            for (int a = 0; a < 4; ++a) {
+                std::fill(slot.begin(), slot.end(), -1);
+                for (int64_t t = 0; t < P->n_tiles; ++t) {
+                    const double v = P->tile_theta[t * 4 + a] + 0.0;   // one zero
+                    uint64_t h;
+                    memcpy(&h, &v, 8);
+                    h *= 0x9E3779B97F4A7C15ull;
+                    size_t i = (size_t)(h >> 20) & (slots - 1);
+                    while (slot[i] >= 0 && uv[a][slot[i]] != v) i = (i + 1) & (slots - 1);
+                    if (slot[i] < 0) {
+                        slot[i] = (int32_t)uv[a].size();
+                        uv[a].push_back(v);
+                    }
+                    order[t].c[a] = slot[i];
+                }
+                by.resize(uv[a].size());
+                rank.resize(uv[a].size());
+                std::iota(by.begin(), by.end(), 0);
+                std::sort(by.begin(), by.end(), [&](int32_t x, int32_t y) { return uv[a][x] < uv[a][y]; });
+                for (size_t i = 0; i < by.size(); ++i) rank[by[i]] = (int32_t)i;
+                for (auto &o : order) o.c[a] = rank[o.c[a]];
+                std::sort(uv[a].begin(), uv[a].end());
+            }
         }
         std::sort(order.begin(), order.end(), [](const At &x, const At &y) {
-            return std::make_tuple(x.n, x.c[0], x.c[1], x.c[2] / 8, x.c[3] / 8, x.c[2], x.c[3], x.tile) <
-                   std::make_tuple(y.n, y.c[0], y.c[1], y.c[2] / 8, y.c[3] / 8, y.c[2], y.c[3], y.tile);
+            if (x.n != y.n) return x.n < y.n;
+            if (x.c[0] != y.c[0]) return x.c[0] < y.c[0];
+            if (x.c[1] != y.c[1]) return x.c[1] < y.c[1];
+            if ((x.c[2] ^ y.c[2]) >> 3) return x.c[2] < y.c[2];
+            if ((x.c[3] ^ y.c[3]) >> 3) return x.c[3] < y.c[3];
+            if (x.c[2] != y.c[2]) return x.c[2] < y.c[2];
+            return x.c[3] != y.c[3] ? x.c[3] < y.c[3] : x.tile < y.tile;
         });
         // threshold groups: per simulation count and arm, the coordinates present, 8 to a group
         std::vector<Grp4> grps;
@@ -640,15 +666,19 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         P->n_grp4 = (int32_t)grps.size();
         std::vector<int32_t> at(P->n_tiles);
         std::vector<uint32_t> rows;
+        // place of row i of group g (its codes: 8 + i) in the list that begins at row_at, appended if new
+        std::vector<int64_t> row_place(16 * grps.size(), -1);
+        auto row_of = [&](int64_t row_at, int32_t g, int32_t i) {
+            int64_t &q = row_place[16 * (size_t)g + i];
+            if (q < row_at) {
+                q = (int64_t)rows.size();
+                rows.push_back((uint32_t)(grps[g].row + i * grps[g].stride));
+            }
+            return (uint16_t)(q - row_at);
+        };
         for (size_t i = 0; i < order.size();) {
             H4Set S{};
             S.row_at = (int64_t)rows.size();
-            auto row_of = [&](int64_t r) {   // place of the row in the set's list (the latest first: neighbours share)
-                for (int64_t q = (int64_t)rows.size() - 1; q >= S.row_at; --q)
-                    if (rows[q] == (uint32_t)r) return (uint16_t)(q - S.row_at);
-                rows.push_back((uint32_t)r);
-                return (uint16_t)(rows.size() - 1 - S.row_at);
-            };
             S.n_sims = order[i].n;
             S.key_base = P->n_keys;
             while (S.n_lanes < WAVE && i < order.size() && order[i].n == S.n_sims) {
@@ -658,9 +688,8 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
                 S.cfg[l] = (uint32_t)P->tile_cfg[o.tile];
                 for (int a = 0; a < 4; ++a) {
                     const auto pl = at_arm[a][i];
-                    const Grp4 &g = grps[pl.first];
-                    S.row[a][l] = row_of(g.row + pl.second * g.stride);
-                    if (a >= 2) S.row[a + 2][l] = row_of(g.row + (8 + pl.second) * g.stride);
+                    S.row[a][l] = row_of(S.row_at, pl.first, pl.second);
+                    if (a >= 2) S.row[a + 2][l] = row_of(S.row_at, pl.first, 8 + pl.second);
                 }
                 at[o.tile] = (int32_t)(P->h4set.size() * WAVE) + l;
                 ++i;
@@ -681,6 +710,79 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             P->h4set.push_back(S);
         }
         P->n_blocks = P->n_h4set = (int64_t)P->h4set.size();
+        // runs along arm 3: the tiles of one count, thresholds of arms 0, 1 and 2 and configuration, in
+        // pieces of up to H4_RUN
+        {
+            std::vector<At> by = order;   // at: place in `order`
+            for (size_t i = 0; i < by.size(); ++i) by[i].at = (int32_t)i;
+            for (size_t i = 0, j; i < by.size(); i = j) {   // a count and pair of thresholds of arms 0 and 1 at a time
+                for (j = i + 1; j < by.size() && std::tie(by[i].n, by[i].c[0], by[i].c[1]) == std::tie(by[j].n, by[j].c[0], by[j].c[1]);)
+                    ++j;
+                std::sort(by.begin() + i, by.begin() + j, [](const At &x, const At &y) {
+                    if (x.cfg != y.cfg) return x.cfg < y.cfg;
+                    if (x.c[2] != y.c[2]) return x.c[2] < y.c[2];
+                    return x.c[3] != y.c[3] ? x.c[3] < y.c[3] : x.tile < y.tile;
+                });
+            }
+            auto end_of = [&](size_t i) {
+                const At &x = by[i];
+                size_t j = i + 1;
+                while (j < by.size() && std::tie(x.n, x.c[0], x.c[1], x.cfg, x.c[2]) ==
+                                            std::tie(by[j].n, by[j].c[0], by[j].c[1], by[j].cfg, by[j].c[2]))
+                    ++j;
+                return j;
+            };
+            auto close = [&](int lanes) {
+                H4Run &S = P->h4run.back();
+                for (int l = lanes; l < WAVE; ++l) {
+                    for (int r = 0; r < H4_RUN; ++r) S.tile[r][l] = -1;
+                    for (int a = 0; a < 3 + H4_RUN; ++a) S.row[a][l] = S.row[a][0];
+                    S.cfg[l] = S.cfg[0];
+                }
+                S.n_rows = (int32_t)((int64_t)rows.size() - S.row_at);
+                P->h4_run_rows = std::max(P->h4_run_rows, S.n_rows);
+            };
+            int lanes = 0;
+            // pieces of one length together: a set takes as long as its longest
+            struct Piece {
+                int32_t n, len;
+                size_t b;
+            };
+            std::vector<Piece> pieces;
+            for (size_t i = 0, j; i < by.size(); i = j) {
+                j = end_of(i);
+                const int64_t len = (int64_t)(j - i), parts = (len + H4_RUN - 1) / H4_RUN;
+                for (int64_t q = 0; q < parts; ++q) {
+                    const size_t b = i + (size_t)(len * q / parts), e = i + (size_t)(len * (q + 1) / parts);
+                    pieces.push_back({by[b].n, (int32_t)(e - b), b});
+                }
+            }
+            std::stable_sort(pieces.begin(), pieces.end(), [](const Piece &x, const Piece &y) {
+                return std::make_tuple(x.n, -x.len) < std::make_tuple(y.n, -y.len);
+            });
+            for (const Piece &pc : pieces) {
+                if (P->h4run.empty() || lanes == WAVE || P->h4run.back().n_sims != pc.n ||
+                    (int64_t)rows.size() - P->h4run.back().row_at > H4_ROWS * WAVE - (3 + H4_RUN)) {
+                    if (!P->h4run.empty()) close(lanes);
+                    P->h4run.emplace_back();
+                    P->h4run.back().n_sims = pc.n;
+                    P->h4run.back().row_at = (int64_t)rows.size();
+                    lanes = 0;
+                }
+                H4Run &S = P->h4run.back();
+                S.cfg[lanes] = (uint32_t)by[pc.b].cfg;
+                for (int a = 0; a < 3; ++a) S.row[a][lanes] = row_of(S.row_at, at_arm[a][by[pc.b].at].first, at_arm[a][by[pc.b].at].second);
+                for (int r = 0; r < H4_RUN; ++r) {
+                    const At &o = by[r < pc.len ? pc.b + r : pc.b];
+                    S.tile[r][lanes] = r < pc.len ? o.tile : -1;
+                    S.row[3 + r][lanes] = row_of(S.row_at, at_arm[3][o.at].first, at_arm[3][o.at].second);
+                }
+                S.n_run = std::max(S.n_run, pc.len);
+                ++lanes;
+            }
+            if (lanes) close(lanes);
+            stage.add(&P->d_h4run, P->h4run.data(), P->h4run.size());
+        }
         stage.add(&P->d_grp4, grps.data(), grps.size());
         stage.add(&P->d_h4at, at.data(), at.size());
         stage.add(&P->d_h4rows, rows.data(), rows.size());
@@ -700,10 +802,9 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             CSE_HIP_TRY(launch_basket_table(P->n_per_arm, design->theta0, P->d_h4tbl, P->d_hnodes, nullptr));
         else
             CSE_HIP_TRY(launch_hier4_table(P->n_per_arm, P->d_h4tbl, P->d_hnodes, nullptr));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4mask, (size_t)P->h4_outcomes));
-        CSE_HIP_TRY(launch_h4_mask(P->d_h4tbl, P->h4_outcomes, (float)design->cut, kind == CSE_BASKET4 ? 4 : 3,
-                                   P->d_h4mask, nullptr));
         const int n_cfg = kind == CSE_BASKET4 ? 15 : 7;
+        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4bits, (size_t)n_cfg * H4_BITS * sizeof(uint64_t)));
+        CSE_HIP_TRY(launch_h4_bits(P->d_h4tbl, (float)design->cut, n_cfg, P->d_h4bits, nullptr));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_h4plane, (size_t)n_cfg * H4_PLANE * sizeof(float)));
         CSE_HIP_TRY(launch_h4_planes(P->d_h4tbl, n_cfg, P->d_h4plane, nullptr));
         CSE_HIP_TRY(hipDeviceSynchronize());
@@ -1120,7 +1221,32 @@ int plan_h4_items(Platten *P, int64_t target_wgs) {
             items.push_back(it);
         }
     }
+    // runs: the longest slices that make target_wgs items (a workgroup each)
+    std::vector<H4Item> run_items;
+    auto run_wgs = [&](int64_t slice) {
+        int64_t n = 0;
+        for (auto &S : P->h4run) n += (((int64_t)S.n_sims + GRAN2 - 1) / GRAN2 + slice - 1) / slice;
+        return n;
+    };
+    int64_t rs = 16;   // a chunk per wave
+    while (rs < H4_SLICE_MAX && run_wgs(2 * rs) >= target_wgs) rs *= 2;
+    for (size_t i = 0; i < P->h4run.size(); ++i) {
+        const int64_t ng = ((int64_t)P->h4run[i].n_sims + GRAN2 - 1) / GRAN2;
+        for (int64_t s = 0; s * rs < ng; ++s) {
+            H4Item it{};
+            it.set = (int32_t)i;
+            it.slice = (int32_t)s;
+            it.g_begin = (uint32_t)(s * rs);
+            it.g_end = (uint32_t)std::min<int64_t>(ng, (s + 1) * rs);
+            run_items.push_back(it);
+        }
+    }
     P->shape_gen->fetch_add(1);   // plans captured on the old arrays become stale
+    if (P->d_h4runitem) CSE_HIP_TRY(hipFree(P->d_h4runitem));
+    P->d_h4runitem = nullptr;
+    P->n_h4runitem = (int64_t)run_items.size();
+    if (P->n_h4runitem)
+        if (int e = upload(&P->d_h4runitem, run_items.data(), run_items.size())) return e;
     for (void *q : {(void *)P->d_h4item, (void *)P->d_h4set, (void *)P->d_h4cnt})
         if (q) CSE_HIP_TRY(hipFree(q));
     P->d_h4item = nullptr;
@@ -1265,7 +1391,7 @@ void free_platten(Platten *P) {
                     P->d_cls_off, P->d_cp_base, P->d_cp_mark, P->d_cp_tbl,  P->d_radii,
                     P->d_is_box, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
                     P->d_queue,  P->d_p23mem, P->d_p23row, P->d_p23tilerow, P->d_p23counts, P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
-                    P->d_h4mask, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
+                    P->d_h4run, P->d_h4runitem, P->d_h4bits, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
                     P->d_grp4, P->d_h4rows, P->d_h4set, P->d_h4item, P->d_b4tab, P->d_h4u, P->d_h4eq, P->d_h4at, P->d_h4cnt, P->d_h4fb, P->d_h4plane};
     auto in_arena = [&](void *q) {
         for (auto &a : P->arenas)
