@@ -138,6 +138,7 @@ constexpr int H4_PILOT_MIN_N = 1024;     // fewer simulations: every key is kept
 constexpr int H4_PILOT_MAX = 2048;
 constexpr int H4_CAND_MAX = 3072;        // candidates selected from LDS (more: exact path)
 constexpr double H4_CAND_K = 832.0;      // largest (max N + 1) * alpha that takes candidates
+constexpr int64_t H4_CAND_KEYS = (int64_t)48 << 20;   // keys of the platten from which candidates are kept
 constexpr double H4_CAND_ALPHA = 0.05;   // and largest alpha
 // candidate slots of a tile per slice of `slice` granules (a pilot leaves an eighth of the keys at most;
 // a set's slots fit its keys' place in the workspace)
@@ -272,6 +273,8 @@ struct Platten {
     double *d_verts = nullptr;
     double *d_radii = nullptr;           // [n_tiles * d] half-widths of the tile's box
     int32_t *d_is_box = nullptr;         // [n_tiles] 1 when the tile is its whole box
+    std::vector<int32_t> border;         // tiles in the order of the bound's search (empty: as they are)
+    int32_t *d_border = nullptr;
     int32_t *d_in_null = nullptr;        // [n_tiles] 1 when the tile lies in the null space
     int64_t *d_key_off = nullptr;        // [n_tiles] each tile's first key in d_keys
     int64_t *d_key_stride = nullptr;     // [n_tiles] distance between its 64-simulation chunks
@@ -307,6 +310,7 @@ struct Platten {
     uint32_t *d_h4cnt = nullptr;
     int32_t *d_h4at = nullptr;
     uint32_t *d_h4fb = nullptr;
+    bool h4_candidates = false;          // candidates at any size
     float h4_margin = 6.0f;              // pilot margin in standard deviations of the rank
 
     // design tables (device)

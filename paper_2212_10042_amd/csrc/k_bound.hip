@@ -39,39 +39,55 @@ __device__ __forceinline__ double softplus(double x) {
 // ---- regularized incomplete beta ----
 __device__ double lbeta(double a, double b) { return lgamma(a) + lgamma(b) - lgamma(a + b); }
 
-// 1 / (1 + d1/(1 + d2/(1 + ...))) of DLMF 8.17.22 by the modified Lentz method.
-__device__ double beta_cf(double a, double b, double x) {
+// n / d for operands and quotients well inside the normal range: the steps of the compiler's division
+// without its scaling, hence the same bits.
+__device__ __forceinline__ double div_mid(double n, double d) {
+    const double r = rcp_nr(d), q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+
+// 1 / (1 + d1/(1 + d2/(1 + ...))) of DLMF 8.17.22 by the modified Lentz method, two terms at a time, so
+// that the next two coefficients are computed in the shadow of the chain C, D.
+__device__ __forceinline__ double beta_cf(double a, double b, double x) {
     const double tiny = 1e-300, eps = 1e-16;
+    auto odd = [&](double m) { return div_mid(-(a + m) * (a + b + m) * x, (a + 2.0 * m) * (a + 2.0 * m + 1.0)); };   // d_{2m+1}
+    auto even = [&](double m) { return div_mid(m * (b - m) * x, (a + 2.0 * m - 1.0) * (a + 2.0 * m)); };              // d_{2m}
     double f = 1.0, C = 1.0, D = 0.0;
-    for (int j = 1; j <= 100000; ++j) {
-        double dj;
-        if (j & 1) {
-            const double m = (double)((j - 1) / 2);
-            dj = -(a + m) * (a + b + m) * x / ((a + 2.0 * m) * (a + 2.0 * m + 1.0));
-        } else {
-            const double m = (double)(j / 2);
-            dj = m * (b - m) * x / ((a + 2.0 * m - 1.0) * (a + 2.0 * m));
-        }
+    auto step = [&](double dj) {
         D = 1.0 + dj * D;
         if (fabs(D) < tiny) D = tiny;
-        C = 1.0 + dj / C;
+        C = 1.0 + div_mid(dj, C);
         if (fabs(C) < tiny) C = tiny;
-        D = 1.0 / D;
+        D = div_mid(1.0, D);
         const double delta = C * D;
         f *= delta;
-        if (fabs(delta - 1.0) < eps) break;
+        return fabs(delta - 1.0) < eps;
+    };
+    double m = 0.0, d1 = odd(0.0), d2 = even(1.0);
+    for (int j = 0; j < 50000; ++j) {
+        const double n1 = odd(m + 1.0), n2 = even(m + 2.0);
+        const bool last = step(d1);
+        const double f1 = f;
+        if (step(d2) || last) {
+            if (last) f = f1;
+            break;
+        }
+        d1 = n1;
+        d2 = n2;
+        m += 1.0;
     }
     return 1.0 / f;
 }
 
 // Upper tail Q(x) = 1 - I_x(a, b) given lb = log B(a, b): the fraction is evaluated on the
 // side where it converges fast (x < (a+1)/(a+b+2) for I_x(a,b), else I_{1-x}(b,a) directly).
-__device__ double ibeta_upper(double a, double b, double x, double lb) {
+__device__ __forceinline__ double ibeta_upper(double a, double b, double x, double lb) {
     if (x <= 0.0) return 1.0;
     if (x >= 1.0) return 0.0;
     const double lf = a * log(x) + b * log1p(-x) - lb;
-    if (x < (a + 1.0) / (a + b + 2.0)) return 1.0 - exp(lf) / a * beta_cf(a, b, x);
-    return exp(lf) / b * beta_cf(b, a, 1.0 - x);
+    const bool left = x < (a + 1.0) / (a + b + 2.0);   // (one fraction for both sides: lanes differ)
+    const double cf = beta_cf(left ? a : b, left ? b : a, left ? x : 1.0 - x);
+    return left ? 1.0 - exp(lf) / a * cf : exp(lf) / b * cf;
 }
 
 // Clopper-Pearson (1 - delta) upper bound: the x with P(Binom(N, x) <= R) = Q(x; R+1, N-R) = delta.
@@ -79,7 +95,7 @@ __device__ double ibeta_upper(double a, double b, double x, double lb) {
 // mean + z sd (z = upper delta quantile of N(0,1), from the host) and take Halley steps on
 // h(x) = log Q(x) - log delta inside a bisection bracket:  h' = -r, h'' = -r (g + r) with
 // r = density / Q and g = (a-1)/x - (b-1)/(1-x) the log-derivative of the density.
-__device__ double cp_upper(int R, int N, double delta, double z) {
+__device__ __forceinline__ double cp_upper(int R, int N, double delta, double z) {
     if (R >= N) return 1.0;
     if (R == 0) return -expm1(log(delta) / (double)N);
     const double a = (double)R + 1.0, b = (double)(N - R);
@@ -157,12 +173,11 @@ struct TileGeom {
     double A0;
     // general form with shared terms: the vertices' displacement along arm a takes at most SHU
     // distinct values uv[a * SHU + .] (the pieces of a box cut at the null boundaries of the
-    // grids here keep two: the box's own faces), and bit a of vidx[j] picks vertex j's value;
-    // each arm's log-partition term is then evaluated once per distinct value instead of once
-    // per vertex
+    // grids here keep two: the box's own faces); each arm's log-partition term is then evaluated
+    // once per distinct value instead of once per vertex
     bool shared;
     const double *uv;
-    const uint8_t *vidx;
+    const double *cpsi1;      // psi(theta, v, 1) per combination of values (bit a: arm a's second), +inf where no vertex
 };
 
 // log-partition term of one arm at natural parameter x (without the patient count)
@@ -195,13 +210,21 @@ __device__ double max_tilt_term(const TileGeom<D> &T, double q) {
         for (int a = 0; a < D; ++a)
 #pragma unroll
             for (int c = 0; c < SHU; ++c) sp[a][c] = arm_term<FAM>(T.th[a] + q * T.uv[a * SHU + c]);
-        for (int j = 0; j < T.nv; ++j) {
-            const uint32_t code = T.vidx[j];
-            double sum = 0.0;   // the same terms in the same order as part()
+        // every combination, whether a vertex or not: the same terms in the same order as part(), sums of
+        // the first arms shared (28 additions for 16 combinations of four arms)
+        double sum[1 << D];
+        sum[0] = 0.0;
 #pragma unroll
-            for (int a = 0; a < D; ++a) sum += ((code >> a) & 1u) ? sp[a][1] : sp[a][0];
-            const double psiq = ((FAM == FAM_NORMAL) ? sum : (double)T.n * sum) - T.A0;
-            w = fmax(w, psiq * iq - T.psi1[j]);
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+            for (int c = (1 << a) - 1; c >= 0; --c) {
+                sum[c | (1 << a)] = sum[c] + sp[a][1];
+                sum[c] = sum[c] + sp[a][0];
+            }
+#pragma unroll
+        for (int c = 0; c < (1 << D); ++c) {
+            const double psiq = ((FAM == FAM_NORMAL) ? sum[c] : (double)T.n * sum[c]) - T.A0;
+            w = fmax(w, psiq * iq - T.cpsi1[c]);
         }
         return w;
     }
@@ -226,8 +249,8 @@ __device__ double objective(const TileGeom<D> &T, double loga, double s) {
 // theta, so log U ~ (1 - 1/q) L + (q - 1) sigma^2 / 2 (sigma^2 the largest v'H v over the
 // vertices), least at q = sqrt(2 |L| / sigma^2); returns log(q - 1), or NaN when the expansion
 // gives no point.  The same point serves the inverse (its optimum differs at higher order).
-template <int FAM, int D>
-__device__ double start_s(const TileGeom<D> &T, double L) {
+template <int LANES, int FAM, int D>
+__device__ double start_s(int lane, const TileGeom<D> &T, double L) {   // the tile's lanes share its vertices
     double h[D];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
@@ -243,12 +266,14 @@ __device__ double start_s(const TileGeom<D> &T, double L) {
 #pragma unroll
         for (int a = 0; a < D; ++a) s2 += T.r[a] * T.r[a] * h[a];
     } else {
-        for (int j = 0; j < T.nv; ++j) {
+        for (int j = lane; j < T.nv; j += LANES) {
             double t = 0.0;
 #pragma unroll
             for (int a = 0; a < D; ++a) t += T.V[j * D + a] * T.V[j * D + a] * h[a];
             s2 = fmax(s2, t);
         }
+#pragma unroll
+        for (int m = 1; m < LANES; m <<= 1) s2 = fmax(s2, __shfl_xor(s2, m));
     }
     if (!(s2 > 0.0) || !(L < 0.0)) return NAN;
     const double q = sqrt(-2.0 * L / s2);
@@ -264,7 +289,7 @@ __device__ double section_search(int lane, const TileGeom<D> &T, double loga, do
     // a first round on s0 +- 1 around the expansion's optimum: when its best point is interior
     // the optimum lies in the two intervals around it (unimodal objective) and 9 more rounds
     // reach the full search's bracket width (0.44 (2/9)^9 < 60 (2/9)^12); else the full search
-    const double s0 = start_s<FAM, D>(T, loga);   // the same in every lane of the tile
+    const double s0 = start_s<GB, FAM, D>(lane, T, loga);   // the same in every lane of the tile
     if (s0 > -29.0 && s0 < 29.0) {
         const double l0 = s0 - 1.0, h = 2.0 / (double)(GB + 1);
         double f = sg * objective<FAM, D, INV>(T, loga, l0 + (lane + 1) * h);
@@ -340,7 +365,7 @@ __device__ double brent_search(const TileGeom<D> &T, double loga, double *s_best
     // lies within s0 +- 1 (the objective is unimodal), else on the side of the lower end; the
     // search then starts from those points with a parabolic step.  The start changes the work,
     // not the optimum found (to BRENT_TOL).
-    const double s0 = start_s<FAM, D>(T, loga);
+    const double s0 = start_s<1, FAM, D>(0, T, loga);
     bool seeded = false;
     if (s0 > -29.0 && s0 < 29.0) {
         const double sl = s0 - 1.0, sh = s0 + 1.0;
@@ -439,6 +464,12 @@ __device__ __forceinline__ double search(int lane, const TileGeom<D> &T, double 
 
 __global__ void k_negate1(double *x) { x[0] = -x[0]; }
 
+// Bound by its float64 instructions (58% of the issue slots at 60,112 four-arm tiles, the rest latency),
+// so a wave holds tiles of one kind where it can (order: whole boxes, then pieces by vertex count; a wave
+// that holds both runs both forms), the pieces' vertices are combinations of two values per arm, summed
+// once per combination, and the lanes of a tile share the set-up of its vertices.  Inversion of 16^4
+// four-arm boxes 275 -> 125 us, of 5^4 53 -> 33 us; the evaluations and so the results are the same.
+//
 // mode 0: validate (CP then tilt), mode 1: invert (alpha', k), mode 2: tilt of given a,
 // mode 3: lower validation bound (Remark 2: the tilt of 1 - cp_lower = cp_upper(N - R), then
 // lower = 1 - that; cp_out receives cp_lower).
@@ -447,10 +478,11 @@ __global__ void k_negate1(double *x) { x[0] = -x[0]; }
 // sized for mv vertices (the launch's largest tile), bound_lds_bytes: sized for the 64-vertex
 // maximum, one-lane blocks would hold 38 KB each and a CU would fit only one wave per SIMD.
 static size_t bound_lds_bytes(int d, int tpb, int mv) {
-    return (size_t)tpb * ((size_t)mv * sizeof(double) + (size_t)d * SHU * sizeof(double) + (size_t)mv);
+    return (size_t)tpb * ((size_t)mv + ((size_t)1 << d) + (size_t)d * SHU) * sizeof(double);
 }
 template <int FAM, int D, int L>
 __global__ __launch_bounds__(L == 1 ? 64 : 256) void k_bound(int mode, int n, int64_t n_tiles, int mv,
+                                               const int32_t *__restrict__ order,
                                                const double *__restrict__ theta,
                                                const int32_t *__restrict__ vert_off,
                                                const double *__restrict__ verts,
@@ -470,12 +502,12 @@ __global__ __launch_bounds__(L == 1 ? 64 : 256) void k_bound(int mode, int n, in
     extern __shared__ double s_dyn[];
     double *s_psi1 = s_dyn;                                          // [TPB][mv]
     double *s_uv = s_dyn + (size_t)TPB * mv;                         // [TPB][D * SHU]
-    uint8_t *s_vidx = reinterpret_cast<uint8_t *>(s_uv + TPB * D * SHU);   // [TPB][mv]
+    double *s_cpsi1 = s_uv + TPB * D * SHU;                          // [TPB][1 << D]
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x % L, grp = threadIdx.x / L;
-    int64_t t = gid / L;
-    const bool valid = t < n_tiles;
-    if (!valid) t = n_tiles - 1;   // idle groups shadow the last tile and write nothing
+    const bool valid = gid / L < n_tiles;
+    const int64_t i = valid ? gid / L : n_tiles - 1;   // idle groups shadow the last tile and write nothing
+    const int64_t t = order ? order[i] : i;
     TileGeom<D> T;
     T.n = n;
     T.box = is_box[t] != 0;
@@ -498,35 +530,47 @@ __global__ __launch_bounds__(L == 1 ? 64 : 256) void k_bound(int mode, int n, in
     }
     T.shared = false;
     if (!T.box) {
-        for (int j = lane; j < T.nv; j += L) s_psi1[grp * mv + j] = part<FAM, D>(n, T.th, 1.0, T.V + j * D) - T.A0;
-        // distinct displacement values per arm, in order of first appearance (every lane of the
-        // group finds the same ones); an arm with one value repeats it in the second slot
-        bool shared = true;
+        // the displacement values of each arm: v0 the first vertex's, v1 another one's; shared if there
+        // are no more.  The tile's lanes share the vertices; every lane finds the same values.
         double v0[D], v1[D];
-        bool two[D];
 #pragma unroll
-        for (int a = 0; a < D; ++a) {
-            v0[a] = T.V[a];
-            v1[a] = v0[a];
-            two[a] = false;
-        }
-        for (int j = 0; j < T.nv; ++j) {
+        for (int a = 0; a < D; ++a) v1[a] = v0[a] = T.V[a];
+        for (int j = lane; j < T.nv; j += L)
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+                const double x = T.V[j * D + a];
+                if (x != v0[a]) v1[a] = x;
+            }
+#pragma unroll
+        for (int m = 1; m < L; m <<= 1)
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+                const double o = __shfl_xor(v1[a], m);
+                // (of two other values the lower lane's: all lanes end with one)
+                if (o != v0[a] && (v1[a] == v0[a] || (lane & m))) v1[a] = o;
+            }
+        double *cp = s_cpsi1 + grp * (1 << D);
+        for (int c = lane; c < (1 << D); c += L) cp[c] = INFINITY;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        bool shared = true;
+        for (int j = lane; j < T.nv; j += L) {
+            const double psi1 = part<FAM, D>(n, T.th, 1.0, T.V + j * D) - T.A0;
             uint32_t code = 0u;
 #pragma unroll
             for (int a = 0; a < D; ++a) {
                 const double x = T.V[j * D + a];
                 if (x != v0[a]) {
-                    if (!two[a]) {
-                        v1[a] = x;
-                        two[a] = true;
-                    } else if (x != v1[a]) {
-                        shared = false;
-                    }
                     code |= 1u << a;
+                    shared = shared && x == v1[a];
                 }
             }
-            if (j % L == lane) s_vidx[grp * mv + j] = (uint8_t)code;
+            s_psi1[grp * mv + j] = psi1;
+            cp[code] = psi1;   // vertices of one combination are one point
         }
+#pragma unroll
+        for (int m = 1; m < L; m <<= 1) shared = __shfl_xor((int)shared, m) && shared;
         if (lane == 0)
 #pragma unroll
             for (int a = 0; a < D; ++a) {
@@ -537,7 +581,7 @@ __global__ __launch_bounds__(L == 1 ? 64 : 256) void k_bound(int mode, int n, in
     }
     __syncthreads();
     T.psi1 = s_psi1 + grp * mv;
-    T.vidx = s_vidx + grp * mv;
+    T.cpsi1 = s_cpsi1 + grp * (1 << D);
     T.uv = s_uv + grp * D * SHU;
 
     if (mode == 1) {
@@ -740,8 +784,22 @@ hipError_t launch_confset(const Platten &P, const double *s_obs, int64_t s_strid
     return hipGetLastError();
 }
 
-// Clopper-Pearson once per (N class, R) present in this call: mark, then solve marked entries.
-// flip: mark N - R instead (the lower bound, cp_lower(R) = 1 - cp_upper(N - R)).
+// Clopper-Pearson of the (N class, R) present in this call.  Up to CP_DIRECT tiles, each
+// tile solves its own (equal ones write one value twice); above, present ones are marked and each is
+// solved once.  One wave per SIMD takes 65,536 tiles, and their time is one entry's: 33 k tiles 44 us
+// against 5 + 5 + 46 us for clearing, marking and solving, 60 k tiles 50 us; 2^19 tiles take 5 + 21 + 104 us
+// marked.  Latency of a chain of divisions, 35 pairs of fraction terms times four iterations (64 tiles:
+// 29 us, 41 us term by term).  flip: N - R instead (the lower bound, cp_lower(R) = 1 - cp_upper(N - R)).
+constexpr int64_t CP_DIRECT = 65536;
+__global__ void k_cp_tiles(int64_t n_tiles, const uint32_t *__restrict__ R, const int32_t *__restrict__ N,
+                           const int64_t *__restrict__ cp_base, bool flip, double delta, double zq,
+                           double *__restrict__ tbl) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n_tiles) return;
+    const uint32_t n = (uint32_t)N[t], r = min(R[t], n), e = flip ? n - r : r;
+    tbl[cp_base[t] + e] = cp_upper((int)e, (int)n, delta, zq);
+}
+
 __global__ void k_cp_mark(int64_t n_tiles, const uint32_t *__restrict__ R, const int32_t *__restrict__ N,
                           const int64_t *__restrict__ cp_base, bool flip, uint32_t *__restrict__ mark) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -778,13 +836,18 @@ hipError_t launch_bound(const Platten &P, int mode, const uint32_t *R, const dou
                         double level, double *out, double *q_out, int32_t *k_out, double *cp_out,
                         hipStream_t st) {
     if (mode == 0 || mode == 3) {
-        hipError_t e = launch_zero(P.d_cp_mark, (size_t)P.n_cp * sizeof(uint32_t), st);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_cp_mark, dim3((uint32_t)((P.n_tiles + 255) / 256)), dim3(256), 0, st,
-                           P.n_tiles, R, P.d_N, P.d_cp_base, mode == 3, P.d_cp_mark);
         const double zq = normal_upper_quantile(level);
-        hipLaunchKernelGGL(k_cp_table, dim3((uint32_t)((P.max_cls_N + 1 + 63) / 64), (uint32_t)P.n_cls),
-                           dim3(64), 0, st, P.d_cls_N, P.d_cls_off, P.d_cp_mark, level, zq, P.d_cp_tbl);
+        if (P.n_tiles <= CP_DIRECT) {
+            hipLaunchKernelGGL(k_cp_tiles, dim3((uint32_t)((P.n_tiles + 63) / 64)), dim3(64), 0, st, P.n_tiles, R, P.d_N,
+                               P.d_cp_base, mode == 3, level, zq, P.d_cp_tbl);
+        } else {
+            hipError_t e = launch_zero(P.d_cp_mark, (size_t)P.n_cp * sizeof(uint32_t), st);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(k_cp_mark, dim3((uint32_t)((P.n_tiles + 255) / 256)), dim3(256), 0, st,
+                               P.n_tiles, R, P.d_N, P.d_cp_base, mode == 3, P.d_cp_mark);
+            hipLaunchKernelGGL(k_cp_table, dim3((uint32_t)((P.max_cls_N + 1 + 63) / 64), (uint32_t)P.n_cls),
+                               dim3(64), 0, st, P.d_cls_N, P.d_cls_off, P.d_cp_mark, level, zq, P.d_cp_tbl);
+        }
     }
     // enough tiles to give every SIMD work with one lane per tile: Brent's search (fewer
     // evaluations); otherwise GB lanes per tile shorten each tile's chain of evaluations
@@ -798,12 +861,12 @@ hipError_t launch_bound(const Platten &P, int mode, const uint32_t *R, const dou
         if (one_lane)                                                                                   \
             hipLaunchKernelGGL((k_bound<FAM, D, 1>), dim3((uint32_t)grid), dim3(bs),                     \
                                bound_lds_bytes(D, 64, mv), st,      mode, P.n_per_arm,                  \
-                               P.n_tiles, mv, P.d_theta, P.d_vert_off, P.d_verts, P.d_radii, P.d_is_box, P.d_N, R, \
+                               P.n_tiles, mv, P.d_border, P.d_theta, P.d_vert_off, P.d_verts, P.d_radii, P.d_is_box, P.d_N, R, \
                                a_in, level, P.d_cp_tbl, P.d_cp_base, out, q_out, k_out, cp_out);          \
         else                                                                                            \
             hipLaunchKernelGGL((k_bound<FAM, D, GB>), dim3((uint32_t)grid), dim3(bs),                   \
                                bound_lds_bytes(D, 256 / GB, mv), st,      mode, P.n_per_arm,            \
-                               P.n_tiles, mv, P.d_theta, P.d_vert_off, P.d_verts, P.d_radii, P.d_is_box, P.d_N, R, \
+                               P.n_tiles, mv, P.d_border, P.d_theta, P.d_vert_off, P.d_verts, P.d_radii, P.d_is_box, P.d_N, R, \
                                a_in, level, P.d_cp_tbl, P.d_cp_base, out, q_out, k_out, cp_out);          \
     } while (0)
     if (P.family == FAM_NORMAL && P.d == 1)

@@ -1111,6 +1111,18 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
     stage.add(&P->d_verts, P->verts.data(), P->verts.size());
     stage.add(&P->d_radii, P->tile_radii.data(), P->tile_radii.size());
     stage.add(&P->d_is_box, P->tile_is_box.data(), P->tile_is_box.size());
+    // order of the tiles in the bound's search: whole boxes, then pieces by their vertices (a wave takes as
+    // long as its longest tile, and both forms where it holds both); as they are where all are of one kind
+    if (std::find(P->tile_is_box.begin(), P->tile_is_box.end(), 1) != P->tile_is_box.end() &&
+        std::find(P->tile_is_box.begin(), P->tile_is_box.end(), 0) != P->tile_is_box.end()) {
+        auto cls = [&](int64_t t) { return P->tile_is_box[t] ? 0 : 1 + std::min<int32_t>(P->vert_off[t + 1] - P->vert_off[t], 255); };
+        std::vector<int64_t> at(258, 0);
+        for (int64_t t = 0; t < P->n_tiles; ++t) ++at[cls(t) + 1];
+        for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+        P->border.resize(P->n_tiles);
+        for (int64_t t = 0; t < P->n_tiles; ++t) P->border[at[cls(t)]++] = (int32_t)t;
+        stage.add(&P->d_border, P->border.data(), P->border.size());
+    }
     stage.add(&P->d_in_null, P->tile_in_null.data(), P->tile_in_null.size());
     if (kind != CSE_BINOM2_Z) {
         stage.add(&P->d_key_off, key_off.data(), key_off.size());
@@ -1389,7 +1401,7 @@ void free_platten(Platten *P) {
                     P->d_S_group, P->d_keys, P->d_Rw,      P->d_Tw,     P->d_Zw,
                     P->d_apw,    P->d_kw,    P->d_lamw,    P->d_lamg,   P->d_cls_N,
                     P->d_cls_off, P->d_cp_base, P->d_cp_mark, P->d_cp_tbl,  P->d_radii,
-                    P->d_is_box, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
+                    P->d_is_box, P->d_border, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
                     P->d_queue,  P->d_p23mem, P->d_p23row, P->d_p23tilerow, P->d_p23counts, P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
                     P->d_h4run, P->d_h4runitem, P->d_h4bits, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
                     P->d_grp4, P->d_h4rows, P->d_h4set, P->d_h4item, P->d_b4tab, P->d_h4u, P->d_h4eq, P->d_h4at, P->d_h4cnt, P->d_h4fb, P->d_h4plane};
