@@ -325,7 +325,7 @@ def cse_autotune(h, seed=0, max_trials=1 << 24, stream=None):
 
 CSE_OPT_B2_MARGIN = 1   # 2-arm calibration: bracket margin (standard deviations of the count)
 CSE_OPT_H4_MARGIN = 2   # 4-arm calibration: margin of the candidates' bound (standard deviations of the pilot rank)
-CSE_OPT_H4_BRACKET = 3   # accepted and without effect: candidate keys are used where they are few
+CSE_OPT_H4_BRACKET = 3   # 4-arm calibration: candidate keys at any size (1) or where that is faster (0)
 
 
 def cse_platten_set_option(h, option, value):

@@ -264,10 +264,14 @@ int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alph
                    double *tile_bound, hipStream_t st, bool full_keys = false) {
     double *ap = alpha_prime ? alpha_prime : P.d_apw;
     // 4-arm designs: candidate keys where a tile's candidates stay few (alpha' <= alpha, so k is at most
-    // (N + 1) alpha), unless every key is asked for (the randomised tie-break reads them); beyond,
-    // every key and the two-sided bracket of the f32 selection
+    // (N + 1) alpha) and the keys many, unless every key is asked for (the randomised tie-break reads
+    // them); else every key and the two-sided bracket of the f32 selection.  Candidates cost a pilot, which
+    // waits for k: with every key, 9.6 to 39 million keys take 0.90 to 1.10 of the time with candidates, 73
+    // million 1.31, 2 billion twice the time, and fewer than 9 million 0.62 to 0.95; tiles of fewer
+    // simulations than a pilot keep every key anyway (0.78 to 0.93)
     const bool h4c = (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys &&
-                     alpha <= cse::H4_CAND_ALPHA && alpha * ((double)P.max_N + 1.0) <= cse::H4_CAND_K;
+                     alpha <= cse::H4_CAND_ALPHA && alpha * ((double)P.max_N + 1.0) <= cse::H4_CAND_K &&
+                     (P.h4_candidates || (P.max_N >= cse::H4_PILOT_MIN_N && P.n_keys >= cse::H4_CAND_KEYS));
     int32_t *kk = k ? k : P.d_kw;
     double *lam = lambda_tile ? lambda_tile : P.d_lamw;
     // The step's dependencies: alpha' -> k -> selection; simulation -> selection, finish and
@@ -856,6 +860,7 @@ int cse_platten_set_option(cse_platten *p, int32_t option, double value) {
             set_error("cse_platten_set_option: CSE_OPT_H4_BRACKET takes 0 or 1");
             return CSE_EINVAL;
         }
+        p->P.h4_candidates = value != 0.0;
         return CSE_OK;
     }
     if (option != CSE_OPT_B2_MARGIN && option != CSE_OPT_H4_MARGIN) {

@@ -149,7 +149,7 @@ hipError_t launch_h4_planes(const float4 *tbl, int nb, float *planes, hipStream_
 // counts; per simulation the table offset is one packed 16-bit dot product.  A calibration stores
 // only candidate keys (k_h4_pilot).
 // Bound by the gathers' addresses (40 cache lines looked up per instruction).  16^4 boxes x 32,768
-// simulations, 4-arm calibration: counts 0.012, pilot 0.18, tiles 2.13 ms (4.40 with Philox words
+// simulations, 4-arm calibration: counts 0.012, pilot 0.155, tiles 2.13 ms (4.40 with Philox words
 // and counts per batch of 64 boxes, lane = simulation, and 7.9 GB of keys stored) and the selection
 // 1.52 -> 0.77 ms.  Rows of 36 or 64 floats instead of 4 x 8 tiles: 2.33 and 2.22 ms.
 //
@@ -304,6 +304,7 @@ __global__ __launch_bounds__(WG) void k_h4_pilot(const H4Set *__restrict__ sets,
     __shared__ uint32_t hist[H4P_BINS * WAVE / 2];   // 16-bit counts, two lanes per word
     __shared__ uint2 range[WAVE];                    // per tile: the keys' bits [x, y) being divided
     __shared__ uint32_t more;
+    __shared__ float part[NWV][WAVE];                // keys per segment of the bins
     const int lane = threadIdx.x & (WAVE - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const H4Set *__restrict__ S = sets + blockIdx.x;
@@ -364,13 +365,29 @@ __global__ __launch_bounds__(WG) void k_h4_pilot(const H4Set *__restrict__ sets,
             }
         }
         __syncthreads();
+        // each wave sums a segment of the bins per tile, wave 0 finds the segment and then the bin (one walk
+        // over 337 bins: 180 us at 16^4 boxes, 155 so)
+        const int nb = pass == 0 ? H4P_BINS : 256, seg = (nb + NWV - 1) / NWV;
+        auto bin = [&](int b) { return (float)((hist[b * (WAVE / 2) + (lane >> 1)] >> (16 * (lane & 1))) & 0xFFFFu); };
+        {
+            float c = 0.0f;   // whole numbers below 2^24: exact in any order
+            const int e = min(nb, (wv + 1) * seg);
+#pragma unroll 4
+            for (int b = wv * seg; b < e; ++b) c += bin(b);
+            part[wv][lane] = c;
+        }
+        __syncthreads();
         if (open) {
             float run = below;
             int b = 0;
-            const int nb = pass == 0 ? H4P_BINS : 256;
+            for (int w = 0; w < NWV && run + part[w][lane] < rank; ++w) {
+                run += part[w][lane];
+                b += seg;
+            }
+            b = min(b, nb);
             float c = 0.0f;
             for (; b < nb; ++b) {
-                c = (float)((hist[b * (WAVE / 2) + (lane >> 1)] >> (16 * (lane & 1))) & 0xFFFFu);
+                c = bin(b);
                 if (run + c >= rank) break;
                 run += c;
             }
