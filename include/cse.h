@@ -459,7 +459,7 @@ int cse_work_counters(const cse_platten *p, int64_t out[4], void *stream);
  *        alpha <= 0.05 the calibration can keep candidate keys alone (a pilot over the first
  *        simulations, a sixteenth of them, 256 to 2,048, bounds each tile's k-th key from above;
  *        the pass over all simulations keeps the keys below the bound).  0 (default): where that
- *        is faster, from 2^20 * 48 keys and 1,024 simulations on; 1: at any size.  Otherwise, and
+ *        is faster, from 2^26 keys and 1,024 simulations on; 1: at any size.  Otherwise, and
  *        always in cse_calibrate_tiebreak, it keeps every float32 key.  Same results either way.
  *   CSE_OPT_H4_MARGIN (the calibration from candidates): the bound's margin in standard
  *        deviations of the pilot rank (default 6).  Results do not depend on it: a tile whose k-th

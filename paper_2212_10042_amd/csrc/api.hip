@@ -266,9 +266,9 @@ int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alph
     // 4-arm designs: candidate keys where a tile's candidates stay few (alpha' <= alpha, so k is at most
     // (N + 1) alpha) and the keys many, unless every key is asked for (the randomised tie-break reads
     // them); else every key and the two-sided bracket of the f32 selection.  Candidates cost a pilot, which
-    // waits for k: with every key, 9.6 to 39 million keys take 0.90 to 1.10 of the time with candidates, 73
-    // million 1.31, 2 billion twice the time, and fewer than 9 million 0.62 to 0.95; tiles of fewer
-    // simulations than a pilot keep every key anyway (0.78 to 0.93)
+    // waits for k: with every key, up to 64 million keys take 0.71 to 1.13 of the time with candidates, 73
+    // to 150 million 0.91 to 1.4, 700 million 1.7 (hier4 and basket, 5^4 to 12^4 boxes x 3,000 to 33,000);
+    // tiles of fewer simulations than a pilot keep every key anyway (0.78 to 0.93)
     const bool h4c = (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys &&
                      alpha <= cse::H4_CAND_ALPHA && alpha * ((double)P.max_N + 1.0) <= cse::H4_CAND_K &&
                      (P.h4_candidates || (P.max_N >= cse::H4_PILOT_MIN_N && P.n_keys >= cse::H4_CAND_KEYS));

@@ -138,7 +138,7 @@ constexpr int H4_PILOT_MIN_N = 1024;     // fewer simulations: every key is kept
 constexpr int H4_PILOT_MAX = 2048;
 constexpr int H4_CAND_MAX = 3072;        // candidates selected from LDS (more: exact path)
 constexpr double H4_CAND_K = 832.0;      // largest (max N + 1) * alpha that takes candidates
-constexpr int64_t H4_CAND_KEYS = (int64_t)48 << 20;   // keys of the platten from which candidates are kept
+constexpr int64_t H4_CAND_KEYS = (int64_t)64 << 20;   // keys of the platten from which candidates are kept
 constexpr double H4_CAND_ALPHA = 0.05;   // and largest alpha
 // candidate slots of a tile per slice of `slice` granules (a pilot leaves an eighth of the keys at most;
 // a set's slots fit its keys' place in the workspace)

@@ -452,7 +452,7 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
     const float look = fmaxf(cut, bound >= 0.0f && bound < INFINITY ? __uint_as_float(__float_as_uint(bound) + 1u) : bound);
     uint32_t ncand = 0u, neq = 0u, cap = 0u;
     float *__restrict__ kp = keys;
-    if (!CAND) kp = keys + S->key_base + (int64_t)lane * WAVE;
+    if (!CAND) kp = keys + S->key_base;
     if (CAND) {
         cap = (uint32_t)h4_cap(N, S->slice);
         kp = keys + S->key_base + ((int64_t)lane * S->n_slices + I->slice) * cap;
@@ -493,11 +493,22 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
             for (int j = 0; j < 4; ++j)
                 v[4 * q + j] = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(planes) + off[j]);
         }
-        if (!CAND && t >= 0) {
-            float *__restrict__ kc = kp + (int64_t)(g / 4) * kstride + (g % 4) * GRAN2;
+        if (!CAND) {
+            // 16 keys of each of 64 tiles, through LDS: four lanes store a tile's 64 bytes (a lane's own 16 keys
+            // in four stores of 16 bytes, each to a line of its own: 5.4 ms where this takes 3.8)
+            uint4 *__restrict__ tr = h4_lds + (size_t)(WG / WAVE) * max_rows * H4_ROW_LDS + (size_t)wv * WAVE * H4_ROW_LDS;
+            wave_sync4();
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4 *>(kc + 4 * q) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+                tr[lane * H4_ROW_LDS + q] = make_uint4(__float_as_uint(v[4 * q]), __float_as_uint(v[4 * q + 1]),
+                                                       __float_as_uint(v[4 * q + 2]), __float_as_uint(v[4 * q + 3]));
+            wave_sync4();
+            float *__restrict__ kc = kp + (int64_t)(g / 4) * kstride + (g % 4) * GRAN2;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int l = 16 * r + (lane >> 2);
+                if (l < S->n_lanes) *reinterpret_cast<uint4 *>(kc + l * WAVE + 4 * (lane & 3)) = tr[l * H4_ROW_LDS + (lane & 3)];
+            }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -660,7 +671,7 @@ hipError_t launch_hier4(const Platten &P, uint64_t seed, uint32_t *R, unsigned l
     const dim3 grid((uint32_t)((P.n_h4item + WG / WAVE - 1) / (WG / WAVE)));
     const size_t lds = (size_t)(WG / WAVE) * P.h4_max_rows * H4_ROW_LDS * sizeof(uint4);
 #define CSE_H4_LAUNCH(M, SC)                                                                                          \
-    hipLaunchKernelGGL((k_h4_tiles<M, SC>), grid, dim3(WG), lds, st, P.d_h4set, P.d_h4item, P.n_h4item, P.d_h4rows,     \
+    hipLaunchKernelGGL((k_h4_tiles<M, SC>), grid, dim3(WG), (M) ? lds : lds + (size_t)WG * H4_ROW_LDS * sizeof(uint4), st, P.d_h4set, P.d_h4item, P.n_h4item, P.d_h4rows,     \
                        P.h4_max_rows, P.d_b4tab, wb,                                                                  \
                        we, P.d_h4plane, cut, R, sumT, keys, P.d_h4u, P.d_h4eq, P.d_h4cnt)
 #define CSE_H4_SC(M)             \
