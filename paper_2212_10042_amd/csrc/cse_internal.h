@@ -304,6 +304,7 @@ struct Platten {
     int64_t b4_units = 0, b4_win = 0;
     uint32_t *d_h4rows = nullptr;        // the sets' row lists
     int32_t h4_max_rows = 0;             // longest of them
+    size_t table_bytes = 0;              // of d_b2tab or d_b4tab
     uint4 *d_b4tab = nullptr;
     float *d_h4u = nullptr;
     uint32_t *d_h4eq = nullptr;

@@ -220,6 +220,43 @@ void give_side_stream(int device, hipStream_t s) {
     (void)hipStreamDestroy(s);
 }
 
+// Count table of the last destroyed platten, per device (one buffer, at most B2_TABLE_MAX bytes and a
+// little), for the next one: adaptive runs create a platten per round, and allocations of tens of MB cost
+// ~190 us each.  A platten is destroyed only after the device has been synchronised.  The buffer is given
+// back when a platten needs a larger one.
+struct TableBuf {
+    void *p = nullptr;
+    size_t bytes = 0;
+};
+std::mutex g_table_mu;
+std::map<int, TableBuf> g_table_cache;
+constexpr size_t TABLE_CACHE_MIN = (size_t)2 << 20;   // smaller allocations are cheap
+
+hipError_t take_table(int device, size_t bytes, TableBuf *t) {
+    if (bytes >= TABLE_CACHE_MIN) {
+        std::lock_guard<std::mutex> g(g_table_mu);
+        TableBuf &c = g_table_cache[device];
+        if (c.bytes >= bytes) {
+            *t = c;
+            c = TableBuf();
+            return hipSuccess;
+        }
+        if (c.p) (void)hipFree(c.p);
+        c = TableBuf();
+    }
+    t->bytes = bytes;
+    return hipMalloc(&t->p, bytes);
+}
+
+void give_table(int device, TableBuf t) {
+    {
+        std::lock_guard<std::mutex> g(g_table_mu);
+        TableBuf &c = g_table_cache[device];
+        if (t.bytes >= TABLE_CACHE_MIN && t.bytes <= (size_t)B2_TABLE_MAX + 4096 && t.bytes > c.bytes) std::swap(c, t);
+    }
+    if (t.p) (void)hipFree(t.p);
+}
+
 // Uploads gathered into one host buffer and copied with a single transfer into a device arena
 // (one synchronous copy per arena instead of one per array: each costs ~15 us of fixed
 // overhead).  The destinations are assigned when the arena is flushed and must not be read
@@ -787,7 +824,12 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         stage.add(&P->d_h4at, at.data(), at.size());
         stage.add(&P->d_h4rows, rows.data(), rows.size());
         // chunks of four granules are read whole: up to three units past a row's end
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_b4tab, (size_t)(P->b4_units + 4) * 16));
+        {
+            TableBuf t;
+            CSE_HIP_TRY(take_table(P->device, (size_t)(P->b4_units + 4) * 16, &t));
+            P->d_b4tab = (uint4 *)t.p;
+            P->table_bytes = t.bytes;
+        }
         CSE_HIP_TRY(hipMalloc((void **)&P->d_h4u, (size_t)P->n_tiles * sizeof(float)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_h4eq, (size_t)P->n_tiles * sizeof(uint32_t)));
 
@@ -1164,7 +1206,10 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
     CSE_HIP_TRY(hipMalloc((void **)&P->d_lamg, sizeof(double)));
     CSE_HIP_TRY(hipMalloc((void **)&P->d_minpart, 2 * MIN_PARTS * sizeof(double)));
     if (kind == CSE_BINOM2_Z) {
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2tab, (size_t)P->b2_units * UNIT2));
+        TableBuf t;
+        CSE_HIP_TRY(take_table(P->device, (size_t)P->b2_units * UNIT2, &t));
+        P->d_b2tab = (uint4 *)t.p;
+        P->table_bytes = t.bytes;
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2cut, (size_t)P->n_blocks * B2U * (NP35 + 1) * sizeof(uint4)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2br, nt * sizeof(int2)));
         CSE_HIP_TRY(hipMalloc((void **)&P->d_b2fb, sizeof(uint32_t)));
@@ -1403,8 +1448,8 @@ void free_platten(Platten *P) {
                     P->d_cls_off, P->d_cp_base, P->d_cp_mark, P->d_cp_tbl,  P->d_radii,
                     P->d_is_box, P->d_border, P->d_key_stride, P->d_h4tbl, P->d_tileT, P->d_cfg,
                     P->d_queue,  P->d_p23mem, P->d_p23row, P->d_p23tilerow, P->d_p23counts, P->d_p23items, P->d_gh, P->d_p23stats, P->d_p23look1, P->d_hnodes,
-                    P->d_h4run, P->d_h4runitem, P->d_h4bits, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_b2tab, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
-                    P->d_grp4, P->d_h4rows, P->d_h4set, P->d_h4item, P->d_b4tab, P->d_h4u, P->d_h4eq, P->d_h4at, P->d_h4cnt, P->d_h4fb, P->d_h4plane};
+                    P->d_h4run, P->d_h4runitem, P->d_h4bits, P->d_S_pos, P->d_b2br, P->d_b2fb, P->d_b2cut, P->d_grp2, P->d_minpart, P->d_gstart, P->d_gcut, P->d_sqitems,
+                    P->d_grp4, P->d_h4rows, P->d_h4set, P->d_h4item, P->d_h4u, P->d_h4eq, P->d_h4at, P->d_h4cnt, P->d_h4fb, P->d_h4plane};
     auto in_arena = [&](void *q) {
         for (auto &a : P->arenas)
             if ((unsigned char *)q >= (unsigned char *)a.first && (unsigned char *)q < (unsigned char *)a.first + a.second)
@@ -1415,6 +1460,9 @@ void free_platten(Platten *P) {
         if (q && !in_arena(q)) (void)hipFree(q);
     for (auto &a : P->arenas) (void)hipFree(a.first);
     P->arenas.clear();
+    for (void *q : {(void *)P->d_b2tab, (void *)P->d_b4tab})
+        if (q) give_table(P->device, {q, P->table_bytes});
+    P->d_b2tab = P->d_b4tab = nullptr;
     for (hipEvent_t e : {P->ev_sim, P->ev_val, P->ev_fork, P->ev_inv})
         if (e) (void)hipEventDestroy(e);
     if (P->side) give_side_stream(P->device, P->side);
