@@ -9,8 +9,8 @@ also measures the 256 x 256 calibration grid and the 4-arm hierarchical calibrat
 
 One step = one call of cse_calibrate with every output requested: the inverted Tilt-Bound
 target alpha'_i and k_i, the fused simulation (Philox common random numbers, draws, design
-statistic, rejection counts at the fixed cut, score sums for the gradient, per-simulation
-calibration records), the order-statistic selection lambda*_i and its count below,
+statistic, rejection counts at the fixed cut, score sums for the gradient, the counts or keys that
+the selection reads), the order-statistic selection lambda*_i and its count below,
 lambda* = min over the tiles in the null space, the gradient, and the Clopper-Pearson +
 Tilt-Bound of every tile.  The basket workload is validation only.  The platten (null clipping,
 vertices, thresholds, batch plan, 4-arm posterior table) is built once before timing and
@@ -36,60 +36,22 @@ sys.path.insert(0, ROOT)
 METRIC = "sim·tiles/s, TIE+gradient+calibration vs plain fwd at equal bound; % roofline"
 VALU_PEAK = 256 * 4 * 64 * 2.4e9 / 4   # lane-ops/s: 256 CUs x 4 SIMDs x one wave64 op per 4 clocks
 
-# Algorithmic integer work per unit (lane-ops), by fused kernel:
-#   2-arm: per (workgroup, simulation) 18 Philox blocks x 10 rounds x (2 32x32->64 products
-#   + 2 xor3), shared by the 16 batches of the group's 4 x 4 square, and the square's 8 sets of
-#   8 thresholds x 35 words x (compare + add), each counted once; per (simulation, tile) decision
-#   (med3), packed multiply-add and its share of the count unpacking (the calibration record is
-#   one 16-byte store per (simulation, batch)).
-B2_PHILOX, B2_COUNT_G, B2_TILE_CAL, B2_TILE_FWD = 18 * 10 * 4, 8 * 8 * 35 * 2, 4, 4
-#   4-arm: per (workgroup, simulation) 35 Philox blocks; per (batch, simulation) 35 words x
-#   (4 + 4 + 2 + 2) thresholds x (compare + add); per (simulation, box) outcome index (3),
-#   table gather (1), 3 compares, mask, 2 accumulates; per (simulation, tile) min + key store
-#   (the score sums add per rejecting simulation only, a few % of the simulations).
-H4_PHILOX, H4_COUNT, H4_BOX, H4_TILE = 35 * 10 * 4, 35 * 12 * 2, 9, 3
-#   basket (the same kernel, one configuration per slot): per (simulation, piece) outcome index
-#   (3), table gather (1), 4 compares, mask, event test, accumulate.
-BK_SLOT = 11
-
-#   Phase II/III: float64 lane-ops of one posterior look (hier_post.hpp), counted by operation
-#   (exp 20, log 30, log1p series 22, erfc 40, reciprocal 5, sqrt 10; the per-node constants
-#   come from a table): per node 400 outside Newton and the normal tails, 200 per Newton step,
-#   104 per arm whose tails a look needs (two erfc); per Phase II look p_best 6,500 + p_success
-#   300 (no tails); per Phase III look one p_success (100) and the selected arm's tails.  The
-#   first look of a trial is a table lookup (no posterior).  Looks and Newton steps are the
-#   kernel's own counters for the launch (cse_work_counters).
-P23_NODE, P23_NEWTON, P23_TAIL, P23_P2_EXTRA, P23_P3_EXTRA = 400, 200, 104, 6800, 100
-
-# HBM bytes per dispatch of the dominant kernel, by workload, from FETCH_SIZE + WRITE_SIZE counter
-# runs (profiles/<workload>_counters.md, scaled by what the counters read for a copy of known
-# size).  Valid only while that kernel is unchanged; workloads not listed report null.
-TRAFFIC = {
-    "binom2_1024_full": 4_388_248_490,   # k_binom2<true>: 17.8 MB read, 4,370.5 MB written (records + sums)
-    "hier4_16": 11_977_047_296,          # k_hier4<1, false, true>: 3,567.7 MB read, 8,409.3 MB written
-    "phase23_c5_sub256": 1_625_325_749,  # k_phase23: 228.7 MB read, 1,396.7 MB written
+# Vector lane-operations (SQ_INSTS_VALU x 64) and HBM bytes (FETCH_SIZE + WRITE_SIZE, scaled by what the
+# counters read for a copy of known size) per launch of the simulation stage, all of its kernels
+# together, by workload: counted, since the kernels skip what a batch's extremes decide and evaluate each
+# distinct state once, which no formula of the sizes tells (profiles/<workload>_counters.md).  Valid only
+# while those kernels are unchanged; workloads not listed report null.
+COUNTED = {   # workload: (vector lane-operations, HBM bytes)
+    "binom2_1024_full": (10_546_026_688, 368_939_610),
+    "binom2_256_tri": (555_885_312, 37_225_411),
+    "hier4_16": (22_016_046_272, 7_293_847_984),
+    "phase23_c5_sub256": (425_107_558_208, 16_032_566_225),
+    "basket4_16": (11_749_568_512, 137_284_247),
 }
 
 DEFAULT = "binom2_1024_full"
 SUB_RECORDS = ("binom2_256_tri", "hier4_16")
 
-
-def b2_method_min_ops(P, w, calibrating):
-    """The 2-arm method's own integer work per launch, each distinct threshold counted once per
-    simulation: per (N class, simulation) 18 Philox blocks and 35 compare-adds at every distinct
-    arm-0 and arm-1 threshold of the class, plus the per-(simulation, tile) decision and accumulate
-    (and record share) -- the count that batching can approach but not go below."""
-    import numpy as np
-
-    th = np.asarray(P.tiles["theta"])
-    sims = np.asarray(w["sims"])[np.asarray(P.tiles["box"])]
-    total = 0
-    for N in np.unique(sims):
-        sel = sims == N
-        u = len(np.unique(th[sel, 0])) + len(np.unique(th[sel, 1]))
-        total += int(N) * (B2_PHILOX + u * 35 * 2) + int(N) * int(sel.sum()) * (B2_TILE_CAL if calibrating
-                                                                                else B2_TILE_FWD)
-    return total
 
 WORKLOADS = {
     "binom2_256_tri": "binom2 n=35 pooled-z, 256x256 boxes on [-3,1]^2 kept to theta1<=theta0 "
@@ -279,7 +241,7 @@ def main():
     ap.add_argument("--b2-margin", type=float, default=None,
                     help="2-arm calibration: the selection's bracket margin in standard deviations (default 5)")
     ap.add_argument("--h4-bracket", action="store_true",
-                    help="4-arm calibration from bracketed keys (pilot + in-bracket candidates) instead of every key")
+                    help="4-arm calibration from candidate keys at any size (by default where that is faster)")
     ap.add_argument("--no-extensions", action="store_true",
                     help="skip the lower-bound, confidence-set and randomised-calibration timings")
     ap.add_argument("--progress", action="store_true",
@@ -422,7 +384,7 @@ def measure(name, w, design, args, full=True):
                   "basket4": "basket4"}[design] + \
         ("_calib" if calibrating else "")
     kern = {}
-    for kn in (sim_kernel, "select", "b2_bracket", "hier4_pilot", "h4_bracket", "bound_invert", "bound_validate"):
+    for kn in (sim_kernel, "select", "b2_bracket", "bound_invert", "bound_validate"):
         cnt, ms = cse.cse_profile_get(kn)
         if cnt:
             kern[kn] = round(ms / cnt, 5)
@@ -512,51 +474,21 @@ def measure(name, w, design, args, full=True):
             print("bench.py: graph replay outputs differ from the eager step", file=sys.stderr)
             sys.exit(1)
 
-    # roofline of the dominant kernel: the fused simulation
-    ops_min = None
-    if design == "binom2":
-        ops = (st["group_sims"] * (B2_PHILOX + B2_COUNT_G)
-               + st["total_sims"] * (B2_TILE_CAL if calibrating else B2_TILE_FWD))
-        ops_min = b2_method_min_ops(P, w, calibrating)
-        kname = f"k_binom2<KEYS={'true' if calibrating else 'false'}>"
-    elif design == "hier4":
-        boxes = np.unique(P.tiles["box"])
-        box_sims = int(np.asarray(w["sims"])[boxes].sum())
-        ops = (st["group_sims"] * H4_PHILOX + st["batch_sims"] * H4_COUNT + box_sims * H4_BOX
-               + st["total_sims"] * H4_TILE)
-        kname = "k_hier4<1, false, true>"
-        if args.h4_bracket:   # the timed kernel is the pass after the 2,048-simulation pilot
-            sims = np.asarray(w["sims"])[boxes].astype(np.int64)
-            ops = ops * float(np.maximum(sims - 2048, 0).sum()) / float(sims.sum())
-            kname = "k_hier4<2, false, true>"
-    elif design == "basket4":
-        ops = st["group_sims"] * H4_PHILOX + st["batch_sims"] * H4_COUNT + st["total_sims"] * BK_SLOT
-        kname = "k_hier4<0, true, true>"
-    elif design == "phase23":
-        wc = cse.cse_work_counters(P.handle)
-        ops = (wc["looks_phase2"] * (90 * P23_NODE + P23_P2_EXTRA)
-               + wc["looks_phase3"] * (90 * (P23_NODE + P23_TAIL) + P23_P3_EXTRA)
-               + wc["newton_steps"] * P23_NEWTON)
-        kname = "k_phase23"
-    else:
-        ops = None
-        kname = "k_ztest1<KEYS=true>"
+    # roofline of the simulation stage
+    kname = {"binom2": "k_b2_count + k_b2_tiles", "hier4": "k_h4_count + k_h4_pilot + k_h4_tiles",
+             "basket4": "k_h4_count + k_h4_runs", "phase23": "k_p23_count + k_p23_open + k_p23_post + k_p23_step",
+             "ztest1": "k_ztest1"}[design]
     k_s = kern.get(sim_kernel, 0.0) * 1e-3
     roof = None
-    if ops is not None and k_s > 0:
+    if name in COUNTED and k_s > 0:
+        ops, traffic = COUNTED[name]
         achieved = ops / k_s
         roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK / 1e12,
                 "unit": "Tops/s (float64 VALU)" if design == "phase23" else "Tops/s (int32 VALU)",
-                "frac": achieved / VALU_PEAK, "traffic": None,
+                "frac": achieved / VALU_PEAK, "traffic": traffic, "traffic_unit": "bytes per launch",
                 "kernel": kname, "kernel_ms": kern[sim_kernel], "ops_per_launch": ops}
         if design == "phase23":
-            roof["work"] = wc
-        if ops_min is not None:
-            roof["ops_method_minimal"] = ops_min
-            roof["frac_method_minimal"] = ops_min / k_s / VALU_PEAK
-        if name in TRAFFIC:
-            roof["traffic"] = TRAFFIC[name]
-            roof["traffic_unit"] = "bytes per launch"
+            roof["work"] = cse.cse_work_counters(P.handle)
 
     # the plain forward-only per-tile path, same tiles, seed and N: identical counts (equal bound)
     plain = None
