@@ -789,8 +789,11 @@ hipError_t launch_confset(const Platten &P, const double *s_obs, int64_t s_strid
 // solved once.  One wave per SIMD takes 65,536 tiles, and their time is one entry's: 33 k tiles 44 us
 // against 5 + 5 + 46 us for clearing, marking and solving, 60 k tiles 50 us; 2^19 tiles take 5 + 21 + 104 us
 // marked.  Latency of a chain of divisions, 35 pairs of fraction terms times four iterations (64 tiles:
-// 29 us, 41 us term by term).  flip: N - R instead (the lower bound, cp_lower(R) = 1 - cp_upper(N - R)).
-constexpr int64_t CP_DIRECT = 65536;
+// 29 us, 41 us term by term).  The lower bound's entries lie near N, where the residual's rounding keeps up to
+// 33 iterations going: there a wave of 64 different entries takes longer than one of neighbouring ones
+// (lower bound of 33 k / 60 k / 25 k tiles: 208 / 497 / 298 us per tile, 177 / 460 / 220 us marked; of 4,096
+// tiles 39 and 58 us).  flip: N - R instead (the lower bound, cp_lower(R) = 1 - cp_upper(N - R)).
+constexpr int64_t CP_DIRECT = 65536, CP_DIRECT_LOWER = 8192;
 __global__ void k_cp_tiles(int64_t n_tiles, const uint32_t *__restrict__ R, const int32_t *__restrict__ N,
                            const int64_t *__restrict__ cp_base, bool flip, double delta, double zq,
                            double *__restrict__ tbl) {
@@ -837,7 +840,7 @@ hipError_t launch_bound(const Platten &P, int mode, const uint32_t *R, const dou
                         hipStream_t st) {
     if (mode == 0 || mode == 3) {
         const double zq = normal_upper_quantile(level);
-        if (P.n_tiles <= CP_DIRECT) {
+        if (P.n_tiles <= (mode == 3 ? CP_DIRECT_LOWER : CP_DIRECT)) {
             hipLaunchKernelGGL(k_cp_tiles, dim3((uint32_t)((P.n_tiles + 63) / 64)), dim3(64), 0, st, P.n_tiles, R, P.d_N,
                                P.d_cp_base, mode == 3, level, zq, P.d_cp_tbl);
         } else {
