@@ -151,7 +151,7 @@ hipError_t launch_h4_planes(const float4 *tbl, int nb, float *planes, hipStream_
 // Bound by the gathers' addresses (40 cache lines looked up per instruction).  16^4 boxes x 32,768
 // simulations, 4-arm calibration: counts 0.012, pilot 0.155, tiles 2.13 ms (4.40 with Philox words
 // and counts per batch of 64 boxes, lane = simulation, and 7.9 GB of keys stored) and the selection
-// 1.52 -> 0.77 ms.  Rows of 36 or 64 floats instead of 4 x 8 tiles: 2.33 and 2.22 ms.
+// 1.52 -> 0.56 ms.  Rows of 36 or 64 floats instead of 4 x 8 tiles: 2.33 and 2.22 ms.
 //
 // k_h4_runs (without keys) takes up to 8 tiles per lane that differ in arm 3's threshold alone.
 // ------------------------------------------------------------------------------------------
