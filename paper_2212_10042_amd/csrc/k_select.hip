@@ -211,7 +211,7 @@ __device__ void b2_full_tile(const Recs2 &rb, int n, int32_t k, int s, const dou
             if (__ballot(hit)) {
                 if (hit) {
                     *lam = S_tbl[S_order[p]];
-                    *rej_at = (int32_t)cumx[S_group[p]];
+                    if (rej_at) *rej_at = (int32_t)cumx[S_group[p]];
                 }
                 break;
             }
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(NWV *WAVE) void k_b2_select(
         W = b.y - b.x + 1;
     } else if (my_t >= 0 && wv == 0) {   // outside Theorem 4's range: +-inf, no selection
         lam[my_t] = my_k <= 0 ? -INFINITY : INFINITY;
-        rej_at[my_t] = my_k <= 0 ? 0 : N;
+        if (rej_at) rej_at[my_t] = my_k <= 0 ? 0 : N;
     }
     {
         int x = W;
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(NWV *WAVE) void k_b2_select(
                 const int g = S_group[lo + i] - lo;
                 for (int j = g; j < i; ++j) run -= hist_get(my_h0 + j);
                 lam[my_t] = S_tbl[S_order[lo + i]];
-                rej_at[my_t] = (int32_t)run;
+                if (rej_at) rej_at[my_t] = (int32_t)run;
                 done = true;
             }
         }
@@ -428,7 +428,8 @@ __global__ __launch_bounds__(NWV *WAVE) void k_b2_select(
     for (uint32_t f = 0; f < nf; ++f) {
         const int s = fail[f];
         const int32_t t = B->tile[s];
-        b2_full_tile<NTH>(rb, N, kk[t], s, S_tbl, S_order, S_group, hist, hist + B2_NOUT, &lam[t], &rej_at[t]);
+        b2_full_tile<NTH>(rb, N, kk[t], s, S_tbl, S_order, S_group, hist, hist + B2_NOUT, &lam[t],
+                          rej_at ? &rej_at[t] : nullptr);
     }
 }
 
