@@ -85,6 +85,7 @@ struct Grp4 {
 // distinct count-table rows of the set are listed from row_at on; a lane's four count rows and two
 // code rows (arms 2 and 3) are places in that list.
 constexpr int H4_ROWS = 6;
+constexpr int H4_SET_ROWS = 368;   // distinct rows of a set at most: four waves' rows beside the pilot's histogram in LDS
 struct H4Set {
     int32_t tile[64];
     uint16_t row[H4_ROWS][64];

@@ -287,6 +287,12 @@ struct H4Rows {
 // four waves share the pilot's simulations.
 constexpr int H4P_LOG = 18 * 8, H4P_BINS = H4P_LOG + 192 + 1;
 constexpr uint32_t H4P_BIN0 = (127u - 20u) << 3;
+// LDS of a workgroup of four waves (160 KB): the rows of a set, and the pilot's static arrays (histogram, ranges,
+// segments) or the keys' transposes of the every-key pass; sets of runs hold as many rows as fit without either.
+constexpr int H4_LDS = 160 << 10, H4P_STATIC = H4P_BINS * WAVE / 2 * 4 + WAVE * 8 + WG * 4 + 256;
+static_assert(4 * H4_SET_ROWS * H4_ROW_LDS * 16 + H4P_STATIC <= H4_LDS, "the pilot fits");
+static_assert((4 * H4_SET_ROWS + WG) * H4_ROW_LDS * 16 <= H4_LDS, "the every-key pass fits");
+static_assert(4 * H4_ROWS * WAVE * H4_ROW_LDS * 16 <= H4_LDS, "runs fit");
 __device__ __forceinline__ int h4p_bin(float v) {   // v in [0, 1]
     const int lo = max((int)(__float_as_uint(v) >> 20) - (int)H4P_BIN0, 0);
     const int hi = H4P_LOG - 64 + (int)(v * 256.0f);

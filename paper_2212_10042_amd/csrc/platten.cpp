@@ -718,7 +718,8 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             S.row_at = (int64_t)rows.size();
             S.n_sims = order[i].n;
             S.key_base = P->n_keys;
-            while (S.n_lanes < WAVE && i < order.size() && order[i].n == S.n_sims) {
+            while (S.n_lanes < WAVE && i < order.size() && order[i].n == S.n_sims &&
+                   (int64_t)rows.size() - S.row_at + H4_ROWS <= H4_SET_ROWS) {
                 const At &o = order[i];
                 const int l = S.n_lanes++;
                 S.tile[l] = o.tile;
