@@ -414,7 +414,8 @@ int cse_plan_destroy(cse_plan *plan);
  *                          kernel {512, 1024, 2048} workgroups, timed on a strided sample of
  *                          tiles holding at most max_trials trials.
  * The fastest is kept in the platten.  Results of every later call are unchanged (integer
- * reductions are order-independent and keys are laid out by tile, not by launch shape).
+ * reductions are order-independent, keys are laid out by tile, not by launch shape, and a Phase II/III
+ * posterior is the same bits however many lanes share it).
  * Plans captured on this platten before the call become stale (cse_plan_launch refuses them).
  *   out  host int64 [2]: the chosen value and, for CSE_PHASE23, the grid (else 0).
  * Errors: CSE_EINVAL (NULL out, max_trials < 1), CSE_ENOMEM, CSE_EHIP.

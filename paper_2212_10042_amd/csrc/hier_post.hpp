@@ -36,20 +36,29 @@ constexpr double HP_NEWTON_TOL = 1e-6;
 // Per-node constants (HierNode, cse_internal.h) are computed once on the host.
 
 // 1/d for finite d > 0: hardware reciprocal and two Newton steps (error below one ulp).
-__device__ __forceinline__ double rcp_nr(double d) {
+// (The Phase II/III posterior's functions are compiled for the host too, for its tests: there by division.)
+__host__ __device__ __forceinline__ double rcp_nr(double d) {
+#ifdef __HIP_DEVICE_COMPILE__
     double r = __builtin_amdgcn_rcp(d);
     double e = fma(-d, r, 1.0);
     r = fma(r, e, r);
     e = fma(-d, r, 1.0);
     return fma(r, e, r);
+#else
+    return 1.0 / d;
+#endif
 }
 
 // 1/sqrt(d) for finite d > 0: hardware estimate and two Newton steps (error about one ulp).
-__device__ __forceinline__ double rsq_nr(double d) {
+__host__ __device__ __forceinline__ double rsq_nr(double d) {
+#ifdef __HIP_DEVICE_COMPILE__
     double y = __builtin_amdgcn_rsq(d);
     const double h = 0.5 * d;
     y = fma(y, fma(-h * y, y, 0.5), y);
     return fma(y, fma(-h * y, y, 0.5), y);
+#else
+    return 1.0 / sqrt(d);
+#endif
 }
 
 // expit(x), and with it softplus(x) = max(x, 0) + log1p(exp(-|x|)) from the same exponential.
@@ -70,7 +79,7 @@ __device__ __forceinline__ double hp_expit_softplus(double x, double &sp) {
 // the values here: 1 + e in (1, 2], curvatures in [1e-3, 1e6 + n/4]).  The treatment arms'
 // cofactors are x0 times the product of the other two in ascending arm order, so arms 1..3
 // with equal x get bit-identical results and ties between them stay exact ties.
-__device__ __forceinline__ void rcp4(const double x[4], double r[4]) {
+__host__ __device__ __forceinline__ void rcp4(const double x[4], double r[4]) {
     const double x12 = x[1] * x[2], x13 = x[1] * x[3], x23 = x[2] * x[3];
     const double inv = rcp_nr(x[0] * (x12 * x[3]));
     r[0] = inv * (x12 * x[3]);
@@ -178,53 +187,75 @@ __device__ __forceinline__ void hier_complements(const int y[4], const double n[
     for (int i = 0; i < 3; ++i) Sc[i] = accS[i] / wsum;
 }
 
-// Phase II/III posterior: the sums over nodes [j0, j1), all relative to the same weight exp(ref), so
-// that the sums of ranges add up.
+// Phase II/III posterior: sums over nodes, all relative to the same weight exp(ref), so that the sums of
+// ranges add up.
 struct HierSums {
     double w, P[3], Sc[3], m1[4], m2[4], d2[3];
     float th0[4];   // reference point of the moments: the empirical logits
 };
 
-// The sums of counts y[4] out of n[4] over nodes [j0, j1).  Bit i-1 of `need` (uniform over the wave)
+__host__ __device__ __forceinline__ void hier_zero(HierSums &H) {
+    H.w = 0.0;
+    for (int i = 0; i < 3; ++i) H.P[i] = H.Sc[i] = H.d2[i] = 0.0;
+    for (int a = 0; a < 4; ++a) H.m1[a] = H.m2[a] = 0.0;
+}
+
+// A state's nodes are summed in HP_SEGS segments, whose sums are added in ascending order.  One lane takes them
+// all or HP_SEGS lanes one each, so that the result is the same bits either way.
+constexpr int HP_SEGS = 4;
+// 1 - exp(-h) and exp(h) - 1 at the nodes' distance h = log(1e9) / 89
+constexpr float HP_STEP_LO = 0.2077249f, HP_STEP_HI = 0.2621886f;
+__host__ __device__ __forceinline__ int hp_seg(int s) { return HP_NODES * s / HP_SEGS; }   // its first node
+
+// The sums of counts y[4] out of n[4] over nodes [j0, j1), H.th0 and ref given.  Bit i-1 of `need` (uniform over the wave)
 // asks for P_i and 1 - P_i (the others are left 0).
 //
 // 90 nodes x (265 instructions per iteration + 400) per state and no memory traffic: the time is the
 // operations, so
 //   * the mode's start comes from the last four modes (backward differences in log s2, float32: only
-//     a start), and each iteration adds to Newton's step the second-order correction (Chebyshev's
-//     method): 1.21 iterations per node where Newton's from the last two modes took 2.15;
+//     a start; before a segment's second node from the first one's derivative), and each iteration adds
+//     to Newton's step the second-order correction (Chebyshev's method): 1.25 iterations per node where
+//     Newton's from the last two modes took 2.15;
 //   * the values at the mode come from the last iteration's exponentials, times exp(-step) for the step
 //     of at most HP_STEP_TOL;
 //   * normal tails are erfc_pos, without branches, and only those that are asked for;
 //   * the evidence's determinant enters the weight as 1 / sqrt, not through a logarithm, and weights are
 //     relative to the likelihood at the empirical logits, not to a running maximum (their largest lies
 //     between exp(-30) and exp(30) times that over all counts).
-// Errors against 128-bit arithmetic over the sample sizes of the design, before and after (rms): P
-// 9e-13 and 9e-13, 1 - P 5e-13 and 5e-13, means 4e-14 and 3e-14, variances 3e-13 and 2e-13.
+// Errors against 128-bit arithmetic over 20,000 states of the design's sample sizes (rms; in brackets all nodes as
+// one segment): P 9.7e-13 (9.3e-13), 1 - P 8.3e-13 (8.1e-13), means 3.8e-14 (3.8e-14), variances 2.3e-13
+// (2.2e-13).  Four segments cost 0.035 iterations per node: 11.88 ms of posteriors on the benchmark sample
+// where one took 11.7 ms, but then each number of lanes gave a result of its own.
 constexpr double HP_STEP_TOL = 1e-4;   // convergence is cubic: what remains is below 0.7 times its cube
 
-__device__ __forceinline__ void hier_sums(const int y[4], const double n[4], const HierNode *nodes, int j0, int j1,
-                                          HierSums &H, int *newton_steps, int need) {
+__host__ __device__ __forceinline__ void hier_sums(const int y[4], const double n[4], const HierNode *nodes, int j0, int j1,
+                                                   double ref, HierSums &H, int *newton_steps, int need) {
     const double M0 = -1.34;
-    double th[4], ref = 0.0;
-    for (int a = 0; a < 4; ++a) {
-        th[a] = log((y[a] + 0.5) / (n[a] - y[a] + 0.5));
-        H.th0[a] = (float)th[a];
-        ref += y[a] * th[a] - n[a] * softplus_fast(th[a]);
+    double th[4];
+    HierNode nd = nodes[j0];
+    {   // start of the range: the logits shrunk towards their common mean as normal ones would be
+        double d[4], w[4], sw = 0.0, sm = 0.0;
+        for (int a = 0; a < 4; ++a) {
+            const double yes = y[a] + 0.5, no = n[a] - y[a] + 0.5;
+            d[a] = nd.s2 + (yes + no) * rcp_nr(yes * no);
+        }
+        rcp4(d, w);
+        for (int a = 0; a < 4; ++a) {
+            sw += w[a];
+            sm += w[a] * (double)H.th0[a];
+        }
+        const double mu = sm * rcp_nr(sw);
+        for (int a = 0; a < 4; ++a) th[a] = mu + nd.s2 * w[a] * ((double)H.th0[a] - mu);
     }
     float last[4], df1[4], df2[4];   // the last mode and its backward differences
     for (int a = 0; a < 4; ++a) last[a] = df1[a] = df2[a] = 0.0f;
-    H.w = 0.0;
-    for (int i = 0; i < 3; ++i) H.P[i] = H.Sc[i] = H.d2[i] = 0.0;
-    for (int a = 0; a < 4; ++a) H.m1[a] = H.m2[a] = 0.0;
-    HierNode nd = nodes[j0];
+    hier_zero(H);
     for (int t = 0; j0 + t < j1; ++t) {
         const double inv_s2 = nd.inv_s2, c = nd.c, beta = nd.beta, lconst = nd.lconst;
-        nd = nodes[min(j0 + t + 1, HP_NODES - 1)];
-        const float f1 = t >= 2 ? 1.0f : 0.0f, f2 = t >= 3 ? 1.0f : 0.0f, f3 = t >= 4 ? 1.0f : 0.0f;
-        for (int a = 0; a < 4; ++a) {
+        nd = nodes[j0 + t + 1 < HP_NODES ? j0 + t + 1 : HP_NODES - 1];
+        for (int a = 0; a < 4 && t > 0; ++a) {
             const float cur = (float)th[a];
-            const float e1 = f1 * (cur - last[a]), e2 = f2 * (e1 - df1[a]), e3 = f3 * (e2 - df2[a]);
+            const float e1 = cur - last[a], e2 = e1 - df1[a], e3 = e2 - df2[a];
             last[a] = cur;
             df1[a] = e1;
             df2[a] = e2;
@@ -308,6 +339,20 @@ __device__ __forceinline__ void hier_sums(const int y[4], const double n[4], con
         for (int a = 0; a < 4; ++a) su += u[a];
         const double om = 1.0 - beta * su;
         gam = beta * rcp_nr(om);
+        if (t == 0) {   // the nodes before the range, from the mode's derivative in log s2, as a + b s2 or a + b / s2
+            const float back = j0 < HP_NODES / 2 ? HP_STEP_LO : HP_STEP_HI, bend = j0 < HP_NODES / 2 ? HP_STEP_LO : -HP_STEP_HI;
+            double q[4], uq = 0.0;
+            for (int a = 0; a < 4; ++a) {
+                q[a] = ((th[a] - M0) - c * dsum) * inv_s2;
+                uq += u[a] * q[a];
+            }
+            for (int a = 0; a < 4; ++a) {
+                const float d = (float)(u[a] * (q[a] + gam * uq)) * back;   // the last step
+                last[a] = (float)th[a] - d;
+                df1[a] = d * (1.0f - bend);
+                df2[a] = df1[a] * bend;
+            }
+        }
         const double lw = (ll - ref) + (lconst - 0.5 * ((sq - c * dsum * dsum) * inv_s2));
         const double wj = exp_short(fmax(lw, -700.0)) * rsq_nr(prodD * om);   // both factors in range
         H.w += wj;
@@ -330,23 +375,51 @@ __device__ __forceinline__ void hier_sums(const int y[4], const double n[4], con
     }
 }
 
-// The sums of a state whose nodes `split` neighbouring lanes share (a power of 2; every lane calls).
-__device__ __forceinline__ void hier_join(HierSums &H, int split) {
-    for (int m = 1; m < split; m *= 2) {
-        H.w += __shfl_xor(H.w, m);
-        for (int i = 0; i < 3; ++i) {
-            H.P[i] += __shfl_xor(H.P[i], m);
-            H.Sc[i] += __shfl_xor(H.Sc[i], m);
-            H.d2[i] += __shfl_xor(H.d2[i], m);
-        }
-        for (int a = 0; a < 4; ++a) {
-            H.m1[a] += __shfl_xor(H.m1[a], m);
-            H.m2[a] += __shfl_xor(H.m2[a], m);
-        }
+// T += H, each sum of H as `at` gives it.
+template <class At>
+__host__ __device__ __forceinline__ void hier_add(HierSums &T, const HierSums &H, At at) {
+    T.w += at(H.w);
+    for (int i = 0; i < 3; ++i) {
+        T.P[i] += at(H.P[i]);
+        T.Sc[i] += at(H.Sc[i]);
+        T.d2[i] += at(H.d2[i]);
+    }
+    for (int a = 0; a < 4; ++a) {
+        T.m1[a] += at(H.m1[a]);
+        T.m2[a] += at(H.m2[a]);
     }
 }
 
-__device__ __forceinline__ void hier_summary(const HierSums &H, HierSummary &out) {
+// Segments [s0, s1), one after the other.
+__host__ __device__ __forceinline__ void hier_segments(const int y[4], const double n[4], const HierNode *nodes, int s0, int s1,
+                                                       HierSums &T, int *newton_steps, int need) {
+    HierSums H;
+    double ref = 0.0;   // the log likelihood at the empirical logits
+    for (int a = 0; a < 4; ++a) {
+        const double th = log((y[a] + 0.5) / (n[a] - y[a] + 0.5));
+        H.th0[a] = T.th0[a] = (float)th;
+        ref += y[a] * th - n[a] * softplus_fast(th);
+    }
+    hier_zero(T);
+    for (int s = s0; s < s1; ++s) {
+        hier_sums(y, n, nodes, hp_seg(s), hp_seg(s + 1), ref, H, newton_steps, need);
+        hier_add(T, H, [](double v) { return v; });
+    }
+}
+
+// All segments, by this lane alone or (shared, uniform) one by each of HP_SEGS neighbouring lanes, which all call.
+__device__ __forceinline__ void hier_all(const int y[4], const double n[4], const HierNode *nodes, bool shared, HierSums &T,
+                                         int *newton_steps, int need) {
+    const int part = (int)threadIdx.x & (HP_SEGS - 1);
+    hier_segments(y, n, nodes, shared ? part : 0, shared ? part + 1 : HP_SEGS, T, newton_steps, need);
+    if (shared) {
+        const HierSums H = T;
+        hier_zero(T);
+        for (int s = 0; s < HP_SEGS; ++s) hier_add(T, H, [&](double v) { return __shfl(v, s, HP_SEGS); });
+    }
+}
+
+__host__ __device__ __forceinline__ void hier_summary(const HierSums &H, HierSummary &out) {
     for (int i = 0; i < 3; ++i) {
         out.Sc[i] = H.Sc[i] / H.w;
         out.P[i] = H.P[i] / H.w;
@@ -367,7 +440,7 @@ __device__ __forceinline__ void hier_summary(const HierSums &H, HierSummary &out
 __device__ __forceinline__ void hier_posterior(const int y[4], const double n[4], const HierNode *__restrict__ nodes,
                                                HierSummary &out, int *newton_steps, int need) {
     HierSums H;
-    hier_sums(y, n, nodes, 0, HP_NODES, H, newton_steps, need);
+    hier_segments(y, n, nodes, 0, HP_SEGS, H, newton_steps, need);
     hier_summary(H, out);
 }
 

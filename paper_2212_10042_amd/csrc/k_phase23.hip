@@ -69,16 +69,6 @@ __device__ __forceinline__ double p23_psucc(double md, double vd, double m0, dou
     return p23_Phi((md - z95 * sqrt(vf)) / sd_mean);
 }
 
-// v[i] for a run-time i in 0..3 without dynamic register indexing.
-template <class T>
-__device__ __forceinline__ T pick4(const T (&v)[4], int i) {
-    return i == 0 ? v[0] : (i == 1 ? v[1] : (i == 2 ? v[2] : v[3]));
-}
-template <class T>
-__device__ __forceinline__ T pick3(const T (&v)[3], int i) {
-    return i == 0 ? v[0] : (i == 1 ? v[1] : v[2]);
-}
-
 // Pairs of treatment arms with equal counts and sizes (bit 0: arms 1, 2; bit 1: 1, 3; bit 2: 2, 3).
 __device__ __forceinline__ int p23_ties(int y1, int y2, int y3, int n1, int n2, int n3) {
     return ((y1 == y2 && n1 == n2) ? 1 : 0) | ((y1 == y3 && n1 == n3) ? 2 : 0) | ((y2 == y3 && n2 == n3) ? 4 : 0);
@@ -143,6 +133,61 @@ __device__ __forceinline__ int p23_phase2(const HierSummary &s, int ties, int lo
     return (active << 2) | ((active == 0 ? 1 : 0) << 5);
 }
 
+// Sample sizes between Phase II looks (50 + 25, 33 or 50 per step), by 4-bit code.
+__device__ __forceinline__ int p23_ncode(int n) {
+    return n == 50 ? 0 : (n == 75 ? 1 : (n == 83 ? 2 : (n == 100 ? 3 : (n == 108 ? 4 : (n == 116 ? 5 : (n == 125 ? 6 : (n == 133 ? 7 : 8)))))));
+}
+__device__ __forceinline__ int p23_ncode_size(int c) {
+    return c == 0 ? 50 : (c == 1 ? 75 : (c == 2 ? 83 : (c == 3 ? 100 : (c == 4 ? 108 : (c == 5 ? 116 : (c == 6 ? 125 : (c == 7 ? 133 : 150)))))));
+}
+
+// The state of a trial about to be looked at, treatment arms in a canonical order (position p holds
+// arm (perm >> 2 p) & 3): Phase II by (active, size, count), ties in arm order, so that "the lowest
+// index among tied arms" is the same arm in both orders; Phase III the selected arm first, then the
+// others.  Bits: y0..y3 9 each, size codes 4 each (without the patients of Phase III), look 3,
+// active 3, top bit set.
+__device__ __forceinline__ uint64_t p23_state(const int y[4], const int n[4], int look, int sel, int active, uint32_t &perm) {
+    const int extra = look >= 3 ? 100 * (look - 2) : 0;   // Phase III patients of control and the selected arm
+    uint32_t c[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const bool s = look >= 3 && sel == i + 1;
+        const int code = p23_ncode(n[i + 1] - (s ? extra : 0));
+        const uint32_t first = look >= 3 ? (s ? 0u : 1u) : (uint32_t)((active >> i) & 1);
+        c[i] = (((first << 4 | (uint32_t)code) << 9 | (uint32_t)y[i + 1]) << 2) | (uint32_t)(i + 1);
+    }
+    auto order = [](uint32_t &a, uint32_t &b) {
+        const uint32_t lo = min(a, b), hi = max(a, b);
+        a = lo;
+        b = hi;
+    };
+    order(c[0], c[1]);
+    order(c[1], c[2]);
+    order(c[0], c[1]);
+    perm = (c[0] & 3u) | (c[1] & 3u) << 2 | (c[2] & 3u) << 4;
+    uint64_t s = (uint64_t)y[0] | (uint64_t)p23_ncode(n[0] - extra) << 36;
+    uint32_t act = 0u;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        s |= (uint64_t)((c[p] >> 2) & 511u) << (9 * (p + 1)) | (uint64_t)((c[p] >> 11) & 15u) << (36 + 4 * (p + 1));
+        if (look < 3) act |= ((c[p] >> 15) & 1u) << p;
+    }
+    return s | (uint64_t)look << 52 | (uint64_t)act << 55 | 1ull << 63;
+}
+
+// A Phase II code's arms from positions back to arms.
+__device__ __forceinline__ int p23_arms(int code, uint32_t perm) {
+    const int sel = code & 3, act = (code >> 2) & 7;
+    int a_sel = 0, a_act = 0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const int arm = (int)((perm >> (2 * p)) & 3u);
+        if (sel == p + 1) a_sel = arm;
+        if ((act >> p) & 1) a_act |= 1 << (arm - 1);
+    }
+    return a_sel | a_act << 2 | (code & 32);
+}
+
 }  // namespace
 
 // Decision of the first look (50 patients per arm) for every outcome y in {0..50}^4, index
@@ -169,6 +214,66 @@ hipError_t launch_p23_look1(const Platten &P, hipStream_t st) {
     hipLaunchKernelGGL(k_p23_look1, dim3((uint32_t)((n_out + 127) / 128)), dim3(128), 0, st, n_out, P.d_p23look1,
                        P.d_hnodes, P.d_gh, P.p23.sqrt_pi, P.p23.z95);
     return hipGetLastError();
+}
+
+// A state's outcome and the iterations of its posterior; shared (uniform): HP_SEGS neighbouring lanes have the same
+// state and share its nodes.  Functions of their own, not inlined: the constants of their polynomials are then held
+// in registers over one loop at a time, not over all loops of a kernel at once; and both paths below form
+// the same bits.
+#define P23_EVAL __device__ __attribute__((noinline))
+__device__ __forceinline__ void p23_counts(uint64_t s, int extra, int y[4], int n[4]) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        y[a] = (int)((s >> (9 * a)) & 511u);
+        n[a] = p23_ncode_size((int)((s >> (36 + 4 * a)) & 15u)) + (a < 2 ? extra : 0);
+    }
+}
+// Phase II: the decision code, by position.
+P23_EVAL uint2 p23_eval2(uint64_t s, bool shared, const HierNode *nodes, const double *gh, double sqrt_pi, double z95) {
+    int y[4], n[4], steps = 0;
+    p23_counts(s, 0, y, n);
+    const double nd[4] = {(double)n[0], (double)n[1], (double)n[2], (double)n[3]};
+    HierSums H;
+    HierSummary h;
+    hier_all(y, nd, nodes, shared, H, &steps, 0);
+    hier_summary(H, h);
+    return make_uint2((uint32_t)p23_phase2(h, p23_ties(y[1], y[2], y[3], n[1], n[2], n[3]), (int)((s >> 52) & 7u),
+                                           (int)((s >> 55) & 7u), gh, sqrt_pi, z95),
+                      (uint32_t)steps);
+}
+// Phase III (the selected arm is at position 1): interim 0 (go on), 1 (success) or 2 (futility), final analysis the
+// bits of the float32 statistic.
+__device__ __forceinline__ uint32_t p23_phase3(const HierSummary &h, int look, double z95) {
+    if (look == 4) return __float_as_uint((float)h.Sc[0]);
+    if (h.P[0] > 0.95) return 1u;
+    return p23_psucc(h.mean[1] - h.mean[0], h.dvar[0], h.mean[0], h.mean[1], 100.0, z95) < 0.20 ? 2u : 0u;
+}
+P23_EVAL uint2 p23_eval3(uint64_t s, bool shared, const HierNode *nodes, double z95) {
+    const int look = (int)((s >> 52) & 7u);
+    int y[4], n[4], steps = 0;
+    p23_counts(s, 100 * (look - 2), y, n);
+    const double nd[4] = {(double)n[0], (double)n[1], (double)n[2], (double)n[3]};
+    HierSums H;
+    HierSummary h;
+    hier_all(y, nd, nodes, shared, H, &steps, 1);
+    hier_summary(H, h);
+    return make_uint2(p23_phase3(h, look, z95), (uint32_t)steps);
+}
+
+// Either, for the lanes of a wave in any phase (tail, uniform: some are in Phase III).
+P23_EVAL uint2 p23_eval(uint64_t s, bool tail, const HierNode *nodes, const double *gh, double sqrt_pi, double z95) {
+    const int look = (int)((s >> 52) & 7u);
+    int y[4], n[4], steps = 0;
+    p23_counts(s, look >= 3 ? 100 * (look - 2) : 0, y, n);
+    const double nd[4] = {(double)n[0], (double)n[1], (double)n[2], (double)n[3]};
+    HierSums H;
+    HierSummary h;
+    hier_all(y, nd, nodes, false, H, &steps, tail ? 1 : 0);
+    hier_summary(H, h);
+    const int code = look < 3 ? p23_phase2(h, p23_ties(y[1], y[2], y[3], n[1], n[2], n[3]), look, (int)((s >> 55) & 7u), gh, sqrt_pi,
+                                           z95)
+                              : (int)p23_phase3(h, look, z95);
+    return make_uint2((uint32_t)code, (uint32_t)steps);
 }
 
 // One tile by itself, trial by trial: a persistent grid; each wave pops items (simulation ranges) from
@@ -289,40 +394,27 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             // ---- enrol the patients of the next look, then one posterior look ----
 #pragma unroll
             for (int a = 0; a < 4; ++a) p23_draw(a, add[a], T[a], k, A.key0, A.key1, n[a], y[a]);
-            HierSummary s;
-            {
-                const double nd[4] = {(double)n[0], (double)n[1], (double)n[2], (double)n[3]};
-                // tails the wave needs (a uniform mask keeps the branch scalar)
-                const int mine = look < 3 ? 0 : 1 << (sel - 1);
-                int wneed = 0;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) wneed |= __ballot((mine >> i) & 1) ? (1 << i) : 0;
-                hier_posterior(y, nd, A.nodes, s, &c_newton, __builtin_amdgcn_readfirstlane(wneed));
-            }
-            if (look < 3) c_look2 += 1; else c_look3 += 1;
+            uint32_t perm;
+            const uint64_t st = p23_state(y, n, look, sel, active, perm);
+            const uint2 o = p23_eval(st, __ballot(look >= 3) != 0ull, A.nodes, A.gh, A.sqrt_pi, A.z95);
+            c_newton += (int)o.y;
             if (look < 3) {
-                apply(p23_phase2(s, p23_ties(y[1], y[2], y[3], n[1], n[2], n[3]), look, active, A.gh, A.sqrt_pi,
-                                 A.z95));
+                c_look2 += 1;
+                apply(p23_arms((int)o.x, perm));
             } else {
+                const uint32_t out = o.x;
+                c_look3 += 1;
                 const bool in_b = (cfg >> (sel - 1)) & 1;
-                if (look == 3) {
-                    // Phase III interim
-                    const double ms = pick4(s.mean, sel);
-                    if (pick3(s.P, sel - 1) > 0.95) {
-                        S = in_b ? -INFINITY : INFINITY;
-                        done = true;
-                    } else if (p23_psucc(ms - s.mean[0], pick3(s.dvar, sel - 1), s.mean[0], ms, 100.0, A.z95) <
-                               0.20) {
-                        done = true;
-                    } else {
+                done = true;
+                if (look == 4) {
+                    S = in_b ? __uint_as_float(out) : INFINITY;   // final analysis
+                } else if (out == 1u) {
+                    S = in_b ? -INFINITY : INFINITY;              // early success
+                } else if (out == 0u) {
+                    done = false;
 #pragma unroll
-                        for (int a = 0; a < 4; ++a) add[a] = (a == 0 || a == sel) ? 100 : 0;
-                        look = 4;
-                    }
-                } else {
-                    // final analysis
-                    S = in_b ? (float)pick3(s.Sc, sel - 1) : INFINITY;
-                    done = true;
+                    for (int a = 0; a < 4; ++a) add[a] = (a == 0 || a == sel) ? 100 : 0;
+                    look = 4;
                 }
             }
             if (done) finish();
@@ -365,19 +457,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // one addition per wave and list made them 9.4, 9.1, 3.9 and 0.6 ms on the benchmark sample (23.3
 // million trials), about 10 ns per addition to a line.  So a workgroup keeps its trials in a range of
 // its own from the first look on, collects new slots in LDS for P23_STEPS passes, and adds once: 0.75,
-// 0.8, 0.4 and 0.2 ms.  post (4.2, 5.2, 1.9 and 0.4 ms) is float64 arithmetic (hier_sums; 6.4, 8.3, 2.9
+// 0.8, 0.4 and 0.2 ms.  post (4.2, 5.3, 1.9 and 0.4 ms) is float64 arithmetic (hier_sums; 6.4, 8.3, 2.9
 // and 0.6 ms with Newton's method and the library's functions).  All together: 144.8 ms trial by trial,
 // 17 ms so.
 // ------------------------------------------------------------------------------------------
 namespace {
-
-// Sample sizes between Phase II looks (50 + 25, 33 or 50 per step), by 4-bit code.
-__device__ __forceinline__ int p23_ncode(int n) {
-    return n == 50 ? 0 : (n == 75 ? 1 : (n == 83 ? 2 : (n == 100 ? 3 : (n == 108 ? 4 : (n == 116 ? 5 : (n == 125 ? 6 : (n == 133 ? 7 : 8)))))));
-}
-__device__ __forceinline__ int p23_ncode_size(int c) {
-    return c == 0 ? 50 : (c == 1 ? 75 : (c == 2 ? 83 : (c == 3 ? 100 : (c == 4 ? 108 : (c == 5 ? 116 : (c == 6 ? 125 : (c == 7 ? 133 : 150)))))));
-}
 
 // Enrol arm a up to n patients in all (of them 100 phase in Phase III): its successes from the count
 // table, or counted among the new patients' words.
@@ -391,40 +475,6 @@ __device__ __forceinline__ void p23_enrol(const P23Args &A, uint32_t tile, uint3
     } else {
         p23_draw(a, add, A.tileT[4 * (int64_t)tile + a], k, A.key0, A.key1, n, y);
     }
-}
-
-// The state of a trial about to be looked at, treatment arms in a canonical order (position p holds
-// arm (perm >> 2 p) & 3): Phase II by (active, size, count), ties in arm order, so that "the lowest
-// index among tied arms" is the same arm in both orders; Phase III the selected arm first, then the
-// others.  Bits: y0..y3 9 each, size codes 4 each (without the patients of Phase III), look 3,
-// active 3, top bit set.
-__device__ __forceinline__ uint64_t p23_state(const int y[4], const int n[4], int look, int sel, int active, uint32_t &perm) {
-    const int extra = look >= 3 ? 100 * (look - 2) : 0;   // Phase III patients of control and the selected arm
-    uint32_t c[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const bool s = look >= 3 && sel == i + 1;
-        const int code = p23_ncode(n[i + 1] - (s ? extra : 0));
-        const uint32_t first = look >= 3 ? (s ? 0u : 1u) : (uint32_t)((active >> i) & 1);
-        c[i] = (((first << 4 | (uint32_t)code) << 9 | (uint32_t)y[i + 1]) << 2) | (uint32_t)(i + 1);
-    }
-    auto order = [](uint32_t &a, uint32_t &b) {
-        const uint32_t lo = min(a, b), hi = max(a, b);
-        a = lo;
-        b = hi;
-    };
-    order(c[0], c[1]);
-    order(c[1], c[2]);
-    order(c[0], c[1]);
-    perm = (c[0] & 3u) | (c[1] & 3u) << 2 | (c[2] & 3u) << 4;
-    uint64_t s = (uint64_t)y[0] | (uint64_t)p23_ncode(n[0] - extra) << 36;
-    uint32_t act = 0u;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        s |= (uint64_t)((c[p] >> 2) & 511u) << (9 * (p + 1)) | (uint64_t)((c[p] >> 11) & 15u) << (36 + 4 * (p + 1));
-        if (look < 3) act |= ((c[p] >> 15) & 1u) << p;
-    }
-    return s | (uint64_t)look << 52 | (uint64_t)act << 55 | 1ull << 63;
 }
 
 constexpr int P23_PROBES = 32;
@@ -679,46 +729,6 @@ __global__ __launch_bounds__(WG) void k_p23_open(P23Args A, P23Memo M, int per) 
     if (threadIdx.x == 0) M.range[blockIdx.x] = make_uint2(begin, L.kept);
 }
 
-// A state's outcome and its Newton steps.  Functions of their own, not inlined: the constants of their
-// polynomials are then held in registers over a state's node loop only, not over all loops of the
-// kernel at once.
-// `split` neighbouring lanes share the state's nodes, each a range of them.
-#define P23_EVAL __device__ __attribute__((noinline))
-P23_EVAL uint2 p23_eval2(int4 y, int4 n, int look, int active, int split, const HierNode *nodes, const double *gh,
-                         double sqrt_pi, double z95) {
-    const int yy[4] = {y.x, y.y, y.z, y.w};
-    const double nd[4] = {(double)n.x, (double)n.y, (double)n.z, (double)n.w};
-    HierSums H;
-    HierSummary h;
-    int steps = 0;
-    const int part = (int)threadIdx.x & (split - 1);
-    hier_sums(yy, nd, nodes, HP_NODES * part / split, HP_NODES * (part + 1) / split, H, &steps, 0);
-    hier_join(H, split);
-    hier_summary(H, h);
-    const int code = p23_phase2(h, p23_ties(y.y, y.z, y.w, n.y, n.z, n.w), look, active, gh, sqrt_pi, z95);
-    return make_uint2((uint32_t)code, (uint32_t)steps);
-}
-P23_EVAL uint2 p23_eval3(int4 y, int4 n, int look, int split, const HierNode *nodes, double z95) {
-    const int yy[4] = {y.x, y.y, y.z, y.w};
-    const double nd[4] = {(double)n.x, (double)n.y, (double)n.z, (double)n.w};
-    HierSums H;
-    HierSummary h;
-    int steps = 0;
-    const int part = (int)threadIdx.x & (split - 1);
-    hier_sums(yy, nd, nodes, HP_NODES * part / split, HP_NODES * (part + 1) / split, H, &steps, 1);
-    hier_join(H, split);
-    hier_summary(H, h);
-    uint32_t out;
-    if (look == 3)
-        out = h.P[0] > 0.95 ? 1u
-                            : (p23_psucc(h.mean[1] - h.mean[0], h.dvar[0], h.mean[0], h.mean[1], 100.0, z95) < 0.20 ? 2u : 0u);
-    else
-        out = __float_as_uint((float)h.Sc[0]);
-    return make_uint2(out, (uint32_t)steps);
-}
-
-constexpr int P23_SPLIT = 8;
-
 // Outcome of every new state of the round, one per lane or, where they are few, per `split` lanes: Phase
 // II the decision code, Phase III interim 0 (go on), 1 (success) or 2 (futility), final analysis the bits
 // of the float32 statistic.  Bound by its vector instructions, 740 per node and wave of 64 states, which
@@ -732,10 +742,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(P23_WAVES, P
     // Lanes per state: the batches that a wave takes one after the other, times the time of a lane's nodes
     // (a quarter more where lanes of a wave are at different nodes, since the wave iterates as long as its
     // slowest lane) and of a start and an end, about five nodes.  Rounds of the 3^4 x 1,024 grid with one
-    // lane per state: 275, 280, 155 and 147 us; the last two, with 4 and 8 lanes, 67 and 32 us.
+    // lane per state: 275, 280, 155 and 147 us; the last two, with HP_SEGS lanes, 61 and 51 us.  The outcome
+    // is the same bits either way (hier_all).
     int split = 1;
     uint32_t best = ~0u;
-    for (int q = 1; q <= P23_SPLIT; q *= 2) {
+    for (int q = 1; q <= HP_SEGS; q *= HP_SEGS) {
         const uint32_t nb = (n2 * q + WAVE - 1) / WAVE + (n3 * q + WAVE - 1) / WAVE;
         const uint32_t cost = ((nb + waves - 1) / waves) * (uint32_t)((q == 1 ? HP_NODES : HP_NODES * 5 / 4 / q) + 5);
         if (cost < best) {
@@ -750,19 +761,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(P23_WAVES, P
         const uint32_t i = ((p3 ? b - b2 : b) * WAVE + (uint32_t)lane) >> __builtin_ctz(split), last = (p3 ? n3 : n2) - 1u;
         const uint32_t slot = M.list[p3 ? 1 : 0][min(i, last)];
         const uint64_t s = slot <= M.mask ? M.state[slot] : M.own[slot - M.mask - 1u];
-        const int look = (int)((s >> 52) & 7u), active = (int)((s >> 55) & 7u);
-        const int extra = p3 ? 100 * (look - 2) : 0;
-        int y[4], n[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            y[a] = (int)((s >> (9 * a)) & 511u);
-            n[a] = p23_ncode_size((int)((s >> (36 + 4 * a)) & 15u)) + (a < 2 ? extra : 0);
-        }
-        // (uniform branch)
-        const uint2 o = p3 ? p23_eval3(make_int4(y[0], y[1], y[2], y[3]), make_int4(n[0], n[1], n[2], n[3]), look, split, A.nodes,
-                                       A.z95)
-                           : p23_eval2(make_int4(y[0], y[1], y[2], y[3]), make_int4(n[0], n[1], n[2], n[3]), look, active,
-                                       split, A.nodes, A.gh, A.sqrt_pi, A.z95);
+        const uint2 o = p3 ? p23_eval3(s, split > 1, A.nodes, A.z95)   // (uniform branch)
+                           : p23_eval2(s, split > 1, A.nodes, A.gh, A.sqrt_pi, A.z95);
         if (i <= last) {
             c_newton += (int)o.y;
             if ((lane & (split - 1)) == 0) M.value[slot] = o.x;
@@ -814,16 +814,8 @@ __global__ __launch_bounds__(WG) void k_p23_step(P23Args A, P23Memo M, int round
             int add[4] = {0, 0, 0, 0};
             float S = INFINITY;
             bool done;
-            if (t.look < 3) {   // the code's arms from canonical positions back to arms
-                const int sel = (int)(out & 3u), act = (int)((out >> 2) & 7u);
-                int a_sel = 0, a_act = 0;
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    const int arm = (int)((perm >> (2 * p)) & 3u);
-                    if (sel == p + 1) a_sel = arm;
-                    if ((act >> p) & 1) a_act |= 1 << (arm - 1);
-                }
-                done = p23_apply(a_sel | a_act << 2 | (int)(out & 32u), t, add);
+            if (t.look < 3) {
+                done = p23_apply(p23_arms((int)out, perm), t, add);
             } else {
                 const bool in_b = (A.cfg[t.tile] >> (t.sel - 1)) & 1;
                 done = true;
