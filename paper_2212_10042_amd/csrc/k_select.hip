@@ -442,14 +442,14 @@ __device__ __forceinline__ float ord2f(uint32_t u) {
     return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u);
 }
 
-// k-th smallest (k >= 1) of the n order-preserving keys get(j), j < n, by three radix passes
-// (11/11/10 bits) with an LDS histogram; also the number of keys strictly below it.  With
-// PASSES = 2 only the top 22 bits are resolved: key is then the smallest value of the 1024-wide
+// k-th smallest (k >= 1) of the order-preserving keys that each(f) hands to f, every thread its own ones, by three
+// radix passes (11/11/10 bits) with an LDS histogram; also the number of keys strictly below it.
+// With PASSES = 2 only the top 22 bits are resolved: key is then the smallest value of the 1024-wide
 // bin that holds the k-th smallest, and below counts the keys under that bin.  Called by the
 // whole workgroup.
-template <int PASSES = 3, class Get>
-__device__ void radix_kth(int n, uint32_t k, Get get, uint32_t *hist, uint32_t *part, uint32_t *s_bin,
-                          uint32_t *s_below, uint32_t &key, uint32_t &below_out) {
+template <int PASSES = 3, class Each>
+__device__ void radix_kth_each(uint32_t k, Each each, uint32_t *hist, uint32_t *part, uint32_t *s_bin,
+                               uint32_t *s_below, uint32_t &key, uint32_t &below_out) {
     constexpr int BINS = 2048;
     const int tid = threadIdx.x;
     uint32_t prefix = 0u, below = 0u, need = k;
@@ -460,10 +460,9 @@ __device__ void radix_kth(int n, uint32_t k, Get get, uint32_t *hist, uint32_t *
         const uint32_t mask_hi = pass == 0 ? 0u : (0xFFFFFFFFu << (sh + wd));
         for (int j = tid; j < BINS; j += SEL_WG) hist[j] = 0u;
         __syncthreads();
-        for (int j = tid; j < n; j += SEL_WG) {
-            const uint32_t u = get(j);
+        each([&](uint32_t u) {
             if ((u & mask_hi) == prefix) atomicAdd(&hist[(u >> sh) & ((1u << wd) - 1u)], 1u);
-        }
+        });
         __syncthreads();
         const int nb = 1 << wd;
         const int per = nb / SEL_WG;
@@ -486,6 +485,14 @@ __device__ void radix_kth(int n, uint32_t k, Get get, uint32_t *hist, uint32_t *
     }
     key = prefix;
     below_out = below;
+}
+// The same of the n keys get(j), j < n.
+template <int PASSES = 3, class Get>
+__device__ __forceinline__ void radix_kth(int n, uint32_t k, Get get, uint32_t *hist, uint32_t *part, uint32_t *s_bin,
+                                          uint32_t *s_below, uint32_t &key, uint32_t &below_out) {
+    radix_kth_each<PASSES>(k, [&](auto f) {
+        for (int j = threadIdx.x; j < n; j += SEL_WG) f(get(j));
+    }, hist, part, s_bin, s_below, key, below_out);
 }
 
 // Selection of lambda*_i for float32 keys.  Tiles of at most SEL_SAMPLE keys are selected in
@@ -748,11 +755,90 @@ __device__ __forceinline__ void wave_kth_pad(const uint32_t *v, uint32_t n, uint
     lt = below;
 }
 
+// One tile (lane l of set S) by the whole workgroup, three radix passes: over the candidates (mem: they hold the
+// k-th key), in LDS where they fit behind the histogram (buf: H4_BUF words), or over all keys regenerated.  Not
+// inlined: k_h4_select's registers are its selection's.
+constexpr int H4_BUF = SEL_WG / WAVE * H4_CAND_MAX;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;   // (pointers of such a function are generic otherwise)
+typedef const __attribute__((address_space(1))) uint32_t glb_u32;
+typedef const __attribute__((address_space(1))) float glb_f32;
+__device__ __attribute__((noinline)) void h4_whole_tile(const H4Set *__restrict__ S, int l, int32_t k, bool mem,
+                                                        glb_u32 *__restrict__ cnt, glb_f32 *__restrict__ cand,
+                                                        const uint32_t *__restrict__ tileT, const float4 *__restrict__ tbl,
+                                                        uint32_t key0, uint32_t key1, lds_u32 *buf, lds_u32 *part, lds_u32 *s_bin,
+                                                        lds_u32 *s_below, uint32_t *__restrict__ fb, double *lam, int32_t *rej_at) {
+    constexpr int NWV = SEL_WG / WAVE;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t b = S->cfg[l];
+    const int32_t n = S->n_sims;
+    const int cap = h4_cap(n, S->slice);
+    glb_f32 *__restrict__ cp = cand + S->key_base + (int64_t)l * S->n_slices * cap;
+    // f(place among the candidates, its float bits), the waves four slices at a time in turn
+    auto each_cand = [&](auto f) {
+        uint32_t before = 0u;   // candidates of the slices before
+        for (int s0 = 0; s0 < S->n_slices; s0 += WAVE) {
+            const int ns = min(WAVE, S->n_slices - s0);
+            const uint32_t c = lane < ns ? cnt[S->cnt_base + (int64_t)(s0 + lane) * WAVE + l] : 0u;
+            uint32_t x = c;
+            for (int off = 1; off < WAVE; off <<= 1) {
+                const uint32_t y = __shfl_up(x, off);
+                if (lane >= off) x += y;
+            }
+            for (int s = 4 * wv; s < ns; s += 4 * NWV) {
+                uint32_t m[4], o[4], v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    m[j] = (uint32_t)__builtin_amdgcn_readlane((int)c, s + j);   // 0 past the slices
+                    o[j] = before + (uint32_t)__builtin_amdgcn_readlane((int)x, s + j) - m[j];
+                    if ((uint32_t)lane < m[j]) v[j] = __float_as_uint(cp[(int64_t)(s0 + s + j) * cap + lane]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if ((uint32_t)lane < m[j]) f(o[j] + (uint32_t)lane, v[j]);
+                    for (uint32_t i = (uint32_t)lane + WAVE; i < m[j]; i += WAVE)
+                        f(o[j] + i, __float_as_uint(cp[(int64_t)(s0 + s + j) * cap + i]));
+                }
+            }
+            before += __shfl(x, WAVE - 1);
+        }
+        return before;
+    };
+    uint32_t T[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) T[i] = tileT[i];
+    if (tid == 0 && !mem) atomicAdd(&fb[0], 1u);
+    // the candidates in LDS behind the histogram where they fit, the other tiles' ones being selected
+    constexpr uint32_t HIST = 2048, ROOM = H4_BUF - HIST;
+    uint32_t *const hist = (uint32_t *)buf, *const all = hist + HIST;
+    uint32_t total = 0u;
+    if (mem)
+        total = each_cand([&](uint32_t i, uint32_t v) {
+            if (i < ROOM) all[i] = v;
+        });
+    __syncthreads();
+    uint32_t key = 0u, below = 0u;
+    radix_kth_each((uint32_t)k, [&](auto f) {
+        if (mem && total <= ROOM)
+            for (uint32_t j = tid; j < total; j += SEL_WG) f(all[j] | 0x80000000u);   // f2ord of keys >= 0
+        else if (mem)
+            each_cand([&](uint32_t, uint32_t v) { f(v | 0x80000000u); });
+        else
+            for (int j = tid; j < n; j += SEL_WG) f(f2ord(h4_regen_key((uint32_t)j, T, b, key0, key1, tbl)));
+    }, hist, (uint32_t *)part, (uint32_t *)s_bin, (uint32_t *)s_below, key, below);
+    if (tid == 0) {
+        *lam = (double)ord2f(key);
+        if (rej_at) *rej_at = (int32_t)below;
+    }
+    __syncthreads();   // buf may be rewritten
+}
+
 // One wave per tile: the candidates (every key below the pilot's bound, in slice order) go to LDS
 // and the k-th smallest is found bit by bit in registers; when only the keys equal to the bound
-// reach rank k, it is the bound.  Candidates that do not hold the k-th
-// key, that a slice could not keep or that outnumber H4_CAND_MAX send the tile to the whole
-// workgroup, which takes three radix passes over the tile's keys regenerated one by one.  Bound by the
+// reach rank k, it is the bound.  Otherwise the whole workgroup takes the tile by three radix passes: over
+// the candidates themselves where they outnumber H4_CAND_MAX, over the tile's keys regenerated one by one where
+// the candidates do not hold the k-th key or a slice could not keep them.  (From some 200,000 simulations on a
+// pilot's bound leaves more than H4_CAND_MAX: 3^4 boxes x 2^20 at alpha 0.0005, 7,000 per tile, 204 ms with
+// all regenerated, 1.6 ms so.)  Bound by the
 // latency of its loads at 12 waves per CU (48 KB of LDS and 168 registers each): 16^4 boxes 650 us with 64
 // candidates loaded at a time, 550 with four slices in flight (16 bytes per lane) and three waves per SIMD.
 __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_h4_select(const H4Set *__restrict__ sets, const int32_t *__restrict__ at,
@@ -768,6 +854,7 @@ __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 3))) 
     __shared__ uint32_t part[SEL_WG];
     __shared__ uint32_t s_bin, s_below;
     __shared__ int32_t fail[NWV];
+    __shared__ bool many[NWV];   // the candidates in memory hold the k-th key
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t t = (int64_t)blockIdx.x * NWV + wv;
     if (lane == 0) fail[wv] = -1;
@@ -790,6 +877,18 @@ __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 3))) 
                 const int ns = min(WAVE, S->n_slices - s0);
                 const uint32_t c = lane < ns ? cnt[S->cnt_base + (int64_t)(s0 + lane) * WAVE + l] : 0u;
                 over = over || __ballot(c > (uint32_t)cap) != 0ull;
+                if (cap <= 2 * WAVE) {   // short slices: a lane takes one
+                    uint32_t x = c;
+                    for (int off = 1; off < WAVE; off <<= 1) {
+                        const uint32_t y = __shfl_up(x, off);
+                        if (lane >= off) x += y;
+                    }
+                    const uint32_t o = total + x - c;
+                    total += __shfl(x, WAVE - 1);
+                    if (!over && total <= (uint32_t)H4_CAND_MAX)
+                        for (uint32_t i = 0; i < c; ++i) buf[wv][o + i] = __float_as_uint(cp[(int64_t)(s0 + lane) * cap + i]);
+                    continue;
+                }
                 for (int s = 0; s < ns; s += 4) {   // four slices' first 256 candidates in flight
                     uint32_t m[4], o[4];
                     uint4 v[4];
@@ -836,6 +935,7 @@ __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 3))) 
                 }
             } else if (lane == 0) {
                 fail[wv] = (int32_t)t;
+                many[wv] = !over && total >= (uint32_t)k;
             }
         }
     }
@@ -844,22 +944,8 @@ __global__ __launch_bounds__(SEL_WG) __attribute__((amdgpu_waves_per_eu(3, 3))) 
         const int32_t ft = fail[w];
         if (ft < 0) continue;   // uniform
         const int32_t a = at[ft];
-        const H4Set *__restrict__ S = sets + (a >> 6);
-        const uint32_t b = S->cfg[a & 63];
-        const int32_t n = S->n_sims, k = kk[ft];
-        uint32_t T[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) T[i] = tileT[4 * (int64_t)ft + i];
-        if (tid == 0) atomicAdd(&fb[0], 1u);
-        __syncthreads();
-        uint32_t key = 0u, below = 0u;
-        radix_kth(n, (uint32_t)k, [&](int j) { return f2ord(h4_regen_key((uint32_t)j, T, b, key0, key1, tbl)); },
-                  &buf[0][0], part, &s_bin, &s_below, key, below);
-        if (tid == 0) {
-            lam[ft] = (double)ord2f(key);
-            if (rej_at) rej_at[ft] = (int32_t)below;
-        }
-        __syncthreads();
+        h4_whole_tile(sets + (a >> 6), a & 63, kk[ft], many[w], (glb_u32 *)cnt, (glb_f32 *)cand, tileT + 4 * (int64_t)ft, tbl, key0, key1,
+                      (lds_u32 *)&buf[0][0], (lds_u32 *)part, (lds_u32 *)&s_bin, (lds_u32 *)&s_below, fb, &lam[ft], rej_at ? &rej_at[ft] : nullptr);
     }
 }
 
