@@ -463,8 +463,8 @@ int cse_work_counters(const cse_platten *p, int64_t out[4], void *stream);
  *        is faster, from 2^26 keys and 1,024 simulations on; 1: at any size.  Otherwise, and
  *        always in cse_calibrate_tiebreak, it keeps every float32 key.  Same results either way.
  *   CSE_OPT_H4_MARGIN (the calibration from candidates): the bound's margin in standard
- *        deviations of the pilot rank (default 6).  Results do not depend on it: a tile whose k-th
- *        key is not among the candidates is selected from its keys regenerated one by one from the
+ *        deviations of the pilot rank (default 6; the rank is at most a fifth of the pilot).  Results do
+ *        not depend on it: a tile whose k-th key is not among the candidates is selected from its keys regenerated one by one from the
  *        counter-based generator (slow; cse_work_counters counts them).
  * Errors: CSE_EINVAL (bad handle, unknown option, value outside [0, 100]; 0 or 1 for
  * CSE_OPT_H4_BRACKET).

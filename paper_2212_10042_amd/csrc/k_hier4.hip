@@ -331,10 +331,13 @@ __global__ __launch_bounds__(WG) void k_h4_pilot(const H4Set *__restrict__ sets,
     const uint4 *__restrict__ l0 = rr.lds + S->row[0][lane] * H4_ROW_LDS, *__restrict__ l1 = rr.lds + S->row[1][lane] * H4_ROW_LDS,
                 *__restrict__ l2 = rr.lds + S->row[4][lane] * H4_ROW_LDS, *__restrict__ l3 = rr.lds + S->row[5][lane] * H4_ROW_LDS;
     const float pr = (float)k / (float)N, mean = pr * (float)m;
-    const float rank = mean + margin * sqrtf(mean * (1.0f - pr)) + margin * margin * (1.0f / 6.0f) + 1.0f;
-    // pilot keys the bound may admit before its bin is divided: those of 1,800 candidates, or a quarter
-    // over rank
-    const float most = fmaxf(1.25f * rank + 8.0f, 1800.0f * (float)m / (float)N);
+    // at most a fifth of the pilot: a slice has room for half of its keys (a wide margin, CSE_OPT_H4_MARGIN, ends there)
+    const float rank = fminf(mean + margin * sqrtf(mean * (1.0f - pr)) + margin * margin * (1.0f / 6.0f) + 1.0f, 0.2f * (float)m);
+    // pilot keys the bound may admit before its bin is divided: those of 1,800 candidates or a fifth of the
+    // pilot, or a quarter over rank.  (Without the fifth, tiles deep in the null, whose keys crowd in one bin,
+    // admitted nearly all keys of up to 2,048 simulations, so that slices overflowed and all was regenerated:
+    // 6^4 boxes x 1,500 721 us, 150 so.)
+    const float most = fmaxf(1.25f * rank + 8.0f, fminf(1800.0f * (float)m / (float)N, 0.2f * (float)m));
     uint2 r = make_uint2(0u, 0xFFFFFFFFu);    // first pass: the fixed bins
     float below = 0.0f;                       // pilot keys below the range (wave 0)
     bool open = sel && wv == 0;               // wave 0: the tile's bound is not final
