@@ -456,16 +456,17 @@ int cse_work_counters(const cse_platten *p, int64_t out[4], void *stream);
  *        full histogram of their outcomes (cse_work_counters counts them); a smaller margin lists
  *        fewer simulations in the bracketed pass but leaves more tiles to that.  A plan
  *        captured earlier keeps the margin it was captured with.
- *   CSE_OPT_H4_BRACKET (CSE_HIER4 and CSE_BASKET4 calibration): with (max N + 1) alpha <= 832 and
- *        alpha <= 0.05 the calibration can keep candidate keys alone (a pilot over the first
- *        simulations, a sixteenth of them, 256 to 2,048, bounds each tile's k-th key from above;
- *        the pass over all simulations keeps the keys below the bound).  0 (default): where that
+ *   CSE_OPT_H4_BRACKET (CSE_HIER4 and CSE_BASKET4 calibration): with alpha <= 0.05 the calibration
+ *        can keep candidate keys alone (a pilot over the first simulations, a sixteenth of them, 256
+ *        to 2,048, bounds each tile's k-th key from above; the pass over all simulations keeps the
+ *        keys below the bound).  0 (default): where that
  *        is faster, from 2^26 keys and 1,024 simulations on; 1: at any size.  Otherwise, and
  *        always in cse_calibrate_tiebreak, it keeps every float32 key.  Same results either way.
  *   CSE_OPT_H4_MARGIN (the calibration from candidates): the bound's margin in standard
- *        deviations of the pilot rank (default 6; the rank is at most a fifth of the pilot).  Results do
- *        not depend on it: a tile whose k-th key is not among the candidates is selected from its keys regenerated one by one from the
- *        counter-based generator (slow; cse_work_counters counts them).
+ *        deviations of the pilot rank (default 6; the rank is at most a fifth of the pilot).  Results
+ *        do not depend on it: a tile whose k-th key is not among the candidates is selected from its
+ *        keys regenerated one by one from the counter-based generator (slow; cse_work_counters counts
+ *        them).
  * Errors: CSE_EINVAL (bad handle, unknown option, value outside [0, 100]; 0 or 1 for
  * CSE_OPT_H4_BRACKET).
  */

@@ -263,14 +263,16 @@ int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alph
                    int32_t *reject, int64_t *score_T, double *score_Z, double *grad, double *cp_upper,
                    double *tile_bound, hipStream_t st, bool full_keys = false) {
     double *ap = alpha_prime ? alpha_prime : P.d_apw;
-    // 4-arm designs: candidate keys where a tile's candidates stay few (alpha' <= alpha, so k is at most
-    // (N + 1) alpha) and the keys many, unless every key is asked for (the randomised tie-break reads
-    // them); else every key and the two-sided bracket of the f32 selection.  Candidates cost a pilot, which
-    // waits for k: with every key, up to 64 million keys take 0.71 to 1.13 of the time with candidates, 73
-    // to 150 million 0.91 to 1.4, 700 million 1.7 (hier4 and basket, 5^4 to 12^4 boxes x 3,000 to 33,000);
-    // tiles of fewer simulations than a pilot keep every key anyway (0.78 to 0.93)
+    // 4-arm designs: candidate keys where a tile's candidates are a small part of its keys (alpha' <= alpha) and the
+    // keys many, unless every key is asked for (the randomised tie-break reads them); else every key and the
+    // two-sided bracket of the f32 selection.  Candidates cost a pilot, which waits for k: with every key, up to
+    // 64 million keys take 0.71 to 1.13 of the time with candidates, 73 to 150 million 0.91 to 1.4, 700 million
+    // 1.7 (hier4 and basket, 5^4 to 12^4 boxes x 3,000 to 33,000); tiles of fewer simulations than a pilot keep
+    // every key anyway (0.78 to 0.93).  The rank needs no limit: 8^4 boxes x 34,000 / 58,000 and 12^4 x 90,000
+    // at alpha 0.025 596 / 965 / 6,233 us with every key, 492 / 725 / 3,558 with candidates, 4^4 x 2^20
+    // (k = 26,000) 7.2 and 3.2 ms, at 0.05 12^4 x 65,536 5.7 and 3.4 ms
     const bool h4c = (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys &&
-                     alpha <= cse::H4_CAND_ALPHA && alpha * ((double)P.max_N + 1.0) <= cse::H4_CAND_K &&
+                     alpha <= cse::H4_CAND_ALPHA &&
                      (P.h4_candidates || (P.max_N >= cse::H4_PILOT_MIN_N && P.n_keys >= cse::H4_CAND_KEYS));
     int32_t *kk = k ? k : P.d_kw;
     double *lam = lambda_tile ? lambda_tile : P.d_lamw;

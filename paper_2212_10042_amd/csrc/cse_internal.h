@@ -137,10 +137,9 @@ constexpr int64_t H4_SLICE_MAX = 256;    // granules per item at most (4,096 sim
 constexpr int64_t H4_WGS = 2048;         // workgroups of four waves, default
 constexpr int H4_PILOT_MIN_N = 1024;     // fewer simulations: every key is kept
 constexpr int H4_PILOT_MAX = 2048;
-constexpr int H4_CAND_MAX = 3072;        // candidates selected from LDS (more: exact path)
-constexpr double H4_CAND_K = 832.0;      // largest (max N + 1) * alpha that takes candidates
+constexpr int H4_CAND_MAX = 3072;        // candidates a wave selects in LDS (more: the workgroup)
 constexpr int64_t H4_CAND_KEYS = (int64_t)64 << 20;   // keys of the platten from which candidates are kept
-constexpr double H4_CAND_ALPHA = 0.05;   // and largest alpha
+constexpr double H4_CAND_ALPHA = 0.05;   // and largest alpha: the rank stays below a fifth of every pilot
 // candidate slots of a tile per slice of `slice` granules (a pilot leaves an eighth of the keys at most;
 // a set's slots fit its keys' place in the workspace)
 __host__ __device__ inline int h4_cap(int n, int slice) { return n < H4_PILOT_MIN_N ? slice * GRAN2 : slice * GRAN2 / 2; }

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (5, 262_144, 0.003),         # the same from longer slices
     (2, 1 << 20, 0.0005),        # 7,300
     (2, (1 << 21) + 5, 0.0004),  # 13,500
+    (2, 60_000, 0.025),          # 2,950, k = 1,500
+    (2, 300_001, 0.05),          # 25,000, k = 15,000
 ])
 def test_selected_from_the_candidates(m, n, alpha):
     print(f"[h4 many candidates] {m}^4 boxes x {n}, alpha {alpha}", flush=True)
