@@ -407,9 +407,11 @@ int cse_plan_destroy(cse_plan *plan);
  * candidates on the current device (synchronises `stream`):
  *   CSE_ZTEST1:            waves of the grid, from {4096 .. 262144} (powers of 2);
  *   CSE_BINOM2_Z, HIER4, BASKET4: workgroups of the grid (simulation ranges per group of
- *                          batches), from {1024 .. 65536} (powers of 2; at least 4
- *                          chunks of 64 simulations per item), timed on the calibration
- *                          launch plus the validation launch;
+ *                          batches or tiles), from {1024 .. 65536} (powers of 2; at least 32
+ *                          simulations per item of the 2-arm design, 64 of the others), timed on
+ *                          the calibration launch plus the validation launch; 4-arm designs: on
+ *                          the keys that cse_calibrate keeps at alpha = 0.025 (every key, or
+ *                          candidates with their selection; CSE_OPT_H4_BRACKET);
  *   CSE_PHASE23:           trials per work item {64, 128, 256, 512} x grid of the posterior
  *                          kernel {512, 1024, 2048} workgroups, timed on a strided sample of
  *                          tiles holding at most max_trials trials.

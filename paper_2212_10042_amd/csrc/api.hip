@@ -257,23 +257,26 @@ int validate_impl(const cse::Platten &P, uint64_t seed, double delta, int32_t *r
     return CSE_OK;
 }
 
+// 4-arm designs: candidate keys where a tile's candidates are a small part of its keys (alpha' <= alpha) and the
+// keys many, unless every key is asked for (the randomised tie-break reads them); else every key and the
+// two-sided bracket of the f32 selection.  Candidates cost a pilot, which waits for k: with every key, up to
+// 64 million keys take 0.71 to 1.13 of the time with candidates, 73 to 150 million 0.91 to 1.4, 700 million
+// 1.7 (hier4 and basket, 5^4 to 12^4 boxes x 3,000 to 33,000); tiles of fewer simulations than a pilot keep
+// every key anyway (0.78 to 0.93).  The rank needs no limit: 8^4 boxes x 34,000 / 58,000 and 12^4 x 90,000
+// at alpha 0.025 596 / 965 / 6,233 us with every key, 492 / 725 / 3,558 with candidates, 4^4 x 2^20
+// (k = 26,000) 7.2 and 3.2 ms, at 0.05 12^4 x 65,536 5.7 and 3.4 ms
+bool takes_candidates(const cse::Platten &P, double alpha, bool full_keys) {
+    return (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys && alpha <= cse::H4_CAND_ALPHA &&
+           (P.h4_candidates || (P.max_N >= cse::H4_PILOT_MIN_N && P.n_keys >= cse::H4_CAND_KEYS));
+}
+
 // Calibration (Algorithm 2) on stream st with the key workspace `keys` (key_bytes(P) bytes).
 int calibrate_impl(const cse::Platten &P, void *keys, uint64_t seed, double alpha, double *alpha_prime, int32_t *k,
                    double *lambda_tile, double *lambda_global, int32_t *reject_at_lambda, double delta,
                    int32_t *reject, int64_t *score_T, double *score_Z, double *grad, double *cp_upper,
                    double *tile_bound, hipStream_t st, bool full_keys = false) {
     double *ap = alpha_prime ? alpha_prime : P.d_apw;
-    // 4-arm designs: candidate keys where a tile's candidates are a small part of its keys (alpha' <= alpha) and the
-    // keys many, unless every key is asked for (the randomised tie-break reads them); else every key and the
-    // two-sided bracket of the f32 selection.  Candidates cost a pilot, which waits for k: with every key, up to
-    // 64 million keys take 0.71 to 1.13 of the time with candidates, 73 to 150 million 0.91 to 1.4, 700 million
-    // 1.7 (hier4 and basket, 5^4 to 12^4 boxes x 3,000 to 33,000); tiles of fewer simulations than a pilot keep
-    // every key anyway (0.78 to 0.93).  The rank needs no limit: 8^4 boxes x 34,000 / 58,000 and 12^4 x 90,000
-    // at alpha 0.025 596 / 965 / 6,233 us with every key, 492 / 725 / 3,558 with candidates, 4^4 x 2^20
-    // (k = 26,000) 7.2 and 3.2 ms, at 0.05 12^4 x 65,536 5.7 and 3.4 ms
-    const bool h4c = (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys &&
-                     alpha <= cse::H4_CAND_ALPHA &&
-                     (P.h4_candidates || (P.max_N >= cse::H4_PILOT_MIN_N && P.n_keys >= cse::H4_CAND_KEYS));
+    const bool h4c = takes_candidates(P, alpha, full_keys);
     int32_t *kk = k ? k : P.d_kw;
     double *lam = lambda_tile ? lambda_tile : P.d_lamw;
     // The step's dependencies: alpha' -> k -> selection; simulation -> selection, finish and
@@ -658,6 +661,10 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
         return !group ? cse::plan_work_items(&P, v)
                       : (P.design.kind == CSE_BINOM2_Z ? cse::plan_group_items(&P, v) : cse::plan_h4_items(&P, v));
     };
+    // 4-arm designs: the path that cse_calibrate takes at the level of the paper, 2.5%
+    const double level = 0.025;
+    const bool cand = takes_candidates(P, level, false);
+    if (cand) CSE_LAUNCH(cse::launch_bound(P, 1, nullptr, nullptr, level, P.d_apw, nullptr, P.d_kw, nullptr, st));
     const int64_t cands[7] = {1024, 2048, 4096, 8192, 16384, 32768, 65536};
     const int64_t wave_cands[7] = {4096, 8192, 16384, 32768, 65536, 131072, 262144};
     float best = 3.4e38f;
@@ -665,10 +672,15 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
     for (int i = 0; i < 7; ++i) {
         const int64_t v = group ? cands[i] : wave_cands[i];
         if (int e = replan(v)) return e;
-        // the calibration launch (keys) and the validation launch (no keys) together: the
-        // best shape of one need not be the best of the other
+        // the calibration launch (keys, or candidates and their selection) and the validation launch (no keys)
+        // together: the best shape of one need not be the best of the other
         float ms = 0.0f, ms_val = 0.0f;
-        if (int e = timeit([&]() { return run_sim(P, seed, P.d_keys, st); }, 3, &ms)) return e;
+        if (int e = timeit([&]() -> int {
+                if (int e = run_sim(P, seed, P.d_keys, st, false, cand ? P.d_kw : nullptr)) return e;
+                if (cand) CSE_LAUNCH(cse::launch_h4_select(P, seed, (const float *)P.d_keys, P.d_kw, P.d_lamw, nullptr, st));
+                return CSE_OK;
+            }, 3, &ms))
+            return e;
         if (int e = timeit([&]() { return run_sim(P, seed, nullptr, st); }, 3, &ms_val)) return e;
         ms += ms_val;
         if (ms < best) {
