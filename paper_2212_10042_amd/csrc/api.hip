@@ -632,12 +632,10 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
             d_it.p = nullptr;
             CSE_HIP_TRY(hipMalloc((void **)&d_it.p, items.size() * sizeof(cse::WorkItem)));
             CSE_HIP_TRY(hipMemcpy(d_it.p, items.data(), items.size() * sizeof(cse::WorkItem), hipMemcpyHostToDevice));
-            const int64_t full = std::max<int64_t>(1, ((int64_t)items.size() + 3) / 4);
             for (int64_t g : grids) {
-                const int64_t gg = std::min(g, full);
                 float ms = 0.0f;
                 if (int e = timeit([&]() -> int {
-                        CSE_LAUNCH(cse::launch_phase23_list(P, seed, d_it.p, items.data(), (int64_t)items.size(), gg, P.d_Rw, nullptr,
+                        CSE_LAUNCH(cse::launch_phase23_list(P, seed, d_it.p, items.data(), (int64_t)items.size(), g, P.d_Rw, nullptr,
                                                             nullptr, nullptr, st));
                         return CSE_OK;
                     }, 1, &ms))

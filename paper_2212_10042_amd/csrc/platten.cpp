@@ -1435,8 +1435,7 @@ int plan_queue_items(Platten *P, int32_t chunk, int64_t grid) {
     P->p23_chunk = chunk;
     P->p23.items = P->d_p23items;
     P->p23.n_items = (int64_t)items.size();
-    const int64_t full = std::max<int64_t>(1, (P->p23.n_items + 3) / 4);
-    P->p23_grid = grid > 0 ? std::min<int64_t>(grid, full) : P23_GRID;
+    P->p23_grid = grid > 0 ? grid : P23_GRID;   // its work is the states, up to HP_SEGS lanes each, not the items
     P->p23_items = std::move(items);
     return CSE_OK;
 }

@@ -29,3 +29,19 @@ def test_4arm_times_the_calibration_that_runs():
     for name in ("reject", "score_T", "k", "lambda_tile", "reject_at_lambda", "tile_bound"):
         assert torch.equal(before[name], after[name]), name
     P.close()
+
+
+def test_phase23_small_platten():
+    """Few items, many new states: every grid of the posterior kernel is timed and kept as it is, the default (trials per
+    item 256, grid 512) among them, not cut down to a workgroup per four items."""
+    w = W.phase23_grid((2, 2, 2, 2), 200, seed=3)
+    print("[autotune] phase23, few items", flush=True)
+    P = cse.Platten.create("phase23", w["theta"], w["radii"], w["sims"], cut=w["cut"])
+    before = P.calibrate(9)
+    chunk, grid = cse.cse_autotune(P.handle, seed=9)
+    assert chunk in (64, 128, 256, 512) and grid in (512, 1024, 2048)
+    after = P.calibrate(9)
+    torch.cuda.synchronize()
+    for name in ("reject", "score_T", "k", "lambda_tile", "reject_at_lambda", "tile_bound"):
+        assert torch.equal(before[name], after[name]), name
+    P.close()
