@@ -15,6 +15,7 @@
 
 #include "cse_internal.h"
 #include "kernels.h"
+#include "value_slot.hpp"
 
 namespace cse {
 
@@ -617,17 +618,15 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         }
         std::vector<double> uv[4];   // distinct values, ascending; found in an open-addressed table first
         {
-            size_t slots = 64;
-            while (slots < 2 * (size_t)P->n_tiles) slots *= 2;
+            int bits = 6;
+            while (((size_t)1 << bits) < 2 * (size_t)P->n_tiles) ++bits;
+            const size_t slots = (size_t)1 << bits;
             std::vector<int32_t> slot(slots), rank, by;
             for (int a = 0; a < 4; ++a) {
                 std::fill(slot.begin(), slot.end(), -1);
                 for (int64_t t = 0; t < P->n_tiles; ++t) {
                     const double v = P->tile_theta[t * 4 + a] + 0.0;   // one zero
-                    uint64_t h;
-                    memcpy(&h, &v, 8);
-                    h *= 0x9E3779B97F4A7C15ull;
-                    size_t i = (size_t)(h >> 20) & (slots - 1);
+                    size_t i = (size_t)value_slot(v, bits);
                     while (slot[i] >= 0 && uv[a][slot[i]] != v) i = (i + 1) & (slots - 1);
                     if (slot[i] < 0) {
                         slot[i] = (int32_t)uv[a].size();
