@@ -120,6 +120,13 @@ int cse_platten_create(const cse_design *design, int64_t n_boxes, const double *
 /* Release the platten and its device workspaces (synchronises the device first). */
 int cse_platten_destroy(cse_platten *p);
 
+/*
+ * cse_release_cached_memory -- free the device memory that the library keeps for later plattens after a platten
+ * is destroyed: one count-table buffer per device, at most 128 MiB.  (The library frees it by itself when an
+ * allocation of its own fails.)  Always CSE_OK.
+ */
+int cse_release_cached_memory(void);
+
 /* Number of tiles (box pieces) in the platten; < 0 on a NULL handle. */
 int64_t cse_platten_size(const cse_platten *p);
 

@@ -34,7 +34,7 @@ EXPORTED = ("cse_platten_create", "cse_platten_destroy", "cse_platten_size", "cs
             "cse_plan_launch", "cse_plan_nodes", "cse_plan_destroy", "cse_autotune", "cse_taylor",
             "cse_validate_lower", "cse_confidence_set", "cse_calibrate_tiebreak", "cse_adagrid_decide",
             "cse_adagrid_apply", "cse_platten_tiles", "cse_calibrate_noalloc", "cse_platten_set_option",
-            "cse_last_error")
+            "cse_release_cached_memory", "cse_last_error")
 
 
 class CseError(RuntimeError):
@@ -64,6 +64,7 @@ def _load():
     P, i32, i64, u64, dbl = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64, ctypes.c_double
     L.cse_platten_create.argtypes = [ctypes.POINTER(cse_design), i64, P, P, P, i32, ctypes.POINTER(P)]
     L.cse_platten_destroy.argtypes = [P]
+    L.cse_release_cached_memory.argtypes = []
     L.cse_platten_size.argtypes = [P]
     L.cse_platten_size.restype = i64
     L.cse_platten_describe.argtypes = [P, P, P, P, P]
@@ -170,6 +171,11 @@ def cse_platten_create(design: cse_design, theta, radii, sims, flags: int = 0):
 
 def cse_platten_destroy(h):
     _check("cse_platten_destroy", _L.cse_platten_destroy(h))
+
+
+def cse_release_cached_memory():
+    """Free the device memory kept for later plattens (one count-table buffer per device)."""
+    _check("cse_release_cached_memory", _L.cse_release_cached_memory())
 
 
 def cse_platten_size(h) -> int:

@@ -208,8 +208,7 @@ int ensure_keys(cse::Platten &P) {
         (void)hipFree(P.d_keys);
         P.d_keys = nullptr;
     }
-    if (hipMalloc(&P.d_keys, need) != hipSuccess) {
-        (void)hipGetLastError();
+    if (cse::dev_malloc(&P.d_keys, need) != hipSuccess) {
         set_error("cse_calibrate: cannot allocate the calibration key workspace");
         return CSE_ENOMEM;
     }
@@ -376,6 +375,11 @@ int cse_platten_destroy(cse_platten *p) {
     if (!p) return CSE_OK;
     cse::free_platten(&p->P);
     delete p;
+    return CSE_OK;
+}
+
+int cse_release_cached_memory(void) {
+    cse::release_cached_memory();
     return CSE_OK;
 }
 
@@ -630,7 +634,7 @@ int cse_autotune(cse_platten *p, uint64_t seed, int64_t max_trials, int64_t out[
                 }
             if (d_it.p) CSE_HIP_TRY(hipFree(d_it.p));
             d_it.p = nullptr;
-            CSE_HIP_TRY(hipMalloc((void **)&d_it.p, items.size() * sizeof(cse::WorkItem)));
+            CSE_HIP_TRY(cse::dev_malloc((void **)&d_it.p, items.size() * sizeof(cse::WorkItem)));
             CSE_HIP_TRY(hipMemcpy(d_it.p, items.data(), items.size() * sizeof(cse::WorkItem), hipMemcpyHostToDevice));
             for (int64_t g : grids) {
                 float ms = 0.0f;

@@ -251,7 +251,7 @@ struct Platten {
     int32_t family = 0;
     int32_t n_per_arm = 0;
     int64_t n_boxes = 0, n_tiles = 0;
-    int device = 0;
+    int device = -1;
 
     // host copies
     std::vector<int64_t> tile_box;
@@ -423,6 +423,9 @@ const char *get_error();
 int build_platten(const cse_design *design, int64_t n_boxes, const double *theta,
                   const double *radii, const int32_t *sims, int32_t flags, Platten *P);
 void free_platten(Platten *P);
+// hipMalloc on the current device; short of memory, the buffers that the library keeps for later plattens go first.
+hipError_t dev_malloc(void **p, size_t bytes);
+void release_cached_memory();
 int plan_work_items(Platten *P, int64_t target_waves);
 int plan_group_items(Platten *P, int64_t target_wgs);
 int plan_h4_items(Platten *P, int64_t target_wgs);

@@ -223,8 +223,9 @@ void give_side_stream(int device, hipStream_t s) {
 
 // Count table of the last destroyed platten, per device (one buffer, at most B2_TABLE_MAX bytes and a
 // little), for the next one: adaptive runs create a platten per round, and allocations of tens of MB cost
-// ~190 us each.  A platten is destroyed only after the device has been synchronised.  The buffer is given
-// back when a platten needs a larger one.
+// ~190 us each.  A platten is destroyed only after the device has been synchronised.  The buffer is
+// freed when a platten needs a larger one, when an allocation of the library fails (dev_malloc), and by
+// cse_release_cached_memory.
 struct TableBuf {
     void *p = nullptr;
     size_t bytes = 0;
@@ -233,20 +234,32 @@ std::mutex g_table_mu;
 std::map<int, TableBuf> g_table_cache;
 constexpr size_t TABLE_CACHE_MIN = (size_t)2 << 20;   // smaller allocations are cheap
 
+// Frees the buffer of `device`, which is current; false when there is none.
+bool drop_table(int device) {
+    TableBuf t;
+    {
+        std::lock_guard<std::mutex> g(g_table_mu);
+        std::swap(t, g_table_cache[device]);
+    }
+    if (t.p) (void)hipFree(t.p);
+    return t.p != nullptr;
+}
+
 hipError_t take_table(int device, size_t bytes, TableBuf *t) {
     if (bytes >= TABLE_CACHE_MIN) {
-        std::lock_guard<std::mutex> g(g_table_mu);
-        TableBuf &c = g_table_cache[device];
-        if (c.bytes >= bytes) {
-            *t = c;
-            c = TableBuf();
-            return hipSuccess;
+        {
+            std::lock_guard<std::mutex> g(g_table_mu);
+            TableBuf &c = g_table_cache[device];
+            if (c.bytes >= bytes) {
+                *t = c;
+                c = TableBuf();
+                return hipSuccess;
+            }
         }
-        if (c.p) (void)hipFree(c.p);
-        c = TableBuf();
+        drop_table(device);
     }
     t->bytes = bytes;
-    return hipMalloc(&t->p, bytes);
+    return dev_malloc(&t->p, bytes);
 }
 
 void give_table(int device, TableBuf t) {
@@ -257,6 +270,18 @@ void give_table(int device, TableBuf t) {
     }
     if (t.p) (void)hipFree(t.p);
 }
+
+// The device of a platten made current, and the caller's again.
+struct DeviceGuard {
+    int cur = -1;
+    bool other = false;
+    explicit DeviceGuard(int device) {   // (-1: none yet)
+        other = device >= 0 && hipGetDevice(&cur) == hipSuccess && cur != device && hipSetDevice(device) == hipSuccess;
+    }
+    ~DeviceGuard() {
+        if (other) (void)hipSetDevice(cur);
+    }
+};
 
 // Uploads gathered into one host buffer and copied with a single transfer into a device arena
 // (one synchronous copy per arena instead of one per array: each costs ~15 us of fixed
@@ -277,7 +302,7 @@ struct Stager {
     int flush(Platten *P) {
         if (dst.empty()) return CSE_OK;
         void *a = nullptr;
-        CSE_HIP_TRY(hipMalloc(&a, host.size()));
+        CSE_HIP_TRY(dev_malloc(&a, host.size()));
         P->arenas.emplace_back(a, host.size());
         CSE_HIP_TRY(hipMemcpy(a, host.data(), host.size(), hipMemcpyHostToDevice));
         for (auto &d : dst) *d.first = (unsigned char *)a + d.second;
@@ -293,12 +318,20 @@ int upload(T **dst, const T *src, size_t n) {
         *dst = nullptr;
         return CSE_OK;
     }
-    CSE_HIP_TRY(hipMalloc((void **)dst, n * sizeof(T)));
+    CSE_HIP_TRY(dev_malloc((void **)dst, n * sizeof(T)));
     CSE_HIP_TRY(hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice));
     return CSE_OK;
 }
 
 }  // namespace
+
+hipError_t dev_malloc(void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    int dev = 0;
+    if (e == hipErrorOutOfMemory && hipGetDevice(&dev) == hipSuccess && drop_table(dev)) e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();   // reported here, not by the next launch
+    return e;
+}
 
 int build_platten(const cse_design *design, int64_t n_boxes, const double *theta,
                   const double *radii, const int32_t *sims, int32_t flags, Platten *P) {
@@ -830,29 +863,29 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             P->d_b4tab = (uint4 *)t.p;
             P->table_bytes = t.bytes;
         }
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4u, (size_t)P->n_tiles * sizeof(float)));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4eq, (size_t)P->n_tiles * sizeof(uint32_t)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_h4u, (size_t)P->n_tiles * sizeof(float)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_h4eq, (size_t)P->n_tiles * sizeof(uint32_t)));
 
         // posterior table of the design (once per platten)
         const std::vector<HierNode> nodes = hier_nodes();
         if (int e = upload(&P->d_hnodes, nodes.data(), nodes.size())) return e;
         const int64_t m = P->n_per_arm + 1;
         P->h4_outcomes = m * m * m * m;
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4tbl, (size_t)P->h4_outcomes * sizeof(float4)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_h4tbl, (size_t)P->h4_outcomes * sizeof(float4)));
         const auto t0 = std::chrono::steady_clock::now();
         if (kind == CSE_BASKET4)
             CSE_HIP_TRY(launch_basket_table(P->n_per_arm, design->theta0, P->d_h4tbl, P->d_hnodes, nullptr));
         else
             CSE_HIP_TRY(launch_hier4_table(P->n_per_arm, P->d_h4tbl, P->d_hnodes, nullptr));
         const int n_cfg = kind == CSE_BASKET4 ? 15 : 7;
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4bits, (size_t)n_cfg * H4_BITS * sizeof(uint64_t)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_h4bits, (size_t)n_cfg * H4_BITS * sizeof(uint64_t)));
         CSE_HIP_TRY(launch_h4_bits(P->d_h4tbl, (float)design->cut, n_cfg, P->d_h4bits, nullptr));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4plane, (size_t)n_cfg * H4_PLANE * sizeof(float)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_h4plane, (size_t)n_cfg * H4_PLANE * sizeof(float)));
         CSE_HIP_TRY(launch_h4_planes(P->d_h4tbl, n_cfg, P->d_h4plane, nullptr));
         CSE_HIP_TRY(hipDeviceSynchronize());
         P->table_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         if (int e = upload(&P->d_tileT, P->tile_T.data(), P->tile_T.size())) return e;   // regenerated keys
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_h4fb, sizeof(uint32_t)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_h4fb, sizeof(uint32_t)));
         CSE_HIP_TRY(hipMemset(P->d_h4fb, 0, sizeof(uint32_t)));
     } else if (kind == CSE_PHASE23) {
         // one trial per lane: keys contiguous per tile, work items of p23_chunk simulations
@@ -880,7 +913,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
             const size_t o_state = take(slots * 8), o_value = take((slots + cap) * 4), o_own = take(cap * 8),
                          o_l0 = take(cap * 4), o_l1 = take(cap * 4), o_t0 = take(cap * 32), o_t1 = take(cap * 32),
                          o_range = take(P23_BLOCKS * sizeof(uint2)), o_ctr = take(P23_COUNTERS * P23_CTR * sizeof(uint32_t));
-            CSE_HIP_TRY(hipMalloc(&P->d_p23mem, off));
+            CSE_HIP_TRY(dev_malloc(&P->d_p23mem, off));
             unsigned char *m = (unsigned char *)P->d_p23mem;
             M.state = (unsigned long long *)(m + o_state);
             M.value = (uint32_t *)(m + o_value);
@@ -894,8 +927,8 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         }
         if (int e = upload(&P->d_tileT, P->tile_T.data(), P->tile_T.size())) return e;
         if (int e = upload(&P->d_cfg, P->tile_cfg.data(), P->tile_cfg.size())) return e;
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_queue, sizeof(uint32_t)));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_p23stats, 4 * sizeof(unsigned long long)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_queue, sizeof(uint32_t)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_p23stats, 4 * sizeof(unsigned long long)));
         // count table rows: each arm's distinct thresholds, for the simulations of its longest tile
         {
             std::vector<P23Row> rows;
@@ -928,7 +961,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
                 P->n_p23row = (int32_t)rows.size();
                 if (int e = upload(&P->d_p23row, rows.data(), rows.size())) return e;
                 if (int e = upload(&P->d_p23tilerow, tile_row.data(), tile_row.size())) return e;
-                CSE_HIP_TRY(hipMalloc((void **)&P->d_p23counts, at * 64 * sizeof(uint16_t)));
+                CSE_HIP_TRY(dev_malloc((void **)&P->d_p23counts, at * 64 * sizeof(uint16_t)));
             }
         }
         P23Args &A = P->p23;
@@ -948,7 +981,7 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         A.sqrt_pi = sqrt(M_PI);
         A.z95 = normal_q95();
         // decisions of the first look (50 patients per arm) for every outcome, once per platten
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_p23look1, (size_t)51 * 51 * 51 * 51));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_p23look1, (size_t)51 * 51 * 51 * 51));
         A.look1 = P->d_p23look1;
         {
             const auto t0 = std::chrono::steady_clock::now();
@@ -1194,28 +1227,28 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         stage.add(&P->d_cp_base, base.data(), base.size());
         if (int r = stage.flush(P)) return r;
         if (kind == CSE_PHASE23) P->p23.key_off = P->d_key_off;
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_cp_mark, (size_t)e * sizeof(uint32_t)));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_cp_tbl, (size_t)e * sizeof(double)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_cp_mark, (size_t)e * sizeof(uint32_t)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_cp_tbl, (size_t)e * sizeof(double)));
     }
     const size_t nt = (size_t)P->n_tiles;
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_Rw, nt * sizeof(uint32_t)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_Rw, nt * sizeof(uint32_t)));
     // score sums: sum of T per arm; the Phase II/III design also sums the observed n per arm
     const size_t tw = (kind == CSE_PHASE23) ? 2 * (size_t)d : (size_t)d;
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_Tw, nt * tw * sizeof(unsigned long long)));
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_Zw, nt * sizeof(unsigned long long)));
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_apw, nt * sizeof(double)));
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_kw, nt * sizeof(int32_t)));
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_lamw, nt * sizeof(double)));
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_lamg, sizeof(double)));
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_minpart, 2 * MIN_PARTS * sizeof(double)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_Tw, nt * tw * sizeof(unsigned long long)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_Zw, nt * sizeof(unsigned long long)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_apw, nt * sizeof(double)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_kw, nt * sizeof(int32_t)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_lamw, nt * sizeof(double)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_lamg, sizeof(double)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_minpart, 2 * MIN_PARTS * sizeof(double)));
     if (kind == CSE_BINOM2_Z) {
         TableBuf t;
         CSE_HIP_TRY(take_table(P->device, (size_t)P->b2_units * UNIT2, &t));
         P->d_b2tab = (uint4 *)t.p;
         P->table_bytes = t.bytes;
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2cut, (size_t)P->n_blocks * B2U * (NP35 + 1) * sizeof(uint4)));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2br, nt * sizeof(int2)));
-        CSE_HIP_TRY(hipMalloc((void **)&P->d_b2fb, sizeof(uint32_t)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_b2cut, (size_t)P->n_blocks * B2U * (NP35 + 1) * sizeof(uint4)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_b2br, nt * sizeof(int2)));
+        CSE_HIP_TRY(dev_malloc((void **)&P->d_b2fb, sizeof(uint32_t)));
     }
     CSE_HIP_TRY(take_side_stream(P->device, &P->side));
     for (hipEvent_t *e : {&P->ev_sim, &P->ev_val, &P->ev_fork, &P->ev_inv})
@@ -1316,7 +1349,7 @@ int plan_h4_items(Platten *P, int64_t target_wgs) {
     P->n_gitems = (P->n_h4item + WG / WAVE - 1) / (WG / WAVE);
     P->group_sims = gs;
     P->tune_wgs = target_wgs;
-    CSE_HIP_TRY(hipMalloc((void **)&P->d_h4cnt, (size_t)cnt * sizeof(uint32_t)));
+    CSE_HIP_TRY(dev_malloc((void **)&P->d_h4cnt, (size_t)cnt * sizeof(uint32_t)));
     if (int e = upload(&P->d_h4set, P->h4set.data(), P->h4set.size())) return e;
     return upload(&P->d_h4item, items.data(), items.size());
 }
@@ -1437,6 +1470,19 @@ int plan_queue_items(Platten *P, int32_t chunk, int64_t grid) {
     P->p23_grid = grid > 0 ? grid : P23_GRID;   // its work is the states, up to HP_SEGS lanes each, not the items
     P->p23_items = std::move(items);
     return CSE_OK;
+}
+
+void release_cached_memory() {
+    std::vector<int> devices;
+    {
+        std::lock_guard<std::mutex> g(g_table_mu);
+        for (auto &c : g_table_cache)
+            if (c.second.p) devices.push_back(c.first);
+    }
+    for (int d : devices) {
+        DeviceGuard guard(d);
+        drop_table(d);
+    }
 }
 
 void free_platten(Platten *P) {

@@ -1,0 +1,64 @@
+"""GPU: the device memory that the library keeps and asks for."""
+import contextlib
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2212_10042_amd as cse
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+MB = 1 << 20
+
+
+def _free():
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+@contextlib.contextmanager
+def _left(nbytes):
+    """All but nbytes of the device's memory taken."""
+    hog = torch.empty(_free() - nbytes, dtype=torch.uint8, device="cuda")
+    try:
+        yield
+    finally:
+        del hog
+        torch.cuda.empty_cache()
+
+
+def _keep_a_table():
+    """A destroyed platten whose count table (about 109 MB) is kept."""
+    cse.cse_release_cached_memory()
+    w = W.binom2_grid(300, 120_000, lower_triangle=False)
+    P = cse.Platten.create("binom2", w["theta"], w["radii"], w["sims"], keep_all=True)
+    P.close()
+
+
+def test_kept_table_is_released():
+    print("[memory] release", flush=True)
+    _keep_a_table()
+    kept = _free()
+    cse.cse_release_cached_memory()
+    assert _free() - kept >= 100 * MB
+    cse.cse_release_cached_memory()   # nothing left: no error
+
+
+def test_kept_table_makes_room():
+    """Short of memory, the library gives the kept table up before it reports an error."""
+    print("[memory] kept table makes room for keys", flush=True)
+    w = W.ztest_1d(64, 1 << 20)   # 256 MiB of keys
+    P = cse.Platten.create("ztest1", w["theta"], w["radii"], w["sims"])
+    ap, lam = (torch.empty(64, dtype=torch.float64, device="cuda") for _ in range(2))
+    low, k = torch.empty(1, dtype=torch.float64, device="cuda"), torch.empty(64, dtype=torch.int32, device="cuda")
+    _keep_a_table()
+    with _left(206 * MB):
+        plan = cse.cse_plan_calibrate(P.handle, 3, 0.025, ap, k, lam, low)   # allocates the keys; launches nothing
+        cse.cse_plan_destroy(plan)
+    g = P.calibrate(3)
+    torch.cuda.synchronize()
+    assert np.isfinite(g["lambda_tile"].cpu().numpy()).all()
+    P.close()
