@@ -223,7 +223,7 @@ void give_side_stream(int device, hipStream_t s) {
 
 // Count table of the last destroyed platten, per device (one buffer, at most B2_TABLE_MAX bytes and a
 // little), for the next one: adaptive runs create a platten per round, and allocations of tens of MB cost
-// ~190 us each.  A platten is destroyed only after the device has been synchronised.  The buffer is
+// ~190 us each.  A platten gives its table back after its own device has been synchronised.  The buffer is
 // freed when a platten needs a larger one, when an allocation of the library fails (dev_malloc), and by
 // cse_release_cached_memory.
 struct TableBuf {
@@ -1488,6 +1488,7 @@ void release_cached_memory() {
 void free_platten(Platten *P) {
     if (!P) return;
     if (P->shape_gen) P->shape_gen->store(PLATTEN_GONE);   // plans on this platten refuse to replay
+    DeviceGuard guard(P->device);   // its work may be in flight while another device is current
     (void)hipDeviceSynchronize();
     void *ptrs[] = {P->d_theta, P->d_N,    P->d_vert_off, P->d_verts,   P->d_key_off,
                     P->d_blocks, P->d_items, P->d_cut_tbl, P->d_S_tbl,  P->d_S_order,
