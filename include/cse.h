@@ -110,7 +110,9 @@ typedef struct cse_platten cse_platten;
  * partition, Section 5), enumerates each tile's vertices in float64 (the supremum of
  * the bound over a convex polytope is attained at a vertex, Theorem 3), computes the
  * per-arm Bernoulli thresholds round(2^32 expit(theta)) in float64, plans the tile
- * batches the kernels run, and uploads everything to the current HIP device.
+ * batches the kernels run, and uploads everything to the current HIP device.  A CSE_PHASE23 platten
+ * keeps workspaces of up to 100 bytes per trial (4.4 GB at most) and a count table of up to 1 GiB,
+ * each at most an eighth of the free device memory; with less it works in shorter chunks of trials.
  * Errors: CSE_EINVAL (bad sizes/values, no box meets a null), CSE_ENOMEM, CSE_EHIP.
  */
 int cse_platten_create(const cse_design *design, int64_t n_boxes, const double *theta,
@@ -445,7 +447,7 @@ int cse_simulate_per_tile(const cse_platten *p, uint64_t seed, int64_t tile_begi
  * cse_work_counters -- work done by the last simulation launch on a CSE_PHASE23 platten
  * (cse_simulate / cse_validate / cse_calibrate): out (host int64 [4]) = trials simulated,
  * posterior evaluations at Phase II looks and at Phase III looks (one per distinct state of the
- * call, however many trials reach it; the first look of every trial is a table lookup and is
+ * call that its table has a place for, however many trials reach it; the first look of every trial is a table lookup and is
  * not counted), Newton steps over all nodes of those evaluations.
  * On a CSE_BINOM2_Z platten: out[0] = tiles that the last calibration's bracketed selection
  * left to the exact full-histogram pass (k-th statistic outside the bracket, or the batch's

@@ -227,6 +227,7 @@ constexpr int P23_ROUNDS = 5;                          // looks after the first,
 constexpr int64_t P23_BLOCKS = 8192;                  // workgroups of k_p23_open and k_p23_step, at most
 constexpr int P23_CTR = 32, P23_COUNTERS = 3 * P23_ROUNDS + 1;
 constexpr int64_t P23_CAP_MAX = (int64_t)32 << 20;     // trials of a chunk
+constexpr int64_t P23_CAP_MIN = 512, P23_SLOTS_MIN = 4096;   // an item's trials at least
 struct P23Memo {
     unsigned long long *state;
     uint32_t *value;

@@ -896,24 +896,37 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         }
         if (int e = plan_queue_items(P, P->p23_chunk, -1)) return e;
         {
-            // the records of a chunk's trials, and a table of twice as many slots as trials (2^27 at
-            // most), in one allocation
-            P->p23_cap = std::max<int64_t>(512, std::min<int64_t>(P->total_sims, P23_CAP_MAX));
-            uint64_t slots = 1u << 12;
+            // the records of a chunk's trials, and a table of at least as many slots as trials (2^27 at most),
+            // in one allocation: at most an eighth of the free memory (fewer trials a chunk, fewer slots), or
+            // half as much again and again where that cannot be had
+            size_t free_bytes = 0, all_bytes = 0;
+            CSE_HIP_TRY(hipMemGetInfo(&free_bytes, &all_bytes));
+            P->p23_cap = std::max<int64_t>(P23_CAP_MIN, std::min<int64_t>(P->total_sims, P23_CAP_MAX));
+            uint64_t slots = P23_SLOTS_MIN;
             while (slots < (1u << 27) && slots < (uint64_t)P->total_sims) slots *= 2;
             P23Memo &M = P->p23memo;
+            size_t off, o_state, o_value, o_own, o_l0, o_l1, o_t0, o_t1, o_range, o_ctr;
+            for (;;) {
+                const size_t cap = (size_t)P->p23_cap;
+                off = 0;
+                auto take = [&](size_t bytes) {
+                    const size_t at = off;
+                    off += (bytes + 255) & ~(size_t)255;
+                    return at;
+                };
+                o_state = take(slots * 8), o_value = take((slots + cap) * 4), o_own = take(cap * 8), o_l0 = take(cap * 4),
+                o_l1 = take(cap * 4), o_t0 = take(cap * 32), o_t1 = take(cap * 32), o_range = take(P23_BLOCKS * sizeof(uint2)),
+                o_ctr = take(P23_COUNTERS * P23_CTR * sizeof(uint32_t));
+                const bool least = P->p23_cap == P23_CAP_MIN && slots == P23_SLOTS_MIN;
+                if (off <= free_bytes / 8 || least) {
+                    const hipError_t e = dev_malloc(&P->d_p23mem, off);
+                    if (e == hipSuccess) break;
+                    if (least) CSE_HIP_TRY(e);
+                }
+                P->p23_cap = std::max<int64_t>(P23_CAP_MIN, P->p23_cap / 2);
+                slots = std::max<uint64_t>(P23_SLOTS_MIN, slots / 2);
+            }
             M.mask = (uint32_t)(slots - 1);
-            const size_t cap = (size_t)P->p23_cap;
-            size_t off = 0;
-            auto take = [&](size_t bytes) {
-                const size_t at = off;
-                off += (bytes + 255) & ~(size_t)255;
-                return at;
-            };
-            const size_t o_state = take(slots * 8), o_value = take((slots + cap) * 4), o_own = take(cap * 8),
-                         o_l0 = take(cap * 4), o_l1 = take(cap * 4), o_t0 = take(cap * 32), o_t1 = take(cap * 32),
-                         o_range = take(P23_BLOCKS * sizeof(uint2)), o_ctr = take(P23_COUNTERS * P23_CTR * sizeof(uint32_t));
-            CSE_HIP_TRY(dev_malloc(&P->d_p23mem, off));
             unsigned char *m = (unsigned char *)P->d_p23mem;
             M.state = (unsigned long long *)(m + o_state);
             M.value = (uint32_t *)(m + o_value);
@@ -957,11 +970,15 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
                     tile_row[4 * t + a] = make_uint2(it->at, it->stride);
                 }
             }
-            if (at * 64 * sizeof(uint16_t) <= (uint64_t)P23_TABLE_MAX) {
+            size_t free_bytes = 0, all_bytes = 0;
+            CSE_HIP_TRY(hipMemGetInfo(&free_bytes, &all_bytes));
+            const size_t bytes = at * 64 * sizeof(uint16_t);
+            // (an eighth of the free memory at most; without it trials draw their own words)
+            if (at * 64 * sizeof(uint16_t) <= (uint64_t)P23_TABLE_MAX && bytes <= free_bytes / 8 &&
+                dev_malloc((void **)&P->d_p23counts, bytes) == hipSuccess) {
                 P->n_p23row = (int32_t)rows.size();
                 if (int e = upload(&P->d_p23row, rows.data(), rows.size())) return e;
                 if (int e = upload(&P->d_p23tilerow, tile_row.data(), tile_row.size())) return e;
-                CSE_HIP_TRY(dev_malloc((void **)&P->d_p23counts, at * 64 * sizeof(uint16_t)));
             }
         }
         P23Args &A = P->p23;

@@ -62,3 +62,28 @@ def test_kept_table_makes_room():
     torch.cuda.synchronize()
     assert np.isfinite(g["lambda_tile"].cpu().numpy()).all()
     P.close()
+
+
+def test_phase23_in_little_memory():
+    """A Phase II/III platten of 34 million trials keeps 3.5 GB of states, records and counts; where 2 GiB are free it is
+    created with less (shorter chunks, no counts) and gives the same results."""
+    print("[memory] phase23 in 2 GiB", flush=True)
+    w = W.phase23_grid((2, 2, 2, 2), 750_000)
+
+    def run():
+        before = _free()
+        P = cse.Platten.create("phase23", w["theta"], w["radii"], w["sims"], cut=w["cut"])
+        used = before - _free()
+        v = P.validate(5)
+        torch.cuda.synchronize()
+        P.close()
+        return used, {k: v[k].clone() for k in ("reject", "score_T", "tile_bound")}
+
+    cse.cse_release_cached_memory()
+    used, whole = run()
+    assert used > 2048 * MB
+    with _left(2048 * MB):
+        used, little = run()
+    assert used < 1024 * MB
+    for name in whole:
+        assert torch.equal(whole[name], little[name]), name
