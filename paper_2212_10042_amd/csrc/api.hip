@@ -266,6 +266,7 @@ int validate_impl(const cse::Platten &P, uint64_t seed, double delta, int32_t *r
 // (k = 26,000) 7.2 and 3.2 ms, at 0.05 12^4 x 65,536 5.7 and 3.4 ms
 bool takes_candidates(const cse::Platten &P, double alpha, bool full_keys) {
     return (P.design.kind == CSE_HIER4 || P.design.kind == CSE_BASKET4) && !full_keys && alpha <= cse::H4_CAND_ALPHA &&
+           (P.b4_win >= cse::H4_SLICE_MAX || P.b4_win * cse::GRAN2 >= P.max_N) &&   // slices and pilots in one window
            (P.h4_candidates || (P.max_N >= cse::H4_PILOT_MIN_N && P.n_keys >= cse::H4_CAND_KEYS));
 }
 

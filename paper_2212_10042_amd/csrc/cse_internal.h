@@ -134,6 +134,7 @@ __host__ __device__ inline uint32_t h4_code3(uint32_t y) { return ((y >> 3) << 5
 // simulations of a set gives each tile an upper bound of its k-th smallest key; the pass over all
 // simulations keeps only the keys below it.
 constexpr int64_t H4_SLICE_MAX = 256;    // granules per item at most (4,096 simulations)
+constexpr int64_t H4_TABLE_MAX = (int64_t)4 << 30;   // count-table bytes of windows of H4_SLICE_MAX granules (more: shorter ones)
 constexpr int64_t H4_WGS = 2048;         // workgroups of four waves, default
 constexpr int H4_PILOT_MIN_N = 1024;     // fewer simulations: every key is kept
 constexpr int H4_PILOT_MAX = 2048;

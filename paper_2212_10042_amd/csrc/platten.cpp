@@ -723,6 +723,14 @@ int build_platten(const cse_design *design, int64_t n_boxes, const double *theta
         P->b4_win = H4_SLICE_MAX;
         while (P->b4_win < granules(P->max_N)) P->b4_win *= 2;
         while (P->b4_win > H4_SLICE_MAX && units(P->b4_win) * 16 > B2_TABLE_MAX) P->b4_win /= 2;
+        // boxes without common thresholds take 24 KB each at that window: beyond H4_TABLE_MAX, or an eighth of the
+        // free memory, shorter ones (then without candidates, whose pilot and slices lie in one window)
+        if (units(P->b4_win) * 16 > B2_TABLE_MAX) {
+            size_t free_bytes = 0, all_bytes = 0;
+            CSE_HIP_TRY(hipMemGetInfo(&free_bytes, &all_bytes));
+            const int64_t most = std::max<int64_t>(B2_TABLE_MAX, std::min<int64_t>(H4_TABLE_MAX, (int64_t)(free_bytes / 8)));
+            while (P->b4_win > 4 && units(P->b4_win) * 16 > most) P->b4_win /= 2;
+        }
         for (auto &g : grps) {
             g.stride = std::min(P->b4_win, granules(g.n_sims));
             g.row = P->b4_units;

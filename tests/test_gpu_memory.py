@@ -87,3 +87,47 @@ def test_phase23_in_little_memory():
     assert used < 1024 * MB
     for name in whole:
         assert torch.equal(whole[name], little[name]), name
+
+
+def _scattered(n, sims):
+    """n basket boxes in the null that share no threshold, one tile each."""
+    r = np.random.default_rng(n)
+    th = r.uniform(-4.0, -1.8, (n, 4))
+    return th, np.full(th.shape, 1e-4), np.full(n, sims, np.int32)
+
+
+def test_scattered_boxes_in_little_memory():
+    """12,000 boxes without a common threshold have a count table of 290 MB at the usual window; where 400 MiB are free a
+    shorter one serves, and the validation is the same."""
+    print("[memory] scattered boxes in 400 MiB", flush=True)
+    grid = _scattered(12_000, 4_200)
+
+    def run():
+        P = cse.Platten.create("basket4", *grid)
+        v = P.validate(5)
+        torch.cuda.synchronize()
+        P.close()
+        return {k: v[k].clone() for k in ("reject", "score_T", "tile_bound")}
+
+    cse.cse_release_cached_memory()
+    whole = run()
+    with _left(400 * MB):
+        little = run()
+    for name in whole:
+        assert torch.equal(whole[name], little[name]), name
+
+
+def test_many_scattered_boxes():
+    """2.9 million boxes without a common threshold: more rows of the usual window than the table's 32-bit places reach,
+    so shorter windows.  Sampled tiles against the per-tile path."""
+    print("[memory] 2.9 million scattered boxes", flush=True)
+    n = 2_900_000
+    P = cse.Platten.create("basket4", *_scattered(n, 4_096))
+    assert P.n_tiles == n
+    v = P.simulate(5)
+    R = torch.empty_like(v["reject"])
+    for t in (0, 1, 64, 1_234_567, n - 1):
+        cse.cse_simulate_per_tile(P.handle, 5, t, t + 1, R)
+        torch.cuda.synchronize()
+        assert int(R[t]) == int(v["reject"][t]), t
+    P.close()
