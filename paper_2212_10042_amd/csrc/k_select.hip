@@ -236,6 +236,10 @@ __device__ void b2_full_tile(const Recs2 &rb, int n, int32_t k, int s, const dou
 // NWV waves per workgroup: 16 up to B2_FEWBLK batches (one per CU), which leave most of the chip idle
 // otherwise, 4 beyond (16 / 4 waves, us: 32 x 32 triangle x 4,096 29 / 71, 128 x 128 x 8,192 20 / 41;
 // 200 x 200 x 1,000, 325 batches, 51 / 28).
+// Few simulations (512 with 16 waves, 128 with 4): their brackets span most positions, so that the batch takes many
+// rounds; the waves then select slots from all simulations' positions in registers (calls of 20 x 20 triangle x
+// 200 / 400 228 / 181 us with rounds, 161 / 165 so, 64 x 64 x 100 220 / 149; 500 x 500 x 64 497 / 445, but
+// x 200 439 / 456).
 // Bound by issue and LDS latency.  Us, against a byte-wise classification of every (simulation,
 // tile) from 16-byte records: 1024 x 1024 boxes x 16,384 simulations 1,990 -> 515
 // (beside the validation bound), 256 x 256 triangle x 8,192 88 -> 34, 20 x 20 x 1,001 50 -> 47.
@@ -290,6 +294,34 @@ __global__ __launch_bounds__(NWV *WAVE) void k_b2_select(
         start = x - W;
     }
     const Recs2 rb(recs, B);
+    // few simulations (uniform): every one's position in a wave's registers, a wave per slot
+    constexpr int B2_DIRECT = NWV == 16 ? 8 * WAVE : 2 * WAVE;
+    if (N <= B2_DIRECT) {
+        __syncthreads();   // spos is complete
+        for (int s = wv; s < NT; s += NWV) {
+            if (__builtin_amdgcn_readlane(W, s) == 0) continue;
+            const int32_t t = __builtin_amdgcn_readlane(my_t, s), k = __builtin_amdgcn_readlane(my_k, s);
+            int x[B2_DIRECT / WAVE], p = 0;
+#pragma unroll
+            for (int q = 0; q < B2_DIRECT / WAVE; ++q)
+                x[q] = q * WAVE + lane < N ? (int)spos[rec_outcome(rb[q * WAVE + lane], s)] : 2047;
+            for (int b = 10; b >= 0; --b) {   // as wave_kth
+                int le = 0;
+#pragma unroll
+                for (int q = 0; q < B2_DIRECT / WAVE; ++q) le += __popcll(__ballot(x[q] <= (p | ((1 << b) - 1))));
+                if (le < k) p |= 1 << b;
+            }
+            const int g = S_group[p];
+            int lt = 0;
+#pragma unroll
+            for (int q = 0; q < B2_DIRECT / WAVE; ++q) lt += __popcll(__ballot(x[q] < g));
+            if (lane == 0) {
+                lam[t] = S_tbl[S_order[p]];
+                if (rej_at) rej_at[t] = lt;
+            }
+        }
+        return;
+    }
     const int hs = N <= 0xFFFF ? 1 : 0;   // uniform: two bins per word
     auto hist_add = [&](int i) { atomicAdd(&hist[i >> hs], 1u << (16 * (i & hs))); };
     auto hist_get = [&](int i) { return (hist[i >> hs] >> (16 * (i & hs))) & (hs ? 0xFFFFu : 0xFFFFFFFFu); };
