@@ -457,7 +457,7 @@ __global__ __launch_bounds__(WG) void k_h4_tiles(const H4Set *__restrict__ sets,
                 *__restrict__ l3 = lrow(3), *__restrict__ c2 = lrow(4), *__restrict__ c3 = lrow(5);
     const uint32_t base = (cfg - 1u) * (uint32_t)(4 * H4_PLANE);
     const float bound = CAND ? (t >= 0 ? U[t] : -INFINITY) : 0.0f;
-    // MODE 2: keys at or above it matter to nothing (the float after the bound: keys equal to it count)
+    // CAND: keys at or above it matter to nothing (the float after the bound: keys equal to it count)
     const float look = fmaxf(cut, bound >= 0.0f && bound < INFINITY ? __uint_as_float(__float_as_uint(bound) + 1u) : bound);
     uint32_t ncand = 0u, neq = 0u, cap = 0u;
     float *__restrict__ kp = keys;
