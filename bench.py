@@ -42,11 +42,11 @@ VALU_PEAK = 256 * 4 * 64 * 2.4e9 / 4   # lane-ops/s: 256 CUs x 4 SIMDs x one wav
 # distinct state once, which no formula of the sizes tells (profiles/<workload>_counters.md).  Valid only
 # while those kernels are unchanged; workloads not listed report null.
 COUNTED = {   # workload: (vector lane-operations, HBM bytes)
-    "binom2_1024_full": (10_546_026_688, 368_939_610),
-    "binom2_256_tri": (555_885_312, 37_225_411),
-    "hier4_16": (22_016_046_272, 7_293_847_984),
-    "phase23_c5_sub256": (425_107_558_208, 16_032_566_225),
-    "basket4_16": (11_749_568_512, 137_284_247),
+    "binom2_1024_full": (10_546_026_688, 367_788_554),
+    "binom2_256_tri": (555_885_312, 37_223_472),
+    "hier4_16": (22_016_768_192, 7_323_427_162),
+    "phase23_c5_sub256": (433_519_255_083, 18_045_677_097),
+    "basket4_16": (11_749_568_512, 137_817_897),
 }
 
 DEFAULT = "binom2_1024_full"
