@@ -110,9 +110,9 @@ typedef struct cse_platten cse_platten;
  * partition, Section 5), enumerates each tile's vertices in float64 (the supremum of
  * the bound over a convex polytope is attained at a vertex, Theorem 3), computes the
  * per-arm Bernoulli thresholds round(2^32 expit(theta)) in float64, plans the tile
- * batches the kernels run, and uploads everything to the current HIP device.  A CSE_PHASE23 platten
- * keeps workspaces of up to 100 bytes per trial (4.4 GB at most) and a count table of up to 1 GiB,
- * each at most an eighth of the free device memory; with less it works in shorter chunks of trials.
+ * batches the kernels run, and uploads everything to the current HIP device.  A CSE_PHASE23
+ * platten keeps workspaces of up to 108 bytes per trial (4.4 GB at most) and a count table of up to
+ * 1 GiB, each at most an eighth of the free device memory; with less it works in shorter chunks.
  * Errors: CSE_EINVAL (bad sizes/values, no box meets a null), CSE_ENOMEM, CSE_EHIP.
  */
 int cse_platten_create(const cse_design *design, int64_t n_boxes, const double *theta,
@@ -123,9 +123,9 @@ int cse_platten_create(const cse_design *design, int64_t n_boxes, const double *
 int cse_platten_destroy(cse_platten *p);
 
 /*
- * cse_release_cached_memory -- free the device memory that the library keeps for later plattens after a platten
- * is destroyed: one count-table buffer per device, at most 128 MiB.  (The library frees it by itself when an
- * allocation of its own fails.)  Always CSE_OK.
+ * cse_release_cached_memory -- free the device memory that the library keeps for later plattens
+ * after a platten is destroyed: one count-table buffer per device, at most 128 MiB.  (The library
+ * frees it by itself when an allocation of its own fails.)  Always CSE_OK.
  */
 int cse_release_cached_memory(void);
 
@@ -425,8 +425,8 @@ int cse_plan_destroy(cse_plan *plan);
  *                          kernel {512, 1024, 2048} workgroups, timed on a strided sample of
  *                          tiles holding at most max_trials trials.
  * The fastest is kept in the platten.  Results of every later call are unchanged (integer
- * reductions are order-independent, keys are laid out by tile, not by launch shape, and a Phase II/III
- * posterior is the same bits however many lanes share it).
+ * reductions are order-independent, keys are laid out by tile, not by launch shape, and a Phase
+ * II/III posterior is the same bits however many lanes share it).
  * Plans captured on this platten before the call become stale (cse_plan_launch refuses them).
  *   out  host int64 [2]: the chosen value and, for CSE_PHASE23, the grid (else 0).
  * Errors: CSE_EINVAL (NULL out, max_trials < 1), CSE_ENOMEM, CSE_EHIP.
@@ -447,8 +447,8 @@ int cse_simulate_per_tile(const cse_platten *p, uint64_t seed, int64_t tile_begi
  * cse_work_counters -- work done by the last simulation launch on a CSE_PHASE23 platten
  * (cse_simulate / cse_validate / cse_calibrate): out (host int64 [4]) = trials simulated,
  * posterior evaluations at Phase II looks and at Phase III looks (one per distinct state of the
- * call that its table has a place for, however many trials reach it; the first look of every trial is a table lookup and is
- * not counted), Newton steps over all nodes of those evaluations.
+ * call that its table has a place for, however many trials reach it; the first look of every trial
+ * is a table lookup and is not counted), Newton steps over all nodes of those evaluations.
  * On a CSE_BINOM2_Z platten: out[0] = tiles that the last calibration's bracketed selection
  * left to the exact full-histogram pass (k-th statistic outside the bracket, or the batch's
  * brackets too wide for the histogram), out[1..3] = 0.  On a CSE_HIER4 platten: out[0] = tiles

@@ -22,7 +22,10 @@ def _free():
 @contextlib.contextmanager
 def _left(nbytes):
     """All but nbytes of the device's memory taken."""
-    hog = torch.empty(_free() - nbytes, dtype=torch.uint8, device="cuda")
+    try:
+        hog = torch.empty(_free() - nbytes, dtype=torch.uint8, device="cuda")
+    except torch.OutOfMemoryError:
+        pytest.skip("the device's free memory cannot be taken in one piece")
     try:
         yield
     finally:
